@@ -62,9 +62,7 @@ __global__ void k_schain_fill(const SChainPage* pgs, const uint32_t* seg_page, c
 __global__ void k_schain_seq(const SChainPage* pgs, int npg, const uint32_t* ok, uint32_t* strck, PageDev* pages,
                              uint32_t* err);
 __global__ void k_snappy(const ColScan* cols, SegTable seg, uint8_t* ws, int record, uint32_t* err);
-__global__ void k_snappy_blk(const ColScan* cols, SegTable seg, const uint32_t* sord, uint32_t cap, uint8_t* ws,
-                             uint32_t* err, int dicts);
-__global__ void k_snap_order(const ColScan* cols, SegTable seg, uint8_t* ws, uint32_t* sord, uint32_t cap, int mode);
+__global__ void k_snappy_blk(const ColScan* cols, SegTable seg, uint8_t* ws, uint32_t* err, int dicts);
 __global__ void k_snap_index(const ColScan* cols, SegTable seg);
 __global__ void k_prep(const ColScan* cols, SegTable seg);
 __global__ void k_edges(const uint8_t* ws, const ColScan* cols, SegTable seg);
@@ -311,6 +309,7 @@ struct pq_file_s {
   uint32_t* d_strck = nullptr;
   uint32_t* d_sblk = nullptr;       // Snappy block index (stream offset per 64 KiB output block)
   uint32_t* d_sblk_page = nullptr;  // page of each block
+  uint16_t* d_sbits = nullptr;      // element start bits of the compressed pages
   uint64_t total_sblk = 0;
   uint32_t* d_ckl = nullptr;  // level checkpoints, NLCK per tile
   Ck* d_ckv = nullptr;  // value-stream checkpoints, NSUB per tile
@@ -395,6 +394,7 @@ static void free_handle(pq_file f) {
   if (f->d_strck) (void)hipFree(f->d_strck);
   if (f->d_sblk) (void)hipFree(f->d_sblk);
   if (f->d_sblk_page) (void)hipFree(f->d_sblk_page);
+  if (f->d_sbits) (void)hipFree(f->d_sbits);
   if (f->d_ckl) (void)hipFree(f->d_ckl);
   if (f->d_ckv) (void)hipFree(f->d_ckv);
   if (f->d_chunks) (void)hipFree(f->d_chunks);
@@ -617,7 +617,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   // ---- host layout: rows, dictionary links, tiles, scratch, checkpoints ----
   f->chunk_tile0.assign(nchunks + 1, 0);
   f->scratch_prefix.assign(npages + 1, 0);
-  uint64_t tiles = 0, strck = 0, scratch = 0, sblk = 0;
+  uint64_t tiles = 0, strck = 0, scratch = 0, sblk = 0, sbits = 0;
   std::vector<uint32_t> sblk_page;
   for (int q = 0; q < nchunks; ++q) {
     const ChunkDev& cd = f->chunks[q];
@@ -643,6 +643,9 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         const uint64_t nb = (slen + SNAP_BLOCK - 1) / SNAP_BLOCK;
         for (uint64_t j = 0; j < nb; ++j) sblk_page.push_back(p);
         sblk += nb;
+        const uint32_t lev = pg.kind == PAGE_DATA_V2 ? (uint32_t)pg.rep_len + (uint32_t)pg.def_len : 0u;
+        pg.sbit_begin = sbits;
+        sbits += 2ull * snap_bit_words((uint32_t)((pg.payload + lev) & 15), pg.comp_size > lev ? pg.comp_size - lev : 0);
       }
       if (cd.codec == 1 && (pg.kind != PAGE_DATA_V2 || pg.v2_compressed) && pg.kind != PAGE_DICT)
         scratch += align_up(slen + SCRATCH_PAD, 16);
@@ -741,8 +744,9 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   // Snappy block index, built by the decompression below
   f->total_sblk = sblk;
   if (sblk) {
-    if (hipMalloc(&f->d_sblk, 2 * sizeof(uint32_t) * sblk) != hipSuccess ||  // offsets, then element counts
-        hipMalloc(&f->d_sblk_page, sizeof(uint32_t) * sblk) != hipSuccess) {
+    if (hipMalloc(&f->d_sblk, sizeof(uint32_t) * sblk) != hipSuccess ||
+        hipMalloc(&f->d_sblk_page, sizeof(uint32_t) * sblk) != hipSuccess ||
+        hipMalloc(&f->d_sbits, sizeof(uint16_t) * (sbits + 2)) != hipSuccess) {
       cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: block index allocation");
     }
     if (hipMemcpy(f->d_sblk_page, sblk_page.data(), sizeof(uint32_t) * sblk, hipMemcpyHostToDevice) != hipSuccess) {
@@ -775,10 +779,10 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     cs.fd.pages = f->d_pages;
     cs.fd.sblk = f->d_sblk;
     cs.fd.sblk_page = f->d_sblk_page;
-    cs.fd.sblk_ne = f->d_sblk + f->total_sblk;
+    cs.fd.sbits = f->d_sbits;
     OPEN_HIP(hipMemcpyAsync(d_cs, &cs, sizeof(cs), hipMemcpyHostToDevice, s));
     std::vector<Segment> segs{Segment{0, 0, npages, 0}};
-    hipLaunchKernelGGL(k_snap_index, dim3(npages), dim3(64), 0, s, d_cs, make_segs(segs));
+    hipLaunchKernelGGL(k_snap_index, dim3(npages), dim3(1024), 0, s, d_cs, make_segs(segs));
     if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_snap_index launch failed"); }
   }
   for (const OpenPass& P : passes) {
@@ -802,7 +806,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       cs.fd.pages = f->d_pages;
       cs.fd.sblk = f->d_sblk;
       cs.fd.sblk_page = f->d_sblk_page;
-    cs.fd.sblk_ne = f->d_sblk + f->total_sblk;
+      cs.fd.sbits = f->d_sbits;
       cs.scratch_base = P.s0;
       cs.open_sel = P.dict ? 1 : 2;
       OPEN_HIP(hipMemcpyAsync(d_cs, &cs, sizeof(cs), hipMemcpyHostToDevice, s));
@@ -811,8 +815,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       const uint32_t b0 = f->pages[P.p0].sblk_begin, b1 = P.p1 < npages ? f->pages[P.p1].sblk_begin : (uint32_t)sblk;
       if (b1 > b0) {
         std::vector<Segment> bsegs{Segment{0, b0, b1, 0}};
-        hipLaunchKernelGGL(k_snappy_blk, dim3((b1 - b0 + 4 * SNAP_LANES - 1) / (4 * SNAP_LANES)), dim3(256), 0, s, d_cs,
-                           make_segs(bsegs), (const uint32_t*)nullptr, 0u, d_scratch, f->d_err, 1);
+        hipLaunchKernelGGL(k_snappy_blk, dim3(b1 - b0), dim3(512), 0, s, d_cs, make_segs(bsegs), d_scratch, f->d_err, 1);
       }
       hipLaunchKernelGGL(k_snappy, dim3(P.p1 - P.p0), dim3(64), 0, s, d_cs, st2, d_scratch, 1, f->d_err);
       if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_snappy launch failed"); }
@@ -1149,7 +1152,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   f->fd.strck = f->d_strck;
   f->fd.sblk = f->d_sblk;
   f->fd.sblk_page = f->d_sblk_page;
-  f->fd.sblk_ne = f->d_sblk ? f->d_sblk + f->total_sblk : nullptr;
+  f->fd.sbits = f->d_sbits;
   f->fd.dicts = f->d_dicts;
   cleanup_open();
 
@@ -1177,7 +1180,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   S.open_ms_device = ms + prefix_ms;
   f->device_bytes += 4 + sizeof(ChunkDev) * (uint64_t)nchunks + sizeof(PageDev) * (uint64_t)npages +
                      (sizeof(TileDev) + 4ull * NLCK + sizeof(Ck) * NSUB) * tiles + 4ull * strck +
-                     12ull * sblk +  // Snappy block index: offset, element count, page
+                     8ull * sblk + 2ull * sbits +  // Snappy block index: offset, page; element start bits
                      8ull * (tiles + 1) + sizeof(DictSlot) * (uint64_t)nchunks;
   S.device_bytes = f->device_bytes;
   (void)t0;
@@ -1382,11 +1385,10 @@ struct Plan {
   std::vector<Segment> snappy_segs, prep_segs, pre_segs, fixed_segs[8], delta_segs, str_segs[2], edge_segs;
   std::vector<int32_t> str_cols;    // string ColScan indices (k_str_total)
   // units: pages (k_snappy), tiles (k_prep threads; one wave per tile elsewhere)
-  std::vector<Segment> sblk_segs;  // k_snappy_blk: blocks of the compressed pages, one lane each
+  std::vector<Segment> sblk_segs;  // k_snappy_blk: blocks of the compressed pages, one workgroup each
   std::vector<Segment> dba_segs;   // k_dba: pages of columns with DELTA_BYTE_ARRAY pages, one wave each
   uint32_t dba_waves = 0;
-  uint32_t sblk_lanes = 0;
-  uint64_t ws_sord = 0;  // k_snap_order's density buckets (0: blocks taken in segment order)
+  uint32_t sblk_wgs = 0;
   bool str_spread[2] = {false, false}, fixed_spread[8] = {};  // columns interleaved wave by wave
   uint32_t snappy_waves = 0, prep_threads = 0, pre_units = 0, fixed_units[8] = {}, delta_units = 0, str_units[2] = {0, 0},
            edge_threads = 0;
@@ -1535,8 +1537,8 @@ pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& 
       P.snappy_segs.push_back(Segment{idx, cs.page_begin, cs.page_end, P.snappy_waves});
       P.snappy_waves += cs.page_end - cs.page_begin;
       if (k.b1 > k.b0) {
-        P.sblk_segs.push_back(Segment{idx, k.b0, k.b1, P.sblk_lanes});
-        P.sblk_lanes += k.b1 - k.b0;
+        P.sblk_segs.push_back(Segment{idx, k.b0, k.b1, P.sblk_wgs});
+        P.sblk_wgs += k.b1 - k.b0;
       }
     }
     if (k.xbytes) {
@@ -1564,10 +1566,6 @@ pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& 
     P.str_spread[k] = true;
     P.str_units[k] = (uint32_t)P.str_segs[k].size() * most;
   }
-  if (!index && P.sblk_lanes && f->total_sblk < (1ull << SNAP_ORD_BITS) && P.cols.size() <= 64) {
-    P.ws_sord = off;  // SNAP_BUCKETS counters, then SNAP_BUCKETS lists of sblk_lanes entries
-    off = align_up(off + 256 + sizeof(uint32_t) * SNAP_BUCKETS * (uint64_t)P.sblk_lanes, 256);
-  }
   if (f->host && !index && !P.cols.empty()) {
     uint64_t most = 0;
     for (int g = rg_b; g < rg_e; ++g) {
@@ -1577,6 +1575,7 @@ pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& 
         lo = std::min(lo, ch.start);
         hi = std::max(hi, ch.end);
       }
+      lo &= ~15ull;  // a stream keeps its address modulo 16
       P.rg_lo.push_back(lo);
       most = std::max(most, hi - lo);
     }
@@ -1617,10 +1616,8 @@ static pq_status upload_header(Plan& P, uint8_t* ws, hipStream_t s) {
 
 // Snappy decompression of the plan's compressed data pages (column table
 // d_cols).
-// sord_off, sord_cap: the workspace region of k_snap_order's buckets and
-// their capacity (a plan's ws_sord and sblk_lanes; 0: segment order).
 static pq_status enqueue_decompress(pq_file f, const Plan& P, const ColScan* d_cols, uint8_t* ws, uint32_t* err,
-                                    hipStream_t s, uint64_t sord_off, uint32_t sord_cap) {
+                                    hipStream_t s) {
   for (const auto* v : {&P.snappy_segs, &P.sblk_segs, &P.dba_segs, &P.prep_segs, &P.pre_segs, &P.fixed_segs[0], &P.fixed_segs[1], &P.fixed_segs[2],
                         &P.fixed_segs[3], &P.fixed_segs[4], &P.fixed_segs[6], &P.delta_segs, &P.str_segs[0], &P.str_segs[1],
                         &P.edge_segs})
@@ -1630,19 +1627,9 @@ static pq_status enqueue_decompress(pq_file f, const Plan& P, const ColScan* d_c
     hipLaunchKernelGGL(k_snappy, dim3(P.snappy_waves), dim3(64), 0, s, d_cols, make_segs(P.snappy_segs), ws, 0, err);
     HIP_OR(hipGetLastError());
   }
-  if (P.sblk_lanes) {
+  if (P.sblk_wgs) {
     ProfScope ps_(f, KP_SNAPPY_BLK, s);
-    uint32_t* sord = nullptr;
-    if (sord_off && sord_cap >= P.sblk_lanes) {  // the blocks in buckets of density, the densest first
-      sord = (uint32_t*)(ws + sord_off);
-      hipLaunchKernelGGL(k_snap_order, dim3(1), dim3(256), 0, s, d_cols, make_segs(P.sblk_segs), ws, sord,
-                         sord_cap, 0);
-      hipLaunchKernelGGL(k_snap_order, dim3((P.sblk_lanes + 255) / 256), dim3(256), 0, s, d_cols,
-                         make_segs(P.sblk_segs), ws, sord, sord_cap, 1);
-      HIP_OR(hipGetLastError());
-    }
-    hipLaunchKernelGGL(k_snappy_blk, dim3((P.sblk_lanes + 4 * SNAP_LANES - 1) / (4 * SNAP_LANES)), dim3(256), 0, s,
-                       d_cols, make_segs(P.sblk_segs), (const uint32_t*)sord, sord_cap, ws, err, 0);
+    hipLaunchKernelGGL(k_snappy_blk, dim3(P.sblk_wgs), dim3(512), 0, s, d_cols, make_segs(P.sblk_segs), ws, err, 0);
     HIP_OR(hipGetLastError());
   }
   if (P.dba_waves) {  // DELTA_BYTE_ARRAY pages (after their decompression) to the PLAIN layout
@@ -1658,7 +1645,7 @@ static pq_status enqueue_decompress(pq_file f, const Plan& P, const ColScan* d_c
 static pq_status enqueue_front(pq_file f, Plan& P, uint8_t* ws, uint32_t* err, hipStream_t s) {
   pq_status st = upload_header(P, ws, s);
   if (st != PQ_OK) return st;
-  return enqueue_decompress(f, P, reinterpret_cast<ColScan*>(ws + P.ws_cols), ws, err, s, P.ws_sord, P.sblk_lanes);
+  return enqueue_decompress(f, P, reinterpret_cast<ColScan*>(ws + P.ws_cols), ws, err, s);
 }
 
 // The open-time prefix pass of a plan made with index = true: per-tile DELTA
@@ -2042,8 +2029,7 @@ extern "C" pq_status pq_scan_streamed(pq_file f, uint64_t col_mask, int32_t rg_b
     Plan Pg;  // the launch lists of row group g alone (same column order)
     st = make_plan(f, col_mask, g, g + 1, Pg);
     const ColScan* d_cols = reinterpret_cast<const ColScan*>(ws + P.ws_rgcols + sizeof(ColScan) * P.cols.size() * (size_t)i);
-    // (Pg's workspace offsets are not this workspace's: the buckets are P's)
-    if (st == PQ_OK) st = enqueue_decompress(f, Pg, d_cols, ws, err, s, P.ws_sord, P.sblk_lanes);
+    if (st == PQ_OK) st = enqueue_decompress(f, Pg, d_cols, ws, err, s);
     if (st == PQ_OK) st = enqueue_decode(f, Pg, d_cols, ws, err, s);
     if (st == PQ_OK && hipEventRecord(freed[slot], s) != hipSuccess) st = fail(PQ_EHIP, "event record failed");
   }
@@ -2100,7 +2086,7 @@ struct BatchPlan {
   std::vector<int32_t> str_cols;
   std::vector<int64_t> chars;  // per column, in request order
   std::vector<Segment> snappy_segs, sblk_segs, edge_segs, prep_segs, dba_segs;
-  uint32_t snappy_waves = 0, sblk_lanes = 0, edge_threads = 0, prep_threads = 0, dba_waves = 0;
+  uint32_t snappy_waves = 0, sblk_wgs = 0, edge_threads = 0, prep_threads = 0, dba_waves = 0;
   // same-kind tile runs: consecutive pages of one column with one decoder
   // and work class
   struct Run { uint32_t cs, t0, t1, kind, cls, chunk; };
@@ -2177,8 +2163,8 @@ pq_status make_batch_plan(const pq_request* reqs, int32_t n, BatchPlan& P) {
         P.snappy_segs.push_back(Segment{idx, cs.page_begin, cs.page_end, P.snappy_waves});
         P.snappy_waves += cs.page_end - cs.page_begin;
         if (k.b1 > k.b0) {
-          P.sblk_segs.push_back(Segment{idx, k.b0, k.b1, P.sblk_lanes});
-          P.sblk_lanes += k.b1 - k.b0;
+          P.sblk_segs.push_back(Segment{idx, k.b0, k.b1, P.sblk_wgs});
+          P.sblk_wgs += k.b1 - k.b0;
         }
       }
       if (k.xbytes) {
@@ -2352,10 +2338,10 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
                          ws, 0, err);
       HIP_OR(hipGetLastError());
     }
-    if (P.sblk_lanes) {
+    if (P.sblk_wgs) {
       ProfScope ps_(prof, KP_SNAPPY_BLK, s);
-      hipLaunchKernelGGL(k_snappy_blk, dim3((P.sblk_lanes + 4 * SNAP_LANES - 1) / (4 * SNAP_LANES)), dim3(256), 0, s,
-                         d_cols, seg_table(P.sblk_segs, ws, P.ws_sblk), (const uint32_t*)nullptr, 0u, ws, err, 0);
+      hipLaunchKernelGGL(k_snappy_blk, dim3(P.sblk_wgs), dim3(512), 0, s, d_cols,
+                         seg_table(P.sblk_segs, ws, P.ws_sblk), ws, err, 0);
       HIP_OR(hipGetLastError());
     }
   } else {
@@ -2371,8 +2357,7 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
       if (sp.b1 > sp.b0) {
         ProfScope ps_(prof, KP_SNAPPY_BLK, s);
         std::vector<Segment> one{Segment{sp.cs, sp.b0, sp.b1, 0}};
-        hipLaunchKernelGGL(k_snappy_blk, dim3((sp.b1 - sp.b0 + 4 * SNAP_LANES - 1) / (4 * SNAP_LANES)), dim3(256), 0, s,
-                           d_cols, make_segs(one), (const uint32_t*)nullptr, 0u, ws, err, 0);
+        hipLaunchKernelGGL(k_snappy_blk, dim3(sp.b1 - sp.b0), dim3(512), 0, s, d_cols, make_segs(one), ws, err, 0);
         HIP_OR(hipGetLastError());
       }
     }

@@ -196,4 +196,55 @@ __device__ __forceinline__ uint64_t get_bits(const uint8_t* base4, uint64_t bit,
   return w == 64 ? v : (v & ((1ull << w) - 1));
 }
 
+// LDS and global pointers with their address spaces
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+typedef __attribute__((address_space(1))) const uint8_t glb_u8;
+typedef __attribute__((address_space(1))) const uint32_t glb_u32;
+typedef __attribute__((address_space(1))) const uint64_t glb_u64;
+
+// Inclusive wave scans with DPP moves (no LDS): row_shr 1, 2, 4, 8 scan each
+// row of 16 lanes, then row_bcast:15 and row_bcast:31 carry the rows' totals
+// into rows 1, 3 and 2, 3.  Lanes whose source is outside the row read 0.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp0(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+constexpr int DPP_ROW_SHR = 0x110, DPP_BCAST15 = 0x142, DPP_BCAST31 = 0x143;
+
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
+  v += dpp0<DPP_ROW_SHR | 1, 0xf>(v);
+  v += dpp0<DPP_ROW_SHR | 2, 0xf>(v);
+  v += dpp0<DPP_ROW_SHR | 4, 0xf>(v);
+  v += dpp0<DPP_ROW_SHR | 8, 0xf>(v);
+  v += dpp0<DPP_BCAST15, 0xa>(v);
+  v += dpp0<DPP_BCAST31, 0xc>(v);
+  return v;
+}
+
+// Orders this wave's LDS accesses (no other wave takes part).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The segment holding `unit` (the last one whose first unit is at most
+// `unit`): a scan of the inline table, or a binary search of the device
+// table of a launch with more than MAX_SEGS segments.
+__device__ __forceinline__ Segment seg_lookup(const SegTable& seg, uint32_t unit) {
+  if (seg.n <= MAX_SEGS) {
+    int k = 0;
+    for (int j = 1; j < seg.n; ++j)
+      if (seg.s[j].wg0 <= unit) k = j;
+    return seg.s[k];
+  }
+  uint32_t lo = 0, hi = (uint32_t)seg.n;
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (seg.ptr[mid].wg0 <= unit) lo = mid; else hi = mid;
+  }
+  return seg.ptr[lo];
+}
+
 }  // namespace pqk

@@ -157,6 +157,7 @@ struct PageDev {
   uint64_t x_src;
   uint32_t x_len, x_sfx, x_chars, xlen, x_total, x_scratch;
   uint64_t x_off;
+  uint64_t sbit_begin;   // compressed pages: first 16-bit entry of the page's element start bits
 };
 
 // Definition-level streams of OPTIONAL data pages (the levels before the
@@ -259,20 +260,13 @@ constexpr uint8_t E_UNDECODED = 0xff;
 // blocks; entry b holds the stream offset of the element that starts block
 // b.  A page's first entry is SBLK_NONE when some element straddles a block
 // boundary or a copy reaches before its block's start: such a page is
-// decompressed sequentially, the others one block per lane.
+// decompressed sequentially, the others one workgroup per block.
 constexpr uint32_t SNAP_BLOCK = 65536;
-// k_snappy_blk: blocks decoded per wave; the wave's other lanes only help
-// copy long literals.  A wave runs as many batches as its densest block
-// needs, so more blocks per wave leave more lanes idle, and fewer leave
-// more waves per SIMD: 16 measured best (8, 32 and 64 were slower).
-constexpr uint32_t SNAP_LANES = 16;
 constexpr uint32_t SBLK_NONE = 0xffffffffu;
-// k_snap_order: a scan's blocks in buckets of element count (bucket 0: 8192
-// or more, bucket k: [2^(13-k), 2^(14-k)), the last: fewer than 128), the
-// densest first, so that the blocks of a k_snappy_blk wave take similar
-// numbers of steps.  A bucket entry is (column-table index << 26) | block.
-constexpr uint32_t SNAP_BUCKETS = 8;
-constexpr uint32_t SNAP_ORD_BITS = 26;
+// Start bits of a compressed page's elements, one per stream byte from the
+// 16-byte boundary at or before the stream's first byte (m bytes before it);
+// a page's bits start at an even 16-bit entry, sbit_begin.
+__host__ __device__ inline uint32_t snap_bit_words(uint32_t m, uint32_t n) { return (m + n + 31) / 32; }
 
 // One tile: rows [row0, row0 + min(TILE_ROWS, num_values - row0)) of page `page`.
 struct TileDev {
@@ -334,7 +328,7 @@ struct FileDev {
                                // DELTA_LENGTH_BYTE_ARRAY tiles (NULL when the file has none)
   uint32_t* sblk;              // Snappy block index (written by the open-time pass)
   const uint32_t* sblk_page;   // page of each Snappy block
-  uint32_t* sblk_ne;           // elements of each Snappy block (written with sblk)
+  uint16_t* sbits;             // start bits of the Snappy elements (written with sblk)
   const DictSlot* dicts;       // resident dictionaries, one per chunk (col * nrg + rg)
 };
 

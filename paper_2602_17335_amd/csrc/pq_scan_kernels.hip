@@ -101,12 +101,6 @@ __device__ __forceinline__ Streams page_streams(const PageDev& pg, const ColScan
 // past `len`; every stream lies inside the file (followed by at least its
 // footer) or inside a decompressed region (followed by SCRATCH_PAD bytes).
 // ---------------------------------------------------------------------------
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
-typedef __attribute__((address_space(1))) const uint8_t glb_u8;
-typedef __attribute__((address_space(1))) const uint32_t glb_u32;
-typedef __attribute__((address_space(1))) const uint64_t glb_u64;
-
 template <class T>
 __device__ __forceinline__ __attribute__((address_space(1))) T* gptr(T* p) {
   return (__attribute__((address_space(1))) T*)p;
@@ -227,25 +221,6 @@ __device__ __forceinline__ GSrc32 gsrc32(const uint8_t* base, uint64_t a0, uint6
 // ---------------------------------------------------------------------------
 // wave and workgroup scans
 // ---------------------------------------------------------------------------
-// Inclusive wave scans with DPP moves (no LDS): row_shr 1, 2, 4, 8 scan each
-// row of 16 lanes, then row_bcast:15 and row_bcast:31 carry the rows' totals
-// into rows 1, 3 and 2, 3.  Lanes whose source is outside the row read 0.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t dpp0(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
-}
-constexpr int DPP_ROW_SHR = 0x110, DPP_BCAST15 = 0x142, DPP_BCAST31 = 0x143;
-
-__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
-  v += dpp0<DPP_ROW_SHR | 1, 0xf>(v);
-  v += dpp0<DPP_ROW_SHR | 2, 0xf>(v);
-  v += dpp0<DPP_ROW_SHR | 4, 0xf>(v);
-  v += dpp0<DPP_ROW_SHR | 8, 0xf>(v);
-  v += dpp0<DPP_BCAST15, 0xa>(v);
-  v += dpp0<DPP_BCAST31, 0xc>(v);
-  return v;
-}
-
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint64_t dpp_add_u64(uint64_t v) {
   const uint32_t lo = dpp0<CTRL, ROWS>((uint32_t)v), hi = dpp0<CTRL, ROWS>((uint32_t)(v >> 32));
@@ -267,13 +242,6 @@ __device__ __forceinline__ uint64_t wave_read_u64(uint64_t v, int lane) {
          ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32);
 }
 
-// Orders this wave's LDS accesses (no other wave takes part).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // bits of `m` below this lane
 __device__ __forceinline__ uint32_t rank_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -291,24 +259,6 @@ struct WaveTile {
   uint32_t nrows;
   int64_t out0;    // output row of the tile's first row
 };
-
-// The segment holding `unit` (the last one whose first unit is at most
-// `unit`): a scan of the inline table, or a binary search of the device
-// table of a launch with more than MAX_SEGS segments.
-__device__ __forceinline__ Segment seg_lookup(const SegTable& seg, uint32_t unit) {
-  if (seg.n <= MAX_SEGS) {
-    int k = 0;
-    for (int j = 1; j < seg.n; ++j)
-      if (seg.s[j].wg0 <= unit) k = j;
-    return seg.s[k];
-  }
-  uint32_t lo = 0, hi = (uint32_t)seg.n;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (seg.ptr[mid].wg0 <= unit) lo = mid; else hi = mid;
-  }
-  return seg.ptr[lo];
-}
 
 // A condition the caller knows to be the same in every lane, as the compiler
 // sees it too: an early exit on it is a uniform branch (a divergent one
@@ -1331,549 +1281,6 @@ __global__ __launch_bounds__(64) void k_snappy(const ColScan* cols, SegTable seg
   }
   if (bad && lane == 0) set_err(err, ERR_SNAPPY, p);
 }
-
-// k_snap_index (open): the Snappy block index of every compressed page, from
-// a walk over its element tags alone, one wave per page with the stream
-// staged in LDS (literal bytes are skipped, not read).  Entry b of a page is
-// the stream offset of the element that starts output block b; the page's
-// first entry is SBLK_NONE when an element straddles a block boundary, a
-// copy reaches before the start of its block, or the stream is malformed:
-// such a page is decompressed sequentially by k_snappy, which reports what
-// is wrong.  The walk also counts each block's elements (sblk_ne), by which
-// a scan orders its blocks.  (One lane per page, with a private LDS window
-// each, was three times slower.)
-__global__ __launch_bounds__(64) void k_snap_index(const ColScan* cols, SegTable seg) {
-  __shared__ __align__(16) uint32_t s_in[SNAP_IN / 4 + 4];
-  const uint32_t gw = blockIdx.x;
-  const uint32_t lane = threadIdx.x & 63;
-  const Segment sg = seg_lookup(seg, gw);
-  const uint32_t p = sg.t0 + (gw - sg.wg0);
-  if (p >= sg.t1) return;
-  const ColScan cs = cols[sg.cs];
-  const PageDev pg = cs.fd.pages[p];
-  uint32_t* sblk = cs.fd.sblk;
-  if (pg.scratch_len == 0 || !open_sel_ok(cs, pg)) return;
-  uint64_t src_off = pg.payload, src_len64 = pg.comp_size;
-  if (pg.kind == PAGE_DATA_V2) { src_off += (uint64_t)pg.rep_len + (uint64_t)pg.def_len; src_len64 -= (uint64_t)pg.rep_len + (uint64_t)pg.def_len; }
-  const uint8_t* src = cs.fd.file + src_off;
-  const uint32_t total = pg.scratch_len;
-  const uint32_t m = (uint32_t)((uintptr_t)src & 3);
-  SnapIn in;
-  in.base = (glb_u32*)(src - m);
-  const uint32_t iend = m + (uint32_t)min(src_len64, (uint64_t)0x7fffffffu);
-  in.lim = iend;
-  in.buf = (lds_u32*)&s_in[0];
-  uint32_t ip = m;
-  in.fill(ip);
-  bool ok = src_len64 < 0x7fffffffull;
-  {  // stream length (varint)
-    uint64_t v = 0;
-    int sft = 0;
-    for (;;) {
-      if (!ok || ip >= iend || sft > 28) { ok = false; break; }
-      const uint32_t b = (uint32_t)in.bytes8(in.at(ip++)) & 0xffu;
-      v |= (uint64_t)(b & 0x7f) << sft;
-      if (!(b & 0x80)) break;
-      sft += 7;
-    }
-    if (ok && v != total) ok = false;
-  }
-  const uint32_t first = ip - m;
-  uint32_t op = 0, ne = 0;  // ne: elements of the current block
-  while (ok && ip < iend) {
-    const uint64_t x = in.bytes8(in.at(ip));
-    const uint32_t t = (uint32_t)x & 0xffu;
-    if (op && (op & (SNAP_BLOCK - 1)) == 0) {
-      if (lane == 0) {
-        sblk[pg.sblk_begin + op / SNAP_BLOCK] = ip - m;
-        cs.fd.sblk_ne[pg.sblk_begin + op / SNAP_BLOCK - 1] = ne;
-      }
-      ne = 0;
-    }
-    uint32_t len, hl;
-    if ((t & 3) == 0) {  // literal
-      uint32_t l = t >> 2;
-      hl = 1;
-      if (l >= 60) {
-        const uint32_t nb = l - 59;
-        l = (uint32_t)(x >> 8) & (nb == 4 ? 0xffffffffu : ((1u << (8 * nb)) - 1));
-        hl += nb;
-      }
-      const uint64_t L64 = (uint64_t)l + 1;
-      if ((uint64_t)ip + hl + L64 > iend || L64 > total - op) { ok = false; break; }
-      len = (uint32_t)L64;
-      ip += hl + len;
-    } else {  // copy
-      uint32_t off;
-      if ((t & 3) == 1) {
-        hl = 2;
-        len = 4 + ((t >> 2) & 7);
-        off = ((t >> 5) << 8) | ((uint32_t)(x >> 8) & 0xffu);
-      } else if ((t & 3) == 2) {
-        hl = 3;
-        len = (t >> 2) + 1;
-        off = (uint32_t)(x >> 8) & 0xffffu;
-      } else {
-        hl = 5;
-        len = (t >> 2) + 1;
-        off = (uint32_t)(x >> 8);
-      }
-      if (ip + hl > iend || off == 0 || off > op || len > total - op) { ok = false; break; }
-      if (off > op % SNAP_BLOCK) { ok = false; break; }  // reaches before its block
-      ip += hl;
-    }
-    if (op / SNAP_BLOCK != (op + len - 1) / SNAP_BLOCK) { ok = false; break; }  // straddles a boundary
-    op += len;
-    ++ne;
-  }
-  if (op != total) ok = false;
-  if (lane == 0 && ok && total) cs.fd.sblk_ne[pg.sblk_begin + (total - 1) / SNAP_BLOCK] = ne;
-  if (lane == 0) sblk[pg.sblk_begin] = ok ? first : SBLK_NONE;
-}
-
-// One lane copies n <= 64 bytes src -> dst (no overlap) with one round of
-// loads: five 16-byte loads from the source's dword (16-byte loads need only
-// dword alignment) give the run, and destination dword j (dword-aligned)
-// gets bytes [4 j - d, 4 j - d + 4) of it, realigned with byte funnel
-// shifts.  The lane writes its block front to back, so the bytes before the
-// run (the head of dword 0) are kept, written bytewise, while the at most 3
-// bytes after the run's last dword are left for the next element to
-// overwrite (a block ends on a 16-byte boundary, a page inside its scratch
-// padding).  Reads at most 3 bytes before and 16 after the range.  The
-// source may be this lane's own earlier output: a lane's loads see its
-// earlier stores (program order), so no wait is needed.
-typedef uint32_t u32x4a __attribute__((ext_vector_type(4), aligned(4)));
-// lane_copy64 in two halves: the loads (into w), and the stores of the run
-// from w (sh: the source's byte offset in its dword).
-__device__ __forceinline__ void lane_load64(const uint8_t* src, uint32_t n, uint32_t (&w)[20]) {
-  const uint32_t sh = (uint32_t)((uintptr_t)src & 3);
-  const __attribute__((address_space(1))) u32x4a* q =
-      (const __attribute__((address_space(1))) u32x4a*)((uintptr_t)src & ~(uintptr_t)3);
-  const uint32_t nq = (sh + n + 3) >> 2;  // source dwords, <= 17
-#pragma unroll
-  for (int c = 0; c < 5; ++c) {
-    u32x4a x = {0u, 0u, 0u, 0u};
-    if ((uint32_t)(4 * c) < nq) x = q[c];
-    w[4 * c] = x.x; w[4 * c + 1] = x.y; w[4 * c + 2] = x.z; w[4 * c + 3] = x.w;
-  }
-}
-__device__ __forceinline__ void lane_store64(uint8_t* dst, uint32_t sh, uint32_t n, const uint32_t (&w)[20]) {
-  const uint32_t d = (uint32_t)((uintptr_t)dst & 3);
-  // destination byte 4 j + i holds run byte 4 j + i - d = w byte 4 j + i + (sh - d)
-  const int32_t e = (int32_t)sh - (int32_t)d;  // -3 .. 3
-  const uint32_t fs = (uint32_t)e & 3u;
-  const bool back = e < 0;  // the word's first byte is in w[j - 1]
-  __attribute__((address_space(1))) uint32_t* dw =
-      (__attribute__((address_space(1))) uint32_t*)((uintptr_t)dst & ~(uintptr_t)3);
-  const uint32_t nd = (d + n + 3) >> 2;  // destination dwords, <= 17
-#pragma unroll
-  for (int j = 0; j < 17; ++j) {
-    const uint32_t lo = back ? (j > 0 ? w[j - 1] : 0u) : w[j];
-    const uint32_t hi = back ? w[j] : (j + 1 < 20 ? w[j + 1] : 0u);
-    const uint32_t o = __builtin_amdgcn_alignbyte(hi, lo, fs);
-    if (j == 0 && d) {
-      uint8_t* bp = (uint8_t*)dw;
-#pragma unroll
-      for (int i = 1; i < 4; ++i)
-        if ((uint32_t)i >= d && (uint32_t)i - d < n) bp[i] = (uint8_t)(o >> (8 * i));
-    } else if ((uint32_t)j < nd) {
-      dw[j] = o;
-    }
-  }
-}
-__device__ __forceinline__ void lane_copy64(uint8_t* dst, const uint8_t* src, uint32_t n) {
-  uint32_t w[20];
-  lane_load64(src, n, w);
-  lane_store64(dst, (uint32_t)((uintptr_t)src & 3), n, w);
-}
-
-// The wave's active lanes (rank r of nact) copy n bytes s -> d together (a
-// literal: no overlap), 16 destination bytes per lane and step, the loads of
-// WC_UNROLL steps issued before their stores.  Destination dword k (counted
-// from d's dword) holds source bytes [4 k - sh, 4 k - sh + 4), sh = d & 3;
-// every dword is stored whole except dword 0 when d is not dword-aligned
-// (its bytes before d are earlier output, written bytewise), so up to 3
-// bytes after d + n are overwritten, which the owning lane's next element
-// writes again (a block ends on a 16-byte boundary, a page inside its
-// scratch padding).  Reads at most 3 bytes before s and 7 after s + n.
-constexpr int WC_UNROLL = 2;
-__device__ __forceinline__ void wave_copy(uint8_t* d, const uint8_t* s, uint32_t n, uint32_t r, uint32_t nact) {
-  const uint32_t sh = (uint32_t)((uintptr_t)d & 3);
-  __attribute__((address_space(1))) uint32_t* dw =
-      (__attribute__((address_space(1))) uint32_t*)((uintptr_t)d & ~(uintptr_t)3);
-  const uint32_t nd = (sh + n + 3) >> 2;       // destination dwords
-  const uintptr_t a0 = (uintptr_t)s - sh;      // source byte of destination dword 0's first byte
-  const uint32_t e = (uint32_t)(a0 & 3);
-  const __attribute__((address_space(1))) uint32_t* q =
-      (const __attribute__((address_space(1))) uint32_t*)(a0 & ~(uintptr_t)3);
-  const uint32_t step = 4 * nact;
-  for (uint32_t k0 = 4 * r; k0 < nd; k0 += WC_UNROLL * step) {
-    uint32_t w[WC_UNROLL][5];
-#pragma unroll
-    for (int u = 0; u < WC_UNROLL; ++u) {
-      const uint32_t kk = k0 + u * step;
-#pragma unroll
-      for (int c = 0; c < 5; ++c) w[u][c] = kk + c <= nd ? q[kk + c] : 0u;
-    }
-#pragma unroll
-    for (int u = 0; u < WC_UNROLL; ++u) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t k = k0 + u * step + j;
-        const uint32_t v = __builtin_amdgcn_alignbyte(w[u][j + 1], w[u][j], e);
-        if (k == 0 && sh) {
-          uint8_t* bp = (uint8_t*)dw;
-#pragma unroll
-          for (int i = 1; i < 4; ++i)
-            if ((uint32_t)i >= sh && (uint32_t)i - sh < n) bp[i] = (uint8_t)(v >> (8 * i));
-        } else if (k < nd) {
-          dw[k] = v;
-        }
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// k_snappy_blk: the pages of the Snappy block index, one lane per 64 KiB
-// output block (SNAP_LANES blocks of one or several pages advance together
-// in a wave, whose other lanes join every copy of a literal longer than 64
-// bytes).  A lane decodes its block in batches: up to SNAP_BATCH short
-// elements (at most SNAP_SHORT bytes each) are parsed from the lane's
-// SNAP_WIN-byte window of the stream in LDS, then all their sources are
-// loaded (one 16-byte load each: the literal's stream bytes or the copy's
-// earlier output), then all are stored, so that a batch costs one memory
-// round trip instead of one per element.  A copy whose source lies in the
-// batch's own output reads it from a per-lane LDS copy of that output (a
-// source starting before the copy's first dword ends the batch); a longer
-// element, or a copy overlapping its own output, ends the batch and is
-// decoded on its own after the batch's stores (a literal of at most 64
-// bytes with its stream bytes loaded beside the batch's sources).  Loads see
-// the lane's earlier stores (program order), so no wait is needed between
-// batches.  With sord, a scan's blocks come densest first (k_snap_order), so
-// that the blocks of a wave need similar numbers of batches.
-// ---------------------------------------------------------------------------
-constexpr int SNAP_BATCH = 8;
-constexpr uint32_t SNAP_SHORT = 13;  // a run of up to 13 bytes lies in the 16 bytes from its dword
-constexpr uint32_t SNAP_WIN = 64;
-constexpr uint32_t SNAP_WSTRIDE = 20;  // dwords per lane window (80 bytes: fewer bank conflicts)
-// dwords per lane of the batch's output in LDS (from the dword holding the
-// batch's first byte; 16 bytes per element written, at most SNAP_SHORT apart)
-constexpr uint32_t SNAP_BSTRIDE = ((SNAP_BATCH * SNAP_SHORT + 20 + 15) / 16) * 4 + 4;
-// One lane's block of k_snappy_blk: its page's compressed stream, output
-// region and element range.  False for a lane without a block (past the
-// segment, a page that is not compressed or is decoded by k_snappy).
-struct SnapLane {
-  const uint8_t* src;
-  uint8_t* dst;
-  uint32_t ip, iend, ob, oend, page, pad_;
-  bool bad;
-};
-// Block b of column-table entry csi.
-__device__ __forceinline__ bool snap_lane_at(const ColScan* cols, uint32_t csi, uint32_t b, uint8_t* ws, SnapLane& sl,
-                                             bool dicts) {
-  const ColScan cs = cols[csi];
-  const uint32_t* sblk = cs.fd.sblk;
-  const uint32_t p = cs.fd.sblk_page[b];
-  const PageDev pg = cs.fd.pages[p];
-  if (pg.scratch_len == 0 || (pg.kind == PAGE_DICT && !dicts)) return false;  // dictionaries: decompressed at open
-  if (dicts && !open_sel_ok(cs, pg)) return false;
-  const uint32_t first = pg.sblk_begin;
-  if (sblk[first] == SBLK_NONE) return false;  // decoded sequentially by k_snappy
-  uint64_t src_off = pg.payload, src_len64 = pg.comp_size;
-  if (pg.kind == PAGE_DATA_V2) { src_off += (uint64_t)pg.rep_len + (uint64_t)pg.def_len; src_len64 -= (uint64_t)pg.rep_len + (uint64_t)pg.def_len; }
-  const uint32_t total = pg.scratch_len;
-  const uint32_t src_len = (uint32_t)src_len64;
-  const uint32_t kb = b - first, nblk = (total + SNAP_BLOCK - 1) / SNAP_BLOCK;
-  sl.src = cs.fd.file + src_off;
-  sl.dst = ws + cs.ws_scratch + (pg.scratch_off - cs.scratch_base);
-  sl.ip = sblk[b];
-  sl.iend = kb + 1 < nblk ? sblk[b + 1] : src_len;
-  sl.ob = kb * SNAP_BLOCK;  // the block's first output byte
-  sl.oend = min(sl.ob + SNAP_BLOCK, total);
-  sl.page = p;
-  sl.bad = src_len64 >= 0x7fffffffull || sl.ip > sl.iend || sl.iend > src_len;
-  return true;
-}
-// Lane gid's block: from the density buckets sord (when given), else from
-// the segment table.
-__device__ __forceinline__ bool snap_lane(const ColScan* cols, const SegTable& seg, const uint32_t* sord,
-                                          uint32_t cap, uint8_t* ws, uint32_t gid, SnapLane& sl, bool dicts) {
-  if (sord) {
-    uint32_t base = 0, e = ~0u;
-#pragma unroll
-    for (uint32_t k = 0; k < SNAP_BUCKETS; ++k) {
-      const uint32_t c = sord[k];
-      if (gid >= base && gid - base < c) e = sord[64 + k * cap + (gid - base)];
-      base += c;
-    }
-    if (e == ~0u) return false;
-    return snap_lane_at(cols, e >> SNAP_ORD_BITS, e & ((1u << SNAP_ORD_BITS) - 1), ws, sl, dicts);
-  }
-  const Segment sg = seg_lookup(seg, gid);
-  const uint32_t b = sg.t0 + (gid - sg.wg0);
-  if (b >= sg.t1) return false;
-  return snap_lane_at(cols, sg.cs, b, ws, sl, dicts);
-}
-
-// k_snap_order (scans): mode 0 clears the bucket counters sord[0 ..
-// SNAP_BUCKETS); mode 1 puts every block of the segment table that
-// k_snappy_blk decodes into the bucket of its element count (bucket k's list
-// at sord + 64 + k cap; the order within a bucket is immaterial).
-__global__ __launch_bounds__(WG) void k_snap_order(const ColScan* cols, SegTable seg, uint8_t* ws, uint32_t* sord,
-                                                   uint32_t cap, int mode) {
-  const uint32_t gid = blockIdx.x * WG + threadIdx.x;
-  if (mode == 0) {
-    if (gid < SNAP_BUCKETS) sord[gid] = 0;
-    return;
-  }
-  const Segment sg = seg_lookup(seg, gid);
-  const uint32_t b = sg.t0 + (gid - sg.wg0);
-  SnapLane sl;
-  const bool ok = b < sg.t1 && snap_lane_at(cols, sg.cs, b, ws, sl, false);
-  uint32_t k = SNAP_BUCKETS;
-  if (ok) {
-    const uint32_t ne = max(cols[sg.cs].fd.sblk_ne[b], 1u);
-    const uint32_t lg = 31u - (uint32_t)__builtin_clz(ne);
-    k = lg >= 13u ? 0u : lg <= 6u ? SNAP_BUCKETS - 1 : 13u - lg;
-  }
-  // one atomic per bucket and wave; a lane's slot is its rank among the
-  // wave's lanes of its bucket
-  const uint32_t lane = threadIdx.x & 63;
-  const uint64_t below = (lane ? ~0ull >> (64 - lane) : 0ull);
-  uint32_t slot = 0;
-#pragma unroll
-  for (uint32_t kb = 0; kb < SNAP_BUCKETS; ++kb) {
-    const uint64_t m = __ballot(k == kb);
-    if (!m) continue;
-    const int lead = __builtin_ctzll(m);
-    uint32_t base = 0;
-    if ((int)lane == lead) base = atomicAdd(&sord[kb], (uint32_t)__popcll(m));
-    base = (uint32_t)__builtin_amdgcn_readlane((int)base, lead);
-    if (k == kb) slot = base + (uint32_t)__popcll(m & below);
-  }
-  if (ok) sord[64 + k * cap + slot] = (sg.cs << SNAP_ORD_BITS) | b;
-}
-
-// The 16 bytes from output dword k0 of a short element: bytes [sh, sh + n)
-// of v (sh <= 3, n <= SNAP_SHORT) placed at byte d = dop & 3, the d bytes
-// before them taken from tw (the earlier output of that dword); the bytes
-// after the run are whatever v holds there.
-__device__ __forceinline__ u32x4a place_short(const u32x4a v, uint32_t sh, uint32_t d, uint32_t tw) {
-  // output byte 4 k + i (k = 0..3) is v byte 4 k + i + (sh - d)
-  const int32_t e = (int32_t)sh - (int32_t)d;  // -3 .. 3
-  const uint32_t fs = (uint32_t)e & 3u;
-  const bool back = e < 0;
-  const uint32_t u[6] = {0u, v.x, v.y, v.z, v.w, 0u};  // u[i + 1] = v[i]
-  uint32_t o[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-    o[k] = __builtin_amdgcn_alignbyte(back ? u[k + 1] : u[k + 2], back ? u[k] : u[k + 1], fs);
-  const uint32_t m = (1u << (8 * d)) - 1u;  // the bytes before the run
-  o[0] = (o[0] & ~m) | (tw & m);
-  return u32x4a{o[0], o[1], o[2], o[3]};
-}
-
-// dicts = 1 (open): dictionary pages too.  sord: the density buckets of
-// k_snap_order (cap entries each), or null for the segment table's order.
-__global__ __launch_bounds__(WG) void k_snappy_blk(const ColScan* cols, SegTable seg, const uint32_t* sord,
-                                                   uint32_t cap, uint8_t* ws, uint32_t* err, int dicts) {
-  __shared__ __align__(16) uint32_t s_win[WG / 64][SNAP_LANES][SNAP_WSTRIDE];
-  __shared__ __align__(16) uint32_t s_bat[WG / 64][SNAP_LANES][SNAP_BSTRIDE];
-  const uint32_t lw = threadIdx.x & 63;
-  const uint32_t gid = (blockIdx.x * WG + threadIdx.x) / 64 * SNAP_LANES + lw;
-  // lanes lw >= SNAP_LANES decode no block: they stay in the loop to help
-  // copy long literals
-  SnapLane sl = {nullptr, nullptr, 0u, 0u, 0u, 0u, 0u, 0u, false};
-  const bool live = lw < SNAP_LANES && snap_lane(cols, seg, sord, cap, ws, gid, sl, dicts != 0);
-  const uint8_t* src = sl.src;
-  uint8_t* dst = sl.dst;
-  uint32_t ip = sl.ip, op = sl.ob;
-  const uint32_t iend = sl.iend, ob = sl.ob, oend = sl.oend, p = sl.page;
-  bool bad = sl.bad;
-  lds_u32* win = (lds_u32*)&s_win[threadIdx.x / 64][lw < SNAP_LANES ? lw : 0][0];
-  lds_u32* bat = (lds_u32*)&s_bat[threadIdx.x / 64][lw < SNAP_LANES ? lw : 0][0];
-  typedef const __attribute__((address_space(1))) u32x4a* gq4;
-  typedef __attribute__((address_space(1))) u32x4a* gs4;
-  // loads of unused batch slots and of lanes without a block read this
-  // (valid, never written) address
-  const uintptr_t dummy = (uintptr_t)cols;
-  // the window: the SNAP_WIN stream bytes from the dword holding byte ip,
-  // loaded during the previous batch (pieces that start past the stream's
-  // end read the dummy address instead)
-  const uintptr_t send = (uintptr_t)(src + iend);
-  uintptr_t wa = 0;
-  u32x4a wv[SNAP_WIN / 16];
-  auto wload = [&]() {
-    wa = (uintptr_t)(src + ip) & ~(uintptr_t)3;
-#pragma unroll
-    for (int c = 0; c < (int)(SNAP_WIN / 16); ++c) wv[c] = *(gq4)(wa + 16 * c < send ? wa + 16 * c : dummy);
-  };
-  wload();
-  uint32_t tw = 0;  // the output dword holding byte op (its bytes before op are final)
-  bool run = live && !bad && op < oend;
-  while (__ballot(run)) {
-    // the batch: element j is n bytes (nk[j] & 0xff; nk[j] & 0x100 marks a
-    // copy, & 0x200 one whose source lies in this batch's output) to output
-    // offset dop[j] from offset so[j] of the stream (a literal) or of the
-    // output (a copy)
-    uint32_t dop[SNAP_BATCH], so[SNAP_BATCH], nk[SNAP_BATCH];
-    uint32_t nb = 0;
-    // the element decoded alone after the batch: kind 1 a literal of at most
-    // 64 bytes, 2 a longer literal (the whole wave copies it), 3 a copy
-    // that does not overlap its output, 4 one that does
-    uint32_t skind = 0, sop = 0, ssrc = 0, sn = 0, soff = 0;
-    if (run) {
-#pragma unroll
-      for (int c = 0; c < (int)(SNAP_WIN / 16); ++c)
-        *reinterpret_cast<__attribute__((address_space(3))) u32x4*>(win + 4 * c) =
-            u32x4{wv[c].x, wv[c].y, wv[c].z, wv[c].w};
-    }
-    {
-      const uint32_t bop0 = op;  // the output before bop0 is stored
-      bool act = run;
-#pragma unroll
-      for (int j = 0; j < SNAP_BATCH; ++j) {
-        // every step is computed, and applied only where `take` holds
-        const uint32_t o = (uint32_t)((uintptr_t)(src + ip) - wa);
-        const bool room = o + 5 <= SNAP_WIN;
-        const uint32_t oc = room ? o : 0u;
-        const uint32_t w0 = win[oc >> 2], w1 = win[(oc >> 2) + 1];
-        const uint32_t x = __builtin_amdgcn_alignbyte(w1, w0, oc & 3);  // bytes o .. o + 3
-        const uint32_t x4 = (w1 >> (8 * (oc & 3))) & 0xffu;            // byte o + 4
-        const uint32_t t = x & 0xffu, ty = t & 3u, l6 = t >> 2;
-        const uint32_t b1234 = (x >> 8) | (x4 << 24);  // bytes o + 1 .. o + 4
-        // a literal: length l6 + 1, or (l6 >= 60) the next l6 - 59 bytes + 1
-        const uint32_t nbb = l6 >= 60u ? l6 - 59u : 0u;
-        const uint32_t lsh = (32u - 8u * nbb) & 31u;
-        const uint32_t lext = (b1234 << lsh) >> lsh;
-        const uint32_t llen = (nbb ? lext : l6) + 1u;
-        // a copy with a 1-byte (ty 1), 2-byte (2) or 4-byte (3) offset
-        const uint32_t c1len = 4u + (l6 & 7u), cnlen = l6 + 1u;
-        const uint32_t c1off = ((t >> 5) << 8) | (b1234 & 0xffu);
-        const uint32_t cnoff = b1234 & (0xffffffffu >> (ty == 2u ? 16u : 0u));
-        const bool lit = ty == 0u, c1 = ty == 1u;
-        const uint32_t len = lit ? llen : (c1 ? c1len : cnlen);
-        const uint32_t off = c1 ? c1off : cnoff;
-        const uint32_t hl = lit ? 1u + nbb : ty + 1u + (ty >> 1 & ty & 1u);
-        const bool go = act & (op < oend) & room;
-        const bool ipend = ip >= iend;
-        const uint32_t rin = ipend ? 0u : iend - ip;  // stream bytes left
-        bool bd = ipend | (hl > rin) | (len > oend - op);
-        bd |= lit ? ((len == 0u) | (len > rin - hl)) : ((off == 0u) | (off > op - ob));
-        bd &= go;
-        const bool shortok = (len <= SNAP_SHORT) & (op + 16u <= oend) & (lit | (off >= len));
-        // a source reaching into this batch's output is read from the batch's
-        // copy in LDS, unless it starts before that copy's first dword
-        const bool insrc = !lit & (op - off + len > bop0);
-        const bool conflict = shortok & insrc & (op - off < (bop0 & ~3u));
-        const bool take = go & !bd & !conflict;
-        const bool bat = take & shortok;
-        const bool slw = take & !shortok;
-        dop[j] = op;
-        so[j] = lit ? ip + hl : op - off;
-        nk[j] = len | (lit ? 0u : 0x100u) | (insrc ? 0x200u : 0u);
-        nb = bat ? (uint32_t)j + 1u : nb;
-        const uint32_t kind = lit ? 1u + (uint32_t)(len > 64u) : 3u + (uint32_t)(off < len);
-        skind = slw ? kind : skind;
-        sop = slw ? op : sop;
-        ssrc = slw ? ip + hl : ssrc;
-        sn = slw ? len : sn;
-        soff = slw ? off : soff;
-        bad |= bd;
-        ip = take ? ip + hl + (lit ? len : 0u) : ip;
-        op = take ? op + len : op;
-        act = bat;
-      }
-    }
-    // the batch's sources, then the next window, then the batch's stores
-    u32x4a v[SNAP_BATCH];
-#pragma unroll
-    for (int j = 0; j < SNAP_BATCH; ++j) {
-      const uintptr_t a = (nk[j] & 0x100u) ? (uintptr_t)dst + so[j] : (uintptr_t)src + so[j];
-      v[j] = *(gq4)(((uint32_t)j < nb && !(nk[j] & 0x200u) ? a : dummy) & ~(uintptr_t)3);
-    }
-    run = run && !bad;
-    // a literal of at most 64 bytes decoded alone after the batch: its stream
-    // bytes are loaded with the batch's sources (the stream is never written)
-    uint32_t sw[20];
-    if (run && skind == 1) lane_load64(src + ssrc, sn, sw);
-    wload();
-    // stored in order; when a later element of the batch has its source in
-    // this batch's output, each element's 16 bytes also go to the batch's
-    // copy in LDS (bat, from the dword holding byte bop0), where it reads them
-    const uint32_t bb0 = dop[0] & ~3u;
-    bool usebat = false;  // some element of the batch reads it
-#pragma unroll
-    for (int j = 1; j < SNAP_BATCH; ++j) usebat |= (uint32_t)j < nb && (nk[j] & 0x200u);
-#pragma unroll
-    for (int j = 0; j < SNAP_BATCH; ++j) {
-      if ((uint32_t)j < nb) {
-        const uintptr_t a = (nk[j] & 0x100u) ? (uintptr_t)dst + so[j] : (uintptr_t)src + so[j];
-        const uint32_t n = nk[j] & 0xffu, d = dop[j] & 3u;
-        u32x4a x = v[j];
-        uint32_t sh = (uint32_t)(a & 3);
-        if (nk[j] & 0x200u) {
-          const uint32_t r = so[j] - bb0, k = r >> 2;
-          x = u32x4a{bat[k], bat[k + 1], bat[k + 2], bat[k + 3]};
-          sh = r & 3u;
-        }
-        const u32x4a w = place_short(x, sh, d, tw);
-        *(gs4)((uintptr_t)dst + (dop[j] & ~3u)) = w;
-        if (usebat) {
-          const uint32_t k = ((dop[j] & ~3u) - bb0) >> 2;
-          bat[k] = w.x; bat[k + 1] = w.y; bat[k + 2] = w.z; bat[k + 3] = w.w;
-        }
-        const uint32_t te = (d + n) >> 2;  // the dword holding the element's end
-        tw = te == 0u ? w.x : te == 1u ? w.y : te == 2u ? w.z : w.w;
-      }
-    }
-    // the element decoded alone
-    bool big = false;
-    if (run && skind) {
-      if (skind == 1) {
-        lane_store64(dst + sop, (uint32_t)((uintptr_t)(src + ssrc) & 3), sn, sw);
-      } else if (skind == 2) {
-        big = true;
-      } else if (skind == 3) {
-        lane_copy64(dst + sop, dst + sop - soff, sn);
-      } else {  // bytes repeat with period soff
-        uint32_t r = 0;  // k0 mod soff, carried from chunk to chunk
-        for (uint32_t k0 = 0; k0 < sn; k0 += 8) {
-          uint32_t bb[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            bb[j] = dst[sop - soff + r];
-            r = r + 1 == soff ? 0u : r + 1;
-          }
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            if (k0 + j < sn) dst[sop + k0 + j] = (uint8_t)bb[j];
-        }
-      }
-    }
-    // long literals, one after the other, each copied by all 64 lanes (a
-    // lane's later loads see them: the wave's stores are performed in order)
-    uint64_t m = __ballot(big);
-    while (m) {
-      const int l = __builtin_ctzll(m);
-      m &= m - 1;
-      const uintptr_t bd = (uintptr_t)(dst + sop), bs = (uintptr_t)(src + ssrc);
-      uint8_t* d = (uint8_t*)(((uintptr_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(bd >> 32), l) << 32) |
-                              (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bd, l));
-      const uint8_t* s = (const uint8_t*)(((uintptr_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(bs >> 32), l) << 32) |
-                                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bs, l));
-      wave_copy(d, s, (uint32_t)__builtin_amdgcn_readlane((int)sn, l), lw, 64);
-    }
-    // after an element decoded alone, the output dword holding op is read back
-    if (run && skind && (op & 3u)) tw = *(const __attribute__((address_space(1))) uint32_t*)((uintptr_t)dst + (op & ~3u));
-    run = run && op < oend;
-  }
-  if (!live) return;
-  if (!bad && (op != oend || ip != iend)) bad = true;
-  if (bad) set_err(err, ERR_SNAPPY, p);
-}
-
 
 // ---------------------------------------------------------------------------
 // k_dba: DELTA_BYTE_ARRAY string pages, one wave per page.  Value k is the
