@@ -18,6 +18,7 @@
 namespace pqk {
 
 typedef uint32_t u32x4s __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2s __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) u32x4s lds_u32x4;
 typedef __attribute__((address_space(3))) uint16_t lds_u16;
 
@@ -292,7 +293,10 @@ __global__ __launch_bounds__(SX_WG) void k_snap_index(const ColScan* cols, SegTa
 //     positions, and each thread stores those of its bytes that are literal
 //     data (a literal that began in an earlier thread's bytes is passed on
 //     with the sum);
-//   - copies whose source lies before the pass's output are done at once;
+//   - the copies go into a list in the order of the output, one or two per
+//     thread (in the threads that found them, a dense wave would run each
+//     step for up to 8 copies a lane, a sparse one for a few lanes);
+//   - those whose source lies before the pass's output are done at once;
 //     the others mark their output bytes in a bit map of pending bytes, and,
 //     after a barrier, each is done as soon as no byte of its source is
 //     pending.  Waves need no further barrier for this: a wave's LDS accesses
@@ -304,13 +308,17 @@ __global__ __launch_bounds__(SX_WG) void k_snap_index(const ColScan* cols, SegTa
 // of the wide table, a few in most) and, in blocks of literals, the LDS byte
 // stores and the stream loads in flight.
 // Two workgroups of 512 threads fit a CU's LDS (64 KiB output, 8 KiB bit map).
-// Measured on the 4M-row wide table (5,700 blocks): 1.73 ms a scan; one lane per
-// block with the loads of 8 elements in flight together took 10.8 ms, its
-// densest block's 2,100 round trips, however few the blocks.
+// Measured on the 4M-row wide table (5,056 blocks): 0.87 ms a scan, 7,600 vector
+// instructions per wave and block (0.5 ms of issue); with the copies left to
+// the threads that found them 1.73 ms; with one lane per block and the loads of
+// 8 elements in flight together 10.8 ms, its densest block's 2,100 round trips,
+// however few the blocks.
 // ---------------------------------------------------------------------------
 constexpr uint32_t SB_WG = 512;
 constexpr uint32_t SB_BYTES = 16;  // stream bytes per thread and pass
 constexpr uint32_t SB_PASS = SB_WG * SB_BYTES;
+constexpr uint32_t SB_LIST = 944;  // copies done side by side: what the LDS of two workgroups per CU leaves
+static_assert(SB_LIST <= 2 * SB_WG, "a thread takes at most two copies of the list");
 constexpr int SB_EL = SB_BYTES / 2;  // elements starting in a thread's bytes (each takes two or more)
 
 // Bits [a, a + n) of the pending map, n <= 64: whether any is set.
@@ -374,6 +382,7 @@ __global__ __launch_bounds__(SB_WG, 4) void k_snappy_blk(const ColScan* cols, Se
                                                          int dicts) {
   __shared__ __align__(16) uint32_t s_out[SNAP_BLOCK / 4 + 4];  // (reads run up to 10 bytes past a source)
   __shared__ uint32_t s_pend[SNAP_BLOCK / 32 + 2];
+  __shared__ u32x2s s_list[SB_LIST];
   __shared__ __align__(16) uint32_t s_x[2][SB_WG / 64][4];
   const Segment sg = seg_lookup(seg, blockIdx.x);
   const uint32_t b = sg.t0 + (blockIdx.x - sg.wg0);
@@ -432,7 +441,7 @@ __global__ __launch_bounds__(SB_WG, 4) void k_snappy_blk(const ColScan* cols, Se
     // the elements: el[j] output bytes, ei[j] offset (16 bits; 0: a literal,
     // or invalid), start byte (4 bits), header bytes (3 bits), literal flag
     uint32_t el[SB_EL], ei[SB_EL];
-    uint32_t sum = 0, last_d = ~0u, last_o = 0;
+    uint32_t sum = 0, last_d = ~0u, last_o = 0, nc = 0;  // output bytes, the last element, copies
     {
       uint32_t mk = mask;
 #pragma unroll
@@ -455,11 +464,13 @@ __global__ __launch_bounds__(SB_WG, 4) void k_snappy_blk(const ColScan* cols, Se
           last_d = e.lit && !inv ? q + k + e.hl : ~0u;
           last_o = sum;
           sum += el[j];
+          nc += (ei[j] & 0xffffu) ? 1u : 0u;
         }
       }
     }
     // output positions, and the element that covers the thread's first bytes
     const uint32_t incl = wave_incl_scan_u32(sum), excl = incl - sum;
+    const uint32_t ncin = wave_incl_scan_u32(nc);
     const uint64_t hm = __ballot(mask != 0);
     const uint64_t below = hm & ((1ull << lane) - 1);
     const int from = below ? 63 - __builtin_clzll(below) : 0;
@@ -469,19 +480,21 @@ __global__ __launch_bounds__(SB_WG, 4) void k_snappy_blk(const ColScan* cols, Se
       const int top = hm ? 63 - __builtin_clzll(hm) : 0;
       const uint32_t td = (uint32_t)__builtin_amdgcn_readlane((int)last_d, top);
       const uint32_t to = (uint32_t)__builtin_amdgcn_readlane((int)(excl + last_o), top);
-      if (lane == 63) *(lds_u32x4*)((lds_u32*)&s_x[par][wave][0]) = u32x4s{incl, hm ? 1u : 0u, td, to};
+      if (lane == 63) *(lds_u32x4*)((lds_u32*)&s_x[par][wave][0]) = u32x4s{incl, ncin | (hm ? 0x80000000u : 0u), td, to};
     }
     __syncthreads();
-    uint32_t run = op, wb = 0;
+    uint32_t run = op, wb = 0, ncopy = 0, copyb = 0;
 #pragma unroll
     for (uint32_t w = 0; w < SB_WG / 64; ++w) {
       const u32x4s v = *(lds_u32x4*)((lds_u32*)&s_x[par][w][0]);
       if (w == wave) {
         wb = run;
+        copyb = ncopy + ncin - nc;
         co = below ? co + run : cov_o;
         cd = below ? cd : cov_d;
       }
-      if (v.y) {
+      ncopy += v.y & 0x7fffffffu;
+      if (v.y >> 31) {
         cov_d = v.z;
         cov_o = run + v.w;
       }
@@ -545,42 +558,65 @@ __global__ __launch_bounds__(SB_WG, 4) void k_snappy_blk(const ColScan* cols, Se
         }
       }
     }
-    // copies: first those whose source is final, then, as they become so, the rest
-    uint32_t pm = 0;
+    // copies, in the order of the output, SB_LIST at a time
+    for (uint32_t base = 0; base < ncopy; base += SB_LIST) {
+      {
+        uint32_t o = opb, poff = 0, rs = 0, c = copyb - base;
 #pragma unroll
-    for (int j = 0; j < SB_EL; ++j) pm |= (ei[j] & 0xffffu) ? 1u << j : 0u;
-    for (bool firstp = true; firstp || __ballot(pm != 0); firstp = false) {
-      uint32_t o = opb, poff = 0, rs = 0;
+        for (int j = 0; j < SB_EL; ++j) {
+          const uint32_t off = ei[j] & 0xffffu, n = el[j];
+          if (off) {
+            if (off != poff || off > 64) rs = o;  // the run of copies with this offset starts here
+            const bool wrap = o + n - rs > off;   // the source would reach past the run's start
+            const uint32_t src_o = wrap ? rs - off : o - off;
+            if (off > rs) bad = true;
+            else if (c < SB_LIST)
+              s_list[c] = u32x2s{o | (src_o << 16), n | (wrap ? (off << 8) | (((o - rs) % off) << 16) : 0u)};
+            if (off > rs && c < SB_LIST) s_list[c] = u32x2s{0u, 0u};
+            ++c;
+          }
+          poff = off;
+          o += n;
+        }
+      }
+      __syncthreads();
+      const uint32_t cnt = min(ncopy - base, SB_LIST);
+      uint32_t ex[2], ey[2];
+      bool pend[2];
 #pragma unroll
-      for (int j = 0; j < SB_EL; ++j) {
-        const uint32_t off = ei[j] & 0xffffu, n = el[j];
-        if (off) {
-          if (off != poff || off > 64) rs = o;  // the run of copies with this offset starts here
-          if ((pm >> j) & 1u) {
-            const bool wrap = o + n - rs > off;  // the source would reach past the run's start
-            const uint32_t s = wrap ? rs - off : o - off, sn = wrap ? min(off, 64u) : n;
-            if (off > rs) {
-              bad = true;
-              pm &= ~(1u << j);
-            } else if (firstp ? s + sn <= fin : !pend_any(s_pend, s, sn)) {
-              __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-              snap_copy(out, o, s, n, wrap ? off : 0u, wrap ? (o - rs) % off : 0u);
-              if (!firstp) {
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-                pend_mark<false>(s_pend, o, n);
-              }
-              pm &= ~(1u << j);
-            } else if (firstp) {
-              pend_mark<true>(s_pend, o, n);
-            }
+      for (int u = 0; u < 2; ++u) {
+        const uint32_t i = u * SB_WG + tid;
+        const u32x2s e = i < cnt ? s_list[i] : u32x2s{0u, 0u};
+        ex[u] = e.x;
+        ey[u] = e.y;
+        pend[u] = false;
+        const uint32_t n = e.y & 0x7fu, per = (e.y >> 8) & 0x7fu, o = e.x & 0xffffu, so = e.x >> 16;
+        if (n) {
+          if (so + (per ? per : n) <= fin) {
+            snap_copy(out, o, so, n, per, e.y >> 16);
+          } else {
+            pend_mark<true>(s_pend, o, n);
+            pend[u] = true;
           }
         }
-        poff = off;
-        o += n;
       }
-      if (firstp) __syncthreads();
+      __syncthreads();
+      while (__ballot(pend[0] || pend[1])) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const uint32_t n = ey[u] & 0x7fu, per = (ey[u] >> 8) & 0x7fu, o = ex[u] & 0xffffu, so = ex[u] >> 16;
+          if (pend[u] && !pend_any(s_pend, so, per ? per : n)) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+            snap_copy(out, o, so, n, per, ey[u] >> 16);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+            pend_mark<false>(s_pend, o, n);
+            pend[u] = false;
+          }
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
+    if (ncopy == 0) __syncthreads();
     // the output that became final goes to memory, 16 bytes at a time
     const bool lastp = A + SB_PASS >= qe;
     fin = run;
