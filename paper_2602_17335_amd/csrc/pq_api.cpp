@@ -71,8 +71,9 @@ __global__ void k_dict(const PageDev* pages, const uint32_t* strck, const DictSl
 __global__ void k_prepass(uint8_t* ws, const ColScan* cols, SegTable seg, int mode, uint32_t* err);
 __global__ void k_str_total(const ColScan* cols, const int32_t* which, int32_t n, uint32_t* err);
 __global__ void k_copy(uint8_t* dst, const uint8_t* src, uint64_t n);
+template <bool SMALL>
 __global__ void k_dba(const ColScan* cols, SegTable seg, uint8_t* ws, const uint8_t* open_scratch, uint8_t* open_out,
-                      PageDev* pages_out, int mode, uint32_t* err);
+                      PageDev* pages_out, DbaUnit* units_out, int mode, uint32_t* err);
 enum : int { FX_DICT = 1, FX_WIDE = 2, FX_BSS = 4 };
 template <int KIND>
 __global__ void k_decode_fixed(uint8_t* ws, const ColScan* cols, SegTable seg, uint32_t* err);
@@ -303,6 +304,9 @@ struct pq_file_s {
   std::vector<PageDev> pages;            // host copy (after the index pass)
   std::vector<uint64_t> scratch_prefix;  // per page (+ sentinel): file-wide scratch offset
   std::vector<uint64_t> xscratch_prefix; // per page (+ sentinel): expansion-layout offset (DELTA_BYTE_ARRAY pages)
+  std::vector<uint32_t> dba_unit0;       // per page (+ sentinel): first unit (DELTA_BYTE_ARRAY pages)
+  DbaUnit* d_dbau = nullptr;             // the units, and the bytes they keep (one buffer per open pass)
+  std::vector<uint8_t*> d_dbactx;
   uint64_t total_tiles = 0, total_strck = 0;
   PageDev* d_pages = nullptr;
   TileDev* d_tiles = nullptr;
@@ -395,6 +399,8 @@ static void free_handle(pq_file f) {
   if (f->d_sblk) (void)hipFree(f->d_sblk);
   if (f->d_sblk_page) (void)hipFree(f->d_sblk_page);
   if (f->d_sbits) (void)hipFree(f->d_sbits);
+  if (f->d_dbau) (void)hipFree(f->d_dbau);
+  for (uint8_t* b : f->d_dbactx) (void)hipFree(b);
   if (f->d_ckl) (void)hipFree(f->d_ckl);
   if (f->d_ckv) (void)hipFree(f->d_ckv);
   if (f->d_chunks) (void)hipFree(f->d_chunks);
@@ -617,6 +623,8 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   // ---- host layout: rows, dictionary links, tiles, scratch, checkpoints ----
   f->chunk_tile0.assign(nchunks + 1, 0);
   f->scratch_prefix.assign(npages + 1, 0);
+  f->dba_unit0.assign(npages + 1, 0);
+  uint64_t dba_units = 0;
   uint64_t tiles = 0, strck = 0, scratch = 0, sblk = 0, sbits = 0;
   std::vector<uint32_t> sblk_page;
   for (int q = 0; q < nchunks; ++q) {
@@ -627,6 +635,8 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     f->chunk_tile0[q] = (uint32_t)tiles;
     for (uint32_t p = f->chunk_page0[q]; p < f->chunk_page0[q + 1]; ++p) {
       PageDev& pg = f->pages[p];
+      f->dba_unit0[p] = (uint32_t)dba_units;
+      pg.x_unit0 = (uint32_t)dba_units;
       pg.scratch_off = scratch;  // (dictionary pages: placed after the data pages below)
       f->scratch_prefix[p] = scratch;
       uint64_t slen = 0;
@@ -661,6 +671,8 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       pg.dict_page = dict;
       pg.row0 = row;
       row += pg.num_values;
+      // (its values are at most its rows)
+      if (cd.type == T_BYTE_ARRAY && pg.encoding == E_DBA) dba_units += ((uint64_t)pg.num_values + DBA_UNIT - 1) / DBA_UNIT;
       pg.tile_begin = (uint32_t)tiles;
       tiles += ((uint64_t)pg.num_values + TILE_ROWS - 1) / TILE_ROWS;
       if (cd.type == T_BYTE_ARRAY && (pg.encoding == E_PLAIN || pg.encoding == E_DBA)) {
@@ -671,6 +683,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   }
   f->chunk_tile0[nchunks] = (uint32_t)tiles;
   f->scratch_prefix[npages] = scratch;
+  f->dba_unit0[npages] = (uint32_t)dba_units;
   // the scratch layout: data pages in page order (a scan decompresses a
   // column's data pages into one range), then the dictionary pages, which
   // are decompressed at open only
@@ -768,6 +781,11 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   if (strck) {
     if (hipMalloc(&f->d_strck, sizeof(uint32_t) * strck) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: checkpoint allocation"); }
   }
+  if (dba_units) {
+    if (hipMalloc(&f->d_dbau, sizeof(DbaUnit) * dba_units) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: unit allocation"); }
+    OPEN_HIP(hipMemsetAsync(f->d_dbau, 0xff, sizeof(DbaUnit) * dba_units, s));
+    f->device_bytes += sizeof(DbaUnit) * dba_units;
+  }
   const uint64_t flim = (len + 15) & ~15ull;  // the file is readable up to len rounded up to 16
   if (sblk) {
     // the Snappy block index of every compressed page, from a walk over the
@@ -851,8 +869,8 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         if (xs.size() > MAX_SEGS) { cleanup_open(); free_handle(f); return fail(PQ_EUNSUPPORTED, "too many DELTA_BYTE_ARRAY columns"); }
         if (hipMalloc(&d_xcols, sizeof(ColScan) * xc.size()) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: allocation failed"); }
         OPEN_HIP(hipMemcpyAsync(d_xcols, xc.data(), sizeof(ColScan) * xc.size(), hipMemcpyHostToDevice, s));
-        hipLaunchKernelGGL(k_dba, dim3(xw), dim3(64), 0, s, d_xcols, make_segs(xs), (uint8_t*)nullptr, scr,
-                           (uint8_t*)nullptr, f->d_pages, 0, f->d_err);
+        hipLaunchKernelGGL(k_dba<false>, dim3(xw), dim3(64), 0, s, d_xcols, make_segs(xs), (uint8_t*)nullptr, scr,
+                           (uint8_t*)nullptr, f->d_pages, (DbaUnit*)nullptr, 0, f->d_err);
         if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_dba launch failed"); }
         {
           pq_status stx = read_err(f, s);
@@ -860,6 +878,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         }
         OPEN_HIP(hipMemcpy(f->pages.data() + P.p0, f->d_pages + P.p0, sizeof(PageDev) * (P.p1 - P.p0),
                            hipMemcpyDeviceToHost));
+        uint64_t ctx = 0;  // bytes the pass's units keep
         for (uint32_t pp = P.p0; pp < P.p1; ++pp) {
           PageDev& pg = f->pages[pp];
           f->xscratch_prefix[pp] = xscratch;
@@ -868,14 +887,29 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
             continue;
           pg.x_off = xscratch;
           xscratch += align_up((uint64_t)pg.xlen + SCRATCH_PAD, 16);
+          ctx += pg.x_ctx;
+        }
+        if (ctx) {
+          uint8_t* b = nullptr;
+          if (hipMalloc(&b, ctx) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: unit allocation"); }
+          f->d_dbactx.push_back(b);
+          f->device_bytes += ctx;
+          for (uint32_t pp = P.p0; pp < P.p1; ++pp) {
+            PageDev& pg = f->pages[pp];
+            if (pg.kind == PAGE_DICT || pg.encoding != E_DBA || f->chunks[pg.chunk].type != T_BYTE_ARRAY ||
+                pg.x_total == DBA_UNSUPPORTED)
+              continue;
+            pg.x_ctxp = b;
+            b += pg.x_ctx;
+          }
         }
         OPEN_HIP(hipMemcpyAsync(f->d_pages + P.p0, f->pages.data() + P.p0, sizeof(PageDev) * (P.p1 - P.p0),
                                 hipMemcpyHostToDevice, s));
         if (xscratch > xs0) {
           if (hipMalloc(&d_xscratch_mem, OPEN_GUARD + (xscratch - xs0)) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: no device memory for expansion"); }
           d_xscratch = d_xscratch_mem + OPEN_GUARD;
-          hipLaunchKernelGGL(k_dba, dim3(xw), dim3(64), 0, s, d_xcols, make_segs(xs), (uint8_t*)nullptr, scr,
-                             d_xscratch - xs0, f->d_pages, 1, f->d_err);
+          hipLaunchKernelGGL(k_dba<false>, dim3(xw), dim3(64), 0, s, d_xcols, make_segs(xs), (uint8_t*)nullptr, scr,
+                             d_xscratch - xs0, f->d_pages, f->d_dbau, 1, f->d_err);
           if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_dba launch failed"); }
           xscr = d_xscratch - xs0;
           xscr_lim = xscratch;
@@ -1154,6 +1188,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   f->fd.sblk_page = f->d_sblk_page;
   f->fd.sbits = f->d_sbits;
   f->fd.dicts = f->d_dicts;
+  f->fd.dbau = f->d_dbau;
   cleanup_open();
 
 #undef OPEN_HIP
@@ -1386,8 +1421,9 @@ struct Plan {
   std::vector<int32_t> str_cols;    // string ColScan indices (k_str_total)
   // units: pages (k_snappy), tiles (k_prep threads; one wave per tile elsewhere)
   std::vector<Segment> sblk_segs;  // k_snappy_blk: blocks of the compressed pages, one workgroup each
-  std::vector<Segment> dba_segs;   // k_dba: pages of columns with DELTA_BYTE_ARRAY pages, one wave each
+  std::vector<Segment> dba_segs;   // k_dba: units of columns with DELTA_BYTE_ARRAY pages, one wave each
   uint32_t dba_waves = 0;
+  bool dba_small = false, dba_big = false;
   uint32_t sblk_wgs = 0;
   bool str_spread[2] = {false, false}, fixed_spread[8] = {};  // columns interleaved wave by wave
   uint32_t snappy_waves = 0, prep_threads = 0, pre_units = 0, fixed_units[8] = {}, delta_units = 0, str_units[2] = {0, 0},
@@ -1406,6 +1442,7 @@ struct Plan {
 // `off` on) and which decoders its pages need.
 struct ColSetup {
   ColScan cs;
+  bool dba_small = false, dba_big = false;  // DELTA_BYTE_ARRAY pages of short values, of longer ones
   bool has_delta = false, has_plain = false, has_dict = false, has_slots = false, has_bss = false;
   uint32_t nt = 0;        // tiles
   uint64_t sbytes = 0;    // decompressed bytes of its compressed pages
@@ -1455,6 +1492,7 @@ void col_setup(pq_file f, int c, int32_t rg_b, int32_t rg_e, int64_t rows, uint6
   for (uint32_t p = cs.page_begin; p < cs.page_end; ++p) {
     if (f->pages[p].kind == PAGE_DICT) continue;
     const int e = f->pages[p].encoding;
+    if (e == E_DBA && cs.type == T_BYTE_ARRAY) (f->pages[p].x_maxlen <= DBA_SMALL ? k.dba_small : k.dba_big) = true;
     if (e == E_DELTA) {
       k.has_delta = true;
     } else if (e == E_BSS && cs.type != T_BYTE_ARRAY) {
@@ -1542,8 +1580,11 @@ pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& 
       }
     }
     if (k.xbytes) {
-      P.dba_segs.push_back(Segment{idx, cs.page_begin, cs.page_end, P.dba_waves});
-      P.dba_waves += cs.page_end - cs.page_begin;
+      const uint32_t u0 = f->dba_unit0[cs.page_begin], u1 = f->dba_unit0[cs.page_end];
+      P.dba_segs.push_back(Segment{idx, u0, u1, P.dba_waves});
+      P.dba_waves += u1 - u0;
+      P.dba_small |= k.dba_small;
+      P.dba_big |= k.dba_big;
     }
     P.cols.push_back(cs);
   }
@@ -1614,6 +1655,18 @@ static pq_status upload_header(Plan& P, uint8_t* ws, hipStream_t s) {
   return PQ_OK;
 }
 
+// The units of DELTA_BYTE_ARRAY pages to the PLAIN layout: those of pages of
+// short values, then those of the others, as far as the scan has any.
+static void launch_dba(uint32_t units, const SegTable& segs, bool small, bool big, const ColScan* d_cols, uint8_t* ws,
+                       uint32_t* err, hipStream_t s) {
+  if (small)
+    hipLaunchKernelGGL(k_dba<true>, dim3(units), dim3(64), 0, s, d_cols, segs, ws, (const uint8_t*)nullptr,
+                       (uint8_t*)nullptr, (PageDev*)nullptr, (DbaUnit*)nullptr, 2, err);
+  if (big)
+    hipLaunchKernelGGL(k_dba<false>, dim3(units), dim3(64), 0, s, d_cols, segs, ws, (const uint8_t*)nullptr,
+                       (uint8_t*)nullptr, (PageDev*)nullptr, (DbaUnit*)nullptr, 2, err);
+}
+
 // Snappy decompression of the plan's compressed data pages (column table
 // d_cols).
 static pq_status enqueue_decompress(pq_file f, const Plan& P, const ColScan* d_cols, uint8_t* ws, uint32_t* err,
@@ -1633,8 +1686,7 @@ static pq_status enqueue_decompress(pq_file f, const Plan& P, const ColScan* d_c
     HIP_OR(hipGetLastError());
   }
   if (P.dba_waves) {  // DELTA_BYTE_ARRAY pages (after their decompression) to the PLAIN layout
-    hipLaunchKernelGGL(k_dba, dim3(P.dba_waves), dim3(64), 0, s, d_cols, make_segs(P.dba_segs), ws,
-                       (const uint8_t*)nullptr, (uint8_t*)nullptr, (PageDev*)nullptr, 1, err);
+    launch_dba(P.dba_waves, make_segs(P.dba_segs), P.dba_small, P.dba_big, d_cols, ws, err, s);
     HIP_OR(hipGetLastError());
   }
   return PQ_OK;
@@ -2087,6 +2139,7 @@ struct BatchPlan {
   std::vector<int64_t> chars;  // per column, in request order
   std::vector<Segment> snappy_segs, sblk_segs, edge_segs, prep_segs, dba_segs;
   uint32_t snappy_waves = 0, sblk_wgs = 0, edge_threads = 0, prep_threads = 0, dba_waves = 0;
+  bool dba_small = false, dba_big = false;
   // same-kind tile runs: consecutive pages of one column with one decoder
   // and work class
   struct Run { uint32_t cs, t0, t1, kind, cls, chunk; };
@@ -2095,7 +2148,7 @@ struct BatchPlan {
   std::vector<Run> page_runs;      // one per data page (the per-page form's launches)
   struct SnapPage { uint32_t cs, page, b0, b1; };
   std::vector<SnapPage> snap_pages;  // compressed data pages and their Snappy blocks
-  std::vector<std::pair<uint32_t, uint32_t>> dba_pages;  // (column, page) of DELTA_BYTE_ARRAY pages
+  std::vector<Segment> dba_pages;    // per DELTA_BYTE_ARRAY page, its units
   uint64_t total_tiles = 0;
   uint64_t ws_cols = 0, ws_which = 0, ws_snappy = 0, ws_sblk = 0, ws_edge = 0, ws_prep = 0, ws_units = 0,
            ws_qbeg = 0, ws_qhead = 0, ws_hdr_end = 0, ws_total = 0, ws_dba = 0;
@@ -2168,8 +2221,11 @@ pq_status make_batch_plan(const pq_request* reqs, int32_t n, BatchPlan& P) {
         }
       }
       if (k.xbytes) {
-        P.dba_segs.push_back(Segment{idx, cs.page_begin, cs.page_end, P.dba_waves});
-        P.dba_waves += cs.page_end - cs.page_begin;
+        const uint32_t u0 = f->dba_unit0[cs.page_begin], u1 = f->dba_unit0[cs.page_end];
+        P.dba_segs.push_back(Segment{idx, u0, u1, P.dba_waves});
+        P.dba_waves += u1 - u0;
+      P.dba_small |= k.dba_small;
+      P.dba_big |= k.dba_big;
       }
       if (k.nt) {
         if (cs.optional) {
@@ -2187,7 +2243,7 @@ pq_status make_batch_plan(const pq_request* reqs, int32_t n, BatchPlan& P) {
           const uint32_t nb = (uint32_t)(((uint64_t)pg.scratch_len + SNAP_BLOCK - 1) / SNAP_BLOCK);
           P.snap_pages.push_back(BatchPlan::SnapPage{idx, p, pg.sblk_begin, pg.sblk_begin + nb});
         }
-        if (pg.encoding == E_DBA && cs.type == T_BYTE_ARRAY) P.dba_pages.push_back({idx, p});
+        if (pg.encoding == E_DBA && cs.type == T_BYTE_ARRAY) P.dba_pages.push_back(Segment{idx, f->dba_unit0[p], f->dba_unit0[p + 1], 0});
         const uint32_t nt = (uint32_t)(((uint64_t)(pg.num_values > 0 ? pg.num_values : 0) + TILE_ROWS - 1) / TILE_ROWS);
         if (!nt) continue;
         const uint32_t kind = tile_kind(f, pg, cs), cls = tune_class(kind, pg, nt);
@@ -2365,15 +2421,14 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
   // DELTA_BYTE_ARRAY pages to the PLAIN layout (after their decompression)
   if (!per_page) {
     if (P.dba_waves) {
-      hipLaunchKernelGGL(k_dba, dim3(P.dba_waves), dim3(64), 0, s, d_cols, seg_table(P.dba_segs, ws, P.ws_dba), ws,
-                         (const uint8_t*)nullptr, (uint8_t*)nullptr, (PageDev*)nullptr, 1, err);
+      launch_dba(P.dba_waves, seg_table(P.dba_segs, ws, P.ws_dba), P.dba_small, P.dba_big, d_cols, ws, err, s);
       HIP_OR(hipGetLastError());
     }
   } else {
-    for (const auto& dp : P.dba_pages) {
-      std::vector<Segment> one{Segment{dp.first, dp.second, dp.second + 1, 0}};
-      hipLaunchKernelGGL(k_dba, dim3(1), dim3(64), 0, s, d_cols, make_segs(one), ws, (const uint8_t*)nullptr,
-                         (uint8_t*)nullptr, (PageDev*)nullptr, 1, err);
+    for (const Segment& dp : P.dba_pages) {
+      if (dp.t1 == dp.t0) continue;
+      std::vector<Segment> one{dp};
+      launch_dba(dp.t1 - dp.t0, make_segs(one), P.dba_small, P.dba_big, d_cols, ws, err, s);
       HIP_OR(hipGetLastError());
     }
   }

@@ -157,6 +157,11 @@ struct PageDev {
   uint64_t x_src;
   uint32_t x_len, x_sfx, x_chars, xlen, x_total, x_scratch;
   uint64_t x_off;
+  uint32_t x_unit0;      // first unit (DbaUnit)
+  uint32_t x_maxlen;     // its longest value
+  uint32_t x_ctx;        // bytes its units keep of the values before them (16-byte steps)
+  uint32_t x_pad_;
+  uint8_t* x_ctxp;       // and where
   uint64_t sbit_begin;   // compressed pages: first 16-bit entry of the page's element start bits
 };
 
@@ -254,6 +259,29 @@ struct DiCand {
 // than the expansion's LDS buffer, or a DELTA block shape outside the
 // supported one): its tiles report PQ_EUNSUPPORTED when its column is scanned
 constexpr uint32_t DBA_UNSUPPORTED = 0xffffffffu;
+// Units of a DELTA_BYTE_ARRAY page, expanded side by side: DBA_UNIT values
+// each, with the state of the two length streams before the unit's first
+// value, the positions in the suffix bytes and in the page's expanded layout,
+// and the bytes of the value before it that the unit's first value shares.
+// Written when the file is opened.
+constexpr uint32_t DBA_UNIT = 256;
+constexpr uint32_t DBA_SMALL = 1024;  // pages of values up to this length take k_dba<true>
+struct DbaStream {
+  uint32_t q, mbq, wq;      // next byte after the blocks read, the current miniblock, its block's widths
+  uint32_t last, mind;      // the value before, the block's minimum delta
+  uint32_t blocks;          // blocks read
+  uint32_t at;              // miniblock of the block (bits 20..) and values taken from it (bits 0..19)
+  uint32_t B, M;            // values per block, miniblocks per block
+};
+struct DbaUnit {
+  DbaStream p, s;           // prefix lengths, suffix lengths
+  const uint8_t* ctx;       // ctx_len bytes
+  uint32_t ctx_len;
+  uint32_t page;            // ~0: not a unit (the page has fewer values than rows)
+  uint32_t first;           // first value
+  uint32_t c, pos;          // suffix bytes, expanded bytes before it
+  uint32_t pad_;
+};
 // page encoding given to such a page by the index pass
 constexpr uint8_t E_UNDECODED = 0xff;
 // Snappy block index: a compressed page's output is cut into SNAP_BLOCK-byte
@@ -330,6 +358,7 @@ struct FileDev {
   const uint32_t* sblk_page;   // page of each Snappy block
   uint16_t* sbits;             // start bits of the Snappy elements (written with sblk)
   const DictSlot* dicts;       // resident dictionaries, one per chunk (col * nrg + rg)
+  const DbaUnit* dbau;         // units of the DELTA_BYTE_ARRAY pages
 };
 
 // Per-scan, per-selected-column table (built on the host, copied into the
