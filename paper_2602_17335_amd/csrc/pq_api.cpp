@@ -22,45 +22,47 @@ __global__ void k_walk(const uint8_t* file, uint64_t file_lim, const ChunkDev* c
 __global__ void k_walk_rec(const uint8_t* file, const ChunkDev* chunks, const uint64_t* rec, const uint32_t* rec_base,
                            const uint32_t* page_base, const uint32_t* page_chunk, uint32_t npages, PageDev* pages,
                            uint32_t* err);
-__global__ void k_index(const uint8_t* file, const uint8_t* scratch, PageDev* pages, int npages,
-                        const ChunkDev* chunks, TileDev* tiles, uint32_t* strck, uint32_t* ckl, Ck* ckv,
-                        uint32_t* err, uint64_t file_lim, uint64_t scratch_lim, const uint32_t* order,
-                        const uint8_t* xscratch, uint64_t xscratch_lim, int phase);
-__global__ void k_lv_cand(const LvPage* lps, const uint32_t* seg_page, const PageDev* pages, const uint8_t* file,
-                          const uint8_t* scratch, uint64_t file_lim, uint64_t scratch_lim, LvCand* cand);
-__global__ void k_lv_link(const LvPage* lps, int npg, const PageDev* pages, const LvCand* cand, LvEntry* ent,
-                          uint32_t* ok, uint32_t* err);
-__global__ void k_lv_tiles(const LvPage* lps, const uint32_t* seg_page, const LvEntry* ent, const uint32_t* ok,
-                           PageDev* pages, const uint8_t* file, const uint8_t* scratch, uint64_t file_lim,
-                           uint64_t scratch_lim, TileDev* tiles, uint32_t* ckl, uint32_t* err, int mode);
-__global__ void k_dl_cand(const DlPage* dps, const uint32_t* seg_page, const PageDev* pages, const uint8_t* file,
-                          const uint8_t* scratch, uint64_t file_lim, uint64_t scratch_lim, DlCand* cand,
-                          const uint32_t* err);
-__global__ void k_dl_link(const DlPage* dps, int npg, PageDev* pages, const DlCand* cand, DlEntry* ent, uint32_t* ok,
-                          uint32_t* err);
-__global__ void k_dl_fill(const DlPage* dps, const uint32_t* seg_page, const DlEntry* ent, const uint32_t* ok,
-                          PageDev* pages, const uint8_t* file, const uint8_t* scratch, uint64_t file_lim,
-                          uint64_t scratch_lim, uint32_t* blkpos, uint32_t* err, int mode);
-__global__ void k_dl_tiles(const DlPage* dps, const uint32_t* tile_dp, int ntl, const PageDev* pages, TileDev* tiles,
-                           Ck* ckv, const uint32_t* blkpos, const uint32_t* err);
-__global__ void k_di_cand(const DiPage* dps, const uint32_t* seg_page, const PageDev* pages, const uint8_t* file,
-                          const uint8_t* scratch, uint64_t file_lim, uint64_t scratch_lim, DiCand* cand,
-                          const uint32_t* err);
-__global__ void k_di_link(const DiPage* dps, int npg, const PageDev* pages, const DiCand* cand, DlEntry* ent,
-                          uint32_t* ok, uint32_t* err);
-__global__ void k_di_fill(const DiPage* dps, const uint32_t* seg_page, const DlEntry* ent, const uint32_t* ok,
-                          const PageDev* pages, const uint8_t* file, const uint8_t* scratch, uint64_t file_lim,
-                          uint64_t scratch_lim, TileDev* tiles, uint32_t* err, int mode);
-__global__ void k_di_ckpt(const DiPage* dps, const uint32_t* tile_dp, int ntl, const PageDev* pages,
-                          const TileDev* tiles, const uint8_t* file, const uint8_t* scratch, uint64_t file_lim,
-                          uint64_t scratch_lim, Ck* ckv, const uint32_t* err);
-__global__ void k_schain_cand(const SChainPage* pgs, const uint32_t* seg_page, SChainCand* cand);
-__global__ void k_schain_link(const SChainPage* pgs, int npg, const SChainCand* cand, uint32_t* seg_start,
-                              uint32_t* seg_base, uint32_t* ok);
-__global__ void k_schain_fill(const SChainPage* pgs, const uint32_t* seg_page, const uint32_t* seg_start,
-                              const uint32_t* seg_base, const uint32_t* ok, uint32_t* strck, PageDev* pages, uint32_t* err);
-__global__ void k_schain_seq(const SChainPage* pgs, int npg, const uint32_t* ok, uint32_t* strck, PageDev* pages,
-                             uint32_t* err);
+__global__ void k_layout(uint32_t p0, uint32_t p1, int dicts, PageDev* pages, const ChunkDev* chunks,
+                         const uint8_t* file, const uint8_t* scratch, uint32_t* err);
+template <uint32_t NT>
+__global__ void k_levels(const IxPage* ixs, const uint32_t* list, PageDev* pages, OpenBufs bufs, uint32_t* at,
+                         uint32_t* val, uint8_t* ent, uint32_t* flag, const uint32_t* err);
+__global__ void k_tiles(const IxPage* ixs, uint32_t nix, uint32_t tile0, uint32_t ntiles, const PageDev* pages,
+                        const ChunkDev* chunks, OpenBufs bufs, const uint32_t* at, const uint32_t* val,
+                        const uint8_t* ent, const uint32_t* flag, TileDev* tiles, uint32_t* ckl, Ck* ckv,
+                        const uint32_t* err);
+__global__ void k_values(const IxPage* ixs, uint32_t nix, PageDev* pages, const ChunkDev* chunks, OpenBufs bufs,
+                         const uint32_t* flag, uint32_t* err);
+template <uint32_t NT>
+__global__ void k_strings(const IxPage* ixs, const uint32_t* list, PageDev* pages, OpenBufs bufs, uint32_t* strck,
+                          uint32_t* flag, const uint32_t* err, const uint32_t* seq);
+__global__ void k_str_cand(const IxPage* ixs, const StrLong* sls, const uint32_t* seg_sl, const PageDev* pages,
+                           OpenBufs bufs, uint32_t* exits, const uint32_t* flag, const uint32_t* err);
+__global__ void k_str_link(const IxPage* ixs, const StrLong* sls, const PageDev* pages, OpenBufs bufs,
+                           const uint32_t* exits, uint32_t* entry, uint32_t* seq, const uint32_t* flag,
+                           const uint32_t* err);
+__global__ void k_str_fill(const IxPage* ixs, const StrLong* sls, const uint32_t* seg_sl, PageDev* pages, OpenBufs bufs,
+                           const uint32_t* entry, const uint32_t* seq, uint32_t* at, uint8_t* ent, uint32_t* total,
+                           const uint32_t* flag, const uint32_t* err);
+__global__ void k_str_base(const IxPage* ixs, const StrLong* sls, const PageDev* pages, uint32_t* total,
+                           const uint32_t* seq, uint32_t* flag, const uint32_t* err);
+__global__ void k_str_ck(const IxPage* ixs, const StrLong* sls, const uint32_t* seg_sl, const PageDev* pages,
+                         OpenBufs bufs, const uint32_t* base, const uint32_t* at, const uint8_t* ent,
+                         const uint32_t* seq, uint32_t* strck, const uint32_t* flag, const uint32_t* err);
+template <uint32_t NT>
+__global__ void k_di(const IxPage* ixs, const uint32_t* list, const PageDev* pages, OpenBufs bufs, uint32_t* at,
+                     uint8_t* ent, uint32_t* flag, const uint32_t* err);
+template <uint32_t NT>
+__global__ void k_dl(const IxPage* ixs, const uint32_t* list, PageDev* pages, const ChunkDev* chunks, OpenBufs bufs,
+                     uint32_t* blkpos, uint32_t* flag, const uint32_t* err);
+__global__ void k_value_tiles(const IxPage* ixs, uint32_t nix, uint32_t tile0, uint32_t ntiles, const PageDev* pages,
+                              const ChunkDev* chunks, OpenBufs bufs, const uint32_t* at, const uint8_t* ent,
+                              const uint32_t* blkpos, const uint32_t* strck, const uint32_t* flag, TileDev* tiles,
+                              Ck* ckv, const uint32_t* err);
+__global__ void k_index(const uint8_t* file, const uint8_t* scratch, PageDev* pages, const IxPage* ixs,
+                        const uint32_t* flag, const ChunkDev* chunks, TileDev* tiles, uint32_t* strck, uint32_t* ckl,
+                        Ck* ckv, uint32_t* err, uint64_t file_lim, uint64_t scratch_lim, const uint8_t* xscratch,
+                        uint64_t xscratch_lim);
 __global__ void k_snappy(const ColScan* cols, SegTable seg, uint8_t* ws, int record, uint32_t* err);
 __global__ void k_snappy_blk(const ColScan* cols, SegTable seg, uint8_t* ws, uint32_t* err, int dicts);
 __global__ void k_snap_index(const ColScan* cols, SegTable seg);
@@ -721,28 +723,16 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   uint8_t* d_scratch_mem = nullptr;  // the window, after OPEN_GUARD bytes
   uint8_t* d_scratch = nullptr;
   ColScan* d_cs = nullptr;
-  uint32_t* d_order = nullptr;
-  uint8_t* d_schain = nullptr;  // long string dictionaries: segment tables of the chain walk
-  uint8_t* d_lv = nullptr;      // long level streams: segment tables of their walk
-  uint8_t* d_dl = nullptr;      // long DELTA streams: segment, block and tile tables of their walk
-  uint8_t* d_di = nullptr;      // long dictionary-index streams: segment and tile tables of their walk
+  uint8_t* d_ix = nullptr;            // a pass's page list and chain tables
   uint8_t* d_xscratch_mem = nullptr;  // DELTA_BYTE_ARRAY pages of a pass expanded to the PLAIN layout,
   uint8_t* d_xscratch = nullptr;      // after OPEN_GUARD bytes
   ColScan* d_xcols = nullptr;     // their column tables
   uint64_t xscratch = 0;          // bytes of the file-wide expansion layout so far
   auto free_pass = [&]() {
-    if (d_order) (void)hipFree(d_order);
-    if (d_schain) (void)hipFree(d_schain);
-    if (d_lv) (void)hipFree(d_lv);
-    if (d_dl) (void)hipFree(d_dl);
-    if (d_di) (void)hipFree(d_di);
+    if (d_ix) (void)hipFree(d_ix);
     if (d_xscratch_mem) (void)hipFree(d_xscratch_mem);
     if (d_xcols) (void)hipFree(d_xcols);
-    d_order = nullptr;
-    d_schain = nullptr;
-    d_lv = nullptr;
-    d_dl = nullptr;
-    d_di = nullptr;
+    d_ix = nullptr;
     d_xscratch_mem = d_xscratch = nullptr;
     d_xcols = nullptr;
   };
@@ -924,233 +914,163 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       free_pass();
       continue;
     }
-    // one wave per page, the longest walks first (string dictionaries by
-    // bytes, then data pages by rows), so that they start at once instead of
-    // behind the waves of earlier pages
-    const uint32_t npl = (uint32_t)plist.size();
-    std::vector<uint32_t> order(plist);
-    std::vector<uint64_t> work(npages, 0);
-    std::vector<uint32_t> lv_list;  // pages whose levels the k_lv kernels walk
-    bool any_delta = false;         // pages that may have their blocks walked by the k_dl kernels
-    bool any_dict = false;          // pages that may have their indices walked by the k_di kernels
-    for (uint32_t p : plist) {
-      const PageDev& pg = f->pages[p];
-      const bool sdict = pg.kind == PAGE_DICT && f->chunks[pg.chunk].type == T_BYTE_ARRAY && pg.uncomp_size <= SCHAIN_MIN;
-      work[p] = sdict ? 16ull * pg.uncomp_size : (uint64_t)(pg.num_values > 0 ? pg.num_values : 0);
-      if (pg.kind != PAGE_DICT && lv_page(pg, f->chunks[pg.chunk].optional != 0)) lv_list.push_back(p);
-      if (pg.kind != PAGE_DICT && (pg.encoding == E_DELTA || pg.encoding == E_DLBA)) any_delta = true;
-      if (pg.kind != PAGE_DICT && (pg.encoding == E_PLAIN_DICT || pg.encoding == E_RLE_DICT)) any_dict = true;
-    }
-    std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return work[a] > work[b]; });
-    if (hipMalloc(&d_order, sizeof(uint32_t) * npl) != hipSuccess ||
-        hipMemcpy(d_order, order.data(), sizeof(uint32_t) * npl, hipMemcpyHostToDevice) != hipSuccess) {
-      cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: page order");
-    }
-    hipLaunchKernelGGL(k_index, dim3(npl), dim3(64), 0, s, file, scr, f->d_pages, (int)npl, f->d_chunks, f->d_tiles,
-                       f->d_strck, f->d_ckl, f->d_ckv, f->d_err, flim, scr_lim, d_order, xscr, xscr_lim, 1);
-    if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_index launch failed"); }
-    // long level streams: their exact lengths (stored by the launch above),
-    // then candidates, link, tile entries, checkpoints and the value streams
-    if (!lv_list.empty() || any_delta || any_dict) {
+    // every page's streams, then the chains of each page by one workgroup
+    // (the longest first, so that they start at once instead of behind
+    // those of earlier pages), then all tiles side by side
+    const uint32_t nix = (uint32_t)plist.size();
+    hipLaunchKernelGGL(k_layout, dim3((P.p1 - P.p0 + 63) / 64), dim3(64), 0, s, P.p0, P.p1, P.dict ? 1 : 0, f->d_pages,
+                       f->d_chunks, file, scr, f->d_err);
+    if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_layout launch failed"); }
+    if (!P.dict) {  // the streams' lengths
       OPEN_HIP(hipMemcpyAsync(f->pages.data() + P.p0, f->d_pages + P.p0, sizeof(PageDev) * (P.p1 - P.p0),
                               hipMemcpyDeviceToHost, s));
-      OPEN_HIP(hipStreamSynchronize(s));
+      pq_status stl = read_err(f, s);
+      if (stl != PQ_OK) { cleanup_open(); free_handle(f); return stl; }
     }
-    if (!lv_list.empty()) {
-      std::vector<LvPage> lps;
-      std::vector<uint32_t> seg_page, order2;
-      for (uint32_t p : lv_list) {
-        const PageDev& pg = f->pages[p];
-        LvPage x;
-        x.page = p;
-        x.seg0 = (uint32_t)seg_page.size();
-        x.nseg = (uint32_t)(((uint64_t)(pg.def_len > 0 ? pg.def_len : 0) + LV_SEG - 1) / LV_SEG);
-        for (uint32_t j = 0; j < x.nseg; ++j) seg_page.push_back((uint32_t)lps.size());
-        lps.push_back(x);
-        order2.push_back(p);
+    enum { C_LEVELS, C_STRINGS, C_DI, C_DL, NCHAINS };
+    std::vector<IxPage> ixs(nix);
+    std::vector<std::pair<uint32_t, uint32_t>> lists[NCHAINS];  // (stream bytes, page of the list)
+    uint64_t nlv = 0, nvp = 0, nblk = 0, tile0 = 0, ntl = 0;
+    for (uint32_t i = 0; i < nix; ++i) {
+      const PageDev& pg = f->pages[plist[i]];
+      const bool str = f->chunks[pg.chunk].type == T_BYTE_ARRAY;
+      IxPage& x = ixs[i];
+      x = IxPage{plist[i], 0, 0, 0, 0, 0, 0};
+      if (P.dict) {
+        if (str) lists[C_STRINGS].push_back({pg.uncomp_size, i});
+        continue;
       }
-      std::stable_sort(order2.begin(), order2.end(), [&](uint32_t a, uint32_t b) { return work[a] > work[b]; });
-      const size_t npg = lps.size(), nseg = seg_page.size();
-      const size_t o_seg = align_up(sizeof(LvPage) * npg, 256), o_ord = align_up(o_seg + 4 * nseg, 256),
-                   o_cand = align_up(o_ord + 4 * npg, 256),
-                   o_ent = align_up(o_cand + sizeof(LvCand) * LV_CAND * nseg, 256),
-                   o_ok = align_up(o_ent + sizeof(LvEntry) * nseg, 256), total = o_ok + 4 * npg;
-      if (hipMalloc(&d_lv, total) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: level walk tables"); }
-      LvPage* d_lps = reinterpret_cast<LvPage*>(d_lv);
-      uint32_t* d_segp = reinterpret_cast<uint32_t*>(d_lv + o_seg);
-      uint32_t* d_ord2 = reinterpret_cast<uint32_t*>(d_lv + o_ord);
-      LvCand* d_cand = reinterpret_cast<LvCand*>(d_lv + o_cand);
-      LvEntry* d_ent = reinterpret_cast<LvEntry*>(d_lv + o_ent);
-      uint32_t* d_ok = reinterpret_cast<uint32_t*>(d_lv + o_ok);
-      OPEN_HIP(hipMemcpyAsync(d_lps, lps.data(), sizeof(LvPage) * npg, hipMemcpyHostToDevice, s));
-      if (nseg) OPEN_HIP(hipMemcpyAsync(d_segp, seg_page.data(), 4 * nseg, hipMemcpyHostToDevice, s));
-      OPEN_HIP(hipMemcpyAsync(d_ord2, order2.data(), 4 * npg, hipMemcpyHostToDevice, s));
-      if (nseg)
-        hipLaunchKernelGGL(k_lv_cand, dim3((uint32_t)nseg), dim3(LV_CAND), 0, s, d_lps, d_segp, f->d_pages, file,
-                           scr, flim, scr_lim, d_cand);
-      hipLaunchKernelGGL(k_lv_link, dim3((uint32_t)((npg + 63) / 64)), dim3(64), 0, s, d_lps, (int)npg, f->d_pages,
-                         d_cand, d_ent, d_ok, f->d_err);
-      if (nseg)
-        hipLaunchKernelGGL(k_lv_tiles, dim3((uint32_t)nseg), dim3(64), 0, s, d_lps, d_segp, d_ent, d_ok, f->d_pages,
-                           file, scr, flim, scr_lim, f->d_tiles, f->d_ckl, f->d_err, 0);
-      hipLaunchKernelGGL(k_lv_tiles, dim3((uint32_t)npg), dim3(64), 0, s, d_lps, d_segp, d_ent, d_ok, f->d_pages, file,
-                         scr, flim, scr_lim, f->d_tiles, f->d_ckl, f->d_err, 1);
-      hipLaunchKernelGGL(k_index, dim3((uint32_t)npg), dim3(64), 0, s, file, scr, f->d_pages, (int)npg,
-                         f->d_chunks, f->d_tiles, f->d_strck, f->d_ckl, f->d_ckv, f->d_err, flim, scr_lim,
-                         d_ord2, xscr, xscr_lim, 2);
-      if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_lv launch failed"); }
-    }
-    // long DELTA block chains (headers parsed by the index pass above): block
-    // positions, then every tile's entry block and checkpoints
-    if (any_delta) {
-      std::vector<DlPage> dps;
-      std::vector<uint32_t> seg_page, tile_dp;
-      uint64_t nblk = 0;
-      for (uint32_t p : plist) {
-        const PageDev& pg = f->pages[p];
-        if (!dl_page(pg, f->chunks[pg.chunk].type)) continue;
-        DlPage x;
-        x.page = p;
-        x.seg0 = (uint32_t)seg_page.size();
-        x.nseg = (uint32_t)(((uint64_t)pg.val_len + DL_SEG - 1) / DL_SEG);
-        x.blk0 = (uint32_t)nblk;
-        x.tl0 = (uint32_t)tile_dp.size();
-        x.maxw = f->chunks[pg.chunk].type == T_INT64 ? 64 : 32;
-        nblk += ((uint64_t)pg.num_values + 127) / 128 + 1;  // blocks hold 128 values or more
-        const uint32_t nt = (uint32_t)(((uint64_t)pg.num_values + TILE_ROWS - 1) / TILE_ROWS);
-        for (uint32_t j = 0; j < x.nseg; ++j) seg_page.push_back((uint32_t)dps.size());
-        for (uint32_t j = 0; j < nt; ++j) tile_dp.push_back((uint32_t)dps.size());
-        dps.push_back(x);
+      const uint32_t nv = pg.num_values > 0 ? (uint32_t)pg.num_values : 0u;
+      x.tile0 = pg.tile_begin;
+      x.ntiles = (uint32_t)(((uint64_t)nv + TILE_ROWS - 1) / TILE_ROWS);
+      if (ntl == 0) tile0 = pg.tile_begin;
+      ntl += x.ntiles;
+      if (nv == 0) continue;
+      if (f->chunks[pg.chunk].optional) {
+        const uint32_t dl = pg.def_len > 0 ? (uint32_t)pg.def_len : 0u;
+        x.lv0 = (uint32_t)nlv;
+        x.nlv = chain_pieces(dl);
+        nlv += x.nlv;
+        lists[C_LEVELS].push_back({dl, i});
       }
-      if (nblk > 0xffffffffull) { cleanup_open(); free_handle(f); return fail(PQ_EUNSUPPORTED, "too many DELTA blocks"); }
-      if (!dps.empty()) {
-        const size_t npg = dps.size(), nseg = seg_page.size(), ntl = tile_dp.size();
-        const size_t o_seg = align_up(sizeof(DlPage) * npg, 256), o_tl = align_up(o_seg + 4 * nseg, 256),
-                     o_cand = align_up(o_tl + 4 * ntl, 256),
-                     o_ent = align_up(o_cand + sizeof(DlCand) * DL_CAND * nseg, 256),
-                     o_ok = align_up(o_ent + sizeof(DlEntry) * nseg, 256), o_blk = align_up(o_ok + 4 * npg, 256),
-                     total = o_blk + 4 * (size_t)nblk;
-        if (hipMalloc(&d_dl, total) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: DELTA walk tables"); }
-        DlPage* d_dps = reinterpret_cast<DlPage*>(d_dl);
-        uint32_t* d_segp = reinterpret_cast<uint32_t*>(d_dl + o_seg);
-        uint32_t* d_tlp = reinterpret_cast<uint32_t*>(d_dl + o_tl);
-        DlCand* d_cand = reinterpret_cast<DlCand*>(d_dl + o_cand);
-        DlEntry* d_ent = reinterpret_cast<DlEntry*>(d_dl + o_ent);
-        uint32_t* d_ok = reinterpret_cast<uint32_t*>(d_dl + o_ok);
-        uint32_t* d_blk = reinterpret_cast<uint32_t*>(d_dl + o_blk);
-        OPEN_HIP(hipMemcpyAsync(d_dps, dps.data(), sizeof(DlPage) * npg, hipMemcpyHostToDevice, s));
-        if (nseg) OPEN_HIP(hipMemcpyAsync(d_segp, seg_page.data(), 4 * nseg, hipMemcpyHostToDevice, s));
-        if (ntl) OPEN_HIP(hipMemcpyAsync(d_tlp, tile_dp.data(), 4 * ntl, hipMemcpyHostToDevice, s));
-        if (nseg)
-          hipLaunchKernelGGL(k_dl_cand, dim3((uint32_t)nseg), dim3(DL_CAND), 0, s, d_dps, d_segp, f->d_pages, file,
-                             scr, flim, scr_lim, d_cand, f->d_err);
-        hipLaunchKernelGGL(k_dl_link, dim3((uint32_t)((npg + 63) / 64)), dim3(64), 0, s, d_dps, (int)npg, f->d_pages,
-                           d_cand, d_ent, d_ok, f->d_err);
-        if (nseg)
-          hipLaunchKernelGGL(k_dl_fill, dim3((uint32_t)nseg), dim3(64), 0, s, d_dps, d_segp, d_ent, d_ok, f->d_pages,
-                             file, scr, flim, scr_lim, d_blk, f->d_err, 0);
-        hipLaunchKernelGGL(k_dl_fill, dim3((uint32_t)npg), dim3(64), 0, s, d_dps, d_segp, d_ent, d_ok, f->d_pages,
-                           file, scr, flim, scr_lim, d_blk, f->d_err, 1);
-        if (ntl)
-          hipLaunchKernelGGL(k_dl_tiles, dim3((uint32_t)((ntl + 255) / 256)), dim3(256), 0, s, d_dps, d_tlp, (int)ntl,
-                             f->d_pages, f->d_tiles, f->d_ckv, d_blk, f->d_err);
-        if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_dl launch failed"); }
+      if (pg.encoding == E_PLAIN_DICT || pg.encoding == E_RLE_DICT) {
+        x.v0 = (uint32_t)nvp;
+        x.nv = chain_pieces(pg.val_len);
+        nvp += x.nv;
+        lists[C_DI].push_back({pg.val_len, i});
+      } else if (pg.encoding == E_DELTA || (pg.encoding == E_DLBA && str)) {
+        x.v0 = (uint32_t)nblk;
+        nblk += ((uint64_t)nv + 127) / 128 + 1;  // blocks hold 128 values or more
+        lists[C_DL].push_back({pg.val_len, i});
+      } else if (str && (pg.encoding == E_PLAIN || pg.encoding == E_DBA)) {
+        lists[C_STRINGS].push_back({pg.val_len, i});
       }
     }
-    // long dictionary-index streams (widths parsed by the index pass above):
-    // every tile's entry run and value checkpoints
-    if (any_dict) {
-      std::vector<DiPage> dps;
-      std::vector<uint32_t> seg_page, tile_dp;
-      for (uint32_t p : plist) {
-        const PageDev& pg = f->pages[p];
-        if (!di_page(pg)) continue;
-        DiPage x;
-        x.page = p;
-        x.seg0 = (uint32_t)seg_page.size();
-        x.nseg = (uint32_t)(((uint64_t)pg.val_len + DI_SEG - 1) / DI_SEG);
-        x.tl0 = (uint32_t)tile_dp.size();
-        const uint32_t nt = (uint32_t)(((uint64_t)pg.num_values + TILE_ROWS - 1) / TILE_ROWS);
-        for (uint32_t j = 0; j < x.nseg; ++j) seg_page.push_back((uint32_t)dps.size());
-        for (uint32_t j = 0; j < nt; ++j) tile_dp.push_back((uint32_t)dps.size());
-        dps.push_back(x);
+    if (nlv > 0xffffffffull || nvp > 0xffffffffull || nblk > 0xffffffffull) { cleanup_open(); free_handle(f); return fail(PQ_EUNSUPPORTED, "too many stream pieces"); }
+    // one upload: the pages, the lists (long streams, then short ones) and
+    // the cleared flags
+    std::vector<uint32_t> order;
+    uint32_t first[NCHAINS], nlong[NCHAINS], nshort[NCHAINS];
+    for (int c = 0; c < NCHAINS; ++c) {
+      std::stable_sort(lists[c].begin(), lists[c].end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+      first[c] = (uint32_t)order.size();
+      nlong[c] = 0;
+      for (const auto& l : lists[c]) {
+        order.push_back(l.second);
+        nlong[c] += l.first > CHAIN_SMALL;
       }
-      if (!dps.empty()) {
-        const size_t npg = dps.size(), nseg = seg_page.size(), ntl = tile_dp.size();
-        const size_t o_seg = align_up(sizeof(DiPage) * npg, 256), o_tl = align_up(o_seg + 4 * nseg, 256),
-                     o_cand = align_up(o_tl + 4 * ntl, 256),
-                     o_ent = align_up(o_cand + sizeof(DiCand) * DI_CAND_MAX * nseg, 256),
-                     o_ok = align_up(o_ent + sizeof(DlEntry) * nseg, 256), total = o_ok + 4 * npg;
-        if (hipMalloc(&d_di, total) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: index walk tables"); }
-        DiPage* d_dps = reinterpret_cast<DiPage*>(d_di);
-        uint32_t* d_segp = reinterpret_cast<uint32_t*>(d_di + o_seg);
-        uint32_t* d_tlp = reinterpret_cast<uint32_t*>(d_di + o_tl);
-        DiCand* d_cand = reinterpret_cast<DiCand*>(d_di + o_cand);
-        DlEntry* d_ent = reinterpret_cast<DlEntry*>(d_di + o_ent);
-        uint32_t* d_ok = reinterpret_cast<uint32_t*>(d_di + o_ok);
-        OPEN_HIP(hipMemcpyAsync(d_dps, dps.data(), sizeof(DiPage) * npg, hipMemcpyHostToDevice, s));
-        if (nseg) OPEN_HIP(hipMemcpyAsync(d_segp, seg_page.data(), 4 * nseg, hipMemcpyHostToDevice, s));
-        if (ntl) OPEN_HIP(hipMemcpyAsync(d_tlp, tile_dp.data(), 4 * ntl, hipMemcpyHostToDevice, s));
-        if (nseg)
-          hipLaunchKernelGGL(k_di_cand, dim3((uint32_t)nseg), dim3(256), 0, s, d_dps, d_segp, f->d_pages, file,
-                             scr, flim, scr_lim, d_cand, f->d_err);
-        hipLaunchKernelGGL(k_di_link, dim3((uint32_t)((npg + 63) / 64)), dim3(64), 0, s, d_dps, (int)npg, f->d_pages,
-                           d_cand, d_ent, d_ok, f->d_err);
-        if (nseg)
-          hipLaunchKernelGGL(k_di_fill, dim3((uint32_t)nseg), dim3(64), 0, s, d_dps, d_segp, d_ent, d_ok, f->d_pages,
-                             file, scr, flim, scr_lim, f->d_tiles, f->d_err, 0);
-        hipLaunchKernelGGL(k_di_fill, dim3((uint32_t)npg), dim3(64), 0, s, d_dps, d_segp, d_ent, d_ok, f->d_pages,
-                           file, scr, flim, scr_lim, f->d_tiles, f->d_err, 1);
-        if (ntl)
-          hipLaunchKernelGGL(k_di_ckpt, dim3((uint32_t)((ntl + 3) / 4)), dim3(64), 0, s, d_dps, d_tlp, (int)ntl,
-                             f->d_pages, f->d_tiles, file, scr, flim, scr_lim, f->d_ckv, f->d_err);
-        if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_di launch failed"); }
-      }
+      nshort[c] = (uint32_t)lists[c].size() - nlong[c];
     }
-    // long string dictionaries: their length chains, segments side by side
-    std::vector<SChainPage> scp;
-    std::vector<uint32_t> seg_page;
-    for (uint32_t p : plist) {
-      const PageDev& pg = f->pages[p];
-      if (pg.kind != PAGE_DICT || f->chunks[pg.chunk].type != T_BYTE_ARRAY || pg.uncomp_size <= SCHAIN_MIN) continue;
-      const bool in_scratch = pg.scratch_len > 0;
-      SChainPage x;
-      x.base = in_scratch ? scr : file;
-      x.off = in_scratch ? pg.scratch_off : pg.payload;
-      x.lim = in_scratch ? scr_lim : flim;
-      x.len = (uint32_t)pg.uncomp_size;
-      x.n = pg.num_values > 0 ? (uint32_t)pg.num_values : 0u;
-      x.page = p;
-      x.seg0 = (uint32_t)seg_page.size();
-      x.nseg = (uint32_t)(((uint64_t)x.len + SCHAIN_SEG - 1) / SCHAIN_SEG);
-      x.strck_begin = pg.strck_begin;
-      for (uint32_t j = 0; j < x.nseg; ++j) seg_page.push_back((uint32_t)scp.size());
-      scp.push_back(x);
+    // the very long string pages (the first of their list) and their segments
+    std::vector<StrLong> sls;
+    std::vector<uint32_t> seg_sl;
+    for (const auto& l : lists[C_STRINGS]) {
+      if (l.first <= STR_LONG) break;
+      const uint32_t ns = (uint32_t)(((uint64_t)l.first + 15 + 32767) / 32768);
+      sls.push_back(StrLong{l.second, (uint32_t)seg_sl.size(), ns});
+      seg_sl.resize(seg_sl.size() + ns, (uint32_t)sls.size() - 1);
     }
-    if (!scp.empty()) {
-      const size_t npg = scp.size(), nseg = seg_page.size();
-      const size_t o_seg = align_up(sizeof(SChainPage) * npg, 256), o_cand = align_up(o_seg + 4 * nseg, 256),
-                   o_start = align_up(o_cand + sizeof(SChainCand) * SCHAIN_CAND * nseg, 256),
-                   o_base = align_up(o_start + 4 * nseg, 256), o_ok = align_up(o_base + 4 * nseg, 256),
-                   total = o_ok + 4 * npg;
-      if (hipMalloc(&d_schain, total) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: dictionary chain tables"); }
-      SChainPage* d_pgs = reinterpret_cast<SChainPage*>(d_schain);
-      uint32_t* d_segp = reinterpret_cast<uint32_t*>(d_schain + o_seg);
-      SChainCand* d_cand = reinterpret_cast<SChainCand*>(d_schain + o_cand);
-      uint32_t* d_start = reinterpret_cast<uint32_t*>(d_schain + o_start);
-      uint32_t* d_base = reinterpret_cast<uint32_t*>(d_schain + o_base);
-      uint32_t* d_ok = reinterpret_cast<uint32_t*>(d_schain + o_ok);
-      OPEN_HIP(hipMemcpyAsync(d_pgs, scp.data(), sizeof(SChainPage) * npg, hipMemcpyHostToDevice, s));
-      OPEN_HIP(hipMemcpyAsync(d_segp, seg_page.data(), 4 * nseg, hipMemcpyHostToDevice, s));
-      hipLaunchKernelGGL(k_schain_cand, dim3((uint32_t)nseg), dim3(64), 0, s, d_pgs, d_segp, d_cand);
-      hipLaunchKernelGGL(k_schain_link, dim3((uint32_t)((npg + 63) / 64)), dim3(64), 0, s, d_pgs, (int)npg, d_cand, d_start,
-                         d_base, d_ok);
-      hipLaunchKernelGGL(k_schain_fill, dim3((uint32_t)nseg), dim3(64), 0, s, d_pgs, d_segp, d_start, d_base, d_ok,
-                         f->d_strck, f->d_pages, f->d_err);
-      hipLaunchKernelGGL(k_schain_seq, dim3((uint32_t)npg), dim3(64), 0, s, d_pgs, (int)npg, d_ok, f->d_strck, f->d_pages,
+    const size_t nsl = sls.size(), nsg = seg_sl.size();
+    const size_t o_ord = align_up(sizeof(IxPage) * nix, 256), o_sl = align_up(o_ord + 4 * order.size(), 256),
+                 o_sgs = align_up(o_sl + sizeof(StrLong) * nsl, 256), o_flag = align_up(o_sgs + 4 * nsg, 256),
+                 o_lat = align_up(o_flag + 4ull * nix, 256), o_lval = align_up(o_lat + 4 * nlv, 256),
+                 o_lent = align_up(o_lval + 4 * nlv, 256), o_vat = align_up(o_lent + nlv, 256),
+                 o_vent = align_up(o_vat + 4 * nvp, 256), o_blk = align_up(o_vent + nvp, 256), o_sent = align_up(o_blk + 4 * nblk, 256),
+                 o_stot = align_up(o_sent + 4 * nsg, 256), o_sseq = align_up(o_stot + 4 * nsg, 256),
+                 o_sat = align_up(o_sseq + 4 * nsl, 256), o_spe = align_up(o_sat + 4096 * nsg, 256),
+                 o_sex = align_up(o_spe + 1024 * nsg, 256), ix_total = o_sex + 4096 * nsg;
+    if (hipMalloc(&d_ix, ix_total ? ix_total : 256) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: chain tables"); }
+    std::vector<uint8_t> up(o_lat, 0);
+    memcpy(up.data(), ixs.data(), sizeof(IxPage) * nix);
+    if (!order.empty()) memcpy(up.data() + o_ord, order.data(), 4 * order.size());
+    if (nsl) {
+      memcpy(up.data() + o_sl, sls.data(), sizeof(StrLong) * nsl);
+      memcpy(up.data() + o_sgs, seg_sl.data(), 4 * nsg);
+    }
+    OPEN_HIP(hipMemcpyAsync(d_ix, up.data(), up.size(), hipMemcpyHostToDevice, s));
+    const IxPage* d_ixs = reinterpret_cast<const IxPage*>(d_ix);
+    const uint32_t* d_ord = reinterpret_cast<const uint32_t*>(d_ix + o_ord);
+    uint32_t* d_flag = reinterpret_cast<uint32_t*>(d_ix + o_flag);
+    uint32_t* d_lat = reinterpret_cast<uint32_t*>(d_ix + o_lat);
+    uint32_t* d_lval = reinterpret_cast<uint32_t*>(d_ix + o_lval);
+    uint8_t* d_lent = d_ix + o_lent;
+    uint32_t* d_vat = reinterpret_cast<uint32_t*>(d_ix + o_vat);
+    uint8_t* d_vent = d_ix + o_vent;
+    uint32_t* d_blk = reinterpret_cast<uint32_t*>(d_ix + o_blk);
+    const OpenBufs bufs{file, scr, xscr, flim, scr_lim, xscr_lim};
+    // one workgroup per page of list c: long streams, then short ones
+#define CHAINS(c, kern, ...)                                                                                          \
+  do {                                                                                                                \
+    if (nlong[c]) hipLaunchKernelGGL(kern<1024>, dim3(nlong[c]), dim3(1024), 0, s, d_ixs, d_ord + first[c], __VA_ARGS__); \
+    if (nshort[c])                                                                                                    \
+      hipLaunchKernelGGL(kern<256>, dim3(nshort[c]), dim3(256), 0, s, d_ixs, d_ord + first[c] + nlong[c], __VA_ARGS__); \
+  } while (0)
+    if (!P.dict) {
+      CHAINS(C_LEVELS, k_levels, f->d_pages, bufs, d_lat, d_lval, d_lent, d_flag, f->d_err);
+      if (ntl)
+        hipLaunchKernelGGL(k_tiles, dim3((uint32_t)((ntl + 3) / 4)), dim3(256), 0, s, d_ixs, nix, (uint32_t)tile0,
+                           (uint32_t)ntl, f->d_pages, f->d_chunks, bufs, d_lat, d_lval, d_lent, d_flag, f->d_tiles,
+                           f->d_ckl, f->d_ckv, f->d_err);
+      hipLaunchKernelGGL(k_values, dim3((nix + 63) / 64), dim3(64), 0, s, d_ixs, nix, f->d_pages, f->d_chunks, bufs,
+                         d_flag, f->d_err);
+    }
+    if (nsl) {
+      const StrLong* d_sl = reinterpret_cast<const StrLong*>(d_ix + o_sl);
+      const uint32_t* d_sgs = reinterpret_cast<const uint32_t*>(d_ix + o_sgs);
+      uint32_t* d_sent = reinterpret_cast<uint32_t*>(d_ix + o_sent);
+      uint32_t* d_stot = reinterpret_cast<uint32_t*>(d_ix + o_stot);
+      uint32_t* d_sseq = reinterpret_cast<uint32_t*>(d_ix + o_sseq);
+      uint32_t* d_sat = reinterpret_cast<uint32_t*>(d_ix + o_sat);
+      uint8_t* d_spe = d_ix + o_spe;
+      uint32_t* d_sex = reinterpret_cast<uint32_t*>(d_ix + o_sex);
+      hipLaunchKernelGGL(k_str_cand, dim3((uint32_t)nsg), dim3(1024), 0, s, d_ixs, d_sl, d_sgs, f->d_pages, bufs, d_sex,
+                         d_flag, f->d_err);
+      hipLaunchKernelGGL(k_str_link, dim3((uint32_t)nsl), dim3(256), 0, s, d_ixs, d_sl, f->d_pages, bufs, d_sex, d_sent,
+                         d_sseq, d_flag, f->d_err);
+      hipLaunchKernelGGL(k_str_fill, dim3((uint32_t)nsg), dim3(1024), 0, s, d_ixs, d_sl, d_sgs, f->d_pages, bufs, d_sent,
+                         d_sseq, d_sat, d_spe, d_stot, d_flag, f->d_err);
+      hipLaunchKernelGGL(k_str_base, dim3((uint32_t)nsl), dim3(64), 0, s, d_ixs, d_sl, f->d_pages, d_stot, d_sseq, d_flag,
                          f->d_err);
-      if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_schain launch failed"); }
+      hipLaunchKernelGGL(k_str_ck, dim3((uint32_t)(4 * nsg)), dim3(256), 0, s, d_ixs, d_sl, d_sgs, f->d_pages, bufs,
+                         d_stot, d_sat, d_spe, d_sseq, f->d_strck, d_flag, f->d_err);
+      // those that could not be linked, front to back
+      hipLaunchKernelGGL(k_strings<1024>, dim3((uint32_t)nsl), dim3(1024), 0, s, d_ixs, d_ord + first[C_STRINGS],
+                         f->d_pages, bufs, f->d_strck, d_flag, f->d_err, d_sseq);
+      first[C_STRINGS] += (uint32_t)nsl;
+      nlong[C_STRINGS] -= (uint32_t)nsl;
     }
+    CHAINS(C_STRINGS, k_strings, f->d_pages, bufs, f->d_strck, d_flag, f->d_err, (const uint32_t*)nullptr);
+    CHAINS(C_DI, k_di, f->d_pages, bufs, d_vat, d_vent, d_flag, f->d_err);
+    CHAINS(C_DL, k_dl, f->d_pages, f->d_chunks, bufs, d_blk, d_flag, f->d_err);
+    if (ntl)
+      hipLaunchKernelGGL(k_value_tiles, dim3((uint32_t)((ntl + 3) / 4)), dim3(64), 0, s, d_ixs, nix, (uint32_t)tile0,
+                         (uint32_t)ntl, f->d_pages, f->d_chunks, bufs, d_vat, d_vent, d_blk, f->d_strck, d_flag,
+                         f->d_tiles, f->d_ckv, f->d_err);
+    // the pages that were left
+    hipLaunchKernelGGL(k_index, dim3(nix), dim3(64), 0, s, file, scr, f->d_pages, d_ixs, d_flag, f->d_chunks, f->d_tiles,
+                       f->d_strck, f->d_ckl, f->d_ckv, f->d_err, flim, scr_lim, xscr, xscr_lim);
+    if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "index launch failed"); }
+#undef CHAINS
     if (P.dict) {
       // resident dictionaries, while the window holds the decompressed pages
       {

@@ -222,6 +222,22 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
   return v;
 }
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_add_u64(uint64_t v) {
+  const uint32_t lo = dpp0<CTRL, ROWS>((uint32_t)v), hi = dpp0<CTRL, ROWS>((uint32_t)(v >> 32));
+  return v + ((uint64_t)hi << 32 | lo);
+}
+
+__device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v) {
+  v = dpp_add_u64<DPP_ROW_SHR | 1, 0xf>(v);
+  v = dpp_add_u64<DPP_ROW_SHR | 2, 0xf>(v);
+  v = dpp_add_u64<DPP_ROW_SHR | 4, 0xf>(v);
+  v = dpp_add_u64<DPP_ROW_SHR | 8, 0xf>(v);
+  v = dpp_add_u64<DPP_BCAST15, 0xa>(v);
+  v = dpp_add_u64<DPP_BCAST31, 0xc>(v);
+  return v;
+}
+
 // Orders this wave's LDS accesses (no other wave takes part).
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

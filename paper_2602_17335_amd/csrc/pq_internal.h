@@ -71,32 +71,6 @@ constexpr uint32_t LCK_NONE = 0xffffffffu;
 // BYTE_ARRAY checkpoint spacing (values) inside PLAIN string streams and
 // string dictionary pages.
 constexpr int STR_CK = 32;
-// String dictionary pages longer than SCHAIN_MIN bytes have their length
-// chain walked at open in SCHAIN_SEG-byte segments side by side (candidate
-// chains from each of the first SCHAIN_CAND byte positions of a segment,
-// linked segment by segment afterwards); shorter ones by k_index's walk.
-constexpr uint32_t SCHAIN_MIN = 256 * 1024;
-constexpr uint32_t SCHAIN_SEG = 32768;
-constexpr uint32_t SCHAIN_CAND = 64;
-constexpr uint32_t SCHAIN_NONE = 0xffffffffu;
-struct SChainPage {
-  const uint8_t* base;  // buffer holding the page body (the file, or the decompression buffer)
-  uint64_t off;         // body offset in base
-  uint64_t lim;         // readable bytes of base (a multiple of 16)
-  uint32_t len;         // body bytes
-  uint32_t n;           // entries
-  uint32_t page;        // page index
-  uint32_t seg0;        // first segment (in the segment arrays)
-  uint32_t nseg;
-  uint32_t strck_begin;
-};
-// A candidate chain of one segment: where it leaves the segment, the
-// entries that start in the segment, their longest length, and how it
-// ended (0: left the segment; 1: fewer than 4 bytes left; 2: a length past
-// the body's end).
-struct SChainCand {
-  uint32_t exit, count, maxlen, state;
-};
 // Bytes of slack after every decompressed region (reads run up to 12 bytes
 // past a stream end).
 constexpr int SCRATCH_PAD = 16;
@@ -165,96 +139,33 @@ struct PageDev {
   uint64_t sbit_begin;   // compressed pages: first 16-bit entry of the page's element start bits
 };
 
-// Definition-level streams of OPTIONAL data pages (the levels before the
-// values, Sec. 3.3) are hybrid RLE/bit-packed run chains whose run headers
-// are only found by walking from the start.  Pages whose body may hold more
-// than LV_MIN level bytes are indexed in LV_SEG-byte segments side by side:
-// LV_CAND candidate chains per segment (one from each of its first LV_CAND
-// bytes), a per-page link through the candidates' exits, then the tile
-// entries and level checkpoints per segment.
-constexpr uint32_t LV_MIN = 8192;
-constexpr uint32_t LV_SEG = 2048;
-constexpr uint32_t LV_CAND = 128;
-constexpr uint32_t LV_NONE = 0xffffffffu;
-__host__ __device__ inline bool lv_page(const PageDev& pg, bool optional) {
-  if (!optional || pg.num_values <= 0) return false;
-  if (pg.kind == PAGE_DATA) return pg.uncomp_size >= 4u + LV_MIN;  // level bytes <= body - 4
-  if (pg.kind == PAGE_DATA_V2) return pg.def_len > (int32_t)LV_MIN;
-  return false;
-}
-struct LvPage {
-  uint32_t page, seg0, nseg;  // segments [seg0, seg0 + nseg) of the segment list
+// A page of an open pass (k_layout .. k_index): its tiles and its entries in
+// the pass's temporary tables.  The chain kernels record, for every 32-byte
+// piece of a level or dictionary-index stream (pieces from the 16-byte
+// boundary at or before the stream's first byte), the rows or values before
+// the first run that starts in it and that run's byte in the piece.
+struct IxPage {
+  uint32_t page;
+  uint32_t tile0, ntiles;  // file-wide first tile, tiles (0: dictionary pages)
+  uint32_t lv0, nlv;       // pieces of the level stream
+  uint32_t v0, nv;         // pieces of the dictionary-index stream, or DELTA block positions
 };
-// A candidate chain of one segment: stream offset where it leaves the
-// segment, rows and valid rows of the runs that start in it (saturating at
-// 2^32 - 1), and how it ended (0: left the segment or reached the stream end;
-// 1: at an invalid run; 2: at a run not held by the staged bytes).
-struct LvCand {
-  uint32_t exit, state, rows, valid;
+// The buffers an open pass reads: the file, the decompression layout, the
+// expansion layout, and their readable bytes.
+struct OpenBufs {
+  const uint8_t *file, *scratch, *xscratch;
+  uint64_t file_lim, scratch_lim, xscratch_lim;
 };
-// The true chain's entry into a segment (stream offset; LV_NONE: the segment
-// is not walked) with the rows and valid rows before it.
-struct LvEntry {
-  uint32_t q, rows, valid, pad_;
+// Streams of at most this many bytes take the chain kernels' workgroups of 256
+// threads (8 KiB segments, five per CU), longer ones those of 1024 (32 KiB).
+constexpr uint32_t CHAIN_SMALL = 8192;
+// A string page of more than STR_LONG bytes: its segments are done side by
+// side (segments [seg0, seg0 + nseg) of the pass's list).
+constexpr uint32_t STR_LONG = 1u << 21;
+struct StrLong {
+  uint32_t ix, seg0, nseg;
 };
-// DELTA_BINARY_PACKED value streams (and the length streams of
-// DELTA_LENGTH_BYTE_ARRAY pages) are chains of blocks whose sizes follow
-// from their headers.  Pages whose value stream is longer than DL_MIN bytes
-// have the chain walked at open in DL_SEG-byte segments side by side (DL_CAND
-// candidate chains per segment, as for level streams); the position of every
-// block is stored, and each tile's entry and checkpoints are read from them.
-constexpr uint32_t DL_MIN = 16384;
-constexpr uint32_t DL_SEG = 16384;
-constexpr uint32_t DL_CAND = 256;
-__host__ __device__ inline bool dl_page(const PageDev& pg, int32_t type) {
-  return pg.kind != PAGE_DICT && pg.num_values > 0 &&
-         (pg.encoding == E_DELTA || (pg.encoding == E_DLBA && type == T_BYTE_ARRAY)) && pg.val_len > DL_MIN;
-}
-struct DlPage {
-  uint32_t page, seg0, nseg;  // segments [seg0, seg0 + nseg) of the segment list
-  uint32_t blk0;              // first entry of the page in the block-position list
-  uint32_t tl0;               // first entry of the page in the tile list
-  uint32_t maxw;              // widest miniblock bit width of the column's type
-};
-// A candidate block chain of one segment: where it leaves the segment, the
-// blocks whose header lies in it (every one taken as a full block), and how
-// it ended (0: left the segment; 1: at a block that is invalid as a full
-// block).
-struct DlCand {
-  uint32_t exit, count, state, pad_;
-};
-// The true chain's entry into a segment (value-stream offset; LV_NONE: not
-// walked) and the index of the block there.
-struct DlEntry {
-  uint32_t q, k;
-};
-// Dictionary-index streams (a bit width byte, then hybrid runs of that
-// width) of pages longer than DI_MIN bytes are indexed in DI_SEG-byte
-// segments side by side, with di_cand(w) candidate chains per segment: a
-// bit-packed run of 63 groups of width w takes 1 + 63 w bytes, so the true
-// chain enters a segment within that many bytes of its start (wider runs
-// and more than 1024 bytes: the page is walked whole by one wave).
-constexpr uint32_t DI_MIN = 16384;
-constexpr uint32_t DI_SEG = 32768;
-constexpr uint32_t DI_CAND_MAX = 1024;
-__host__ __device__ inline bool di_page(const PageDev& pg) {
-  return pg.kind != PAGE_DICT && (pg.encoding == E_PLAIN_DICT || pg.encoding == E_RLE_DICT) && pg.num_values > 0 &&
-         pg.val_len > DI_MIN;
-}
-__host__ __device__ inline uint32_t di_cand(uint32_t w) {
-  const uint32_t c = (16 + 64 * w + 63) / 64 * 64;
-  return c > DI_CAND_MAX ? DI_CAND_MAX : c;
-}
-struct DiPage {
-  uint32_t page, seg0, nseg;  // segments [seg0, seg0 + nseg) of the segment list
-  uint32_t tl0;               // first entry of the page in the tile list
-};
-// A candidate of a dictionary-index stream: where it leaves the segment
-// (DI_BAD: at an invalid run) and the values of the runs before (saturating).
-constexpr uint32_t DI_BAD = 0xffffffffu;
-struct DiCand {
-  uint32_t exit, count;
-};
+__host__ __device__ inline uint32_t chain_pieces(uint64_t len) { return (uint32_t)((len + 15 + 31) / 32); }
 // x_total of a DELTA_BYTE_ARRAY page the scan does not decode (a value longer
 // than the expansion's LDS buffer, or a DELTA block shape outside the
 // supported one): its tiles report PQ_EUNSUPPORTED when its column is scanned

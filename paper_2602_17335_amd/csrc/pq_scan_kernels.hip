@@ -220,22 +220,6 @@ __device__ __forceinline__ GSrc32 gsrc32(const uint8_t* base, uint64_t a0, uint6
 // ---------------------------------------------------------------------------
 // wave and workgroup scans
 // ---------------------------------------------------------------------------
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint64_t dpp_add_u64(uint64_t v) {
-  const uint32_t lo = dpp0<CTRL, ROWS>((uint32_t)v), hi = dpp0<CTRL, ROWS>((uint32_t)(v >> 32));
-  return v + ((uint64_t)hi << 32 | lo);
-}
-
-__device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v) {
-  v = dpp_add_u64<DPP_ROW_SHR | 1, 0xf>(v);
-  v = dpp_add_u64<DPP_ROW_SHR | 2, 0xf>(v);
-  v = dpp_add_u64<DPP_ROW_SHR | 4, 0xf>(v);
-  v = dpp_add_u64<DPP_ROW_SHR | 8, 0xf>(v);
-  v = dpp_add_u64<DPP_BCAST15, 0xa>(v);
-  v = dpp_add_u64<DPP_BCAST31, 0xc>(v);
-  return v;
-}
-
 __device__ __forceinline__ uint64_t wave_read_u64(uint64_t v, int lane) {
   return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane) |
          ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32);

@@ -12,6 +12,7 @@
 // so that only copies of copies wait for each other.
 #include <hip/hip_runtime.h>
 
+#include "pq_chain.hpp"
 #include "pq_device.hpp"
 #include "pq_internal.h"
 
@@ -78,38 +79,18 @@ __device__ __forceinline__ SnapSrc snap_src(const uint8_t* file, const PageDev& 
 // block, or the stream is malformed: such a page is decompressed
 // sequentially by k_snappy, which reports what is wrong.
 //
-// The chain is found in 32 KiB segments of the stream, staged in LDS:
-//   1. thread t takes the 32-byte piece t and finds, for each of its bytes as
-//      if an element started there, where the chain from it leaves the piece
-//      (backwards, so that each byte's answer follows from a later one's);
-//   2. wave w follows these exits through its 2 KiB region from each of the
-//      region's first 64 bytes;
-//   3. one lane follows the true chain from region to region;
-//   4. a lane per region follows it from piece to piece, and every thread
-//      walks its piece's elements (at most 16): lengths, a prefix sum over the
-//      pieces, then the checks, the block starts and the start bits.
-// A literal that leaves the segment skips the bytes it covers.
-// What bounds it: the dependent LDS reads of steps 2 to 4.  Measured on a
+// The chain is found in 32 KiB segments (pq_chain.hpp); every thread then
+// walks its piece's elements (at most 16): lengths, a prefix sum over the
+// pieces, the checks, the block starts and the start bits.
+// What bounds it: the dependent LDS reads of the chain's steps.  Measured on a
 // 2M-row wide table with 1 MiB pages: 0.97 ms; one wave per page that walks the
 // tags from a staged window, 51.7 ms (0.2 us per element of the densest page).
 // ---------------------------------------------------------------------------
 constexpr uint32_t SX_WG = 1024;
-constexpr uint32_t SX_PIECE = 32;
-constexpr uint32_t SX_SEG = SX_WG * SX_PIECE;
-constexpr uint32_t SX_REG = 64 * SX_PIECE;   // one wave's region
-constexpr uint32_t SX_STRIDE = SX_PIECE + 2; // exit-table entries per piece (17 dwords: no bank conflicts)
-constexpr uint32_t SX_BAD = 0xffffu;         // the chain meets an invalid element
-constexpr uint32_t SX_LONG = 0xfffeu;        // it leaves by a literal whose end does not fit the table
-constexpr uint32_t SX_CODES = 0xfff0u;
 
 __global__ __launch_bounds__(SX_WG) void k_snap_index(const ColScan* cols, SegTable seg) {
-  __shared__ __align__(16) uint32_t s_in[SX_SEG / 4 + 16];
-  __shared__ uint16_t s_exit[SX_WG * SX_STRIDE];
-  __shared__ uint32_t s_cand[SX_WG / 64][64];
-  __shared__ uint32_t s_rent[SX_WG / 64];
+  __shared__ ChainLds<SX_WG, 64> L;
   __shared__ uint32_t s_sum[SX_WG / 64];
-  __shared__ uint32_t s_link[2];  // the next segment's entry; whether the chain is valid so far
-  __shared__ uint8_t s_pent[SX_WG];
   const Segment sg = seg_lookup(seg, blockIdx.x);
   const uint32_t p = sg.t0 + (blockIdx.x - sg.wg0);
   if (p >= sg.t1) return;
@@ -139,118 +120,31 @@ __global__ __launch_bounds__(SX_WG) void k_snap_index(const ColScan* cols, SegTa
   }
   const uint32_t first = ip - src.m;
   uint32_t op = 0, wz = 0;  // output bytes so far; start-bit words written
-  // five bytes of the staged segment from byte y
-  auto bytes_at = [&](uint32_t y, uint32_t& x, uint32_t& x4) {
-    const uint32_t w0 = s_in[y >> 2], w1 = s_in[(y >> 2) + 1];
-    x = __builtin_amdgcn_alignbyte(w1, w0, y & 3);
-    x4 = (w1 >> (8 * (y & 3))) & 0xffu;
+  auto step = [](uint32_t lo, uint32_t hi, uint32_t left, uint32_t) -> uint32_t {
+    const SnapEl e = snap_el(lo, hi & 0xffu);
+    if (e.hl > left || (e.lit && (e.len - 1u >= SNAP_BLOCK || e.len > left - e.hl))) return STEP_BAD;
+    return e.hl + (e.lit ? e.len : 0u);
   };
-  // exit of the chain from segment byte y < SX_SEG
-  auto exit_at = [&](uint32_t y) -> uint32_t { return s_exit[(y >> 5) * SX_STRIDE + (y & 31)]; };
   while (ok && ip < iend) {
-    const uint32_t S = ip & ~(SX_PIECE - 1);
-    for (uint32_t w = wz + tid; w < min(S / SX_PIECE, nbits); w += SX_WG) bits[w] = 0;
-    // the segment and 64 bytes after it
-    for (uint32_t i = tid; i < (SX_SEG + 64) / 16; i += SX_WG) {
-      u32x4s v = {0u, 0u, 0u, 0u};
-      if (S + 16 * i < src.lim) v = *reinterpret_cast<const u32x4s*>(src.base + S + 16 * i);
-      *(lds_u32x4*)((lds_u32*)&s_in[0] + 4 * i) = v;
-    }
-    __syncthreads();
-    const uint32_t segend = min(SX_SEG, iend - S);  // the chain ends the segment at or after this
-    {  // 1. exits of the piece
-      uint32_t w[10];
-#pragma unroll
-      for (int c = 0; c < 10; ++c) w[c] = s_in[tid * (SX_PIECE / 4) + c];
-      const uint32_t q0 = tid * SX_PIECE;
-      uint16_t* ex = &s_exit[tid * SX_STRIDE];
-#pragma unroll
-      for (int k = (int)SX_PIECE - 1; k >= 0; --k) {
-        const uint32_t x = (k & 3) ? __builtin_amdgcn_alignbyte(w[(k >> 2) + 1], w[k >> 2], k & 3) : w[k >> 2];
-        const uint32_t x4 = (w[(k >> 2) + 1] >> (8 * (k & 3))) & 0xffu;
-        const SnapEl e = snap_el(x, x4);
-        const uint32_t y = q0 + (uint32_t)k;
-        const uint32_t left = y < iend - S ? iend - S - y : 0u;  // stream bytes from y on
-        const bool inv = e.hl > left || (e.lit && (e.len - 1u >= SNAP_BLOCK || e.len > left - e.hl));
-        const uint32_t nx = y + e.hl + (e.lit ? e.len : 0u);
-        uint32_t v;
-        if (inv) v = SX_BAD;
-        else if (nx >= q0 + SX_PIECE || nx >= segend) v = nx < SX_CODES ? nx : SX_LONG;
-        else v = ex[nx - q0];
-        ex[k] = (uint16_t)v;
-      }
-    }
-    s_pent[tid] = 0xff;
-    __syncthreads();
-    {  // 2. the region's candidates
-      const uint32_t rend = min((wave + 1) * SX_REG, segend);
-      uint32_t e = wave * SX_REG + lane;
-      while (e < rend) e = exit_at(e);
-      s_cand[wave][lane] = e;
-    }
-    __syncthreads();
-    if (tid == 0) {  // 3. the true chain's entries
-      uint32_t e = ip - S;
-      bool good = true;
-      for (uint32_t r = 0; r < SX_WG / 64; ++r) {
-        const uint32_t rend = min((r + 1) * SX_REG, segend);
-        if (!good || e >= rend) { s_rent[r] = ~0u; continue; }
-        s_rent[r] = e;
-        const uint32_t c = e - r * SX_REG;  // (entries ascend, so e lies in region r)
-        uint32_t x;
-        if (c < 64) {
-          x = s_cand[r][c];
-        } else {
-          x = e;
-          while (x < rend) x = exit_at(x);
-        }
-        if (x == SX_LONG) {
-          // the last element that starts in the region, from its piece's entry
-          uint32_t y = e;
-          for (uint32_t z; (z = exit_at(y)) < rend;) y = z;
-          for (;;) {
-            uint32_t b, b4;
-            bytes_at(y, b, b4);
-            const SnapEl el = snap_el(b, b4);
-            const uint32_t nx = y + el.hl + (el.lit ? el.len : 0u);
-            if (nx >= SX_CODES || nx >= rend) { x = nx; break; }
-            y = nx;
-          }
-        } else if (x >= SX_CODES) {
-          good = false;
-        }
-        e = x;
-      }
-      s_link[0] = S + e;
-      s_link[1] = good ? 1u : 0u;
-    }
-    __syncthreads();
-    const uint32_t next = s_link[0];
-    ok = s_link[1] != 0;
+    const uint32_t S = ip & ~(CH_PIECE - 1);
+    for (uint32_t w = wz + tid; w < min(S / CH_PIECE, nbits); w += SX_WG) bits[w] = 0;
+    uint32_t code;
+    const uint32_t next = L.find(step, src.base, src.lim, S, ip, iend, code);
+    ok = code == 0;
     if (!ok) break;
-    if (lane == 0) {  // 4. the pieces' entries
-      const uint32_t rend = min((wave + 1) * SX_REG, segend);
-      uint32_t y = s_rent[wave];
-      while (y < rend) {
-        s_pent[y >> 5] = (uint8_t)(y & 31);
-        y = exit_at(y);
-      }
-    }
-    wave_sync();
     // the piece's elements: lengths and start bits
-    const uint32_t pe = s_pent[tid];
-    const uint32_t plen = min(SX_PIECE, segend > tid * SX_PIECE ? segend - tid * SX_PIECE : 0u);
+    const uint32_t plen = L.piece_len(S, iend), y0 = tid * CH_PIECE;
     uint32_t mask = 0, sum = 0;
-    for (uint32_t y = pe; y < plen;) {
-      uint32_t b, b4;
-      bytes_at(tid * SX_PIECE + y, b, b4);
-      const SnapEl e = snap_el(b, b4);
+    for (uint32_t y = L.pent[tid]; y < plen;) {
+      uint32_t lo, hi;
+      L.bytes8(y0 + y, lo, hi);
+      const SnapEl e = snap_el(lo, hi & 0xffu);
       mask |= 1u << y;
       sum += e.len;
       y += e.hl + (e.lit ? e.len : 0u);
     }
-    wz = S / SX_PIECE + SX_WG;
-    if (S / SX_PIECE + tid < nbits) bits[S / SX_PIECE + tid] = mask;
+    wz = S / CH_PIECE + SX_WG;
+    if (S / CH_PIECE + tid < nbits) bits[S / CH_PIECE + tid] = mask;
     const uint32_t incl = wave_incl_scan_u32(sum);
     if (lane == 63) s_sum[wave] = incl;
     __syncthreads();
@@ -265,12 +159,12 @@ __global__ __launch_bounds__(SX_WG) void k_snap_index(const ColScan* cols, SegTa
     bool bad = false;
     for (uint32_t m = mask; m; m &= m - 1) {
       const uint32_t y = (uint32_t)__builtin_ctz(m);
-      uint32_t b, b4;
-      bytes_at(tid * SX_PIECE + y, b, b4);
-      const SnapEl e = snap_el(b, b4);
+      uint32_t lo, hi;
+      L.bytes8(y0 + y, lo, hi);
+      const SnapEl e = snap_el(lo, hi & 0xffu);
       const uint32_t ob = o & (SNAP_BLOCK - 1);
       bad |= o >= total || e.len > total - o || e.len > SNAP_BLOCK - ob || (!e.lit && (e.off == 0 || e.off > ob));
-      if (!bad && ob == 0 && o) sblk[o / SNAP_BLOCK] = S + tid * SX_PIECE + y - src.m;
+      if (!bad && ob == 0 && o) sblk[o / SNAP_BLOCK] = S + y0 + y - src.m;
       o += e.len;
     }
     // (a segment's lengths sum to less than 2^30: pieces hold at most 16
