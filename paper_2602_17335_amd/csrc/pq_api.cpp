@@ -82,6 +82,8 @@ __global__ void k_decode_fixed(uint8_t* ws, const ColScan* cols, SegTable seg, u
 __global__ void k_decode_delta(uint8_t* ws, const ColScan* cols, SegTable seg, uint32_t* err);
 template <bool SLOTS>
 __global__ void k_decode_str(uint8_t* ws, const ColScan* cols, SegTable seg, uint32_t* err);
+__global__ void k_decode_all(uint8_t* ws, const ColScan* cols, SegTable seg, uint32_t units, const int32_t* which,
+                             int32_t nstr, uint32_t* err);
 __global__ void k_batch(uint8_t* ws, const ColScan* cols, const BUnit* units, const uint32_t* qbeg, uint32_t* qhead,
                         uint32_t* err);
 }  // namespace pqk
@@ -291,7 +293,7 @@ inline uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 // ---------------------------------------------------------------------------
 // handle
 // ---------------------------------------------------------------------------
-constexpr int NKERN = 18;  // kernels with a profiling slot (each fixed-width instantiation has its own)
+constexpr int NKERN = 19;  // kernels with a profiling slot (each fixed-width instantiation has its own)
 
 struct pq_file_s {
   const uint8_t* file = nullptr;  // the device-resident file (NULL for a host-resident one)
@@ -350,12 +352,13 @@ struct pq_file_s {
 // 2 PLAIN 8-byte, 3 dictionary 8-byte; k_decode_str<true> decodes the tiles
 // of slot dictionaries, k_decode_str<false> the others.
 enum { KP_SNAPPY, KP_DICT, KP_STR_TOTAL, KP_PREP, KP_FIXED0, KP_STR = KP_FIXED0 + 8, KP_DELTA, KP_EDGES,
-       KP_STR_SLOTS, KP_SNAPPY_BLK, KP_BATCH };
+       KP_STR_SLOTS, KP_SNAPPY_BLK, KP_BATCH, KP_ALL };
 static const char* kKernelNames[NKERN] = {"k_snappy", "k_dict", "k_str_total", "k_prep",
                                           "k_decode_fixed<0>", "k_decode_fixed<1>", "k_decode_fixed<2>",
                                           "k_decode_fixed<3>", "k_decode_fixed<4>", "k_decode_fixed<5>",
                                           "k_decode_fixed<6>", "k_decode_fixed<7>", "k_decode_str<false>",
-                                          "k_decode_delta", "k_edges", "k_decode_str<true>", "k_snappy_blk", "k_batch"};
+                                          "k_decode_delta", "k_edges", "k_decode_str<true>", "k_snappy_blk", "k_batch",
+                                          "k_decode_all"};
 
 static hipEvent_t pool_get(pq_file f) {
   if (!f->event_pool.empty()) {
@@ -1634,10 +1637,70 @@ static pq_status enqueue_index(pq_file f, Plan& P, uint8_t* ws, int mode, hipStr
   return PQ_OK;
 }
 
+// Scans of at most ALL_UNITS k (k + 1) tiles of k kinds decode in one launch of
+// k_decode_all: it saves k - 1 launches and runs kinds with different bounds
+// side by side, but holds fewer waves per SIMD.  Measured, one launch per kind
+// against one for all: the wide table's 6 kinds at 1M rows (15,600 tiles) 169 ->
+// 96 us, at 4M rows (62,500) 391 -> 374 us, at 8M rows (125,000) 772 -> 773 us; its
+// fixed-width columns (5 kinds) at 6M rows (76,000) 338 -> 333 us, at 8M rows
+// (101,600) 446 -> 455 us; six PLAIN columns (2 kinds) at 2M rows (11,700) 45 -> 44
+// us, at 4M rows (23,400) 70 -> 74 us; three string columns (1 kind) at 2M rows
+// (5,900) 120 -> 110 us, at 4M rows (11,700) 148 -> 163 us.
+constexpr uint32_t ALL_UNITS = 3000;
+
+// The segments of every kind in one table (units: their tiles), the slowest
+// tiles first.  False where the scan takes one launch per kind.
+static bool all_segments(const Plan& P, std::vector<Segment>& segs, uint32_t& units) {
+  uint64_t n = 0;
+  uint32_t kinds = 0;
+  auto add = [&](const std::vector<Segment>& v, uint32_t kind) {
+    kinds += !v.empty();
+    for (const Segment& sg : v) {
+      segs.push_back(Segment{sg.cs | (kind << SEG_KIND), sg.t0, sg.t1, (uint32_t)n});
+      n += sg.t1 - sg.t0;
+    }
+  };
+  add(P.str_segs[1], TK_STRSLOT);
+  add(P.str_segs[0], TK_STR);
+  add(P.fixed_segs[FX_DICT | FX_WIDE], TK_FIXED3);
+  add(P.fixed_segs[FX_DICT], TK_FIXED1);
+  add(P.delta_segs, TK_DELTA);
+  add(P.fixed_segs[FX_BSS | FX_WIDE], TK_BSS8);
+  add(P.fixed_segs[FX_BSS], TK_BSS4);
+  add(P.fixed_segs[FX_WIDE], TK_FIXED2);
+  add(P.fixed_segs[0], TK_FIXED0);
+  units = (uint32_t)n;
+  return n > 0 && segs.size() <= (size_t)MAX_SEGS && n <= (uint64_t)ALL_UNITS * kinds * (kinds + 1) && P.str_cols.size() <= 64;
+}
+
+static pq_status enqueue_str_total(pq_file f, const Plan& P, const ColScan* d_cols, uint8_t* ws, uint32_t* err,
+                                   hipStream_t s) {
+  if (P.str_cols.empty()) return PQ_OK;
+  ProfScope ps_(f, KP_STR_TOTAL, s);
+  hipLaunchKernelGGL(k_str_total, dim3(((uint32_t)P.str_cols.size() + 63) / 64), dim3(64), 0, s, d_cols,
+                     reinterpret_cast<const int32_t*>(ws + P.ws_which), (int32_t)P.str_cols.size(), err);
+  HIP_OR(hipGetLastError());
+  return PQ_OK;
+}
+
 // REQUIRED validity and the decode kernels of a plan's tiles (column table
-// d_cols), one launch per kernel kind.
+// d_cols): one launch for all kinds or one per kind.  totals: offsets[rows] of
+// the string columns too.
 static pq_status enqueue_decode(pq_file f, const Plan& P, const ColScan* d_cols, uint8_t* ws, uint32_t* err,
-                                hipStream_t s) {
+                                hipStream_t s, bool totals) {
+  std::vector<Segment> segs;
+  uint32_t units;
+  if (all_segments(P, segs, units)) {
+    ProfScope ps_(f, KP_ALL, s);
+    hipLaunchKernelGGL(k_decode_all, dim3((units + 1 + 3) / 4), dim3(256), 0, s, ws, d_cols, make_segs(segs), units,
+                       reinterpret_cast<const int32_t*>(ws + P.ws_which), totals ? (int32_t)P.str_cols.size() : 0, err);
+    HIP_OR(hipGetLastError());
+    return PQ_OK;
+  }
+  if (totals) {  // (they read only the tile prefix)
+    pq_status st = enqueue_str_total(f, P, d_cols, ws, err, s);
+    if (st != PQ_OK) return st;
+  }
   if (P.prep_threads) {
     ProfScope ps_(f, KP_PREP, s);
     hipLaunchKernelGGL(k_prep, dim3((P.prep_threads + 255) / 256), dim3(256), 0, s, d_cols, make_segs(P.prep_segs));
@@ -1667,21 +1730,20 @@ static pq_status enqueue_decode(pq_file f, const Plan& P, const ColScan* d_cols,
   return PQ_OK;
 }
 
+// The validity words tiles share.
+static pq_status enqueue_edges(pq_file f, const Plan& P, const ColScan* d_cols, uint8_t* ws, hipStream_t s) {
+  if (!P.edge_threads) return PQ_OK;
+  ProfScope ps_(f, KP_EDGES, s);
+  hipLaunchKernelGGL(k_edges, dim3((P.edge_threads + 255) / 256), dim3(256), 0, s, ws, d_cols, make_segs(P.edge_segs));
+  HIP_OR(hipGetLastError());
+  return PQ_OK;
+}
+
 // offsets[rows] of string columns and the validity words tiles share.
 static pq_status enqueue_finish(pq_file f, const Plan& P, const ColScan* d_cols, uint8_t* ws, uint32_t* err,
                                 hipStream_t s) {
-  if (!P.str_cols.empty()) {
-    ProfScope ps_(f, KP_STR_TOTAL, s);
-    hipLaunchKernelGGL(k_str_total, dim3(((uint32_t)P.str_cols.size() + 63) / 64), dim3(64), 0, s, d_cols,
-                       reinterpret_cast<const int32_t*>(ws + P.ws_which), (int32_t)P.str_cols.size(), err);
-    HIP_OR(hipGetLastError());
-  }
-  if (P.edge_threads) {
-    ProfScope ps_(f, KP_EDGES, s);
-    hipLaunchKernelGGL(k_edges, dim3((P.edge_threads + 255) / 256), dim3(256), 0, s, ws, d_cols, make_segs(P.edge_segs));
-    HIP_OR(hipGetLastError());
-  }
-  return PQ_OK;
+  pq_status st = enqueue_str_total(f, P, d_cols, ws, err, s);
+  return st == PQ_OK ? enqueue_edges(f, P, d_cols, ws, s) : st;
 }
 
 static pq_status enqueue(pq_file f, Plan& P, uint8_t* ws, hipStream_t s) {
@@ -1689,22 +1751,8 @@ static pq_status enqueue(pq_file f, Plan& P, uint8_t* ws, hipStream_t s) {
   pq_status st = enqueue_front(f, P, ws, err, s);
   if (st != PQ_OK) return st;
   const ColScan* d_cols = reinterpret_cast<const ColScan*>(ws + P.ws_cols);
-  // the string totals first (they read only the tile prefix), then the
-  // decode kernels, then the shared validity words
-  if (!P.str_cols.empty()) {
-    ProfScope ps_(f, KP_STR_TOTAL, s);
-    hipLaunchKernelGGL(k_str_total, dim3(((uint32_t)P.str_cols.size() + 63) / 64), dim3(64), 0, s, d_cols,
-                       reinterpret_cast<const int32_t*>(ws + P.ws_which), (int32_t)P.str_cols.size(), err);
-    HIP_OR(hipGetLastError());
-  }
-  st = enqueue_decode(f, P, d_cols, ws, err, s);
-  if (st != PQ_OK) return st;
-  if (P.edge_threads) {
-    ProfScope ps_(f, KP_EDGES, s);
-    hipLaunchKernelGGL(k_edges, dim3((P.edge_threads + 255) / 256), dim3(256), 0, s, ws, d_cols, make_segs(P.edge_segs));
-    HIP_OR(hipGetLastError());
-  }
-  return PQ_OK;
+  st = enqueue_decode(f, P, d_cols, ws, err, s, true);
+  return st == PQ_OK ? enqueue_edges(f, P, d_cols, ws, s) : st;
 }
 
 // Builds the tile prefix at open: for every column with string or DELTA
@@ -2002,7 +2050,7 @@ extern "C" pq_status pq_scan_streamed(pq_file f, uint64_t col_mask, int32_t rg_b
     st = make_plan(f, col_mask, g, g + 1, Pg);
     const ColScan* d_cols = reinterpret_cast<const ColScan*>(ws + P.ws_rgcols + sizeof(ColScan) * P.cols.size() * (size_t)i);
     if (st == PQ_OK) st = enqueue_decompress(f, Pg, d_cols, ws, err, s);
-    if (st == PQ_OK) st = enqueue_decode(f, Pg, d_cols, ws, err, s);
+    if (st == PQ_OK) st = enqueue_decode(f, Pg, d_cols, ws, err, s, false);
     if (st == PQ_OK && hipEventRecord(freed[slot], s) != hipSuccess) st = fail(PQ_EHIP, "event record failed");
   }
   if (st == PQ_OK) st = enqueue_finish(f, P, reinterpret_cast<ColScan*>(ws + P.ws_cols), ws, err, s);

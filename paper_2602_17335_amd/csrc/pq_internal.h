@@ -311,6 +311,7 @@ struct Segment {
   uint32_t cs, t0, t1, wg0;
 };
 constexpr int MAX_SEGS = 64;
+constexpr uint32_t SEG_KIND = 16;  // k_decode_all: Segment::cs holds the decoder kind from this bit on
 // With spread set, unit u of the launch is tile u / n of segment u % n (the
 // segments' wg0 unused): consecutive waves take tiles of different segments.
 struct SegTable {

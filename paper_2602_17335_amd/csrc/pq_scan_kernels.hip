@@ -1,13 +1,10 @@
 // pq_scan_kernels.hip -- kernels of one scan (everything pq_scan enqueues),
 // and k_prepass, which pq_open_device runs once to build the tile prefix.
 //
-//   k_snappy        Snappy page bodies -> workspace (one wave per page)
-//   k_snap_index    Snappy block index and element counts (at open, one wave per page)
-//   k_snap_order    a scan's Snappy blocks in buckets of element count
-//   k_snappy_blk    Snappy page bodies with a block index (one lane per 64 KiB block,
-//                   SNAP_LANES blocks per wave, elements in batches)
+//   k_snappy        Snappy page bodies without a block index -> workspace (one wave per page)
 //   k_prep          validity edge words cleared / REQUIRED validity set to ones
 //   k_dict          dictionary pages -> device dictionaries
+//   k_decode_all    every kind of tile of a scan of few tiles in one launch
 //   k_prepass       per-tile DELTA sums and string byte counts (at open)
 //   k_str_total     offsets[rows] and the chars capacity check of string columns
 //   k_decode_fixed  definition levels; PLAIN / dictionary INT32, INT64, DOUBLE values
@@ -1529,14 +1526,15 @@ __global__ __launch_bounds__(WG) void k_dict(const PageDev* __restrict__ pages, 
 // k_str_total: offsets[rows] and the chars capacity check of each string
 // column of a scan (one thread per column), from the tile prefix.
 // ---------------------------------------------------------------------------
-__global__ void k_str_total(const ColScan* __restrict__ cols, const int32_t* __restrict__ which, int32_t n,
-                            uint32_t* __restrict__ err) {
-  const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= n) return;
-  const ColScan& cs = cols[which[i]];
+__device__ __forceinline__ void string_total(const ColScan& cs, uint32_t* err) {
   const uint64_t tot = cs.fd.tpfx[cs.tile_end] - cs.fd.tpfx[cs.tile_begin];
   if (cs.offsets) cs.offsets[cs.rows] = (int64_t)tot;
   if (tot > cs.chars_capacity) set_err(err, ERR_CAPACITY, (uint32_t)cs.col);
+}
+__global__ void k_str_total(const ColScan* __restrict__ cols, const int32_t* __restrict__ which, int32_t n,
+                            uint32_t* __restrict__ err) {
+  const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i < n) string_total(cols[which[i]], err);
 }
 
 // ---------------------------------------------------------------------------
@@ -2284,6 +2282,42 @@ __device__ __forceinline__ void tile_required_validity(const WaveTile& c, uint32
     const int64_t left = c.cs.rows - W * 32;
     reinterpret_cast<uint32_t*>(c.cs.validity)[W] = left >= 32 ? 0xffffffffu : ((1u << left) - 1);
   }
+}
+
+// k_decode_all: the decode step of a scan of few tiles in one launch, one wave
+// per tile: every kind's segments in one table (Segment::cs holds the decoder
+// kind above SEG_KIND), the validity words of REQUIRED columns with the tiles
+// and, by one wave after them, offsets[rows] of the string columns (which[0,
+// nstr)).  What bounds such a scan is the latency of one tile (10-25 us) and of
+// each launch, which the one-launch-per-kind form pays for every kind in turn.
+__global__ __launch_bounds__(WG) void k_decode_all(uint8_t* __restrict__ ws, const ColScan* __restrict__ cols,
+                                                   SegTable seg, uint32_t units, const int32_t* __restrict__ which,
+                                                   int32_t nstr, uint32_t* __restrict__ err) {
+  __shared__ __align__(16) uint32_t s_lds[NWAVES][BATCH_LDS_WORDS];
+  lds_u32* wl = (lds_u32*)&s_lds[threadIdx.x >> 6][0];
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t unit = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * NWAVES + (threadIdx.x >> 6)));
+  if (unit >= units) {
+    if (unit == units && (int32_t)lane < nstr) string_total(cols[which[lane]], err);
+    return;
+  }
+  const Segment sg = seg_lookup(seg, unit);
+  const uint32_t t = sg.t0 + (unit - sg.wg0);
+  if (t >= sg.t1) return;
+  WaveTile c;
+  load_tile(cols, sg.cs & ((1u << SEG_KIND) - 1u), t, ws, c);
+  switch (sg.cs >> SEG_KIND) {
+    case TK_FIXED0: tile_fixed<0, false>(c, ws, err, wl); break;
+    case TK_FIXED1: tile_fixed<FX_DICT, false>(c, ws, err, wl); break;
+    case TK_FIXED2: tile_fixed<FX_WIDE, false>(c, ws, err, wl); break;
+    case TK_FIXED3: tile_fixed<FX_DICT | FX_WIDE, false>(c, ws, err, wl); break;
+    case TK_BSS4: tile_fixed<FX_BSS, false>(c, ws, err, wl); break;
+    case TK_BSS8: tile_fixed<FX_BSS | FX_WIDE, false>(c, ws, err, wl); break;
+    case TK_DELTA: tile_delta<false>(c, ws, err, wl); break;
+    case TK_STR: tile_str<false, false>(c, ws, err, wl); break;
+    default: tile_str<true, false>(c, ws, err, wl); break;
+  }
+  tile_required_validity(c, lane);
 }
 
 __global__ __launch_bounds__(WG) void k_batch(uint8_t* __restrict__ ws, const ColScan* __restrict__ cols,
