@@ -1987,6 +1987,8 @@ extern "C" pq_status pq_scan_noalloc(pq_file f, uint64_t col_mask, int32_t rg_be
 // ---------------------------------------------------------------------------
 // streamed scans of host-resident files
 // ---------------------------------------------------------------------------
+// A copy costs about 10 us before its first byte, the time of 512 KiB at 57 GB/s.
+constexpr uint64_t COPY_GAP = 256 * 1024;
 extern "C" pq_status pq_scan_streamed(pq_file f, uint64_t col_mask, int32_t rg_begin, int32_t rg_end,
                                       const pq_column_out* outs, int32_t n_outs, void* workspace, uint64_t workspace_bytes,
                                       pq_stream copy_stream, pq_stream stream) {
@@ -2032,14 +2034,20 @@ extern "C" pq_status pq_scan_streamed(pq_file f, uint64_t col_mask, int32_t rg_b
     const int g = rg_begin + i, slot = i % 2;
     if (i >= 2 && hipStreamWaitEvent(cs, freed[slot], 0) != hipSuccess) { st = fail(PQ_EHIP, "stream wait failed"); break; }
     uint8_t* base = ws + P.ws_stage + (uint64_t)slot * P.stage_bytes;
+    // the selected chunks in file order, neighbours (and chunks less than
+    // COPY_GAP apart) in one copy
+    std::vector<std::pair<uint64_t, uint64_t>> runs;
     for (const ColScan& c : P.cols) {
       const ChunkDev& ch = f->chunks[(size_t)c.col * f->nrg + g];
-      if (ch.end > ch.start &&
-          hipMemcpyAsync(base + (ch.start - P.rg_lo[(size_t)i]), f->host + ch.start, ch.end - ch.start,
-                         hipMemcpyHostToDevice, cs) != hipSuccess) {
+      if (ch.end > ch.start) runs.push_back({ch.start, ch.end});
+    }
+    std::sort(runs.begin(), runs.end());
+    for (size_t k = 0; k < runs.size() && st == PQ_OK;) {
+      const uint64_t a = runs[k].first;
+      uint64_t e = runs[k].second;
+      for (++k; k < runs.size() && runs[k].first <= e + COPY_GAP; ++k) e = std::max(e, runs[k].second);
+      if (hipMemcpyAsync(base + (a - P.rg_lo[(size_t)i]), f->host + a, e - a, hipMemcpyHostToDevice, cs) != hipSuccess)
         st = fail(PQ_EHIP, "row group %d: host-to-device copy failed", g);
-        break;
-      }
     }
     if (st != PQ_OK) break;
     if (hipEventRecord(copied[slot], cs) != hipSuccess || hipStreamWaitEvent(s, copied[slot], 0) != hipSuccess) {
