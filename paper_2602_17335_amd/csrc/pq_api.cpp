@@ -36,29 +36,37 @@ __global__ void k_values(const IxPage* ixs, uint32_t nix, PageDev* pages, const 
 template <uint32_t NT>
 __global__ void k_strings(const IxPage* ixs, const uint32_t* list, PageDev* pages, OpenBufs bufs, uint32_t* strck,
                           uint32_t* flag, const uint32_t* err, const uint32_t* seq);
-__global__ void k_str_cand(const IxPage* ixs, const StrLong* sls, const uint32_t* seg_sl, const PageDev* pages,
-                           OpenBufs bufs, uint32_t* exits, const uint32_t* flag, const uint32_t* err);
-__global__ void k_str_link(const IxPage* ixs, const StrLong* sls, const PageDev* pages, OpenBufs bufs,
+template <int F>
+__global__ void k_seg_cand(const IxPage* ixs, const SegPage* sps, const uint32_t* seg_sp, const PageDev* pages,
+                           const ChunkDev* chunks, OpenBufs bufs, uint32_t* exits, const uint32_t* flag,
+                           const uint32_t* err);
+template <int F>
+__global__ void k_seg_link(const IxPage* ixs, const SegPage* sps, const PageDev* pages, OpenBufs bufs,
                            const uint32_t* exits, uint32_t* entry, uint32_t* seq, const uint32_t* flag,
                            const uint32_t* err);
-__global__ void k_str_fill(const IxPage* ixs, const StrLong* sls, const uint32_t* seg_sl, PageDev* pages, OpenBufs bufs,
-                           const uint32_t* entry, const uint32_t* seq, uint32_t* at, uint8_t* ent, uint32_t* total,
-                           const uint32_t* flag, const uint32_t* err);
-__global__ void k_str_base(const IxPage* ixs, const StrLong* sls, const PageDev* pages, uint32_t* total,
+template <int F>
+__global__ void k_seg_fill(const IxPage* ixs, const SegPage* sps, const uint32_t* seg_sp, PageDev* pages,
+                           const ChunkDev* chunks, OpenBufs bufs, const uint32_t* entry, const uint32_t* seq,
+                           uint32_t* at, uint8_t* ent, uint32_t* total, const uint32_t* flag, const uint32_t* err);
+template <int F>
+__global__ void k_seg_base(const IxPage* ixs, const SegPage* sps, const PageDev* pages, uint32_t* total,
                            const uint32_t* seq, uint32_t* flag, const uint32_t* err);
-__global__ void k_str_ck(const IxPage* ixs, const StrLong* sls, const uint32_t* seg_sl, const PageDev* pages,
+__global__ void k_str_ck(const IxPage* ixs, const SegPage* sps, const uint32_t* seg_sp, const PageDev* pages,
                          OpenBufs bufs, const uint32_t* base, const uint32_t* at, const uint8_t* ent,
                          const uint32_t* seq, uint32_t* strck, const uint32_t* flag, const uint32_t* err);
+__global__ void k_dl_ck(const IxPage* ixs, const SegPage* sps, const uint32_t* seg_sp, PageDev* pages,
+                        const ChunkDev* chunks, OpenBufs bufs, const uint32_t* base, const uint32_t* at,
+                        const uint8_t* ent, const uint32_t* seq, uint32_t* blkpos, uint32_t* flag, const uint32_t* err);
 template <uint32_t NT>
 __global__ void k_di(const IxPage* ixs, const uint32_t* list, const PageDev* pages, OpenBufs bufs, uint32_t* at,
-                     uint8_t* ent, uint32_t* flag, const uint32_t* err);
+                     uint8_t* ent, uint32_t* flag, const uint32_t* err, const uint32_t* seq);
 template <uint32_t NT>
 __global__ void k_dl(const IxPage* ixs, const uint32_t* list, PageDev* pages, const ChunkDev* chunks, OpenBufs bufs,
-                     uint32_t* blkpos, uint32_t* flag, const uint32_t* err);
+                     uint32_t* blkpos, uint32_t* flag, const uint32_t* err, const uint32_t* seq);
 __global__ void k_value_tiles(const IxPage* ixs, uint32_t nix, uint32_t tile0, uint32_t ntiles, const PageDev* pages,
                               const ChunkDev* chunks, OpenBufs bufs, const uint32_t* at, const uint8_t* ent,
-                              const uint32_t* blkpos, const uint32_t* strck, const uint32_t* flag, TileDev* tiles,
-                              Ck* ckv, const uint32_t* err);
+                              const uint32_t* blkpos, const uint32_t* strck, const SegPage* sps, const uint32_t* base,
+                              const uint32_t* seq, const uint32_t* flag, TileDev* tiles, Ck* ckv, const uint32_t* err);
 __global__ void k_index(const uint8_t* file, const uint8_t* scratch, PageDev* pages, const IxPage* ixs,
                         const uint32_t* flag, const ChunkDev* chunks, TileDev* tiles, uint32_t* strck, uint32_t* ckl,
                         Ck* ckv, uint32_t* err, uint64_t file_lim, uint64_t scratch_lim, const uint8_t* xscratch,
@@ -465,6 +473,7 @@ constexpr uint64_t OPEN_GUARD = 4096;
 // The open of a file in device memory; with host_copy the buffer is a
 // temporary device copy of a host-resident file, so every dictionary is
 // copied into the handle's arena (none may point into the buffer).
+constexpr uint64_t CUS = 256;  // compute units
 static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, bool host_copy, pq_file* out) {
   if (!out) return fail(PQ_EINVAL, "out is NULL");
   *out = nullptr;
@@ -938,7 +947,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       const PageDev& pg = f->pages[plist[i]];
       const bool str = f->chunks[pg.chunk].type == T_BYTE_ARRAY;
       IxPage& x = ixs[i];
-      x = IxPage{plist[i], 0, 0, 0, 0, 0, 0};
+      x = IxPage{plist[i], 0, 0, 0, 0, 0, 0, ~0u};
       if (P.dict) {
         if (str) lists[C_STRINGS].push_back({pg.uncomp_size, i});
         continue;
@@ -984,31 +993,49 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       }
       nshort[c] = (uint32_t)lists[c].size() - nlong[c];
     }
-    // the very long string pages (the first of their list) and their segments
-    std::vector<StrLong> sls;
-    std::vector<uint32_t> seg_sl;
-    for (const auto& l : lists[C_STRINGS]) {
-      if (l.first <= STR_LONG) break;
-      const uint32_t ns = (uint32_t)(((uint64_t)l.first + 15 + 32767) / 32768);
-      sls.push_back(StrLong{l.second, (uint32_t)seg_sl.size(), ns});
-      seg_sl.resize(seg_sl.size() + ns, (uint32_t)sls.size() - 1);
+    // The value streams whose segments are done side by side: the longest of
+    // a kind, in segments of 32 KiB, when that takes fewer rounds of
+    // workgroups (one per CU; each segment's exits are found twice) than the
+    // longest page has segments.
+    static constexpr int seg_list[SEG_KINDS] = {C_STRINGS, C_DI, C_DL};
+    std::vector<SegPage> sps;
+    std::vector<uint32_t> seg_sp;
+    uint32_t sp0[SEG_KINDS], nsp[SEG_KINDS], sg0[SEG_KINDS], nsg[SEG_KINDS];
+    for (int k = 0; k < SEG_KINDS; ++k) {
+      sp0[k] = (uint32_t)sps.size();
+      sg0[k] = (uint32_t)seg_sp.size();
+      nsp[k] = nsg[k] = 0;
+      const auto& l = lists[seg_list[k]];
+      auto segs_of = [](uint32_t len) { return (uint32_t)(((uint64_t)len + 15 + 32767) / 32768); };
+      uint64_t all = 0;
+      for (uint32_t i = 0; i < nlong[seg_list[k]]; ++i) all += segs_of(l[i].first);
+      const uint32_t most = nlong[seg_list[k]] ? segs_of(l[0].first) : 0;
+      if (2 * ((all + CUS - 1) / CUS) + 2 >= most) continue;
+      nsp[k] = nlong[seg_list[k]];
+      for (uint32_t i = 0; i < nsp[k]; ++i) {
+        const uint32_t ns = segs_of(l[i].first);
+        ixs[l[i].second].sp = (uint32_t)sps.size();
+        sps.push_back(SegPage{l[i].second, (uint32_t)seg_sp.size() - sg0[k], ns});
+        seg_sp.resize(seg_sp.size() + ns, i);
+      }
+      nsg[k] = (uint32_t)seg_sp.size() - sg0[k];
     }
-    const size_t nsl = sls.size(), nsg = seg_sl.size();
-    const size_t o_ord = align_up(sizeof(IxPage) * nix, 256), o_sl = align_up(o_ord + 4 * order.size(), 256),
-                 o_sgs = align_up(o_sl + sizeof(StrLong) * nsl, 256), o_flag = align_up(o_sgs + 4 * nsg, 256),
+    const size_t nspa = sps.size(), nsga = seg_sp.size();
+    const size_t o_ord = align_up(sizeof(IxPage) * nix, 256), o_sp = align_up(o_ord + 4 * order.size(), 256),
+                 o_sgs = align_up(o_sp + sizeof(SegPage) * nspa, 256), o_flag = align_up(o_sgs + 4 * nsga, 256),
                  o_lat = align_up(o_flag + 4ull * nix, 256), o_lval = align_up(o_lat + 4 * nlv, 256),
                  o_lent = align_up(o_lval + 4 * nlv, 256), o_vat = align_up(o_lent + nlv, 256),
                  o_vent = align_up(o_vat + 4 * nvp, 256), o_blk = align_up(o_vent + nvp, 256), o_sent = align_up(o_blk + 4 * nblk, 256),
-                 o_stot = align_up(o_sent + 4 * nsg, 256), o_sseq = align_up(o_stot + 4 * nsg, 256),
-                 o_sat = align_up(o_sseq + 4 * nsl, 256), o_spe = align_up(o_sat + 4096 * nsg, 256),
-                 o_sex = align_up(o_spe + 1024 * nsg, 256), ix_total = o_sex + 4096 * nsg;
+                 o_stot = align_up(o_sent + 4 * nsga, 256), o_sseq = align_up(o_stot + 4 * nsga, 256),
+                 o_sat = align_up(o_sseq + 4 * nspa, 256), o_spe = align_up(o_sat + 4096 * nsga, 256),
+                 o_sex = align_up(o_spe + 1024 * nsga, 256), ix_total = o_sex + 8192 * nsga;
     if (hipMalloc(&d_ix, ix_total ? ix_total : 256) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: chain tables"); }
     std::vector<uint8_t> up(o_lat, 0);
     memcpy(up.data(), ixs.data(), sizeof(IxPage) * nix);
     if (!order.empty()) memcpy(up.data() + o_ord, order.data(), 4 * order.size());
-    if (nsl) {
-      memcpy(up.data() + o_sl, sls.data(), sizeof(StrLong) * nsl);
-      memcpy(up.data() + o_sgs, seg_sl.data(), 4 * nsg);
+    if (nspa) {
+      memcpy(up.data() + o_sp, sps.data(), sizeof(SegPage) * nspa);
+      memcpy(up.data() + o_sgs, seg_sp.data(), 4 * nsga);
     }
     OPEN_HIP(hipMemcpyAsync(d_ix, up.data(), up.size(), hipMemcpyHostToDevice, s));
     const IxPage* d_ixs = reinterpret_cast<const IxPage*>(d_ix);
@@ -1037,43 +1064,70 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       hipLaunchKernelGGL(k_values, dim3((nix + 63) / 64), dim3(64), 0, s, d_ixs, nix, f->d_pages, f->d_chunks, bufs,
                          d_flag, f->d_err);
     }
-    if (nsl) {
-      const StrLong* d_sl = reinterpret_cast<const StrLong*>(d_ix + o_sl);
-      const uint32_t* d_sgs = reinterpret_cast<const uint32_t*>(d_ix + o_sgs);
-      uint32_t* d_sent = reinterpret_cast<uint32_t*>(d_ix + o_sent);
-      uint32_t* d_stot = reinterpret_cast<uint32_t*>(d_ix + o_stot);
-      uint32_t* d_sseq = reinterpret_cast<uint32_t*>(d_ix + o_sseq);
-      uint32_t* d_sat = reinterpret_cast<uint32_t*>(d_ix + o_sat);
-      uint8_t* d_spe = d_ix + o_spe;
-      uint32_t* d_sex = reinterpret_cast<uint32_t*>(d_ix + o_sex);
-      hipLaunchKernelGGL(k_str_cand, dim3((uint32_t)nsg), dim3(1024), 0, s, d_ixs, d_sl, d_sgs, f->d_pages, bufs, d_sex,
-                         d_flag, f->d_err);
-      hipLaunchKernelGGL(k_str_link, dim3((uint32_t)nsl), dim3(256), 0, s, d_ixs, d_sl, f->d_pages, bufs, d_sex, d_sent,
-                         d_sseq, d_flag, f->d_err);
-      hipLaunchKernelGGL(k_str_fill, dim3((uint32_t)nsg), dim3(1024), 0, s, d_ixs, d_sl, d_sgs, f->d_pages, bufs, d_sent,
-                         d_sseq, d_sat, d_spe, d_stot, d_flag, f->d_err);
-      hipLaunchKernelGGL(k_str_base, dim3((uint32_t)nsl), dim3(64), 0, s, d_ixs, d_sl, f->d_pages, d_stot, d_sseq, d_flag,
-                         f->d_err);
-      hipLaunchKernelGGL(k_str_ck, dim3((uint32_t)(4 * nsg)), dim3(256), 0, s, d_ixs, d_sl, d_sgs, f->d_pages, bufs,
-                         d_stot, d_sat, d_spe, d_sseq, f->d_strck, d_flag, f->d_err);
-      // those that could not be linked, front to back
-      hipLaunchKernelGGL(k_strings<1024>, dim3((uint32_t)nsl), dim3(1024), 0, s, d_ixs, d_ord + first[C_STRINGS],
-                         f->d_pages, bufs, f->d_strck, d_flag, f->d_err, d_sseq);
-      first[C_STRINGS] += (uint32_t)nsl;
-      nlong[C_STRINGS] -= (uint32_t)nsl;
+    // kind k's pages in segments (SEG_RUN), those that could not be linked by one
+    // workgroup each, then the rest of the kind's list
+    const SegPage* d_sp = reinterpret_cast<const SegPage*>(d_ix + o_sp);
+    const uint32_t* d_sgs = reinterpret_cast<const uint32_t*>(d_ix + o_sgs);
+    uint32_t* d_sent = reinterpret_cast<uint32_t*>(d_ix + o_sent);
+    uint32_t* d_stot = reinterpret_cast<uint32_t*>(d_ix + o_stot);
+    uint32_t* d_sseq = reinterpret_cast<uint32_t*>(d_ix + o_sseq);
+    uint32_t* d_sat = reinterpret_cast<uint32_t*>(d_ix + o_sat);
+    uint8_t* d_spe = d_ix + o_spe;
+    uint32_t* d_sex = reinterpret_cast<uint32_t*>(d_ix + o_sex);
+#define SEG_RUN(k, at_, ent_)                                                                                         \
+  do {                                                                                                                \
+    const size_t g0 = sg0[k];                                                                                         \
+    hipLaunchKernelGGL(k_seg_cand<k>, dim3(nsg[k]), dim3(1024), 0, s, d_ixs, d_sp + sp0[k], d_sgs + g0, f->d_pages,   \
+                       f->d_chunks, bufs, d_sex + 2048 * g0, d_flag, f->d_err);                                       \
+    hipLaunchKernelGGL(k_seg_link<k>, dim3(nsp[k]), dim3(256), 0, s, d_ixs, d_sp + sp0[k], f->d_pages, bufs,          \
+                       d_sex + 2048 * g0, d_sent + g0, d_sseq + sp0[k], d_flag, f->d_err);                            \
+    hipLaunchKernelGGL(k_seg_fill<k>, dim3(nsg[k]), dim3(1024), 0, s, d_ixs, d_sp + sp0[k], d_sgs + g0, f->d_pages,   \
+                       f->d_chunks, bufs, d_sent + g0, d_sseq + sp0[k], at_, ent_, d_stot + g0, d_flag, f->d_err);    \
+    hipLaunchKernelGGL(k_seg_base<k>, dim3(nsp[k]), dim3(64), 0, s, d_ixs, d_sp + sp0[k], f->d_pages, d_stot + g0,    \
+                       d_sseq + sp0[k], d_flag, f->d_err);                                                            \
+  } while (0)
+#define SEG_REST(k, kern, ...)                                                                                        \
+  do {                                                                                                                \
+    hipLaunchKernelGGL(kern<1024>, dim3(nsp[k]), dim3(1024), 0, s, d_ixs, d_ord + first[seg_list[k]], __VA_ARGS__,    \
+                       d_sseq + sp0[k]);                                                                              \
+    first[seg_list[k]] += nsp[k];                                                                                     \
+    nlong[seg_list[k]] -= nsp[k];                                                                                     \
+  } while (0)
+    const uint32_t* no_seq = nullptr;
+    if (nsp[SEG_STR]) {
+      const size_t g0 = sg0[SEG_STR];
+      SEG_RUN(SEG_STR, d_sat + 1024 * g0, d_spe + 1024 * g0);
+      hipLaunchKernelGGL(k_str_ck, dim3(4 * nsg[SEG_STR]), dim3(256), 0, s, d_ixs, d_sp + sp0[SEG_STR], d_sgs + g0,
+                         f->d_pages, bufs, d_stot + g0, d_sat + 1024 * g0, d_spe + 1024 * g0, d_sseq + sp0[SEG_STR],
+                         f->d_strck, d_flag, f->d_err);
+      SEG_REST(SEG_STR, k_strings, f->d_pages, bufs, f->d_strck, d_flag, f->d_err);
     }
-    CHAINS(C_STRINGS, k_strings, f->d_pages, bufs, f->d_strck, d_flag, f->d_err, (const uint32_t*)nullptr);
-    CHAINS(C_DI, k_di, f->d_pages, bufs, d_vat, d_vent, d_flag, f->d_err);
-    CHAINS(C_DL, k_dl, f->d_pages, f->d_chunks, bufs, d_blk, d_flag, f->d_err);
+    CHAINS(C_STRINGS, k_strings, f->d_pages, bufs, f->d_strck, d_flag, f->d_err, no_seq);
+    if (nsp[SEG_DI]) {
+      SEG_RUN(SEG_DI, d_vat, d_vent);
+      SEG_REST(SEG_DI, k_di, f->d_pages, bufs, d_vat, d_vent, d_flag, f->d_err);
+    }
+    CHAINS(C_DI, k_di, f->d_pages, bufs, d_vat, d_vent, d_flag, f->d_err, no_seq);
+    if (nsp[SEG_DL]) {
+      const size_t g0 = sg0[SEG_DL];
+      SEG_RUN(SEG_DL, d_sat + 1024 * g0, d_spe + 1024 * g0);
+      hipLaunchKernelGGL(k_dl_ck, dim3(4 * nsg[SEG_DL]), dim3(256), 0, s, d_ixs, d_sp + sp0[SEG_DL], d_sgs + g0,
+                         f->d_pages, f->d_chunks, bufs, d_stot + g0, d_sat + 1024 * g0, d_spe + 1024 * g0,
+                         d_sseq + sp0[SEG_DL], d_blk, d_flag, f->d_err);
+      SEG_REST(SEG_DL, k_dl, f->d_pages, f->d_chunks, bufs, d_blk, d_flag, f->d_err);
+    }
+    CHAINS(C_DL, k_dl, f->d_pages, f->d_chunks, bufs, d_blk, d_flag, f->d_err, no_seq);
     if (ntl)
       hipLaunchKernelGGL(k_value_tiles, dim3((uint32_t)((ntl + 3) / 4)), dim3(64), 0, s, d_ixs, nix, (uint32_t)tile0,
-                         (uint32_t)ntl, f->d_pages, f->d_chunks, bufs, d_vat, d_vent, d_blk, f->d_strck, d_flag,
-                         f->d_tiles, f->d_ckv, f->d_err);
+                         (uint32_t)ntl, f->d_pages, f->d_chunks, bufs, d_vat, d_vent, d_blk, f->d_strck, d_sp,
+                         d_stot + sg0[SEG_DI], d_sseq, d_flag, f->d_tiles, f->d_ckv, f->d_err);
     // the pages that were left
     hipLaunchKernelGGL(k_index, dim3(nix), dim3(64), 0, s, file, scr, f->d_pages, d_ixs, d_flag, f->d_chunks, f->d_tiles,
                        f->d_strck, f->d_ckl, f->d_ckv, f->d_err, flim, scr_lim, xscr, xscr_lim);
     if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "index launch failed"); }
 #undef CHAINS
+#undef SEG_RUN
+#undef SEG_REST
     if (P.dict) {
       // resident dictionaries, while the window holds the decompressed pages
       {

@@ -149,6 +149,7 @@ struct IxPage {
   uint32_t tile0, ntiles;  // file-wide first tile, tiles (0: dictionary pages)
   uint32_t lv0, nlv;       // pieces of the level stream
   uint32_t v0, nv;         // pieces of the dictionary-index stream, or DELTA block positions
+  uint32_t sp;             // its entry in the pass's SegPage list (~0: none)
 };
 // The buffers an open pass reads: the file, the decompression layout, the
 // expansion layout, and their readable bytes.
@@ -159,10 +160,10 @@ struct OpenBufs {
 // Streams of at most this many bytes take the chain kernels' workgroups of 256
 // threads (8 KiB segments, five per CU), longer ones those of 1024 (32 KiB).
 constexpr uint32_t CHAIN_SMALL = 8192;
-// A string page of more than STR_LONG bytes: its segments are done side by
-// side (segments [seg0, seg0 + nseg) of the pass's list).
-constexpr uint32_t STR_LONG = 1u << 21;
-struct StrLong {
+// A page whose value stream's 32 KiB segments are done side by side: segments
+// [seg0, seg0 + nseg) of its kind's list.
+enum : int { SEG_STR, SEG_DI, SEG_DL, SEG_KINDS };
+struct SegPage {
   uint32_t ix, seg0, nseg;
 };
 __host__ __device__ inline uint32_t chain_pieces(uint64_t len) { return (uint32_t)((len + 15 + 31) / 32); }

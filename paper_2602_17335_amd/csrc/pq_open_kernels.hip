@@ -712,7 +712,9 @@ __global__ void k_layout(uint32_t p0, uint32_t p1, int dicts, PageDev* pages, co
 }
 
 // A run of a w-bit hybrid stream from its first eight bytes, left stream
-// bytes from its header on (run_next's rules; headers of at most 32 bits).
+// bytes from its header on (run_next's rules; headers of at most 28 bits and
+// payloads below 2^24 groups, STEP_ODD otherwise).  The chain kernels decode one
+// at every byte of a stream, so instructions count.
 struct HRun {
   uint32_t adv;  // its bytes, or STEP_BAD / STEP_ODD
   uint32_t hl;   // header bytes
@@ -723,24 +725,14 @@ struct HRun {
 __device__ __forceinline__ HRun hrun(uint32_t lo, uint32_t hi, uint32_t left, uint32_t w) {
   HRun r;
   const uint32_t cont = ~lo & 0x80808080u;  // bytes that end the header
-  uint32_t h = (lo & 0x7fu) | ((lo >> 1) & 0x3f80u) | ((lo >> 2) & 0x1fc000u) | ((lo >> 3) & 0xfe00000u);
-  bool odd = false;
-  if (cont) {
-    r.hl = ((uint32_t)__builtin_ctz(cont) >> 3) + 1;
-    if (r.hl < 4) h &= (1u << (7 * r.hl)) - 1u;
-  } else {
-    r.hl = 5;
-    odd = (hi & 0xf0u) != 0;
-    h |= hi << 28;
-  }
+  const uint32_t h4 = (lo & 0x7fu) | ((lo >> 1) & 0x3f80u) | ((lo >> 2) & 0x1fc000u) | ((lo >> 3) & 0xfe00000u);
+  r.hl = ((uint32_t)__builtin_ctz(cont | 0x80000000u) >> 3) + 1;
+  const uint32_t h = __builtin_amdgcn_ubfe(h4, 0, 7 * r.hl), g = h >> 1;
   r.bp = (h & 1) != 0;
-  const uint32_t g = h >> 1;
-  const uint64_t pay = r.bp ? (uint64_t)g * w : (w + 7) / 8;
+  const uint32_t pay = r.bp ? __umul24(g, w) : (w + 7) / 8;
   r.n = r.bp ? 8 * g : g;
-  const uint64_t v8 = ((uint64_t)hi << 32) | lo;
-  r.val = (uint32_t)(v8 >> (8 * r.hl)) & 0xffu;
-  const bool bad = r.hl > left || (r.bp && g > (1u << 28)) || pay > left - r.hl;
-  r.adv = odd ? STEP_ODD : bad ? STEP_BAD : r.hl + (uint32_t)pay;
+  r.val = (r.hl < 4 ? __builtin_amdgcn_alignbyte(hi, lo, r.hl) : hi) & 0xffu;
+  r.adv = cont == 0 || (r.bp && (g >> 24)) ? STEP_ODD : r.hl + pay > left ? STEP_BAD : r.hl + pay;
   return r;
 }
 // A level run: levels are 0 or 1.
@@ -1108,6 +1100,13 @@ __global__ void k_values(const IxPage* ixs, uint32_t nix, PageDev* pages, const 
 // DELTA_BYTE_ARRAY page or a string dictionary, one workgroup per page: the
 // position of every STR_CK-th value, and a dictionary's longest entry.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t str_step(uint32_t lo, uint32_t left) {
+  return left < 4 || lo > left - 4 ? STEP_BAD : 4 + lo;
+}
+__device__ __forceinline__ uint32_t str_count(const PageDev& pg) {
+  return pg.kind == PAGE_DICT ? (pg.num_values > 0 ? (uint32_t)pg.num_values : 0u) : pg.nonnull;
+}
+
 template <uint32_t NT>
 __global__ __launch_bounds__(NT) void k_strings(const IxPage* ixs, const uint32_t* list, PageDev* pages, OpenBufs bufs,
                                                 uint32_t* strck, uint32_t* flag, const uint32_t* err,
@@ -1117,19 +1116,17 @@ __global__ __launch_bounds__(NT) void k_strings(const IxPage* ixs, const uint32_
   __shared__ uint32_t s_max;
   const uint32_t ixi = list[blockIdx.x], tid = threadIdx.x;
   if (*(const volatile uint32_t*)err != 0 || flag[ixi]) return;
-  if (seq && !seq[blockIdx.x]) return;  // (a very long page that the k_str kernels did)
+  if (seq && !seq[blockIdx.x]) return;  // (a page whose segments the k_seg kernels did)
   const uint32_t p = ixs[ixi].page;
   PageDev& pg = pages[p];
   const bool dict = pg.kind == PAGE_DICT;
-  const uint32_t n = dict ? (pg.num_values > 0 ? (uint32_t)pg.num_values : 0u) : pg.nonnull;
+  const uint32_t n = str_count(pg);
   const ChainSrc st = value_src(pg, bufs, 0);
   uint32_t* ck = strck + pg.strck_begin;
   const uint32_t iend = st.m + st.len;
   uint32_t ip = st.m, k = 0, maxlen = 0;
   if (tid == 0) s_max = 0;
-  auto step = [](uint32_t lo, uint32_t, uint32_t left, uint32_t) -> uint32_t {
-    return left < 4 || lo > left - 4 ? STEP_BAD : 4 + lo;
-  };
+  auto step = [](uint32_t lo, uint32_t, uint32_t left, uint32_t) -> uint32_t { return str_step(lo, left); };
   while (ip < iend && k < n) {
     const uint32_t S = ip & ~(CH_PIECE - 1);
     uint32_t code;
@@ -1184,180 +1181,20 @@ __global__ __launch_bounds__(NT) void k_strings(const IxPage* ixs, const uint32_
 }
 
 // ---------------------------------------------------------------------------
-// Very long string pages (above all dictionaries of high-cardinality columns,
-// tens of MiB), their segments side by side instead of one after the other:
-//   k_str_cand  where the chain from each of a segment's first SL_CAND bytes
-//               leaves the segment;
-//   k_str_link  the true chain's entry into every segment, one workgroup per
-//               page (the exits of 64 segments' first 64 bytes at a time in
-//               LDS); a page whose chain enters a segment past the candidates
-//               is left to k_strings;
-//   k_str_fill  values before every piece, within the segment;
-//   k_str_base  values before every segment;
-//   k_str_ck    the checkpoints, one thread per piece.
-// Measured on four dictionaries of 17.7 MB: 0.58 ms together; k_strings alone
-// 10.9 ms (540 segments in a row at 20 us); candidate walks of 64 lanes per 32 KiB
-// segment, a thread that links them and a second walk: 1.2 ms.
-// ---------------------------------------------------------------------------
-constexpr uint32_t SL_NT = 1024, SL_SEG = SL_NT * CH_PIECE, SL_CAND = 1024;
-__device__ __forceinline__ uint32_t str_step(uint32_t lo, uint32_t left) {
-  return left < 4 || lo > left - 4 ? STEP_BAD : 4 + lo;
-}
-__device__ __forceinline__ uint32_t str_count(const PageDev& pg) {
-  return pg.kind == PAGE_DICT ? (pg.num_values > 0 ? (uint32_t)pg.num_values : 0u) : pg.nonnull;
-}
-
-__global__ __launch_bounds__(SL_NT) void k_str_cand(const IxPage* ixs, const StrLong* sls, const uint32_t* seg_sl,
-                                                    const PageDev* pages, OpenBufs bufs, uint32_t* exits,
-                                                    const uint32_t* flag, const uint32_t* err) {
-  __shared__ ChainLds<SL_NT, 64> L;
-  const StrLong sl = sls[seg_sl[blockIdx.x]];
-  if (*(const volatile uint32_t*)err != 0 || flag[sl.ix]) return;
-  const ChainSrc st = value_src(pages[ixs[sl.ix].page], bufs, 0);
-  const uint32_t S = (blockIdx.x - sl.seg0) * SL_SEG, iend = st.m + st.len;
-  if (S >= iend) return;
-  auto step = [](uint32_t lo, uint32_t, uint32_t left, uint32_t) -> uint32_t { return str_step(lo, left); };
-  L.exits(step, st.base, st.lim, S, iend);
-  exits[(size_t)blockIdx.x * SL_CAND + threadIdx.x] = L.follow(step, threadIdx.x, S, iend);
-}
-
-__global__ __launch_bounds__(256) void k_str_link(const IxPage* ixs, const StrLong* sls, const PageDev* pages,
-                                                  OpenBufs bufs, const uint32_t* exits, uint32_t* entry, uint32_t* seq,
-                                                  const uint32_t* flag, const uint32_t* err) {
-  __shared__ uint32_t s_ex[64][64];
-  __shared__ uint32_t s_pos;
-  const StrLong sl = sls[blockIdx.x];
-  for (uint32_t j = threadIdx.x; j < sl.nseg; j += 256) entry[sl.seg0 + j] = ~0u;
-  if (threadIdx.x == 0) seq[blockIdx.x] = 0;
-  if (*(const volatile uint32_t*)err != 0 || flag[sl.ix]) return;
-  const ChainSrc st = value_src(pages[ixs[sl.ix].page], bufs, 0);
-  const uint32_t iend = st.m + st.len;
-  uint32_t pos = st.m;
-  for (uint32_t b = 0; b < sl.nseg; b += 64) {
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < 64 * 64; i += 256)
-      if (b + i / 64 < sl.nseg) s_ex[i / 64][i % 64] = exits[(size_t)(sl.seg0 + b + i / 64) * SL_CAND + i % 64];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      uint32_t q = pos;
-      while (q < iend && q / SL_SEG < b + 64) {
-        const uint32_t j = q / SL_SEG, c = q % SL_SEG;
-        if (c >= SL_CAND) { seq[blockIdx.x] = 1; q = ~0u; break; }
-        entry[sl.seg0 + j] = q;
-        const uint32_t x = c < 64 ? s_ex[j - b][c] : exits[(size_t)(sl.seg0 + j) * SL_CAND + c];
-        if (x == ~0u) { q = ~0u; break; }  // (the fill finds how many values come before)
-        q = j * SL_SEG + x;
-      }
-      s_pos = q;
-    }
-    __syncthreads();
-    pos = s_pos;
-    if (pos == ~0u) break;
-  }
-}
-
-__global__ __launch_bounds__(SL_NT) void k_str_fill(const IxPage* ixs, const StrLong* sls, const uint32_t* seg_sl,
-                                                    PageDev* pages, OpenBufs bufs, const uint32_t* entry,
-                                                    const uint32_t* seq, uint32_t* at, uint8_t* ent, uint32_t* total,
-                                                    const uint32_t* flag, const uint32_t* err) {
-  __shared__ ChainLds<SL_NT, 64> L;
-  __shared__ uint32_t s_sum[SL_NT / 64];
-  __shared__ uint32_t s_max;
-  const uint32_t sg = blockIdx.x, tid = threadIdx.x;
-  const StrLong sl = sls[seg_sl[sg]];
-  if (*(const volatile uint32_t*)err != 0 || flag[sl.ix] || seq[seg_sl[sg]]) return;
-  if (tid == 0) s_max = 0;
-  const uint32_t ip = entry[sg];
-  uint32_t tot = 0, cnt = 0, maxlen = 0, pe = CH_NONE, before = 0;
-  if (ip != ~0u) {  // (the same in every thread)
-    const ChainSrc st = value_src(pages[ixs[sl.ix].page], bufs, 0);
-    const uint32_t S = (sg - sl.seg0) * SL_SEG, iend = st.m + st.len;
-    auto step = [](uint32_t lo, uint32_t, uint32_t left, uint32_t) -> uint32_t { return str_step(lo, left); };
-    uint32_t code;
-    L.find(step, st.base, st.lim, S, ip, iend, code);
-    const uint32_t plen = L.piece_len(S, iend), y0 = tid * CH_PIECE;
-    pe = L.pent[tid];
-    for (uint32_t y = pe; y < plen;) {
-      uint32_t lo, hi;
-      L.bytes8(y0 + y, lo, hi);
-      const uint32_t a = str_step(lo, iend - S - y0 - y);
-      if (a == STEP_BAD) break;
-      maxlen = max(maxlen, lo);
-      y += a;
-      ++cnt;
-    }
-    before = wg_scan<SL_NT>(cnt, s_sum, tot);
-  }
-  at[(size_t)sg * SL_NT + tid] = before;
-  ent[(size_t)sg * SL_NT + tid] = cnt ? (uint8_t)pe : CH_NONE;
-  if (tid == 0) total[sg] = tot;
-  // a dictionary's longest entry (at least: bytes after the last one may
-  // make it larger, which costs the dictionary its slots at most)
-  __syncthreads();
-  if (maxlen) atomicMax(&s_max, maxlen);
-  __syncthreads();
-  PageDev& pg = pages[ixs[sl.ix].page];
-  if (tid == 0 && pg.kind == PAGE_DICT) atomicMax(&pg.dict_maxlen, s_max);
-}
-
-// total[] becomes the values before every segment (one wave per page).
-__global__ __launch_bounds__(64) void k_str_base(const IxPage* ixs, const StrLong* sls, const PageDev* pages,
-                                                 uint32_t* total, const uint32_t* seq, uint32_t* flag,
-                                                 const uint32_t* err) {
-  const StrLong sl = sls[blockIdx.x];
-  if (*(const volatile uint32_t*)err != 0 || flag[sl.ix] || seq[blockIdx.x]) return;
-  uint32_t k = 0;
-  for (uint32_t b = 0; b < sl.nseg; b += 64) {
-    const uint32_t j = b + threadIdx.x;
-    const uint32_t v = j < sl.nseg ? total[sl.seg0 + j] : 0u;
-    const uint32_t incl = wave_incl_scan_u32(v);
-    if (j < sl.nseg) total[sl.seg0 + j] = k + incl - v;
-    k += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-  }
-  if (threadIdx.x == 0 && k < str_count(pages[ixs[sl.ix].page])) flag[sl.ix] = 1;
-}
-
-__global__ __launch_bounds__(256) void k_str_ck(const IxPage* ixs, const StrLong* sls, const uint32_t* seg_sl,
-                                                const PageDev* pages, OpenBufs bufs, const uint32_t* base,
-                                                const uint32_t* at, const uint8_t* ent, const uint32_t* seq,
-                                                uint32_t* strck, const uint32_t* flag, const uint32_t* err) {
-  const uint32_t sg = blockIdx.x / (SL_NT / 256), pc = blockIdx.x % (SL_NT / 256) * 256 + threadIdx.x;
-  const StrLong sl = sls[seg_sl[sg]];
-  if (*(const volatile uint32_t*)err != 0 || flag[sl.ix] || seq[seg_sl[sg]]) return;
-  uint32_t y = ent[(size_t)sg * SL_NT + pc];
-  if (y == CH_NONE) return;
-  const PageDev& pg = pages[ixs[sl.ix].page];
-  const ChainSrc st = value_src(pg, bufs, 0);
-  const uint32_t n = str_count(pg), iend = st.m + st.len;
-  uint32_t k = base[sg] + at[(size_t)sg * SL_NT + pc];
-  uint32_t q = (sg - sl.seg0) * SL_SEG + pc * CH_PIECE + y;
-  const uint32_t qe = min(q - y + CH_PIECE, iend);
-  // the piece's value at a checkpoint, if it has one (eight values at most)
-  if (k % STR_CK != 0 && k % STR_CK + 8 < STR_CK) return;
-  for (; q < qe && k < n; ++k) {
-    if (k % STR_CK == 0) {
-      strck[pg.strck_begin + k / STR_CK] = q - st.m;
-      return;
-    }
-    const uint32_t a = str_step(ld_u32(st.base, q), iend - q);
-    if (a == STEP_BAD) return;
-    q += a;
-  }
-}
-
-// ---------------------------------------------------------------------------
 // k_di: the runs of a page's dictionary indices, one workgroup per page: the
 // values before every piece.  Measured on the 4M-row wide table (pages of up to
-// 1 MiB, 32 segments in a row): 0.65 ms; up to 1,024 candidate walks per segment, a
+// 1 MiB, 32 segments in a row): 0.66 ms; up to 1,024 candidate walks per segment, a
 // link and one wave per segment: 1.4 ms.
 // ---------------------------------------------------------------------------
 template <uint32_t NT>
 __global__ __launch_bounds__(NT) void k_di(const IxPage* ixs, const uint32_t* list, const PageDev* pages, OpenBufs bufs,
-                                           uint32_t* at, uint8_t* ent, uint32_t* flag, const uint32_t* err) {
+                                           uint32_t* at, uint8_t* ent, uint32_t* flag, const uint32_t* err,
+                                           const uint32_t* seq) {
   __shared__ ChainLds<NT, 64> L;
   __shared__ uint64_t s_sum[NT / 64];
   const uint32_t ixi = list[blockIdx.x], tid = threadIdx.x;
   if (*(const volatile uint32_t*)err != 0 || flag[ixi]) return;
+  if (seq && !seq[blockIdx.x]) return;
   const IxPage ix = ixs[ixi];
   const PageDev& pg = pages[ix.page];
   const uint64_t n = pg.nonnull;
@@ -1412,53 +1249,62 @@ __global__ __launch_bounds__(NT) void k_di(const IxPage* ixs, const uint32_t* li
 // last holds only the miniblocks its values use, whose end follows from its
 // header.
 // ---------------------------------------------------------------------------
-template <uint32_t NT>
-__global__ __launch_bounds__(NT) void k_dl(const IxPage* ixs, const uint32_t* list, PageDev* pages,
-                                           const ChunkDev* chunks, OpenBufs bufs, uint32_t* blkpos, uint32_t* flag,
-                                           const uint32_t* err) {
-  __shared__ ChainLds<NT, 64> L;
-  __shared__ uint32_t s_sum[NT / 64];
-  const uint32_t ixi = list[blockIdx.x], tid = threadIdx.x;
-  if (*(const volatile uint32_t*)err != 0 || flag[ixi]) return;
-  const IxPage ix = ixs[ixi];
-  PageDev& pg = pages[ix.page];
-  const uint64_t total = pg.nonnull;
-  const uint32_t B = pg.enc_w, M = pg.enc_m, per = B / M;
-  if (total <= 1) return;
-  const uint32_t nblocks = (uint32_t)((total - 1 + B - 1) / B);
-  const uint32_t maxw = chunks[pg.chunk].type == T_INT64 ? 64 : 32;
-  const ChainSrc st = value_src(pg, bufs, pg.blocks_at);
-  const uint32_t iend = st.m + st.len;
-  uint32_t ip = st.m, k = 0;
-  bool bad = false;
-  // bytes of a block's minimum delta (0: malformed), and of a block whose
-  // first `used` miniblocks are stored (STEP_BAD: malformed)
-  auto uleb_len = [&](uint32_t lo, uint32_t hi, uint32_t left, uint32_t y) -> uint32_t {
+template <class L>
+struct DlBlocks {
+  const L* lds;
+  uint32_t M, per, maxw;
+  // bytes of the block at segment byte y whose first `used` miniblocks are
+  // stored (STEP_BAD: malformed)
+  __device__ __forceinline__ uint32_t len(uint32_t lo, uint32_t hi, uint32_t left, uint32_t y, uint32_t used) const {
     const uint32_t c0 = ~lo & 0x80808080u, c1 = ~hi & 0x80808080u;
-    uint32_t hl;
+    uint32_t hl;  // bytes of the minimum delta
     if (c0) hl = ((uint32_t)__builtin_ctz(c0) >> 3) + 1;
     else if (c1) hl = ((uint32_t)__builtin_ctz(c1) >> 3) + 5;
-    else {
-      const uint32_t b8 = L.byte(y + 8), b9 = L.byte(y + 9);
-      if (!(b8 & 0x80)) hl = 9;
-      else if (b9 <= 1) hl = 10;
-      else return 0;
-    }
-    return hl > left ? 0 : hl;
-  };
-  auto block_len = [&](uint32_t lo, uint32_t hi, uint32_t left, uint32_t y, uint32_t used) -> uint32_t {
-    const uint32_t hl = uleb_len(lo, hi, left, y);
-    if (hl == 0 || M > left - hl) return STEP_BAD;
+    else if (!(lds->byte(y + 8) & 0x80)) hl = 9;
+    else if (lds->byte(y + 9) <= 1) hl = 10;
+    else return STEP_BAD;
+    if (hl > left || M > left - hl) return STEP_BAD;
     uint32_t body = 0;
     bool wide = false;
     for (uint32_t m = 0; m < used; ++m) {
-      const uint32_t w = L.byte(y + hl + m);
+      const uint32_t w = lds->byte(y + hl + m);
       wide |= w > maxw;
       body += per / 8 * w;
     }
     return wide || body > left - hl - M ? STEP_BAD : hl + M + body;
-  };
-  auto step = [&](uint32_t lo, uint32_t hi, uint32_t left, uint32_t y) -> uint32_t { return block_len(lo, hi, left, y, M); };
+  }
+  __device__ __forceinline__ uint32_t operator()(uint32_t lo, uint32_t hi, uint32_t left, uint32_t y) const {
+    return len(lo, hi, left, y, M);
+  }
+};
+__device__ __forceinline__ uint32_t dl_nblocks(const PageDev& pg) {
+  return pg.nonnull > 1 ? (uint32_t)(((uint64_t)pg.nonnull - 1 + pg.enc_w - 1) / pg.enc_w) : 0u;
+}
+// miniblocks of block b that hold values
+__device__ __forceinline__ uint32_t dl_used(const PageDev& pg, uint32_t b) {
+  const uint64_t left = (uint64_t)pg.nonnull - 1 - (uint64_t)b * pg.enc_w;
+  const uint32_t per = pg.enc_w / pg.enc_m;
+  return (uint32_t)((min(left, (uint64_t)pg.enc_w) + per - 1) / per);
+}
+
+template <uint32_t NT>
+__global__ __launch_bounds__(NT) void k_dl(const IxPage* ixs, const uint32_t* list, PageDev* pages,
+                                           const ChunkDev* chunks, OpenBufs bufs, uint32_t* blkpos, uint32_t* flag,
+                                           const uint32_t* err, const uint32_t* seq) {
+  __shared__ ChainLds<NT, 64> L;
+  __shared__ uint32_t s_sum[NT / 64];
+  const uint32_t ixi = list[blockIdx.x], tid = threadIdx.x;
+  if (*(const volatile uint32_t*)err != 0 || flag[ixi]) return;
+  if (seq && !seq[blockIdx.x]) return;
+  const IxPage ix = ixs[ixi];
+  PageDev& pg = pages[ix.page];
+  const uint32_t nblocks = dl_nblocks(pg);
+  if (nblocks == 0) return;
+  const DlBlocks<ChainLds<NT, 64>> step{&L, pg.enc_m, pg.enc_w / pg.enc_m, chunks[pg.chunk].type == T_INT64 ? 64u : 32u};
+  const ChainSrc st = value_src(pg, bufs, pg.blocks_at);
+  const uint32_t iend = st.m + st.len;
+  uint32_t ip = st.m, k = 0;
+  bool bad = false;
   while (ip < iend && k < nblocks) {
     const uint32_t S = ip & ~(CH_PIECE - 1);
     uint32_t code;
@@ -1479,10 +1325,9 @@ __global__ __launch_bounds__(NT) void k_dl(const IxPage* ixs, const uint32_t* li
       const uint32_t y = y0 + (uint32_t)__builtin_ctz(m), q = S + y - st.m;
       blkpos[ix.v0 + b] = pg.blocks_at + q;
       if (b + 1 == nblocks) {
-        const uint64_t left = total - 1 - (uint64_t)b * B;  // (at most B)
         uint32_t lo, hi;
         L.bytes8(y, lo, hi);
-        const uint32_t a = block_len(lo, hi, iend - S - y, y, ((uint32_t)left + per - 1) / per);
+        const uint32_t a = step.len(lo, hi, iend - S - y, y, dl_used(pg, b));
         if (a == STEP_BAD) bad = true;
         else pg.chars_at = pg.blocks_at + q + a;
       }
@@ -1496,6 +1341,260 @@ __global__ __launch_bounds__(NT) void k_dl(const IxPage* ixs, const uint32_t* li
 }
 
 // ---------------------------------------------------------------------------
+// The segments of long value streams side by side, where a pass has too few
+// pages to fill the chip with one workgroup each (above all the dictionaries
+// of high-cardinality string columns, tens of MiB); F: SEG_STR, SEG_DI, SEG_DL.
+//   k_seg_cand  where the chain from each of a segment's first 1,024 or 2,048 bytes
+//               leaves the segment;
+//   k_seg_link  the true chain's entry into every segment, one workgroup per
+//               page (the exits of 64 segments' first 64 bytes at a time in
+//               LDS); a page whose chain enters a segment past the candidates
+//               is left to the one-workgroup kernel;
+//   k_seg_fill  values (blocks) before every piece, within the segment;
+//   k_seg_base  values (blocks) before every segment;
+//   k_str_ck, k_dl_ck  string checkpoints and block positions, one thread per
+//               piece.
+// A segment's exits are found twice, so with a page for every CU the
+// one-workgroup kernels are faster; the choice is made on the host.
+// Measured on the 4M-row wide table in 1M-row row groups: four string dictionaries of
+// 17.7 MB 0.58 ms (k_strings 10.9 ms, 540 segments in a row at 20 us; candidate walks
+// of 64 lanes per segment, a thread that links them and a second walk 1.2 ms),
+// the index streams of nine columns 0.38 ms (k_di 0.66 ms), one DELTA column 0.12 ms
+// (k_dl 0.53 ms).
+// ---------------------------------------------------------------------------
+using SegLds = ChainLds<1024, 64>;
+constexpr uint32_t SEG_NT = 1024, SEG_BYTES = SEG_NT * CH_PIECE;
+// Candidates per segment (their exits SEG_CAND apart): 63 groups of 32-bit
+// indices, the longest run of the usual writers, take 2,017 bytes.
+constexpr uint32_t SEG_CAND = 2048;
+template <int F>
+constexpr uint32_t seg_cands() { return F == SEG_DI ? SEG_CAND : SEG_NT; }
+static_assert(SEG_CAND <= SegLds::REG, "candidates: within the first region");
+
+template <int F>
+__device__ __forceinline__ ChainSrc seg_src(const PageDev& pg, const OpenBufs& bufs) {
+  return value_src(pg, bufs, F == SEG_STR ? 0u : F == SEG_DI ? 1u : pg.blocks_at);
+}
+template <int F>
+struct SegStep {
+  DlBlocks<SegLds> dl;
+  uint32_t w;
+  __device__ __forceinline__ SegStep(const SegLds* L, const PageDev& pg, const ChunkDev* chunks) {
+    w = pg.enc_w;
+    if (F == SEG_DL) dl = DlBlocks<SegLds>{L, pg.enc_m, pg.enc_w / pg.enc_m, chunks[pg.chunk].type == T_INT64 ? 64u : 32u};
+  }
+  __device__ __forceinline__ uint32_t operator()(uint32_t lo, uint32_t hi, uint32_t left, uint32_t y) const {
+    if constexpr (F == SEG_STR) return str_step(lo, left);
+    else if constexpr (F == SEG_DI) return hrun(lo, hi, left, w).adv;
+    else return dl(lo, hi, left, y);
+  }
+};
+// values (blocks) the page needs from the chain
+template <int F>
+__device__ __forceinline__ uint32_t seg_need(const PageDev& pg) {
+  return F == SEG_STR ? str_count(pg) : F == SEG_DI ? pg.nonnull : dl_nblocks(pg);
+}
+
+template <int F>
+__global__ __launch_bounds__(SEG_NT) void k_seg_cand(const IxPage* ixs, const SegPage* sps, const uint32_t* seg_sp,
+                                                     const PageDev* pages, const ChunkDev* chunks, OpenBufs bufs,
+                                                     uint32_t* exits, const uint32_t* flag, const uint32_t* err) {
+  __shared__ SegLds L;
+  const SegPage sp = sps[seg_sp[blockIdx.x]];
+  if (*(const volatile uint32_t*)err != 0 || flag[sp.ix]) return;
+  const PageDev& pg = pages[ixs[sp.ix].page];
+  if (seg_need<F>(pg) == 0) return;
+  const ChainSrc st = seg_src<F>(pg, bufs);
+  const uint32_t S = (blockIdx.x - sp.seg0) * SEG_BYTES, iend = st.m + st.len;
+  if (S >= iend) return;
+  const SegStep<F> step(&L, pg, chunks);
+  L.exits(step, st.base, st.lim, S, iend);
+  for (uint32_t c = threadIdx.x; c < seg_cands<F>(); c += SEG_NT)
+    exits[(size_t)blockIdx.x * SEG_CAND + c] = L.follow(step, c, S, iend);
+}
+
+template <int F>
+__global__ __launch_bounds__(256) void k_seg_link(const IxPage* ixs, const SegPage* sps, const PageDev* pages,
+                                                  OpenBufs bufs, const uint32_t* exits, uint32_t* entry, uint32_t* seq,
+                                                  const uint32_t* flag, const uint32_t* err) {
+  __shared__ uint32_t s_ex[64][64];
+  __shared__ uint32_t s_pos;
+  const SegPage sp = sps[blockIdx.x];
+  for (uint32_t j = threadIdx.x; j < sp.nseg; j += 256) entry[sp.seg0 + j] = ~0u;
+  if (threadIdx.x == 0) seq[blockIdx.x] = 0;
+  if (*(const volatile uint32_t*)err != 0 || flag[sp.ix]) return;
+  const PageDev& pg = pages[ixs[sp.ix].page];
+  if (seg_need<F>(pg) == 0) return;
+  const ChainSrc st = seg_src<F>(pg, bufs);
+  const uint32_t iend = st.m + st.len;
+  uint32_t pos = st.m;
+  for (uint32_t b = 0; b < sp.nseg; b += 64) {
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < 64 * 64; i += 256)
+      if (b + i / 64 < sp.nseg) s_ex[i / 64][i % 64] = exits[(size_t)(sp.seg0 + b + i / 64) * SEG_CAND + i % 64];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t q = pos;
+      while (q < iend && q / SEG_BYTES < b + 64) {
+        const uint32_t j = q / SEG_BYTES, c = q % SEG_BYTES;
+        if (c >= seg_cands<F>()) { seq[blockIdx.x] = 1; q = ~0u; break; }
+        entry[sp.seg0 + j] = q;
+        const uint32_t x = c < 64 ? s_ex[j - b][c] : exits[(size_t)(sp.seg0 + j) * SEG_CAND + c];
+        if (x == ~0u) { q = ~0u; break; }  // (the fill finds how many values come before)
+        q = j * SEG_BYTES + x;
+      }
+      s_pos = q;
+    }
+    __syncthreads();
+    pos = s_pos;
+    if (pos == ~0u) break;
+  }
+}
+
+// at, ent: the pieces of page ix from v0 on (SEG_DI), or of segment sg from
+// sg SEG_NT on.
+template <int F>
+__global__ __launch_bounds__(SEG_NT) void k_seg_fill(const IxPage* ixs, const SegPage* sps, const uint32_t* seg_sp,
+                                                     PageDev* pages, const ChunkDev* chunks, OpenBufs bufs,
+                                                     const uint32_t* entry, const uint32_t* seq, uint32_t* at,
+                                                     uint8_t* ent, uint32_t* total, const uint32_t* flag,
+                                                     const uint32_t* err) {
+  __shared__ SegLds L;
+  __shared__ uint64_t s_sum[SEG_NT / 64];
+  __shared__ uint32_t s_max;
+  const uint32_t sg = blockIdx.x, tid = threadIdx.x;
+  const SegPage sp = sps[seg_sp[sg]];
+  if (*(const volatile uint32_t*)err != 0 || flag[sp.ix] || seq[seg_sp[sg]]) return;
+  const IxPage ix = ixs[sp.ix];
+  PageDev& pg = pages[ix.page];
+  if (F == SEG_STR && tid == 0) s_max = 0;
+  const uint32_t ip = entry[sg];
+  uint64_t tot = 0, before = 0, cnt = 0;
+  uint32_t maxlen = 0, pe = CH_NONE;
+  if (ip != ~0u) {  // (the same in every thread)
+    const ChainSrc st = seg_src<F>(pg, bufs);
+    const uint32_t S = (sg - sp.seg0) * SEG_BYTES, iend = st.m + st.len;
+    const SegStep<F> step(&L, pg, chunks);
+    uint32_t code;
+    L.find(step, st.base, st.lim, S, ip, iend, code);
+    const uint32_t plen = L.piece_len(S, iend), y0 = tid * CH_PIECE;
+    pe = L.pent[tid];
+    for (uint32_t y = pe; y < plen;) {
+      uint32_t lo, hi;
+      L.bytes8(y0 + y, lo, hi);
+      const uint32_t a = step(lo, hi, iend - S - y0 - y, y0 + y);
+      if (F == SEG_DL) ++cnt;  // (the last block need not be a full one)
+      if (a == STEP_BAD || a == STEP_ODD) break;
+      if (F == SEG_STR) {
+        maxlen = max(maxlen, lo);
+        ++cnt;
+      }
+      if (F == SEG_DI) cnt += hrun(lo, hi, iend - S - y0 - y, step.w).n;
+      y += a;
+    }
+    before = wg_scan64<SEG_NT>(cnt, s_sum, tot);
+  }
+  const size_t pc = F == SEG_DI ? (size_t)ix.v0 + (size_t)(sg - sp.seg0) * SEG_NT + tid : (size_t)sg * SEG_NT + tid;
+  if (F != SEG_DI || (sg - sp.seg0) * SEG_NT + tid < ix.nv) {
+    at[pc] = sat32(before);
+    ent[pc] = (uint8_t)pe;
+  }
+  if (tid == 0) total[sg] = sat32(tot);
+  if (F == SEG_STR && pg.kind == PAGE_DICT) {
+    // the dictionary's longest entry (at least: bytes after the last one may
+    // make it larger, which costs the dictionary its slots at most)
+    __syncthreads();
+    if (maxlen) atomicMax(&s_max, maxlen);
+    __syncthreads();
+    if (tid == 0) atomicMax(&pg.dict_maxlen, s_max);
+  }
+}
+
+// total[] becomes the values (blocks) before every segment (one wave per page).
+template <int F>
+__global__ __launch_bounds__(64) void k_seg_base(const IxPage* ixs, const SegPage* sps, const PageDev* pages,
+                                                 uint32_t* total, const uint32_t* seq, uint32_t* flag,
+                                                 const uint32_t* err) {
+  const SegPage sp = sps[blockIdx.x];
+  if (*(const volatile uint32_t*)err != 0 || flag[sp.ix] || seq[blockIdx.x]) return;
+  uint64_t k = 0;
+  for (uint32_t b = 0; b < sp.nseg; b += 64) {
+    const uint32_t j = b + threadIdx.x;
+    const uint64_t v = j < sp.nseg ? total[sp.seg0 + j] : 0u;
+    const uint64_t incl = wave_incl_scan_u64(v);
+    if (j < sp.nseg) total[sp.seg0 + j] = sat32(k + incl - v);
+    k += (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)incl, 63) |
+         ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(incl >> 32), 63) << 32);
+  }
+  if (threadIdx.x == 0 && k < seg_need<F>(pages[ixs[sp.ix].page])) flag[sp.ix] = 1;
+}
+
+__global__ __launch_bounds__(256) void k_str_ck(const IxPage* ixs, const SegPage* sps, const uint32_t* seg_sp,
+                                                const PageDev* pages, OpenBufs bufs, const uint32_t* base,
+                                                const uint32_t* at, const uint8_t* ent, const uint32_t* seq,
+                                                uint32_t* strck, const uint32_t* flag, const uint32_t* err) {
+  const uint32_t sg = blockIdx.x / (SEG_NT / 256), pc = blockIdx.x % (SEG_NT / 256) * 256 + threadIdx.x;
+  const SegPage sp = sps[seg_sp[sg]];
+  if (*(const volatile uint32_t*)err != 0 || flag[sp.ix] || seq[seg_sp[sg]]) return;
+  const uint32_t y = ent[(size_t)sg * SEG_NT + pc];
+  if (y == CH_NONE) return;
+  const PageDev& pg = pages[ixs[sp.ix].page];
+  const ChainSrc st = value_src(pg, bufs, 0);
+  const uint32_t n = str_count(pg), iend = st.m + st.len;
+  uint32_t k = base[sg] + at[(size_t)sg * SEG_NT + pc];
+  uint32_t q = (sg - sp.seg0) * SEG_BYTES + pc * CH_PIECE + y;
+  const uint32_t qe = min(q - y + CH_PIECE, iend);
+  // the piece's value at a checkpoint, if it has one (eight values at most)
+  if (k % STR_CK != 0 && k % STR_CK + 8 < STR_CK) return;
+  for (; q < qe && k < n; ++k) {
+    if (iend - q < 4) return;
+    const uint32_t a = str_step(ld_u32(st.base, q), iend - q);
+    if (a == STEP_BAD) return;
+    if (k % STR_CK == 0) {
+      strck[pg.strck_begin + k / STR_CK] = q - st.m;
+      return;
+    }
+    q += a;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_dl_ck(const IxPage* ixs, const SegPage* sps, const uint32_t* seg_sp,
+                                               PageDev* pages, const ChunkDev* chunks, OpenBufs bufs,
+                                               const uint32_t* base, const uint32_t* at, const uint8_t* ent,
+                                               const uint32_t* seq, uint32_t* blkpos, uint32_t* flag,
+                                               const uint32_t* err) {
+  const uint32_t sg = blockIdx.x / (SEG_NT / 256), pc = blockIdx.x % (SEG_NT / 256) * 256 + threadIdx.x;
+  const SegPage sp = sps[seg_sp[sg]];
+  if (*(const volatile uint32_t*)err != 0 || flag[sp.ix] || seq[seg_sp[sg]]) return;
+  uint32_t y = ent[(size_t)sg * SEG_NT + pc];
+  if (y == CH_NONE) return;
+  const IxPage ix = ixs[sp.ix];
+  PageDev& pg = pages[ix.page];
+  const ChainSrc st = seg_src<SEG_DL>(pg, bufs);
+  const uint32_t nblocks = dl_nblocks(pg), iend = st.m + st.len;
+  // the stream's bytes as the blocks' step reads them
+  struct Bytes {
+    const ChainSrc* st;
+    __device__ __forceinline__ uint32_t byte(uint32_t q) const { return q < st->m + st->len ? (uint32_t)st->base[q] : 0u; }
+  } by{&st};
+  const DlBlocks<Bytes> step{&by, pg.enc_m, pg.enc_w / pg.enc_m, chunks[pg.chunk].type == T_INT64 ? 64u : 32u};
+  uint32_t q = (sg - sp.seg0) * SEG_BYTES + pc * CH_PIECE + y;
+  const uint32_t qe = min(q - y + CH_PIECE, iend);
+  for (uint32_t b = base[sg] + at[(size_t)sg * SEG_NT + pc]; q < qe && b < nblocks; ++b) {
+    blkpos[ix.v0 + b] = pg.blocks_at + q - st.m;
+    const uint32_t lo = ld_u32(st.base, q), hi = ld_u32(st.base, (uint64_t)q + 4);
+    const bool last = b + 1 == nblocks;
+    const uint32_t a = step.len(lo, hi, iend - q, q, last ? dl_used(pg, b) : pg.enc_m);
+    if (a == STEP_BAD) {
+      flag[sp.ix] = 1;  // (the last block, or a stream that ends early)
+      return;
+    }
+    if (last) pg.chars_at = pg.blocks_at + q - st.m + a;
+    q += a;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // k_value_tiles: 16 lanes per tile: its values and its entry in the value
 // stream, with a dictionary-index checkpoint (of every 64th value) or a block
 // checkpoint per lane.
@@ -1503,7 +1602,8 @@ __global__ __launch_bounds__(NT) void k_dl(const IxPage* ixs, const uint32_t* li
 __global__ __launch_bounds__(64) void k_value_tiles(const IxPage* ixs, uint32_t nix, uint32_t tile0, uint32_t ntiles,
                                                     const PageDev* pages, const ChunkDev* chunks, OpenBufs bufs,
                                                     const uint32_t* at, const uint8_t* ent, const uint32_t* blkpos,
-                                                    const uint32_t* strck, const uint32_t* flag, TileDev* tiles, Ck* ckv,
+                                                    const uint32_t* strck, const SegPage* sps, const uint32_t* base,
+                                                    const uint32_t* seq, const uint32_t* flag, TileDev* tiles, Ck* ckv,
                                                     const uint32_t* err) {
   static_assert(NSUB == 16, "16 lanes per tile");
   __shared__ uint32_t s_row[64][ROW_DW];
@@ -1523,11 +1623,20 @@ __global__ __launch_bounds__(64) void k_value_tiles(const IxPage* ixs, uint32_t 
     if (sub * SUB_ROWS >= nn) return;
     const ChainSrc st = value_src(pg, bufs, 1);
     const uint32_t v = k0 + sub * SUB_ROWS, w = pg.enc_w;
-    const uint32_t pc = piece_of(at + ix.v0, ix.nv, v);
+    uint32_t pc, before = 0;
+    if (ix.sp != ~0u && !seq[ix.sp]) {  // counts within the segment
+      const SegPage sp = sps[ix.sp];
+      const uint32_t j = piece_of(base + sp.seg0, sp.nseg, v);
+      before = base[sp.seg0 + j];
+      pc = j * SEG_NT;
+      pc += piece_of(at + ix.v0 + pc, min(SEG_NT, ix.nv - pc), v - before);
+    } else {
+      pc = piece_of(at + ix.v0, ix.nv, v);
+    }
     uint32_t* rowp = &s_row[threadIdx.x][0];
     row_load(rowp, st, pc);
     bool found;
-    RunCur c = row_run(rowp, st, pc, ent[ix.v0 + pc], at[ix.v0 + pc], v, w, found);
+    RunCur c = row_run(rowp, st, pc, ent[ix.v0 + pc], (uint64_t)before + at[ix.v0 + pc], v, w, found);
     if (!found) return;  // (not for a chain that was followed to its last value)
     c.hp += 1; c.pay += 1; c.next += 1;  // the width byte
     const uint32_t entry = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (int)(threadIdx.x & ~15u), (int)(uint32_t)c.hp);
@@ -1574,11 +1683,25 @@ __global__ __launch_bounds__(64) void k_value_tiles(const IxPage* ixs, uint32_t 
   template __global__ void k_strings<NT>(const IxPage*, const uint32_t*, PageDev*, OpenBufs, uint32_t*, uint32_t*,    \
                                          const uint32_t*, const uint32_t*);                                           \
   template __global__ void k_di<NT>(const IxPage*, const uint32_t*, const PageDev*, OpenBufs, uint32_t*, uint8_t*,    \
-                                    uint32_t*, const uint32_t*);                                                      \
+                                    uint32_t*, const uint32_t*, const uint32_t*);                                     \
   template __global__ void k_dl<NT>(const IxPage*, const uint32_t*, PageDev*, const ChunkDev*, OpenBufs, uint32_t*,   \
-                                    uint32_t*, const uint32_t*);
+                                    uint32_t*, const uint32_t*, const uint32_t*);
 CHAIN_KERNELS(256)
 CHAIN_KERNELS(1024)
 #undef CHAIN_KERNELS
+#define SEG_KERNELS(F)                                                                                                \
+  template __global__ void k_seg_cand<F>(const IxPage*, const SegPage*, const uint32_t*, const PageDev*,              \
+                                         const ChunkDev*, OpenBufs, uint32_t*, const uint32_t*, const uint32_t*);     \
+  template __global__ void k_seg_link<F>(const IxPage*, const SegPage*, const PageDev*, OpenBufs, const uint32_t*,    \
+                                         uint32_t*, uint32_t*, const uint32_t*, const uint32_t*);                     \
+  template __global__ void k_seg_fill<F>(const IxPage*, const SegPage*, const uint32_t*, PageDev*, const ChunkDev*,   \
+                                         OpenBufs, const uint32_t*, const uint32_t*, uint32_t*, uint8_t*, uint32_t*,  \
+                                         const uint32_t*, const uint32_t*);                                           \
+  template __global__ void k_seg_base<F>(const IxPage*, const SegPage*, const PageDev*, uint32_t*, const uint32_t*,   \
+                                         uint32_t*, const uint32_t*);
+SEG_KERNELS(SEG_STR)
+SEG_KERNELS(SEG_DI)
+SEG_KERNELS(SEG_DL)
+#undef SEG_KERNELS
 
 }  // namespace pqk
