@@ -105,9 +105,8 @@ typedef struct {
   int64_t compressed_pages;
   uint64_t encoded_bytes; /* sum of compressed page payload sizes */
   uint64_t uncompressed_bytes;
-  double open_ms_device;  /* time of the open-time passes: page walk and tile
-                             index (device events), dictionaries and tile
-                             prefix (host clock) */
+  double open_ms_device;  /* time of the open-time passes: page walk, tile index,
+                             dictionaries and tile prefix (device events) */
   uint64_t device_bytes;  /* device memory the handle holds until pq_close
                              (index, checkpoints, resident dictionaries) */
 } pq_file_stats;

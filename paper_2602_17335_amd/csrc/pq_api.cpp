@@ -78,6 +78,9 @@ __global__ void k_prep(const ColScan* cols, SegTable seg);
 __global__ void k_edges(const uint8_t* ws, const ColScan* cols, SegTable seg);
 __global__ void k_dict(const PageDev* pages, const uint32_t* strck, const DictSlot* slots, const DictWork* works,
                        uint32_t nworks, uint32_t* err);
+__global__ void k_scan_sums(const uint64_t* v, uint32_t n, uint64_t* sums);
+__global__ void k_scan_prefix(uint64_t* v, uint32_t n, const uint64_t* sums);
+__global__ void k_pick(const uint64_t* v, const uint32_t* at, uint32_t n, uint64_t* out);
 __global__ void k_prepass(uint8_t* ws, const ColScan* cols, SegTable seg, int mode, uint32_t* err);
 __global__ void k_str_total(const ColScan* cols, const int32_t* which, int32_t n, uint32_t* err);
 __global__ void k_copy(uint8_t* dst, const uint8_t* src, uint64_t n);
@@ -332,10 +335,10 @@ struct pq_file_s {
   ChunkDev* d_chunks = nullptr;
   uint32_t* d_err = nullptr;
   // tile prefix: exclusive prefix sum over the file's tiles of each tile's
-  // DELTA sum or string byte count (total_tiles + 1 entries), on the device
-  // and on the host
+  // DELTA sum or string byte count (total_tiles + 1 entries), and on the host
+  // its values at the chunks' first tiles (and the total)
   uint64_t* d_tpfx = nullptr;
-  std::vector<uint64_t> tpfx;
+  std::vector<uint64_t> chunk_pfx;
   uint64_t* d_tpfx2 = nullptr;  // second tile prefix (DELTA_LENGTH_BYTE_ARRAY length streams)
   // resident dictionaries: one DictSlot per chunk (device and host), their
   // decoded arrays in one arena
@@ -460,8 +463,21 @@ static SegTable make_segs(const std::vector<Segment>& v, bool spread = false) {
   return t;
 }
 
-static pq_status build_tile_prefix(pq_file f, hipStream_t s);
 static pq_status build_dicts(pq_file f, const uint8_t* scratch, bool copy_all, hipStream_t s);
+
+// Chars bytes of column c over row groups [g0, g1).
+static int64_t chars_of(pq_file f, int c, int g0, int g1) {
+  if (f->cols[(size_t)c].type != T_BYTE_ARRAY) return 0;
+  return (int64_t)(f->chunk_pfx[(size_t)c * f->nrg + g1] - f->chunk_pfx[(size_t)c * f->nrg + g0]);
+}
+
+// v[0, n) to its exclusive prefix sum, v[n] the total (sums: a word per
+// workgroup of scan_groups(n)).
+static uint32_t scan_groups(uint64_t n) { return (uint32_t)(n / 4096 + 1); }
+static void launch_scan(uint64_t* v, uint32_t n, uint64_t* sums, hipStream_t s) {
+  hipLaunchKernelGGL(k_scan_sums, dim3(scan_groups(n)), dim3(256), 0, s, (const uint64_t*)v, n, sums);
+  hipLaunchKernelGGL(k_scan_prefix, dim3(scan_groups(n)), dim3(256), 0, s, v, n, (const uint64_t*)sums);
+}
 
 // Decompressed bytes of the data pages indexed together at open.
 constexpr uint64_t OPEN_SCRATCH_CAP = 512ull << 20;
@@ -736,15 +752,18 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   uint8_t* d_scratch = nullptr;
   ColScan* d_cs = nullptr;
   uint8_t* d_ix = nullptr;            // a pass's page list and chain tables
+  uint8_t* d_pcols = nullptr;         // the column table of its tiles' values
+  uint8_t* d_sums = nullptr;          // scratch of the prefix sums, the chunks' first tiles and prefixes
   uint8_t* d_xscratch_mem = nullptr;  // DELTA_BYTE_ARRAY pages of a pass expanded to the PLAIN layout,
   uint8_t* d_xscratch = nullptr;      // after OPEN_GUARD bytes
   ColScan* d_xcols = nullptr;     // their column tables
   uint64_t xscratch = 0;          // bytes of the file-wide expansion layout so far
   auto free_pass = [&]() {
     if (d_ix) (void)hipFree(d_ix);
+    if (d_pcols) (void)hipFree(d_pcols);
     if (d_xscratch_mem) (void)hipFree(d_xscratch_mem);
     if (d_xcols) (void)hipFree(d_xcols);
-    d_ix = nullptr;
+    d_ix = d_pcols = nullptr;
     d_xscratch_mem = d_xscratch = nullptr;
     d_xcols = nullptr;
   };
@@ -752,6 +771,8 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     free_pass();
     if (d_scratch_mem) (void)hipFree(d_scratch_mem);
     if (d_cs) (void)hipFree(d_cs);
+    if (d_sums) (void)hipFree(d_sums);
+    d_sums = nullptr;
     d_scratch_mem = d_scratch = nullptr;
     d_cs = nullptr;
   };
@@ -788,6 +809,41 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     OPEN_HIP(hipMemsetAsync(f->d_dbau, 0xff, sizeof(DbaUnit) * dba_units, s));
     f->device_bytes += sizeof(DbaUnit) * dba_units;
   }
+  // the tile prefixes: each pass stores its tiles' values, then their sums
+  std::vector<bool> need((size_t)f->ncols, false), need_dlba((size_t)f->ncols, false);
+  bool any_dlba = false;
+  for (int c = 0; c < f->ncols; ++c) {
+    const bool str = f->cols[(size_t)c].type == T_BYTE_ARRAY;
+    need[(size_t)c] = str;
+    for (uint32_t p = f->chunk_page0[(size_t)c * f->nrg]; p < f->chunk_page0[(size_t)(c + 1) * f->nrg]; ++p) {
+      if (f->pages[p].kind == PAGE_DICT) continue;
+      if (f->pages[p].encoding == E_DELTA) need[(size_t)c] = true;
+      if (f->pages[p].encoding == E_DLBA && str) need_dlba[(size_t)c] = any_dlba = true;
+    }
+  }
+  const size_t npick = (size_t)nchunks + 1;
+  const size_t o_pick = 8ull * scan_groups(tiles), o_pat = o_pick + 8 * npick;
+  if (hipMalloc(&f->d_tpfx, 8ull * (tiles + 1)) != hipSuccess || hipMalloc(&d_sums, o_pat + 4 * npick) != hipSuccess ||
+      (any_dlba && hipMalloc(&f->d_tpfx2, 8ull * (tiles + 1)) != hipSuccess)) {
+    cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: tile prefix allocation");
+  }
+  OPEN_HIP(hipMemsetAsync(f->d_tpfx, 0, 8ull * (tiles + 1), s));
+  if (any_dlba) {
+    OPEN_HIP(hipMemsetAsync(f->d_tpfx2, 0, 8ull * (tiles + 1), s));
+    f->device_bytes += 8ull * (tiles + 1);
+  }
+  f->fd.file = file;
+  f->fd.pages = f->d_pages;
+  f->fd.tiles = f->d_tiles;
+  f->fd.ckl = f->d_ckl;
+  f->fd.ckv = f->d_ckv;
+  f->fd.strck = f->d_strck;
+  f->fd.sblk = f->d_sblk;
+  f->fd.sblk_page = f->d_sblk_page;
+  f->fd.sbits = f->d_sbits;
+  f->fd.dbau = f->d_dbau;
+  f->fd.tpfx = f->d_tpfx;
+  f->fd.tpfx2 = f->d_tpfx2;
   const uint64_t flim = (len + 15) & ~15ull;  // the file is readable up to len rounded up to 16
   if (sblk) {
     // the Snappy block index of every compressed page, from a walk over the
@@ -1128,6 +1184,67 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
 #undef CHAINS
 #undef SEG_RUN
 #undef SEG_REST
+    // the values the tile prefix sums (DELTA sums, string bytes), while the
+    // window holds the pass's decompressed pages; those of DELTA_LENGTH tiles
+    // need the prefix of their lengths' DELTA sums first
+    std::vector<ColScan> pcols;
+    if (!P.dict && ntl) {
+      uint8_t* const wbase = reinterpret_cast<uint8_t*>(f->d_tpfx);  // "workspace": every region by its distance
+      auto dist = [&](const void* p) { return (uint64_t)((uintptr_t)p - (uintptr_t)wbase); };
+      std::vector<Segment> vs, vs2;
+      uint32_t vu = 0, vu2 = 0;
+      for (int c = 0; c < f->ncols; ++c) {
+        if (!need[(size_t)c]) continue;
+        const uint32_t p0 = std::max(P.p0, f->chunk_page0[(size_t)c * f->nrg]),
+                       p1 = std::min(P.p1, f->chunk_page0[(size_t)(c + 1) * f->nrg]);
+        uint32_t tb = ~0u, te = 0;
+        for (uint32_t p = p0; p < p1; ++p) {
+          const PageDev& pg = f->pages[p];
+          if (pg.kind == PAGE_DICT) continue;
+          tb = std::min(tb, pg.tile_begin);
+          te = std::max(te, pg.tile_begin + (uint32_t)(((uint64_t)pg.num_values + TILE_ROWS - 1) / TILE_ROWS));
+        }
+        if (tb >= te) continue;
+        ColScan cs;
+        memset(&cs, 0, sizeof(cs));
+        cs.fd = f->fd;
+        cs.fd.dicts = f->d_dicts;
+        cs.type = f->cols[(size_t)c].type;
+        cs.optional = f->cols[(size_t)c].optional;
+        cs.width = cs.type == T_INT32 ? 4 : (cs.type == T_BYTE_ARRAY ? 0 : 8);
+        cs.col = c;
+        cs.tile_begin = tb;
+        cs.tile_end = te;
+        cs.page_begin = p0;
+        cs.page_end = p1;
+        cs.scratch_base = P.s0;
+        cs.ws_scratch = dist(d_scratch);
+        cs.xscratch_base = 0;
+        cs.ws_xscratch = dist(xscr);
+        cs.ws_tile_aux = dist(f->d_tpfx + tb);
+        vs.push_back(Segment{(uint32_t)pcols.size(), tb, te, vu});
+        vu += te - tb;
+        pcols.push_back(cs);
+        if (!need_dlba[(size_t)c]) continue;
+        cs.ws_tile_aux = dist(f->d_tpfx2 + tb);
+        vs2.push_back(Segment{(uint32_t)pcols.size(), tb, te, vu2});
+        vu2 += te - tb;
+        pcols.push_back(cs);
+      }
+      if (vs.size() > MAX_SEGS) { cleanup_open(); free_handle(f); return fail(PQ_EUNSUPPORTED, "too many columns"); }
+      if (!pcols.empty()) {
+        if (hipMalloc(&d_pcols, sizeof(ColScan) * pcols.size()) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: allocation failed"); }
+        OPEN_HIP(hipMemcpyAsync(d_pcols, pcols.data(), sizeof(ColScan) * pcols.size(), hipMemcpyHostToDevice, s));
+        const ColScan* d_pc = reinterpret_cast<const ColScan*>(d_pcols);
+        if (!vs2.empty()) {
+          hipLaunchKernelGGL(k_prepass, dim3((vu2 + 3) / 4), dim3(256), 0, s, wbase, d_pc, make_segs(vs2), 1, f->d_err);
+          // (only differences within a page are taken from it)
+          launch_scan(f->d_tpfx2 + tile0, (uint32_t)ntl, reinterpret_cast<uint64_t*>(d_sums), s);
+        }
+        hipLaunchKernelGGL(k_prepass, dim3((vu + 3) / 4), dim3(256), 0, s, wbase, d_pc, make_segs(vs), 0, f->d_err);
+        if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_prepass launch failed"); }
+      }
+    }
     if (P.dict) {
       // resident dictionaries, while the window holds the decompressed pages
       {
@@ -1145,6 +1262,18 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     free_pass();
   }
   f->xscratch_prefix[npages] = xscratch;
+  // the tile prefix, and its values at the chunks' first tiles
+  {
+    uint32_t* d_pat = reinterpret_cast<uint32_t*>(d_sums + o_pat);
+    uint64_t* d_pick = reinterpret_cast<uint64_t*>(d_sums + o_pick);
+    launch_scan(f->d_tpfx, (uint32_t)tiles, reinterpret_cast<uint64_t*>(d_sums), s);
+    OPEN_HIP(hipMemcpyAsync(d_pat, f->chunk_tile0.data(), 4 * npick, hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_pick, dim3((uint32_t)((npick + 255) / 256)), dim3(256), 0, s, (const uint64_t*)f->d_tpfx,
+                       (const uint32_t*)d_pat, (uint32_t)npick, d_pick);
+    if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_pick launch failed"); }
+    f->chunk_pfx.resize(npick);
+    OPEN_HIP(hipMemcpyAsync(f->chunk_pfx.data(), d_pick, 8 * npick, hipMemcpyDeviceToHost, s));
+  }
   HIP_OR(hipEventRecord(e1, s));
   {
     pq_status st3 = read_err(f, s);
@@ -1155,29 +1284,12 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (npages) OPEN_HIP(hipMemcpy(f->pages.data(), f->d_pages, sizeof(PageDev) * npages, hipMemcpyDeviceToHost));
-  f->fd.file = file;
-  f->fd.pages = f->d_pages;
-  f->fd.tiles = f->d_tiles;
-  f->fd.ckl = f->d_ckl;
-  f->fd.ckv = f->d_ckv;
-  f->fd.strck = f->d_strck;
-  f->fd.sblk = f->d_sblk;
-  f->fd.sblk_page = f->d_sblk_page;
-  f->fd.sbits = f->d_sbits;
-  f->fd.dicts = f->d_dicts;
-  f->fd.dbau = f->d_dbau;
   cleanup_open();
 
 #undef OPEN_HIP
 #undef OPEN_ERR
 
-  // ---- tile prefix (per-tile DELTA sums and string byte counts) ----
-  const auto tp0 = std::chrono::steady_clock::now();
-  {
-    pq_status st4 = build_tile_prefix(f, s);
-    if (st4 != PQ_OK) { free_handle(f); return st4; }
-  }
-  const double prefix_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - tp0).count();
+  f->fd.dicts = f->d_dicts;
 
   // ---- statistics ----
   pq_file_stats& S = f->stats;
@@ -1189,7 +1301,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     S.uncompressed_bytes += pg.uncomp_size;
   }
   S.tiles = (int64_t)tiles;
-  S.open_ms_device = ms + prefix_ms;
+  S.open_ms_device = ms;
   f->device_bytes += 4 + sizeof(ChunkDev) * (uint64_t)nchunks + sizeof(PageDev) * (uint64_t)npages +
                      (sizeof(TileDev) + 4ull * NLCK + sizeof(Ck) * NSUB) * tiles + 4ull * strck +
                      8ull * sblk + 2ull * sbits +  // Snappy block index: offset, page; element start bits
@@ -1394,7 +1506,7 @@ struct Plan {
   int64_t rows = 0;
   uint64_t ws_cols = 0, ws_which = 0, ws_total = 0;
   // launch lists
-  std::vector<Segment> snappy_segs, prep_segs, pre_segs, fixed_segs[8], delta_segs, str_segs[2], edge_segs;
+  std::vector<Segment> snappy_segs, prep_segs, fixed_segs[8], delta_segs, str_segs[2], edge_segs;
   std::vector<int32_t> str_cols;    // string ColScan indices (k_str_total)
   // units: pages (k_snappy), tiles (k_prep threads; one wave per tile elsewhere)
   std::vector<Segment> sblk_segs;  // k_snappy_blk: blocks of the compressed pages, one workgroup each
@@ -1403,7 +1515,7 @@ struct Plan {
   bool dba_small = false, dba_big = false;
   uint32_t sblk_wgs = 0;
   bool str_spread[2] = {false, false}, fixed_spread[8] = {};  // columns interleaved wave by wave
-  uint32_t snappy_waves = 0, prep_threads = 0, pre_units = 0, fixed_units[8] = {}, delta_units = 0, str_units[2] = {0, 0},
+  uint32_t snappy_waves = 0, prep_threads = 0, fixed_units[8] = {}, delta_units = 0, str_units[2] = {0, 0},
            edge_threads = 0;
   // a host-resident file: two staging slots for row groups in flight and
   // one column table per row group (its file base in its slot)
@@ -1412,9 +1524,7 @@ struct Plan {
 };
 
 // Work lists and workspace layout of a scan of `mask` over row groups
-// [rg_b, rg_e).  With `index`, the plan of the open-time prefix pass instead:
-// decompression and k_prepass of the columns that need a tile prefix, with a
-// per-tile array in the workspace.
+// [rg_b, rg_e).
 // One selected column of a scan: its table entry (workspace offsets from
 // `off` on) and which decoders its pages need.
 struct ColSetup {
@@ -1427,10 +1537,7 @@ struct ColSetup {
   uint32_t b0 = 0, b1 = 0;  // its Snappy blocks
 };
 
-// pr0/pr1 (index plans only): the pages [pr0, pr1) of the chunks instead of
-// all of them.
-void col_setup(pq_file f, int c, int32_t rg_b, int32_t rg_e, int64_t rows, uint64_t& off, bool index, ColSetup& k,
-               uint32_t pr0 = ~0u, uint32_t pr1 = ~0u) {
+void col_setup(pq_file f, int c, int32_t rg_b, int32_t rg_e, int64_t rows, uint64_t& off, ColSetup& k) {
   ColScan& cs = k.cs;
   memset(&cs, 0, sizeof(cs));
   cs.fd = f->fd;
@@ -1445,19 +1552,6 @@ void col_setup(pq_file f, int c, int32_t rg_b, int32_t rg_e, int64_t rows, uint6
   cs.page_end = f->chunk_page0[q1];
   cs.row_base = f->rg_row0[rg_b];
   cs.rows = rows;
-  if (pr0 != ~0u) {
-    cs.page_begin = pr0;
-    cs.page_end = pr1;
-    uint32_t tb = ~0u, te = 0;
-    for (uint32_t p = pr0; p < pr1; ++p) {
-      const PageDev& pg = f->pages[p];
-      if (pg.kind == PAGE_DICT) continue;
-      tb = std::min(tb, pg.tile_begin);
-      te = std::max(te, pg.tile_begin + (uint32_t)(((uint64_t)pg.num_values + TILE_ROWS - 1) / TILE_ROWS));
-    }
-    cs.tile_begin = tb == ~0u ? te : tb;
-    cs.tile_end = te;
-  }
   cs.scratch_base = f->scratch_prefix[cs.page_begin];
   k.sbytes = f->scratch_prefix[cs.page_end] - cs.scratch_base;
   cs.ws_scratch = off;
@@ -1488,18 +1582,13 @@ void col_setup(pq_file f, int c, int32_t rg_b, int32_t rg_e, int64_t rows, uint6
     cs.ws_edge = off;
     off = align_up(off + 8ull * k.nt, 256);
   }
-  if (index && (cs.type == T_BYTE_ARRAY || k.has_delta)) {
-    cs.ws_tile_aux = off;
-    off = align_up(off + 8ull * (k.nt + 1), 256);
-  }
   if (k.sbytes) {
     k.b0 = f->pages[cs.page_begin].sblk_begin;
     k.b1 = cs.page_end < (uint32_t)f->pages.size() ? f->pages[cs.page_end].sblk_begin : (uint32_t)f->total_sblk;
   }
 }
 
-pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& P, bool index = false,
-                    uint32_t pr0 = ~0u, uint32_t pr1 = ~0u) {
+pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& P) {
   if (rg_b < 0 || rg_e > f->nrg || rg_b > rg_e) return fail(PQ_EINVAL, "bad row-group range [%d, %d)", rg_b, rg_e);
   if (f->ncols < 64 && (mask >> f->ncols)) return fail(PQ_EINVAL, "column mask selects missing columns");
   P.rows = f->rg_row0[rg_e] - f->rg_row0[rg_b];
@@ -1511,14 +1600,10 @@ pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& 
   for (int c = 0; c < f->ncols; ++c) {
     if (!((mask >> c) & 1)) continue;
     ColSetup k;
-    col_setup(f, c, rg_b, rg_e, P.rows, off, index, k, pr0, pr1);
+    col_setup(f, c, rg_b, rg_e, P.rows, off, k);
     const ColScan& cs = k.cs;
     const uint32_t nt = k.nt;
     const uint32_t idx = (uint32_t)P.cols.size();
-    if (index && cs.ws_tile_aux && nt) {
-      P.pre_segs.push_back(Segment{idx, cs.tile_begin, cs.tile_end, P.pre_units});
-      P.pre_units += nt;
-    }
     if (nt) {
       if (cs.type == T_BYTE_ARRAY) {
         for (int kk = 0; kk < 2; ++kk) {  // k_decode_str<kk>: tiles of slot dictionaries (1) or the others (0)
@@ -1584,7 +1669,7 @@ pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& 
     P.str_spread[k] = true;
     P.str_units[k] = (uint32_t)P.str_segs[k].size() * most;
   }
-  if (f->host && !index && !P.cols.empty()) {
+  if (f->host && !P.cols.empty()) {
     uint64_t most = 0;
     for (int g = rg_b; g < rg_e; ++g) {
       uint64_t lo = ~0ull, hi = 0;
@@ -1648,7 +1733,7 @@ static void launch_dba(uint32_t units, const SegTable& segs, bool small, bool bi
 // d_cols).
 static pq_status enqueue_decompress(pq_file f, const Plan& P, const ColScan* d_cols, uint8_t* ws, uint32_t* err,
                                     hipStream_t s) {
-  for (const auto* v : {&P.snappy_segs, &P.sblk_segs, &P.dba_segs, &P.prep_segs, &P.pre_segs, &P.fixed_segs[0], &P.fixed_segs[1], &P.fixed_segs[2],
+  for (const auto* v : {&P.snappy_segs, &P.sblk_segs, &P.dba_segs, &P.prep_segs, &P.fixed_segs[0], &P.fixed_segs[1], &P.fixed_segs[2],
                         &P.fixed_segs[3], &P.fixed_segs[4], &P.fixed_segs[6], &P.delta_segs, &P.str_segs[0], &P.str_segs[1],
                         &P.edge_segs})
     if (v->size() > MAX_SEGS) return fail(PQ_EUNSUPPORTED, "too many segments");
@@ -1669,25 +1754,20 @@ static pq_status enqueue_decompress(pq_file f, const Plan& P, const ColScan* d_c
   return PQ_OK;
 }
 
-// Decompression and the upload: the steps the open-time prefix pass and a
-// scan share.
+// Decompression and the upload.
 static pq_status enqueue_front(pq_file f, Plan& P, uint8_t* ws, uint32_t* err, hipStream_t s) {
   pq_status st = upload_header(P, ws, s);
   if (st != PQ_OK) return st;
   return enqueue_decompress(f, P, reinterpret_cast<ColScan*>(ws + P.ws_cols), ws, err, s);
 }
 
-// The open-time prefix pass of a plan made with index = true: per-tile DELTA
-// sums and string byte counts into the workspace's tile arrays (mode 1: the
-// DELTA sums of DELTA_LENGTH_BYTE_ARRAY length streams only).
-static pq_status enqueue_index(pq_file f, Plan& P, uint8_t* ws, int mode, hipStream_t s) {
-  pq_status st = enqueue_front(f, P, ws, f->d_err, s);
-  if (st != PQ_OK) return st;
-  if (P.pre_units) {
-    hipLaunchKernelGGL(k_prepass, dim3((P.pre_units + 3) / 4), dim3(256), 0, s, ws,
-                       reinterpret_cast<ColScan*>(ws + P.ws_cols), make_segs(P.pre_segs), mode, f->d_err);
-    HIP_OR(hipGetLastError());
-  }
+static pq_status enqueue_str_total(pq_file f, const Plan& P, const ColScan* d_cols, uint8_t* ws, uint32_t* err,
+                                   hipStream_t s) {
+  if (P.str_cols.empty()) return PQ_OK;
+  ProfScope ps_(f, KP_STR_TOTAL, s);
+  hipLaunchKernelGGL(k_str_total, dim3(((uint32_t)P.str_cols.size() + 63) / 64), dim3(64), 0, s, d_cols,
+                     reinterpret_cast<const int32_t*>(ws + P.ws_which), (int32_t)P.str_cols.size(), err);
+  HIP_OR(hipGetLastError());
   return PQ_OK;
 }
 
@@ -1725,16 +1805,6 @@ static bool all_segments(const Plan& P, std::vector<Segment>& segs, uint32_t& un
   add(P.fixed_segs[0], TK_FIXED0);
   units = (uint32_t)n;
   return n > 0 && segs.size() <= (size_t)MAX_SEGS && n <= (uint64_t)ALL_UNITS * kinds * (kinds + 1) && P.str_cols.size() <= 64;
-}
-
-static pq_status enqueue_str_total(pq_file f, const Plan& P, const ColScan* d_cols, uint8_t* ws, uint32_t* err,
-                                   hipStream_t s) {
-  if (P.str_cols.empty()) return PQ_OK;
-  ProfScope ps_(f, KP_STR_TOTAL, s);
-  hipLaunchKernelGGL(k_str_total, dim3(((uint32_t)P.str_cols.size() + 63) / 64), dim3(64), 0, s, d_cols,
-                     reinterpret_cast<const int32_t*>(ws + P.ws_which), (int32_t)P.str_cols.size(), err);
-  HIP_OR(hipGetLastError());
-  return PQ_OK;
 }
 
 // REQUIRED validity and the decode kernels of a plan's tiles (column table
@@ -1809,123 +1879,6 @@ static pq_status enqueue(pq_file f, Plan& P, uint8_t* ws, hipStream_t s) {
   return st == PQ_OK ? enqueue_edges(f, P, d_cols, ws, s) : st;
 }
 
-// Builds the tile prefix at open: for every column with string or DELTA
-// pages, the prefix pass over its row groups (in batches whose workspace
-// stays below INDEX_WS_CAP), then the prefix sum on the host.
-constexpr uint64_t INDEX_WS_CAP = 512ull << 20;
-
-// One prefix pass (k_prepass in `mode`) over the tiles of every column that
-// `need` selects, in row-group batches; fills val[t] for their tiles.
-// One index plan over columns `mask` and row groups [g0, g0 + n): its
-// per-tile values into val.
-static pq_status prefix_plan(pq_file f, int mode, Plan& P, std::vector<uint64_t>& val, hipStream_t s) {
-  if (!P.pre_units) return PQ_OK;
-  uint8_t* ws = nullptr;
-  if (hipMalloc(&ws, P.ws_total) != hipSuccess) return fail(PQ_ENOMEM, "open: no device memory for the prefix pass");
-  pq_status st = enqueue_index(f, P, ws, mode, s);
-  for (const ColScan& cs : P.cols) {
-    const uint32_t cnt = cs.tile_end - cs.tile_begin;
-    if (st == PQ_OK && cs.ws_tile_aux && cnt &&
-        hipMemcpyAsync(val.data() + cs.tile_begin, ws + cs.ws_tile_aux, 8ull * cnt, hipMemcpyDeviceToHost, s) !=
-            hipSuccess)
-      st = fail(PQ_EHIP, "open: prefix pass copy");
-  }
-  if (st == PQ_OK) st = read_err(f, s);
-  (void)hipStreamSynchronize(s);
-  (void)hipFree(ws);
-  return st;
-}
-
-static pq_status prefix_pass(pq_file f, int mode, const std::vector<bool>& need, std::vector<uint64_t>& val,
-                             hipStream_t s) {
-  // every needed column at once (one decompression and one prepass launch
-  // per batch of row groups), the batches sized to INDEX_WS_CAP; a single
-  // row group over the cap is taken one column at a time
-  uint64_t mask = 0;
-  for (int c = 0; c < f->ncols; ++c)
-    if (need[(size_t)c]) mask |= 1ull << c;
-  if (!mask) return PQ_OK;
-  for (int g0 = 0; g0 < f->nrg;) {
-    int n = f->nrg - g0;
-    Plan P;
-    for (;;) {
-      P = Plan();
-      pq_status st = make_plan(f, mask, g0, g0 + n, P, true);
-      if (st != PQ_OK) return st;
-      if (P.ws_total <= INDEX_WS_CAP || n == 1) break;
-      n = (n + 1) / 2;
-    }
-    if (P.ws_total <= INDEX_WS_CAP || __builtin_popcountll(mask) == 1) {
-      pq_status st = prefix_plan(f, mode, P, val, s);
-      if (st != PQ_OK) return st;
-    } else {
-      // one column at a time, and a column over the cap in runs of pages
-      for (int c = 0; c < f->ncols; ++c) {
-        if (!((mask >> c) & 1)) continue;
-        Plan Q;
-        pq_status st = make_plan(f, 1ull << c, g0, g0 + n, Q, true);
-        if (st != PQ_OK) return st;
-        if (Q.ws_total <= INDEX_WS_CAP) {
-          st = prefix_plan(f, mode, Q, val, s);
-          if (st != PQ_OK) return st;
-          continue;
-        }
-        const uint32_t pe = f->chunk_page0[(size_t)c * f->nrg + g0 + n];
-        for (uint32_t p0 = f->chunk_page0[(size_t)c * f->nrg + g0]; p0 < pe;) {
-          uint32_t p1 = p0 + 1;
-          auto bytes = [&](uint32_t b) {
-            return (f->scratch_prefix[b] - f->scratch_prefix[p0]) + (f->xscratch_prefix[b] - f->xscratch_prefix[p0]);
-          };
-          while (p1 < pe && bytes(p1 + 1) <= INDEX_WS_CAP / 2) ++p1;
-          Plan R;
-          st = make_plan(f, 1ull << c, g0, g0 + n, R, true, p0, p1);
-          if (st == PQ_OK) st = prefix_plan(f, mode, R, val, s);
-          if (st != PQ_OK) return st;
-          p0 = p1;
-        }
-      }
-    }
-    g0 += n;
-  }
-  return PQ_OK;
-}
-
-static pq_status build_tile_prefix(pq_file f, hipStream_t s) {
-  const uint64_t nt = f->total_tiles;
-  std::vector<bool> need((size_t)f->ncols, false), need_dlba((size_t)f->ncols, false);
-  bool any_dlba = false;
-  for (int c = 0; c < f->ncols; ++c) {
-    need[(size_t)c] = f->cols[c].type == T_BYTE_ARRAY;
-    for (uint32_t p = f->chunk_page0[(size_t)c * f->nrg]; p < f->chunk_page0[(size_t)(c + 1) * f->nrg]; ++p) {
-      if (f->pages[p].kind == PAGE_DICT) continue;
-      if (f->pages[p].encoding == E_DELTA) need[(size_t)c] = true;
-      if (f->pages[p].encoding == E_DLBA && f->cols[c].type == T_BYTE_ARRAY) need_dlba[(size_t)c] = any_dlba = true;
-    }
-  }
-  // the DELTA sums of DELTA_LENGTH_BYTE_ARRAY length streams first: the
-  // string-byte pass needs their carries
-  if (any_dlba) {
-    std::vector<uint64_t> val2(nt, 0);
-    pq_status st = prefix_pass(f, 1, need_dlba, val2, s);
-    if (st != PQ_OK) return st;
-    std::vector<uint64_t> p2(nt + 1, 0);
-    for (uint64_t t = 0; t < nt; ++t) p2[t + 1] = p2[t] + val2[t];
-    HIP_OR(hipMalloc(&f->d_tpfx2, 8ull * (nt + 1)));
-    HIP_OR(hipMemcpy(f->d_tpfx2, p2.data(), 8ull * (nt + 1), hipMemcpyHostToDevice));
-    f->fd.tpfx2 = f->d_tpfx2;
-    f->device_bytes += 8ull * (nt + 1);
-  }
-  std::vector<uint64_t> val(nt, 0);
-  pq_status st = prefix_pass(f, 0, need, val, s);
-  if (st != PQ_OK) return st;
-  f->tpfx.assign(nt + 1, 0);
-  for (uint64_t t = 0; t < nt; ++t) f->tpfx[t + 1] = f->tpfx[t] + val[t];
-  HIP_OR(hipMalloc(&f->d_tpfx, 8ull * (nt + 1)));
-  HIP_OR(hipMemcpy(f->d_tpfx, f->tpfx.data(), 8ull * (nt + 1), hipMemcpyHostToDevice));
-  f->fd.tpfx = f->d_tpfx;
-  return PQ_OK;
-}
-
 extern "C" pq_status pq_plan(pq_file f, uint64_t col_mask, int32_t rg_begin, int32_t rg_end, pq_scan_sizes* out) {
   if (!f || !out) return fail(PQ_EINVAL, "NULL argument");
   Plan P;
@@ -1937,7 +1890,7 @@ extern "C" pq_status pq_plan(pq_file f, uint64_t col_mask, int32_t rg_begin, int
   for (int k = 0; k < 64; ++k) out->chars_bytes[k] = 0;
   for (int32_t k : P.str_cols) {
     const ColScan& cs = P.cols[k];
-    out->chars_bytes[k] = (int64_t)(f->tpfx[cs.tile_end] - f->tpfx[cs.tile_begin]);
+    out->chars_bytes[k] = chars_of(f, cs.col, rg_begin, rg_end);
   }
   return PQ_OK;
 }
@@ -2237,10 +2190,10 @@ pq_status make_batch_plan(const pq_request* reqs, int32_t n, BatchPlan& P) {
     for (int c = 0; c < f->ncols; ++c) {
       if (!((q.col_mask >> c) & 1)) continue;
       ColSetup k;
-      col_setup(f, c, q.rg_begin, q.rg_end, rows, off, false, k);
+      col_setup(f, c, q.rg_begin, q.rg_end, rows, off, k);
       const ColScan& cs = k.cs;
       const uint32_t idx = (uint32_t)P.cols.size();
-      P.chars.push_back(cs.type == T_BYTE_ARRAY ? (int64_t)(f->tpfx[cs.tile_end] - f->tpfx[cs.tile_begin]) : 0);
+      P.chars.push_back(cs.type == T_BYTE_ARRAY ? chars_of(f, c, q.rg_begin, q.rg_end) : 0);
       if (cs.type == T_BYTE_ARRAY) P.str_cols.push_back((int32_t)idx);
       if (k.sbytes) {
         P.snappy_segs.push_back(Segment{idx, cs.page_begin, cs.page_end, P.snappy_waves});
