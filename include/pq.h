@@ -133,13 +133,12 @@ typedef struct {
  * decompressed bytes fit a 512 MiB window, each pass's compressed pages
  * decompressed into that window.  Every dictionary page is decoded once into
  * a resident dictionary kept by the handle (fixed-width arrays; string
- * positions, lengths and 64-byte slots), so scans never rebuild one.  Last,
- * the tile prefix: for every column with DELTA_BINARY_PACKED or BYTE_ARRAY
- * pages, a pass over its tiles (after decompression and dictionary decode,
- * in batches of row groups, or of pages, with at most 512 MiB of temporary
- * device memory) counts each tile's DELTA sum or string bytes, and their
- * exclusive prefix sum over the file's tiles is kept on the device and the
- * host (8 bytes per tile).  A scan takes DELTA carries and string offsets from
+ * positions, lengths and 64-byte slots), so scans never rebuild one.  Each
+ * data pass also counts the DELTA sum or string bytes of its tiles of
+ * DELTA_BINARY_PACKED and BYTE_ARRAY pages; their exclusive prefix sum over
+ * the file's tiles is kept on the device (8 bytes per tile, 8 more in a file
+ * with DELTA_LENGTH_BYTE_ARRAY strings), its values at the column chunks'
+ * first tiles on the host.  A scan takes DELTA carries and string offsets from
  * it, and pq_plan the chars sizes.  Returns PQ_ECORRUPT for a malformed file
  * (including corrupt level, DELTA, dictionary-index or string data found by
  * the index or prefix passes), PQ_EUNSUPPORTED for valid files outside the
@@ -417,8 +416,12 @@ void pq_server_destroy(pq_server s);
    error reporting). */
 const char* pq_server_last_error(void);
 
-/* Frees the handle's host and device memory (not dev_buf).  Sec. 2: the
-   handle is the reader's state for one file. */
+/* Frees the handle's host and device memory (not dev_buf), after waiting for
+   the device's work.  Device blocks of 1 MiB or more of closed handles and
+   finished opens are kept for the next open on the device, at most 256 MiB in
+   all (those unused for 10 s go at the next open or close, all of a device's when
+   an allocation of this library fails).  Sec. 2: the handle is the reader's state
+   for one file. */
 void pq_close(pq_file f);
 
 /* Thread-local description of the last error (Sec. 2: the reader's error

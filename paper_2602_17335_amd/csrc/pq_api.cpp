@@ -10,6 +10,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "pq.h"
@@ -403,28 +404,155 @@ struct ProfScope {
   }
 };
 
+// ---------------------------------------------------------------------------
+// device blocks of opens and closes
+// ---------------------------------------------------------------------------
+// An open allocates and a close frees blocks of megabytes, and the runtime
+// takes 15 to 60 us for such an allocation or free and about 300 us once more than
+// 64 MiB of freed blocks have to be handed back: of 4.4 ms for the open, scan and
+// close of the wide table (4M rows) 1.5 ms, of 5.0 ms for the Snappy table (2M rows)
+// 1.0 ms (now, with the round trips saved too, 2.6 and 4.05 ms).  Blocks
+// of BLOCK_MIN bytes or more that are known to be idle are therefore kept for
+// the next open on their device, up to BLOCK_CAP bytes in all; the oldest go
+// first beyond that, those unused for BLOCK_AGE seconds at the next open or
+// close, and all of a device's when an allocation fails.
+constexpr size_t BLOCK_MIN = 1 << 20, BLOCK_CAP = 256 << 20;
+constexpr int BLOCK_AGE = 10;
+
+namespace {
+struct DevBlock {
+  void* p;
+  size_t n;
+  int dev;
+  std::chrono::steady_clock::time_point t;
+};
+struct DevBlocks {
+  std::mutex m;
+  std::vector<DevBlock> kept;                   // oldest first
+  size_t bytes = 0;                             // their sum
+  std::unordered_map<void*, DevBlock> in_use;   // blocks of BLOCK_MIN bytes or more
+  void drop(size_t i, std::vector<void*>& out) {
+    out.push_back(kept[i].p);
+    bytes -= kept[i].n;
+    kept.erase(kept.begin() + (ptrdiff_t)i);
+  }
+  void expire(std::vector<void*>& out) {
+    const auto now = std::chrono::steady_clock::now();
+    while (!kept.empty() && now - kept[0].t > std::chrono::seconds(BLOCK_AGE)) drop(0, out);
+  }
+};
+// (never destroyed: the runtime may go first)
+DevBlocks& dev_blocks() {
+  static DevBlocks* const b = new DevBlocks;
+  return *b;
+}
+}  // namespace
+
+// hipMalloc, once more without the kept blocks if there is no room
+__attribute__((visibility("hidden"))) hipError_t pq_dev_malloc(void** p, size_t n) {
+  hipError_t e = hipMalloc(p, n);
+  if (e == hipSuccess) return e;
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  std::vector<void*> out;
+  {
+    DevBlocks& B = dev_blocks();
+    std::lock_guard<std::mutex> g(B.m);
+    for (size_t i = B.kept.size(); i-- > 0;)
+      if (B.kept[i].dev == dev) B.drop(i, out);
+  }
+  if (out.empty()) return e;
+  (void)hipGetLastError();
+  for (void* q : out) (void)hipFree(q);
+  return hipMalloc(p, n);
+}
+
+// a block that hipFree frees
+template <class T>
+static hipError_t small_alloc(T** p, size_t n) {
+  void* q = nullptr;
+  const hipError_t e = pq_dev_malloc(&q, n);
+  if (e == hipSuccess) *p = static_cast<T*>(q);
+  return e;
+}
+
+// a block that block_release frees
+template <class T>
+static hipError_t block_alloc(T** p, size_t n) {
+  void* q = nullptr;
+  if (n < BLOCK_MIN) return small_alloc(p, n);
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  DevBlocks& B = dev_blocks();
+  std::vector<void*> out;
+  {
+    std::lock_guard<std::mutex> g(B.m);
+    B.expire(out);
+    size_t best = B.kept.size();
+    for (size_t i = 0; i < B.kept.size(); ++i) {
+      const DevBlock& b = B.kept[i];
+      if (b.dev == dev && b.n >= n && b.n <= n + n / 2 && (best == B.kept.size() || b.n < B.kept[best].n)) best = i;
+    }
+    if (best < B.kept.size()) {
+      q = B.kept[best].p;
+      B.in_use[q] = B.kept[best];
+      B.bytes -= B.kept[best].n;
+      B.kept.erase(B.kept.begin() + (ptrdiff_t)best);
+    }
+  }
+  for (void* o : out) (void)hipFree(o);
+  if (!q) {
+    e = pq_dev_malloc(&q, n);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> g(B.m);
+    B.in_use[q] = DevBlock{q, n, dev, {}};
+  }
+  *p = static_cast<T*>(q);
+  return hipSuccess;
+}
+
+// idle: nothing on the device uses the block any more
+static void block_release(void* p, bool idle) {
+  DevBlocks& B = dev_blocks();
+  std::vector<void*> out;
+  bool kept = false;
+  try {
+    std::lock_guard<std::mutex> g(B.m);
+    B.expire(out);
+    auto it = B.in_use.find(p);
+    if (it != B.in_use.end()) {
+      DevBlock b = it->second;
+      B.in_use.erase(it);
+      if (idle && b.n <= BLOCK_CAP) {
+        b.t = std::chrono::steady_clock::now();
+        B.kept.push_back(b);
+        kept = true;
+        B.bytes += b.n;
+        while (B.bytes > BLOCK_CAP) B.drop(0, out);
+      }
+    }
+  } catch (...) {  // (no host memory)
+  }
+  if (!kept) (void)hipFree(p);
+  for (void* o : out) (void)hipFree(o);
+}
+
 static void free_handle(pq_file f) {
   if (!f) return;
   for (auto& r : f->recs) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
   for (auto e : f->event_pool) (void)hipEventDestroy(e);
   for (auto e : f->stage_ev)
     if (e) (void)hipEventDestroy(e);
-  if (f->d_pages) (void)hipFree(f->d_pages);
-  if (f->d_tiles) (void)hipFree(f->d_tiles);
-  if (f->d_strck) (void)hipFree(f->d_strck);
-  if (f->d_sblk) (void)hipFree(f->d_sblk);
-  if (f->d_sblk_page) (void)hipFree(f->d_sblk_page);
-  if (f->d_sbits) (void)hipFree(f->d_sbits);
-  if (f->d_dbau) (void)hipFree(f->d_dbau);
-  for (uint8_t* b : f->d_dbactx) (void)hipFree(b);
-  if (f->d_ckl) (void)hipFree(f->d_ckl);
-  if (f->d_ckv) (void)hipFree(f->d_ckv);
-  if (f->d_chunks) (void)hipFree(f->d_chunks);
-  if (f->d_err) (void)hipFree(f->d_err);
-  if (f->d_tpfx) (void)hipFree(f->d_tpfx);
-  if (f->d_tpfx2) (void)hipFree(f->d_tpfx2);
-  if (f->d_dicts) (void)hipFree(f->d_dicts);
-  if (f->d_dict_arena) (void)hipFree(f->d_dict_arena);
+  // the small blocks first: hipFree waits for the device, so the blocks after
+  // them are idle
+  bool idle = f->d_err != nullptr;
+  for (void* p : {(void*)f->d_err, (void*)f->d_chunks, (void*)f->d_tpfx, (void*)f->d_tpfx2, (void*)f->d_dicts})
+    if (p && hipFree(p) != hipSuccess) idle = false;
+  for (void* p : {(void*)f->d_pages, (void*)f->d_tiles, (void*)f->d_strck, (void*)f->d_sblk, (void*)f->d_sblk_page,
+                  (void*)f->d_sbits, (void*)f->d_dbau, (void*)f->d_ckl, (void*)f->d_ckv, (void*)f->d_dict_arena})
+    if (p) block_release(p, idle);
+  for (uint8_t* b : f->d_dbactx) block_release(b, idle);
   delete f;
 }
 
@@ -499,17 +627,23 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   hipStream_t s = (hipStream_t)stream;
   auto t0 = std::chrono::steady_clock::now();
   const uint8_t* file = (const uint8_t*)dev_buf;
+  // the end of the file, with most footers whole
+  std::vector<uint8_t> foot((size_t)std::min<uint64_t>(len, 16384));
   uint8_t tail[8], head[4];
-  HIP_OR(hipMemcpyAsync(tail, file + len - 8, 8, hipMemcpyDeviceToHost, s));
+  HIP_OR(hipMemcpyAsync(foot.data(), file + len - foot.size(), foot.size(), hipMemcpyDeviceToHost, s));
   HIP_OR(hipMemcpyAsync(head, file, 4, hipMemcpyDeviceToHost, s));
   HIP_OR(hipStreamSynchronize(s));
+  memcpy(tail, foot.data() + foot.size() - 8, 8);
   if (memcmp(tail + 4, "PAR1", 4) || memcmp(head, "PAR1", 4)) return fail(PQ_ECORRUPT, "bad magic");
   uint64_t flen = (uint64_t)tail[0] | ((uint64_t)tail[1] << 8) | ((uint64_t)tail[2] << 16) | ((uint64_t)tail[3] << 24);
   if (flen + 12 > len) return fail(PQ_ECORRUPT, "footer length exceeds file");
-  std::vector<uint8_t> foot(flen);
-  if (flen) {
+  if (flen + 8 > foot.size()) {
+    foot.resize(flen);
     HIP_OR(hipMemcpyAsync(foot.data(), file + len - 8 - flen, flen, hipMemcpyDeviceToHost, s));
     HIP_OR(hipStreamSynchronize(s));
+  } else {
+    foot.erase(foot.begin(), foot.end() - 8 - (ptrdiff_t)flen);
+    foot.resize(flen);
   }
   pq_file f = new pq_file_s();
   f->file = file;
@@ -555,18 +689,20 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   HIP_OR(hipEventRecord(e0, s));
   uint32_t *d_counts = nullptr, *d_base = nullptr;
   uint8_t* d_rec = nullptr;  // header offsets recorded by the first walk, with their tables
-  auto cleanup_tmp = [&]() {
+  uint32_t* d_pch = nullptr;
+  auto cleanup_tmp = [&](bool idle) {
     if (d_counts) (void)hipFree(d_counts);
     if (d_base) (void)hipFree(d_base);
-    if (d_rec) (void)hipFree(d_rec);
-    d_counts = d_base = nullptr;
+    if (d_rec) block_release(d_rec, idle);
+    if (d_pch) (void)hipFree(d_pch);
+    d_counts = d_base = d_pch = nullptr;
     d_rec = nullptr;
   };
 #define OPEN_HIP(expr)                                                          \
   do {                                                                          \
     hipError_t e_ = (expr);                                                     \
     if (e_ != hipSuccess) {                                                     \
-      cleanup_tmp();                                                            \
+      cleanup_tmp(false);                                                       \
       free_handle(f);                                                           \
       return fail(PQ_EHIP, "%s: %s", #expr, hipGetErrorString(e_));            \
     }                                                                           \
@@ -574,10 +710,10 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
 #define OPEN_ERR()                                                              \
   do {                                                                          \
     pq_status st_ = read_err(f, s);                                             \
-    if (st_ != PQ_OK) { cleanup_tmp(); free_handle(f); return st_; }            \
+    if (st_ != PQ_OK) { cleanup_tmp(false); free_handle(f); return st_; }       \
   } while (0)
 
-  OPEN_HIP(hipMalloc(&f->d_err, 4));
+  OPEN_HIP(small_alloc(&f->d_err, 4));
   OPEN_HIP(hipMemsetAsync(f->d_err, 0, 4, s));
   // The first walk checks every header, counts the pages and records the
   // header offsets of up to one page per KiB of each chunk; the page table
@@ -589,18 +725,19 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     rec_base[q + 1] = rec_base[q] + rec_cap[q];
   }
   const size_t o_rbase = align_up(8ull * rec_base[nchunks], 256), o_rcap = align_up(o_rbase + 4ull * nchunks, 256),
-               o_over = align_up(o_rcap + 4ull * nchunks, 256), o_pch = align_up(o_over + 4, 256);
+               rec_bytes = align_up(o_rcap + 4ull * nchunks, 256);
   uint32_t overflow = 1;
+  std::vector<uint32_t> counts((size_t)nchunks + 1);  // pages of each chunk; more than recorded
   if (nchunks > 0) {
-    OPEN_HIP(hipMalloc(&f->d_chunks, sizeof(ChunkDev) * nchunks));
-    OPEN_HIP(hipMalloc(&d_counts, sizeof(uint32_t) * nchunks));
-    OPEN_HIP(hipMalloc(&d_base, sizeof(uint32_t) * nchunks));
+    OPEN_HIP(small_alloc(&f->d_chunks, sizeof(ChunkDev) * nchunks));
+    OPEN_HIP(small_alloc(&d_counts, sizeof(uint32_t) * (nchunks + 1)));
+    OPEN_HIP(small_alloc(&d_base, sizeof(uint32_t) * nchunks));
     OPEN_HIP(hipMemcpyAsync(f->d_chunks, f->chunks.data(), sizeof(ChunkDev) * nchunks, hipMemcpyHostToDevice, s));
-    const bool record = hipMalloc(&d_rec, o_pch) == hipSuccess;  // (no room: the second walk)
+    const bool record = block_alloc(&d_rec, rec_bytes) == hipSuccess;  // (no room: the second walk)
     uint64_t* d_recs = record ? reinterpret_cast<uint64_t*>(d_rec) : nullptr;
     uint32_t* d_rbase = record ? reinterpret_cast<uint32_t*>(d_rec + o_rbase) : nullptr;
     uint32_t* d_rcap = record ? reinterpret_cast<uint32_t*>(d_rec + o_rcap) : nullptr;
-    uint32_t* d_over = record ? reinterpret_cast<uint32_t*>(d_rec + o_over) : nullptr;
+    uint32_t* d_over = record ? d_counts + nchunks : nullptr;
     if (record) {
       OPEN_HIP(hipMemcpyAsync(d_rbase, rec_base.data(), 4ull * nchunks, hipMemcpyHostToDevice, s));
       OPEN_HIP(hipMemcpyAsync(d_rcap, rec_cap.data(), 4ull * nchunks, hipMemcpyHostToDevice, s));
@@ -609,24 +746,22 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     hipLaunchKernelGGL(k_walk, dim3((uint32_t)nchunks), dim3(64), 0, s, file, (len + 15) & ~15ull, f->d_chunks, nchunks,
                        d_counts, nullptr, nullptr, f->d_err, d_recs, d_rbase, d_rcap, d_over);
     OPEN_HIP(hipGetLastError());
+    OPEN_HIP(hipMemcpyAsync(counts.data(), d_counts, sizeof(uint32_t) * (nchunks + 1), hipMemcpyDeviceToHost, s));
     OPEN_ERR();
-    if (record) OPEN_HIP(hipMemcpy(&overflow, d_over, 4, hipMemcpyDeviceToHost));
+    if (record) overflow = counts[(size_t)nchunks];
   }
-  std::vector<uint32_t> counts(nchunks);
-  if (nchunks) OPEN_HIP(hipMemcpy(counts.data(), d_counts, sizeof(uint32_t) * nchunks, hipMemcpyDeviceToHost));
   f->chunk_page0.assign(nchunks + 1, 0);
   for (int q = 0; q < nchunks; ++q) f->chunk_page0[q + 1] = f->chunk_page0[q] + counts[q];
   const uint32_t npages = f->chunk_page0[nchunks];
   if (npages > 0) {
-    OPEN_HIP(hipMalloc(&f->d_pages, sizeof(PageDev) * npages));
+    OPEN_HIP(block_alloc(&f->d_pages, sizeof(PageDev) * npages));
     OPEN_HIP(hipMemcpyAsync(d_base, f->chunk_page0.data(), sizeof(uint32_t) * nchunks, hipMemcpyHostToDevice, s));
-    uint32_t* d_pch = nullptr;
     std::vector<uint32_t> page_chunk;
     if (!overflow) {
       page_chunk.resize(npages);
       for (int q = 0; q < nchunks; ++q)
         for (uint32_t p = f->chunk_page0[q]; p < f->chunk_page0[q + 1]; ++p) page_chunk[p] = (uint32_t)q;
-      if (hipMalloc(&d_pch, 4ull * npages) != hipSuccess) overflow = 1;
+      if (small_alloc(&d_pch, 4ull * npages) != hipSuccess) overflow = 1;
     }
     if (!overflow) {
       hipError_t e2 = hipMemcpyAsync(d_pch, page_chunk.data(), 4ull * npages, hipMemcpyHostToDevice, s);
@@ -636,19 +771,17 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
                            d_base, d_pch, npages, f->d_pages, f->d_err);
         e2 = hipGetLastError();
       }
-      if (e2 == hipSuccess) e2 = hipStreamSynchronize(s);  // before d_pch and page_chunk go
-      (void)hipFree(d_pch);
       OPEN_HIP(e2);
     } else {
       hipLaunchKernelGGL(k_walk, dim3((uint32_t)nchunks), dim3(64), 0, s, file, (len + 15) & ~15ull, f->d_chunks,
                          nchunks, nullptr, d_base, f->d_pages, f->d_err, nullptr, nullptr, nullptr, nullptr);
       OPEN_HIP(hipGetLastError());
     }
-    OPEN_ERR();
     f->pages.resize(npages);
-    OPEN_HIP(hipMemcpy(f->pages.data(), f->d_pages, sizeof(PageDev) * npages, hipMemcpyDeviceToHost));
+    OPEN_HIP(hipMemcpyAsync(f->pages.data(), f->d_pages, sizeof(PageDev) * npages, hipMemcpyDeviceToHost, s));
+    OPEN_ERR();
   }
-  cleanup_tmp();
+  cleanup_tmp(true);
 
   // ---- host layout: rows, dictionary links, tiles, scratch, checkpoints ----
   f->chunk_tile0.assign(nchunks + 1, 0);
@@ -758,18 +891,22 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   uint8_t* d_xscratch = nullptr;      // after OPEN_GUARD bytes
   ColScan* d_xcols = nullptr;     // their column tables
   uint64_t xscratch = 0;          // bytes of the file-wide expansion layout so far
-  auto free_pass = [&]() {
-    if (d_ix) (void)hipFree(d_ix);
+  // what a pass copies from; lives until the stream has been waited for
+  std::vector<uint8_t> up;
+  std::vector<ColScan> pcols;
+  // idle: the stream has been waited for since the last use
+  auto free_pass = [&](bool idle) {
+    if (d_ix) block_release(d_ix, idle);
     if (d_pcols) (void)hipFree(d_pcols);
-    if (d_xscratch_mem) (void)hipFree(d_xscratch_mem);
+    if (d_xscratch_mem) block_release(d_xscratch_mem, idle);
     if (d_xcols) (void)hipFree(d_xcols);
     d_ix = d_pcols = nullptr;
     d_xscratch_mem = d_xscratch = nullptr;
     d_xcols = nullptr;
   };
-  auto cleanup_open = [&]() {
-    free_pass();
-    if (d_scratch_mem) (void)hipFree(d_scratch_mem);
+  auto cleanup_open = [&](bool idle = false) {
+    free_pass(idle);
+    if (d_scratch_mem) block_release(d_scratch_mem, idle);
     if (d_cs) (void)hipFree(d_cs);
     if (d_sums) (void)hipFree(d_sums);
     d_sums = nullptr;
@@ -780,9 +917,9 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   // Snappy block index, built by the decompression below
   f->total_sblk = sblk;
   if (sblk) {
-    if (hipMalloc(&f->d_sblk, sizeof(uint32_t) * sblk) != hipSuccess ||
-        hipMalloc(&f->d_sblk_page, sizeof(uint32_t) * sblk) != hipSuccess ||
-        hipMalloc(&f->d_sbits, sizeof(uint16_t) * (sbits + 2)) != hipSuccess) {
+    if (block_alloc(&f->d_sblk, sizeof(uint32_t) * sblk) != hipSuccess ||
+        block_alloc(&f->d_sblk_page, sizeof(uint32_t) * sblk) != hipSuccess ||
+        block_alloc(&f->d_sbits, sizeof(uint16_t) * (sbits + 2)) != hipSuccess) {
       cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: block index allocation");
     }
     if (hipMemcpy(f->d_sblk_page, sblk_page.data(), sizeof(uint32_t) * sblk, hipMemcpyHostToDevice) != hipSuccess) {
@@ -790,22 +927,22 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     }
   }
   if (window > 0) {
-    if (hipMalloc(&d_scratch_mem, OPEN_GUARD + window) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: no device memory for decompression"); }
+    if (block_alloc(&d_scratch_mem, OPEN_GUARD + window) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: no device memory for decompression"); }
     d_scratch = d_scratch_mem + OPEN_GUARD;
   }
-  if (hipMalloc(&d_cs, sizeof(ColScan)) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: allocation failed"); }
+  if (small_alloc(&d_cs, sizeof(ColScan)) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: allocation failed"); }
   if (tiles) {
-    if (hipMalloc(&f->d_tiles, sizeof(TileDev) * tiles) != hipSuccess ||
-        hipMalloc(&f->d_ckl, sizeof(uint32_t) * NLCK * tiles) != hipSuccess ||
-        hipMalloc(&f->d_ckv, sizeof(Ck) * NSUB * tiles) != hipSuccess) {
+    if (block_alloc(&f->d_tiles, sizeof(TileDev) * tiles) != hipSuccess ||
+        block_alloc(&f->d_ckl, sizeof(uint32_t) * NLCK * tiles) != hipSuccess ||
+        block_alloc(&f->d_ckv, sizeof(Ck) * NSUB * tiles) != hipSuccess) {
       cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: tile index allocation");
     }
   }
   if (strck) {
-    if (hipMalloc(&f->d_strck, sizeof(uint32_t) * strck) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: checkpoint allocation"); }
+    if (block_alloc(&f->d_strck, sizeof(uint32_t) * strck) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: checkpoint allocation"); }
   }
   if (dba_units) {
-    if (hipMalloc(&f->d_dbau, sizeof(DbaUnit) * dba_units) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: unit allocation"); }
+    if (block_alloc(&f->d_dbau, sizeof(DbaUnit) * dba_units) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: unit allocation"); }
     OPEN_HIP(hipMemsetAsync(f->d_dbau, 0xff, sizeof(DbaUnit) * dba_units, s));
     f->device_bytes += sizeof(DbaUnit) * dba_units;
   }
@@ -823,8 +960,8 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   }
   const size_t npick = (size_t)nchunks + 1;
   const size_t o_pick = 8ull * scan_groups(tiles), o_pat = o_pick + 8 * npick;
-  if (hipMalloc(&f->d_tpfx, 8ull * (tiles + 1)) != hipSuccess || hipMalloc(&d_sums, o_pat + 4 * npick) != hipSuccess ||
-      (any_dlba && hipMalloc(&f->d_tpfx2, 8ull * (tiles + 1)) != hipSuccess)) {
+  if (small_alloc(&f->d_tpfx, 8ull * (tiles + 1)) != hipSuccess || small_alloc(&d_sums, o_pat + 4 * npick) != hipSuccess ||
+      (any_dlba && small_alloc(&f->d_tpfx2, 8ull * (tiles + 1)) != hipSuccess)) {
     cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: tile prefix allocation");
   }
   OPEN_HIP(hipMemsetAsync(f->d_tpfx, 0, 8ull * (tiles + 1), s));
@@ -925,7 +1062,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       for (uint32_t pp = P.p0; pp < P.p1; ++pp) f->xscratch_prefix[pp] = xscratch;
       if (!xc.empty()) {
         if (xs.size() > MAX_SEGS) { cleanup_open(); free_handle(f); return fail(PQ_EUNSUPPORTED, "too many DELTA_BYTE_ARRAY columns"); }
-        if (hipMalloc(&d_xcols, sizeof(ColScan) * xc.size()) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: allocation failed"); }
+        if (small_alloc(&d_xcols, sizeof(ColScan) * xc.size()) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: allocation failed"); }
         OPEN_HIP(hipMemcpyAsync(d_xcols, xc.data(), sizeof(ColScan) * xc.size(), hipMemcpyHostToDevice, s));
         hipLaunchKernelGGL(k_dba<false>, dim3(xw), dim3(64), 0, s, d_xcols, make_segs(xs), (uint8_t*)nullptr, scr,
                            (uint8_t*)nullptr, f->d_pages, (DbaUnit*)nullptr, 0, f->d_err);
@@ -949,7 +1086,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         }
         if (ctx) {
           uint8_t* b = nullptr;
-          if (hipMalloc(&b, ctx) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: unit allocation"); }
+          if (block_alloc(&b, ctx) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: unit allocation"); }
           f->d_dbactx.push_back(b);
           f->device_bytes += ctx;
           for (uint32_t pp = P.p0; pp < P.p1; ++pp) {
@@ -964,7 +1101,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         OPEN_HIP(hipMemcpyAsync(f->d_pages + P.p0, f->pages.data() + P.p0, sizeof(PageDev) * (P.p1 - P.p0),
                                 hipMemcpyHostToDevice, s));
         if (xscratch > xs0) {
-          if (hipMalloc(&d_xscratch_mem, OPEN_GUARD + (xscratch - xs0)) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: no device memory for expansion"); }
+          if (block_alloc(&d_xscratch_mem, OPEN_GUARD + (xscratch - xs0)) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: no device memory for expansion"); }
           d_xscratch = d_xscratch_mem + OPEN_GUARD;
           hipLaunchKernelGGL(k_dba<false>, dim3(xw), dim3(64), 0, s, d_xcols, make_segs(xs), (uint8_t*)nullptr, scr,
                              d_xscratch - xs0, f->d_pages, f->d_dbau, 1, f->d_err);
@@ -979,7 +1116,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         pq_status st5 = build_dicts(f, scr, host_copy, s);
         if (st5 != PQ_OK) { cleanup_open(); free_handle(f); return st5; }
       }
-      free_pass();
+      free_pass(true);
       continue;
     }
     // every page's streams, then the chains of each page by one workgroup
@@ -1085,8 +1222,8 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
                  o_stot = align_up(o_sent + 4 * nsga, 256), o_sseq = align_up(o_stot + 4 * nsga, 256),
                  o_sat = align_up(o_sseq + 4 * nspa, 256), o_spe = align_up(o_sat + 4096 * nsga, 256),
                  o_sex = align_up(o_spe + 1024 * nsga, 256), ix_total = o_sex + 8192 * nsga;
-    if (hipMalloc(&d_ix, ix_total ? ix_total : 256) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: chain tables"); }
-    std::vector<uint8_t> up(o_lat, 0);
+    if (block_alloc(&d_ix, ix_total ? ix_total : 256) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: chain tables"); }
+    up.assign(o_lat, 0);
     memcpy(up.data(), ixs.data(), sizeof(IxPage) * nix);
     if (!order.empty()) memcpy(up.data() + o_ord, order.data(), 4 * order.size());
     if (nspa) {
@@ -1187,11 +1324,11 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     // the values the tile prefix sums (DELTA sums, string bytes), while the
     // window holds the pass's decompressed pages; those of DELTA_LENGTH tiles
     // need the prefix of their lengths' DELTA sums first
-    std::vector<ColScan> pcols;
     if (!P.dict && ntl) {
       uint8_t* const wbase = reinterpret_cast<uint8_t*>(f->d_tpfx);  // "workspace": every region by its distance
       auto dist = [&](const void* p) { return (uint64_t)((uintptr_t)p - (uintptr_t)wbase); };
       std::vector<Segment> vs, vs2;
+      pcols.clear();
       uint32_t vu = 0, vu2 = 0;
       for (int c = 0; c < f->ncols; ++c) {
         if (!need[(size_t)c]) continue;
@@ -1233,7 +1370,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       }
       if (vs.size() > MAX_SEGS) { cleanup_open(); free_handle(f); return fail(PQ_EUNSUPPORTED, "too many columns"); }
       if (!pcols.empty()) {
-        if (hipMalloc(&d_pcols, sizeof(ColScan) * pcols.size()) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: allocation failed"); }
+        if (small_alloc(&d_pcols, sizeof(ColScan) * pcols.size()) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: allocation failed"); }
         OPEN_HIP(hipMemcpyAsync(d_pcols, pcols.data(), sizeof(ColScan) * pcols.size(), hipMemcpyHostToDevice, s));
         const ColScan* d_pc = reinterpret_cast<const ColScan*>(d_pcols);
         if (!vs2.empty()) {
@@ -1247,19 +1384,20 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     }
     if (P.dict) {
       // resident dictionaries, while the window holds the decompressed pages
+      OPEN_HIP(hipMemcpyAsync(f->pages.data(), f->d_pages, sizeof(PageDev) * npages, hipMemcpyDeviceToHost, s));
       {
         pq_status st3 = read_err(f, s);
         if (st3 != PQ_OK) { cleanup_open(); free_handle(f); return st3; }
       }
-      OPEN_HIP(hipMemcpy(f->pages.data(), f->d_pages, sizeof(PageDev) * npages, hipMemcpyDeviceToHost));
       pq_status st5 = build_dicts(f, scr, host_copy, s);
       if (st5 != PQ_OK) { cleanup_open(); free_handle(f); return st5; }
     }
-    {
+    if (!P.dict) {
+      if (&P == &passes.back()) break;  // (the last pass: waited for below)
       pq_status st6 = read_err(f, s);  // the pass is done: its tables may go
       if (st6 != PQ_OK) { cleanup_open(); free_handle(f); return st6; }
     }
-    free_pass();
+    free_pass(true);
   }
   f->xscratch_prefix[npages] = xscratch;
   // the tile prefix, and its values at the chunks' first tiles
@@ -1274,6 +1412,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     f->chunk_pfx.resize(npick);
     OPEN_HIP(hipMemcpyAsync(f->chunk_pfx.data(), d_pick, 8 * npick, hipMemcpyDeviceToHost, s));
   }
+  if (npages) OPEN_HIP(hipMemcpyAsync(f->pages.data(), f->d_pages, sizeof(PageDev) * npages, hipMemcpyDeviceToHost, s));
   HIP_OR(hipEventRecord(e1, s));
   {
     pq_status st3 = read_err(f, s);
@@ -1283,8 +1422,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   (void)hipEventElapsedTime(&ms, e0, e1);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  if (npages) OPEN_HIP(hipMemcpy(f->pages.data(), f->d_pages, sizeof(PageDev) * npages, hipMemcpyDeviceToHost));
-  cleanup_open();
+  cleanup_open(true);
 
 #undef OPEN_HIP
 #undef OPEN_ERR
@@ -1325,7 +1463,7 @@ extern "C" pq_status pq_open_host(const void* host_buf, uint64_t len, pq_stream 
   // the open-time passes read the file on the device: a temporary copy,
   // freed when the index is built
   uint8_t* tmp = nullptr;
-  if (hipMalloc(&tmp, (len + 15) / 16 * 16 + 16) != hipSuccess) return fail(PQ_ENOMEM, "open: no device memory for the file");
+  if (pq_dev_malloc((void**)&tmp, (len + 15) / 16 * 16 + 16) != hipSuccess) return fail(PQ_ENOMEM, "open: no device memory for the file");
   pq_status st = PQ_OK;
   if (hipMemcpyAsync(tmp, host_buf, len, hipMemcpyHostToDevice, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
     st = fail(PQ_EHIP, "open: copy of the host file");
@@ -1444,7 +1582,7 @@ static pq_status build_dicts(pq_file f, const uint8_t* scratch, bool copy_all, h
     }
   }
   if (off) {
-    if (hipMalloc(&f->d_dict_arena, off) != hipSuccess) return fail(PQ_ENOMEM, "open: no device memory for dictionaries");
+    if (block_alloc(&f->d_dict_arena, off) != hipSuccess) return fail(PQ_ENOMEM, "open: no device memory for dictionaries");
     f->device_bytes += off;
   }
   auto rebase = [&](const uint8_t* x) { return f->d_dict_arena + reinterpret_cast<uintptr_t>(x); };
@@ -1465,31 +1603,38 @@ static pq_status build_dicts(pq_file f, const uint8_t* scratch, bool copy_all, h
   for (const Copy& c : copies)
     HIP_OR(hipMemcpyAsync(f->d_dict_arena + c.dst, (c.from_scratch ? scratch : f->file) + c.src, c.n,
                           hipMemcpyDeviceToDevice, s));
-  HIP_OR(hipMalloc(&f->d_dicts, sizeof(DictSlot) * (size_t)(nchunks ? nchunks : 1)));
+  HIP_OR(small_alloc(&f->d_dicts, sizeof(DictSlot) * (size_t)(nchunks ? nchunks : 1)));
+  std::vector<DictSlot> first;  // the table k_dict reads, when the final one differs
+  DictWork* d_work = nullptr;
+  for (const DictSlot& sl : f->dicts)
+    if (sl.page != ~0u && sl.type != T_BYTE_ARRAY && sl.body && first.empty()) first = f->dicts;
+  // fixed-width copies no longer need their source after k_dict; the
+  // decompression buffer is freed after the open
+  for (DictSlot& sl : f->dicts)
+    if (sl.page != ~0u && sl.type != T_BYTE_ARRAY && sl.body) { sl.body = nullptr; sl.body_off = 0; }
   if (nchunks)
-    HIP_OR(hipMemcpyAsync(f->d_dicts, f->dicts.data(), sizeof(DictSlot) * (size_t)nchunks, hipMemcpyHostToDevice, s));
+    HIP_OR(hipMemcpyAsync(f->d_dicts, first.empty() ? f->dicts.data() : first.data(), sizeof(DictSlot) * (size_t)nchunks,
+                          hipMemcpyHostToDevice, s));
   if (units) {
-    DictWork* d_work = nullptr;
-    HIP_OR(hipMalloc(&d_work, sizeof(DictWork) * work.size()));
+    HIP_OR(small_alloc(&d_work, sizeof(DictWork) * work.size()));
     hipError_t e = hipMemcpyAsync(d_work, work.data(), sizeof(DictWork) * work.size(), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
       hipLaunchKernelGGL(k_dict, dim3((units + 3) / 4), dim3(256), 0, s, f->d_pages, f->d_strck, f->d_dicts, d_work,
                          (uint32_t)work.size(), f->d_err);
       e = hipGetLastError();
     }
-    pq_status st = e == hipSuccess ? read_err(f, s) : fail(PQ_EHIP, "open: k_dict: %s", hipGetErrorString(e));
-    (void)hipFree(d_work);
-    if (st != PQ_OK) return st;
-  }
-  // fixed-width copies no longer need their source; the decompression buffer
-  // is freed after the open
-  bool changed = false;
-  for (DictSlot& sl : f->dicts)
-    if (sl.page != ~0u && sl.type != T_BYTE_ARRAY && sl.body) { sl.body = nullptr; sl.body_off = 0; changed = true; }
-  if (changed)
+    if (e == hipSuccess && !first.empty())
+      e = hipMemcpyAsync(f->d_dicts, f->dicts.data(), sizeof(DictSlot) * (size_t)nchunks, hipMemcpyHostToDevice, s);
+    if (e != hipSuccess) {
+      (void)hipFree(d_work);
+      return fail(PQ_EHIP, "open: k_dict: %s", hipGetErrorString(e));
+    }
+  } else if (!first.empty()) {
     HIP_OR(hipMemcpyAsync(f->d_dicts, f->dicts.data(), sizeof(DictSlot) * (size_t)nchunks, hipMemcpyHostToDevice, s));
-  HIP_OR(hipStreamSynchronize(s));
-  return PQ_OK;
+  }
+  pq_status st = read_err(f, s);
+  if (d_work) (void)hipFree(d_work);
+  return st;
 }
 
 // ---------------------------------------------------------------------------

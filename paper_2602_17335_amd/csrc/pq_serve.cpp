@@ -25,6 +25,9 @@
 
 #include "pq.h"
 
+// hipMalloc, once more without the blocks kept for opens if there is no room (pq_api.cpp)
+__attribute__((visibility("hidden"))) hipError_t pq_dev_malloc(void** p, size_t n);
+
 namespace {
 
 using Clock = std::chrono::steady_clock;
@@ -486,7 +489,7 @@ extern "C" pq_status pq_server_create(const pq_file* files, int32_t n_files, uin
     for (int32_t g = 0; g < nrg; ++g) pq_row_group_rows(files[i], g, &r[(size_t)g]);
     s->rg_rows.push_back(r);
   }
-  if (hipMalloc(&s->d_arena, budget_bytes) != hipSuccess) { delete s; return sfail(PQ_ENOMEM, "no device memory for the budget"); }
+  if (pq_dev_malloc((void**)&s->d_arena, budget_bytes) != hipSuccess) { delete s; return sfail(PQ_ENOMEM, "no device memory for the budget"); }
   s->arena.init(s->d_arena, budget_bytes);
   for (int32_t k = 0; k < slots; ++k) {
     hipStream_t st;
