@@ -305,7 +305,9 @@ typedef struct {
    strings of slot dictionaries) x dictionary-index width (2: up to 12 bits,
    wider) x page size (3: one tile, 2-16 tiles, more). */
 #define PQ_TUNE_CLASSES 54
-#define PQ_FORM_BATCHED 0  /* one persistent decode launch over a work queue */
+#define PQ_FORM_BATCHED 0  /* one decode launch: one wave per tile or, with any field below
+                              set to another value than its default, a persistent grid
+                              over work queues */
 #define PQ_FORM_PER_PAGE 1 /* one launch per page and decoder (the plain form) */
 typedef struct {
   int32_t form;          /* PQ_FORM_BATCHED or PQ_FORM_PER_PAGE */
@@ -319,7 +321,7 @@ typedef struct {
   uint8_t pad2_[2];
 } pq_tuning;
 
-/* The default schedule (every field at its default). */
+/* The default schedule (every field at its default): one wave per tile. */
 pq_status pq_tuning_default(pq_tuning* out);
 
 /* Sizes a batch (Sec. 2: each request reads the selected column chunks of
@@ -334,9 +336,9 @@ pq_status pq_plan_batch(const pq_request* reqs, int32_t n, uint64_t* workspace_b
    kernels; Sec. 3, Insight 1: the pages of every request form one grid of
    work).  With PQ_FORM_BATCHED: Snappy decompression of every compressed
    data page (one launch for the page-sequential decoder, one for the
-   block-parallel one), the string totals, one persistent decode launch
-   whose waves take work units from the queues, and the shared validity
-   words of OPTIONAL columns.  With PQ_FORM_PER_PAGE the same work is one
+   block-parallel one), the string totals, one decode launch (one wave per
+   tile, or waves that take work units from the queues), and the shared
+   validity words of OPTIONAL columns.  With PQ_FORM_PER_PAGE the same work is one
    launch per page instead.  `tuning` NULL = the default schedule.  Errors
    as for pq_scan; pq_scan_check(NULL, workspace, stream) reports device
    errors.  Requests must not write overlapping outputs. */

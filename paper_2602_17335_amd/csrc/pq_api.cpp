@@ -2460,6 +2460,37 @@ void make_units(const BatchPlan& P, const pq_tuning& T, std::vector<BUnit>& unit
   }
 }
 
+// The tile runs of a plan as the segments of one k_decode_all launch, the
+// slowest kinds first.
+void make_run_segs(const BatchPlan& P, std::vector<Segment>& segs, uint32_t& units) {
+  uint64_t n = 0;
+  segs.reserve(P.runs.size());
+  for (uint32_t kind : {TK_STRSLOT, TK_STR, TK_FIXED3, TK_FIXED1, TK_DELTA, TK_BSS8, TK_BSS4, TK_FIXED2, TK_FIXED0})
+    for (const BatchPlan::Run& r : P.runs)
+      if (r.kind == kind) {
+        segs.push_back(Segment{r.cs | (kind << SEG_KIND), r.t0, r.t1, (uint32_t)n});
+        n += r.t1 - r.t0;
+      }
+  units = (uint32_t)n;
+}
+
+// Whether a schedule is the default one.  It takes no work queues: one wave
+// per tile in one k_decode_all launch, its work described by the tile runs.  The
+// queues' units cost the host a sort and an upload of 16 bytes per two tiles for
+// each scan, and the waves an atomic per unit; k_batch's loop holds 3 waves per
+// SIMD for k_decode_all's 4.  Measured, the
+// former default of 8 queues, 8 waves per CU and 2 tiles per unit / the best of 24
+// schedules with queues / one wave per tile: 64 files of up to 1M rows 754 / 602 /
+// 444 us, 16 files of up to 200,000 rows 387 / 253 / 192 us, 8 files of up to 50,000
+// rows 183 / 140 / 122 us.
+bool default_schedule(const pq_tuning& T) {
+  if (T.form != PQ_FORM_BATCHED || T.queues == 1) return false;
+  if (T.waves_per_cu > 0 && T.waves_per_cu != (int32_t)DEFAULT_WPC) return false;
+  for (uint8_t t : T.tiles_per_unit)
+    if (t && t != DEFAULT_TPU) return false;
+  return true;
+}
+
 SegTable seg_table(const std::vector<Segment>& v, uint8_t* ws, uint64_t ws_off) {
   SegTable t;
   memset(&t, 0, sizeof(t));
@@ -2496,10 +2527,15 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
   std::vector<BUnit> units;
   uint32_t qbeg[NQUEUE + 1];
   const bool per_page = T.form == PQ_FORM_PER_PAGE;
-  if (!per_page) make_units(P, T, units, qbeg);
-  // the header: error word, column table, string columns, segment tables,
-  // units, queue bounds and heads, in one copy
-  std::vector<uint8_t> hdr(P.ws_hdr_end, 0);
+  // (a run's column index has SEG_KIND bits)
+  const bool direct = default_schedule(T) && P.cols.size() < (1ull << SEG_KIND);
+  std::vector<Segment> run_segs;
+  uint32_t run_units = 0;
+  if (direct) make_run_segs(P, run_segs, run_units);
+  else if (!per_page) make_units(P, T, units, qbeg);
+  // the header: error word, column table, string columns, segment tables, tile
+  // runs or units, queue bounds and heads, in one copy
+  std::vector<uint8_t> hdr(direct ? P.ws_units + sizeof(Segment) * run_segs.size() : P.ws_hdr_end, 0);
   auto put = [&](uint64_t at, const void* src, size_t n) { if (n) memcpy(hdr.data() + at, src, n); };
   put(P.ws_cols, P.cols.data(), sizeof(ColScan) * P.cols.size());
   put(P.ws_which, P.str_cols.data(), sizeof(int32_t) * P.str_cols.size());
@@ -2508,7 +2544,10 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
   put(P.ws_dba, P.dba_segs.data(), sizeof(Segment) * P.dba_segs.size());
   put(P.ws_edge, P.edge_segs.data(), sizeof(Segment) * P.edge_segs.size());
   put(P.ws_prep, P.prep_segs.data(), sizeof(Segment) * P.prep_segs.size());
-  if (!per_page) {
+  static_assert(sizeof(Segment) == sizeof(BUnit), "at most one run per tile");
+  if (direct) {
+    put(P.ws_units, run_segs.data(), sizeof(Segment) * run_segs.size());
+  } else if (!per_page) {
     put(P.ws_units, units.data(), sizeof(BUnit) * units.size());
     put(P.ws_qbeg, qbeg, sizeof(qbeg));
   }
@@ -2560,13 +2599,23 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
       HIP_OR(hipGetLastError());
     }
   }
-  if (!P.str_cols.empty()) {
+  const uint32_t nstr = (uint32_t)P.str_cols.size();
+  const bool totals = direct && run_units && nstr <= 64;  // by one wave of the decode launch
+  if (nstr && !totals) {
     ProfScope ps_(prof, KP_STR_TOTAL, s);
-    hipLaunchKernelGGL(k_str_total, dim3(((uint32_t)P.str_cols.size() + 63) / 64), dim3(64), 0, s, d_cols,
-                       reinterpret_cast<const int32_t*>(ws + P.ws_which), (int32_t)P.str_cols.size(), err);
+    hipLaunchKernelGGL(k_str_total, dim3((nstr + 63) / 64), dim3(64), 0, s, d_cols,
+                       reinterpret_cast<const int32_t*>(ws + P.ws_which), (int32_t)nstr, err);
     HIP_OR(hipGetLastError());
   }
-  if (!per_page) {
+  if (direct) {
+    if (run_units) {
+      ProfScope ps_(prof, KP_ALL, s);
+      hipLaunchKernelGGL(k_decode_all, dim3((uint32_t)(((uint64_t)run_units + 1 + 3) / 4)), dim3(256), 0, s, ws, d_cols,
+                         seg_table(run_segs, ws, P.ws_units), run_units, reinterpret_cast<const int32_t*>(ws + P.ws_which),
+                         totals ? (int32_t)nstr : 0, err);
+      HIP_OR(hipGetLastError());
+    }
+  } else if (!per_page) {
     if (!units.empty()) {
       ProfScope ps_(prof, KP_BATCH, s);
       const uint32_t wpc = T.waves_per_cu > 0 ? (uint32_t)std::min(T.waves_per_cu, 16) : DEFAULT_WPC;

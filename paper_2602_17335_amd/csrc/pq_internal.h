@@ -322,8 +322,8 @@ struct SegTable {
   const Segment* ptr;  // n > MAX_SEGS: the segments in device memory, ascending in wg0
 };
 
-// Batched scans (several files, requests and columns in one launch): every
-// unit of work is a run of tiles of one column that one decoder handles.
+// Batched scans (several files, requests and columns in one launch) under a
+// schedule of work queues: every unit of work is a run of tiles of one column that one decoder handles.
 // The persistent kernel takes units from NQUEUE work queues, queue q first
 // for the workgroups dispatched to XCD q (workgroup i runs on XCD i mod 8),
 // then the others.

@@ -2322,7 +2322,8 @@ __global__ __launch_bounds__(WG) void k_decode_str(uint8_t* __restrict__ ws, con
 
 // ---------------------------------------------------------------------------
 // k_batch: the decode step of a batched scan (many files, requests and
-// columns) in one persistent launch.  Each wave takes units (a run of tiles
+// columns) under a schedule of work queues, in one persistent launch (the
+// default schedule decodes with k_decode_all).  Each wave takes units (a run of tiles
 // of one column with one decoder) from the work queues, its workgroup's home
 // queue first (queue i mod NQUEUE for workgroup i, the XCD it is dispatched
 // to), then the others in turn, and decodes their tiles one after the other
@@ -2347,8 +2348,8 @@ __device__ __forceinline__ void tile_required_validity(const WaveTile& c, uint32
   }
 }
 
-// k_decode_all: the decode step of a scan of few tiles in one launch, one wave
-// per tile: every kind's segments in one table (Segment::cs holds the decoder
+// k_decode_all: the decode step of a scan of few tiles, and of a batched scan
+// under the default schedule, in one launch, one wave per tile: every kind's segments in one table (Segment::cs holds the decoder
 // kind above SEG_KIND), the validity words of REQUIRED columns with the tiles
 // and, by one wave after them, offsets[rows] of the string columns (which[0,
 // nstr)).  What bounds such a scan is the latency of one tile (10-25 us) and of
