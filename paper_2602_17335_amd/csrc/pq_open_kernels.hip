@@ -1347,9 +1347,12 @@ __global__ __launch_bounds__(NT) void k_dl(const IxPage* ixs, const uint32_t* li
 //   k_seg_cand  where the chain from each of a segment's first 1,024 or 2,048 bytes
 //               leaves the segment;
 //   k_seg_link  the true chain's entry into every segment, one workgroup per
-//               page (the exits of 64 segments' first 64 bytes at a time in
-//               LDS); a page whose chain enters a segment past the candidates
-//               is left to the one-workgroup kernel;
+//               page, 64 segments at a time (the exits of their first 64 bytes in
+//               LDS): through 8 groups of 8 segments from every candidate side
+//               by side, from group to group, then through each group; where a
+//               chain leaves the candidates in LDS one thread follows it.  A page
+//               whose chain enters a segment past all candidates is left to the
+//               one-workgroup kernel;
 //   k_seg_fill  values (blocks) before every piece, within the segment;
 //   k_seg_base  values (blocks) before every segment;
 //   k_str_ck, k_dl_ck  string checkpoints and block positions, one thread per
@@ -1357,7 +1360,8 @@ __global__ __launch_bounds__(NT) void k_dl(const IxPage* ixs, const uint32_t* li
 // A segment's exits are found twice, so with a page for every CU the
 // one-workgroup kernels are faster; the choice is made on the host.
 // Measured on the 4M-row wide table in 1M-row row groups: four string dictionaries of
-// 17.7 MB 0.58 ms (k_strings 10.9 ms, 540 segments in a row at 20 us; candidate walks
+// 17.7 MB 0.45 ms (0.58 ms with one thread that links all segments of a page in
+// turn: k_seg_link 170, now 32 us; k_strings 10.9 ms, 540 segments in a row at 20 us; candidate walks
 // of 64 lanes per segment, a thread that links them and a second walk 1.2 ms),
 // the index streams of nine columns 0.38 ms (k_di 0.66 ms), one DELTA column 0.12 ms
 // (k_dl 0.53 ms).
@@ -1417,7 +1421,10 @@ template <int F>
 __global__ __launch_bounds__(256) void k_seg_link(const IxPage* ixs, const SegPage* sps, const PageDev* pages,
                                                   OpenBufs bufs, const uint32_t* exits, uint32_t* entry, uint32_t* seq,
                                                   const uint32_t* flag, const uint32_t* err) {
+  constexpr uint32_t NG = 8, GS = 8;  // groups of segments
+  constexpr uint32_t OUT = 0xff;      // not a candidate of the next segment's first 64 bytes
   __shared__ uint32_t s_ex[64][64];
+  __shared__ uint8_t s_next[64][64], s_grp[NG][64], s_ent[NG];
   __shared__ uint32_t s_pos;
   const SegPage sp = sps[blockIdx.x];
   for (uint32_t j = threadIdx.x; j < sp.nseg; j += 256) entry[sp.seg0 + j] = ~0u;
@@ -1430,11 +1437,58 @@ __global__ __launch_bounds__(256) void k_seg_link(const IxPage* ixs, const SegPa
   uint32_t pos = st.m;
   for (uint32_t b = 0; b < sp.nseg; b += 64) {
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < 64 * 64; i += 256)
-      if (b + i / 64 < sp.nseg) s_ex[i / 64][i % 64] = exits[(size_t)(sp.seg0 + b + i / 64) * SEG_CAND + i % 64];
+    uint32_t ex[64 * 64 / 256];
+#pragma unroll
+    for (uint32_t k = 0; k < 64 * 64 / 256; ++k) {
+      const uint32_t i = threadIdx.x + 256 * k;
+      ex[k] = b + i / 64 < sp.nseg ? exits[(size_t)(sp.seg0 + b + i / 64) * SEG_CAND + i % 64] : ~0u;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < 64 * 64 / 256; ++k) {
+      const uint32_t i = threadIdx.x + 256 * k, c = ex[k] - SEG_BYTES;
+      s_ex[i / 64][i % 64] = ex[k];
+      s_next[i / 64][i % 64] = (uint8_t)(ex[k] >= SEG_BYTES && c < 64 ? c : OUT);
+    }
+    if (threadIdx.x == 0) s_pos = pos;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t h = 0; h < NG * 64 / 256; ++h) {
+      const uint32_t i = threadIdx.x + 256 * h;
+      uint32_t x = i % 64;
+#pragma unroll
+      for (uint32_t k = 0; k < GS; ++k) x = x == OUT ? OUT : s_next[i / 64 * GS + k][x];
+      s_grp[i / 64][i % 64] = (uint8_t)x;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
-      uint32_t q = pos;
+      const uint32_t c = pos - b * SEG_BYTES;  // (pos is not before segment b)
+      uint32_t x = c < 64 && pos < iend ? c : OUT;
+#pragma unroll
+      for (uint32_t g = 0; g < NG; ++g) {
+        s_ent[g] = (uint8_t)x;
+        x = x == OUT ? OUT : s_grp[g][x];
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x < NG) {
+      const uint32_t g = threadIdx.x;
+      uint32_t x = s_ent[g];
+      if (x != OUT) {
+        for (uint32_t k = 0; k < GS; ++k) {
+          const uint32_t j = b + g * GS + k, q = j * SEG_BYTES + x;
+          x = q < iend ? s_next[g * GS + k][x] : OUT;
+          if (q < iend) entry[sp.seg0 + j] = q;
+          if (x == OUT) {  // (in one group at most: the entries of those after it are OUT)
+            s_pos = q;
+            break;
+          }
+          if (g * GS + k == 63) s_pos = (j + 1) * SEG_BYTES + x;
+        }
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t q = s_pos;
       while (q < iend && q / SEG_BYTES < b + 64) {
         const uint32_t j = q / SEG_BYTES, c = q % SEG_BYTES;
         if (c >= seg_cands<F>()) { seq[blockIdx.x] = 1; q = ~0u; break; }
