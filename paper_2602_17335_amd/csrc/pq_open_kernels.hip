@@ -3,6 +3,8 @@
 //   k_layout  stream layout of every page
 //   k_levels, k_strings, k_di, k_dl  the element chains of level streams, string
 //            lengths, dictionary-index runs and DELTA blocks (pq_chain.hpp)
+//   k_seg_cand, k_seg_link, k_seg_fill, k_seg_base, k_str_ck, k_dl_ck  the same for
+//            the segments of long value streams side by side
 //   k_tiles, k_values, k_value_tiles  tile entries and checkpoints from them
 //   k_index  the whole index of one page by one wave, for pages whose
 //            chains the kernels above leave (and to say what is wrong with

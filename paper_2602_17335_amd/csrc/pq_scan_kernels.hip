@@ -1,15 +1,19 @@
-// pq_scan_kernels.hip -- kernels of one scan (everything pq_scan enqueues),
-// and k_prepass, which pq_open_device runs once to build the tile prefix.
+// pq_scan_kernels.hip -- kernels of one scan (all that pq_scan enqueues but the
+// Snappy block and DELTA_BYTE_ARRAY kernels, which have files of their own), and
+// those of the open that build dictionaries and the tile prefix.
 //
 //   k_snappy        Snappy page bodies without a block index -> workspace (one wave per page)
 //   k_prep          validity edge words cleared / REQUIRED validity set to ones
 //   k_dict          dictionary pages -> device dictionaries
-//   k_decode_all    every kind of tile of a scan of few tiles in one launch
+//   k_decode_all    every kind of tile of a scan of few tiles, or of a batch, in one launch
+//   k_batch         the same from work queues, for batches under other schedules
 //   k_prepass       per-tile DELTA sums and string byte counts (at open)
+//   k_scan_sums, k_scan_prefix, k_pick  their prefix sums (at open)
 //   k_str_total     offsets[rows] and the chars capacity check of string columns
 //   k_decode_fixed  definition levels; PLAIN / dictionary INT32, INT64, DOUBLE values
 //   k_decode_delta  definition levels; DELTA_BINARY_PACKED INT32 / INT64 values
 //   k_decode_str    definition levels; PLAIN / dictionary BYTE_ARRAY values -> offsets and chars
+//   k_edges         the validity words that two tiles share
 //
 // The tile prefix (one uint64 per tile of the file, plus one) is the
 // exclusive prefix sum, in file tile order, of each tile's DELTA sum or

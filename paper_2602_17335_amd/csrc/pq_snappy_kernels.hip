@@ -80,10 +80,12 @@ __device__ __forceinline__ SnapSrc snap_src(const uint8_t* file, const PageDev& 
 // sequentially by k_snappy, which reports what is wrong.
 //
 // The chain is found in 32 KiB segments (pq_chain.hpp); every thread then
-// walks its piece's elements (at most 16): lengths, a prefix sum over the
-// pieces, the checks, the block starts and the start bits.
+// walks its piece's elements (at most 16): lengths, the output before the piece
+// that its copies need, a prefix sum over the pieces, the checks, the start bits,
+// and, in a piece where a block starts, the elements again for the block starts.
 // What bounds it: the dependent LDS reads of the chain's steps.  Measured on a
-// 2M-row wide table with 1 MiB pages: 0.97 ms; one wave per page that walks the
+// 2M-row wide table with 1 MiB pages: 1.03 ms (1.08 with every piece's
+// elements walked twice); one wave per page that walks the
 // tags from a staged window, 51.7 ms (0.2 us per element of the densest page).
 // ---------------------------------------------------------------------------
 constexpr uint32_t SX_WG = 1024;
@@ -135,11 +137,17 @@ __global__ __launch_bounds__(SX_WG) void k_snap_index(const ColScan* cols, SegTa
     // the piece's elements: lengths and start bits
     const uint32_t plen = L.piece_len(S, iend), y0 = tid * CH_PIECE;
     uint32_t mask = 0, sum = 0;
+    uint32_t reach = 0;  // output bytes before the piece's that its copies need
+    bool bad = false;
     for (uint32_t y = L.pent[tid]; y < plen;) {
       uint32_t lo, hi;
       L.bytes8(y0 + y, lo, hi);
       const SnapEl e = snap_el(lo, hi & 0xffu);
       mask |= 1u << y;
+      if (!e.lit) {
+        bad |= e.off == 0;
+        reach = max(reach, e.off > sum ? e.off - sum : 0u);
+      }
       sum += e.len;
       y += e.hl + (e.lit ? e.len : 0u);
     }
@@ -155,9 +163,11 @@ __global__ __launch_bounds__(SX_WG) void k_snap_index(const ColScan* cols, SegTa
       if (w < wave) o += v;
       tot += v;
     }
-    // checks and block starts
-    bool bad = false;
-    for (uint32_t m = mask; m; m &= m - 1) {
+    // checks and block starts: element by element where a block starts in the piece
+    const uint32_t ob0 = o & (SNAP_BLOCK - 1);
+    const bool starts = ob0 == 0 || sum > SNAP_BLOCK - ob0;
+    if (mask) bad |= o > total || sum > total - o || (!starts && reach > ob0);
+    for (uint32_t m = starts && !bad ? mask : 0u; m; m &= m - 1) {
       const uint32_t y = (uint32_t)__builtin_ctz(m);
       uint32_t lo, hi;
       L.bytes8(y0 + y, lo, hi);
