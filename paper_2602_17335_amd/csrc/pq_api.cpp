@@ -73,6 +73,7 @@ __global__ void k_index(const uint8_t* file, const uint8_t* scratch, PageDev* pa
                         Ck* ckv, uint32_t* err, uint64_t file_lim, uint64_t scratch_lim, const uint8_t* xscratch,
                         uint64_t xscratch_lim);
 __global__ void k_snappy(const ColScan* cols, SegTable seg, uint8_t* ws, int record, uint32_t* err);
+template <uint32_t OUT>
 __global__ void k_snappy_blk(const ColScan* cols, SegTable seg, uint8_t* ws, uint32_t* err, int dicts);
 __global__ void k_snap_index(const ColScan* cols, SegTable seg);
 __global__ void k_prep(const ColScan* cols, SegTable seg);
@@ -317,6 +318,7 @@ struct pq_file_s {
   std::vector<ChunkDev> chunks;          // col-major
   std::vector<uint32_t> chunk_page0;     // first page of each chunk (+ sentinel)
   std::vector<uint32_t> chunk_tile0;     // first tile of each chunk (+ sentinel)
+  std::vector<uint8_t> chunk_big;        // chunks with a compressed data page of more than SNAP_SMALL bytes
   std::vector<PageDev> pages;            // host copy (after the index pass)
   std::vector<uint64_t> scratch_prefix;  // per page (+ sentinel): file-wide scratch offset
   std::vector<uint64_t> xscratch_prefix; // per page (+ sentinel): expansion-layout offset (DELTA_BYTE_ARRAY pages)
@@ -593,6 +595,24 @@ static SegTable make_segs(const std::vector<Segment>& v, bool spread = false) {
 
 static pq_status build_dicts(pq_file f, const uint8_t* scratch, bool copy_all, hipStream_t s);
 
+// The Snappy blocks of a launch.  The small shape (blocks of at most SNAP_SMALL
+// bytes, 128 threads, 8 workgroups per CU) holds four times as many blocks on the
+// chip as the large one.  Scans of the 4M-row Snappy wide table, every column in
+// the large shape against columns of such pages in the small one: 4 KiB pages 2,281 ->
+// 1,474 us, 8 KiB 1,590 -> 1,133, 12 KiB 1,436 -> 1,009 (16 KiB pages, of a little
+// more than SNAP_SMALL bytes, take the large one: 1,290, 32 KiB 1,175).
+static void launch_sblk(uint32_t wgs, const SegTable& segs, bool big, const ColScan* cols, uint8_t* ws, uint32_t* err,
+                        int dicts, hipStream_t s) {
+  if (big) hipLaunchKernelGGL(k_snappy_blk<SNAP_BLOCK>, dim3(wgs), dim3(512), 0, s, cols, segs, ws, err, dicts);
+  else hipLaunchKernelGGL(k_snappy_blk<SNAP_SMALL>, dim3(wgs), dim3(128), 0, s, cols, segs, ws, err, dicts);
+}
+// Whether column c has a data page for the large shape in row groups [g0, g1).
+static bool snap_big(pq_file f, int c, int g0, int g1) {
+  for (int g = g0; g < g1; ++g)
+    if (f->chunk_big[(size_t)c * f->nrg + g]) return true;
+  return false;
+}
+
 // Chars bytes of column c over row groups [g0, g1).
 static int64_t chars_of(pq_file f, int c, int g0, int g1) {
   if (f->cols[(size_t)c].type != T_BYTE_ARRAY) return 0;
@@ -785,6 +805,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
 
   // ---- host layout: rows, dictionary links, tiles, scratch, checkpoints ----
   f->chunk_tile0.assign(nchunks + 1, 0);
+  f->chunk_big.assign(nchunks, 0);
   f->scratch_prefix.assign(npages + 1, 0);
   f->dba_unit0.assign(npages + 1, 0);
   uint64_t dba_units = 0;
@@ -812,6 +833,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       }
       pg.scratch_len = (uint32_t)slen;
       pg.sblk_begin = (uint32_t)sblk;
+      if (slen > SNAP_SMALL && pg.kind != PAGE_DICT) f->chunk_big[q] = 1;
       if (slen) {
         const uint64_t nb = (slen + SNAP_BLOCK - 1) / SNAP_BLOCK;
         for (uint64_t j = 0; j < nb; ++j) sblk_page.push_back(p);
@@ -1028,7 +1050,9 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       const uint32_t b0 = f->pages[P.p0].sblk_begin, b1 = P.p1 < npages ? f->pages[P.p1].sblk_begin : (uint32_t)sblk;
       if (b1 > b0) {
         std::vector<Segment> bsegs{Segment{0, b0, b1, 0}};
-        hipLaunchKernelGGL(k_snappy_blk, dim3(b1 - b0), dim3(512), 0, s, d_cs, make_segs(bsegs), d_scratch, f->d_err, 1);
+        bool big = P.dict;
+        for (uint32_t p : plist) big |= f->pages[p].scratch_len > SNAP_SMALL;
+        launch_sblk(b1 - b0, make_segs(bsegs), big, d_cs, d_scratch, f->d_err, 1, s);
       }
       hipLaunchKernelGGL(k_snappy, dim3(P.p1 - P.p0), dim3(64), 0, s, d_cs, st2, d_scratch, 1, f->d_err);
       if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_snappy launch failed"); }
@@ -1654,11 +1678,12 @@ struct Plan {
   std::vector<Segment> snappy_segs, prep_segs, fixed_segs[8], delta_segs, str_segs[2], edge_segs;
   std::vector<int32_t> str_cols;    // string ColScan indices (k_str_total)
   // units: pages (k_snappy), tiles (k_prep threads; one wave per tile elsewhere)
-  std::vector<Segment> sblk_segs;  // k_snappy_blk: blocks of the compressed pages, one workgroup each
+  std::vector<Segment> sblk_segs[2];  // k_snappy_blk: blocks of the compressed pages, one workgroup each
+                                      // ([1]: columns for its large shape)
   std::vector<Segment> dba_segs;   // k_dba: units of columns with DELTA_BYTE_ARRAY pages, one wave each
   uint32_t dba_waves = 0;
   bool dba_small = false, dba_big = false;
-  uint32_t sblk_wgs = 0;
+  uint32_t sblk_wgs[2] = {0, 0};
   bool str_spread[2] = {false, false}, fixed_spread[8] = {};  // columns interleaved wave by wave
   uint32_t snappy_waves = 0, prep_threads = 0, fixed_units[8] = {}, delta_units = 0, str_units[2] = {0, 0},
            edge_threads = 0;
@@ -1782,8 +1807,9 @@ pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& 
       P.snappy_segs.push_back(Segment{idx, cs.page_begin, cs.page_end, P.snappy_waves});
       P.snappy_waves += cs.page_end - cs.page_begin;
       if (k.b1 > k.b0) {
-        P.sblk_segs.push_back(Segment{idx, k.b0, k.b1, P.sblk_wgs});
-        P.sblk_wgs += k.b1 - k.b0;
+        const int big = snap_big(f, c, rg_b, rg_e);
+        P.sblk_segs[big].push_back(Segment{idx, k.b0, k.b1, P.sblk_wgs[big]});
+        P.sblk_wgs[big] += k.b1 - k.b0;
       }
     }
     if (k.xbytes) {
@@ -1878,7 +1904,7 @@ static void launch_dba(uint32_t units, const SegTable& segs, bool small, bool bi
 // d_cols).
 static pq_status enqueue_decompress(pq_file f, const Plan& P, const ColScan* d_cols, uint8_t* ws, uint32_t* err,
                                     hipStream_t s) {
-  for (const auto* v : {&P.snappy_segs, &P.sblk_segs, &P.dba_segs, &P.prep_segs, &P.fixed_segs[0], &P.fixed_segs[1], &P.fixed_segs[2],
+  for (const auto* v : {&P.snappy_segs, &P.sblk_segs[0], &P.sblk_segs[1], &P.dba_segs, &P.prep_segs, &P.fixed_segs[0], &P.fixed_segs[1], &P.fixed_segs[2],
                         &P.fixed_segs[3], &P.fixed_segs[4], &P.fixed_segs[6], &P.delta_segs, &P.str_segs[0], &P.str_segs[1],
                         &P.edge_segs})
     if (v->size() > MAX_SEGS) return fail(PQ_EUNSUPPORTED, "too many segments");
@@ -1887,9 +1913,10 @@ static pq_status enqueue_decompress(pq_file f, const Plan& P, const ColScan* d_c
     hipLaunchKernelGGL(k_snappy, dim3(P.snappy_waves), dim3(64), 0, s, d_cols, make_segs(P.snappy_segs), ws, 0, err);
     HIP_OR(hipGetLastError());
   }
-  if (P.sblk_wgs) {
+  for (int big = 1; big >= 0; --big) {
+    if (!P.sblk_wgs[big]) continue;
     ProfScope ps_(f, KP_SNAPPY_BLK, s);
-    hipLaunchKernelGGL(k_snappy_blk, dim3(P.sblk_wgs), dim3(512), 0, s, d_cols, make_segs(P.sblk_segs), ws, err, 0);
+    launch_sblk(P.sblk_wgs[big], make_segs(P.sblk_segs[big]), big != 0, d_cols, ws, err, 0, s);
     HIP_OR(hipGetLastError());
   }
   if (P.dba_waves) {  // DELTA_BYTE_ARRAY pages (after their decompression) to the PLAIN layout
@@ -2265,8 +2292,8 @@ struct BatchPlan {
   std::vector<ColScan> cols;
   std::vector<int32_t> str_cols;
   std::vector<int64_t> chars;  // per column, in request order
-  std::vector<Segment> snappy_segs, sblk_segs, edge_segs, prep_segs, dba_segs;
-  uint32_t snappy_waves = 0, sblk_wgs = 0, edge_threads = 0, prep_threads = 0, dba_waves = 0;
+  std::vector<Segment> snappy_segs, sblk_segs[2], edge_segs, prep_segs, dba_segs;  // (sblk_segs: as Plan's)
+  uint32_t snappy_waves = 0, sblk_wgs[2] = {0, 0}, edge_threads = 0, prep_threads = 0, dba_waves = 0;
   bool dba_small = false, dba_big = false;
   // same-kind tile runs: consecutive pages of one column with one decoder
   // and work class
@@ -2344,8 +2371,9 @@ pq_status make_batch_plan(const pq_request* reqs, int32_t n, BatchPlan& P) {
         P.snappy_segs.push_back(Segment{idx, cs.page_begin, cs.page_end, P.snappy_waves});
         P.snappy_waves += cs.page_end - cs.page_begin;
         if (k.b1 > k.b0) {
-          P.sblk_segs.push_back(Segment{idx, k.b0, k.b1, P.sblk_wgs});
-          P.sblk_wgs += k.b1 - k.b0;
+          const int big = snap_big(f, c, q.rg_begin, q.rg_end);
+          P.sblk_segs[big].push_back(Segment{idx, k.b0, k.b1, P.sblk_wgs[big]});
+          P.sblk_wgs[big] += k.b1 - k.b0;
         }
       }
       if (k.xbytes) {
@@ -2540,7 +2568,8 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
   put(P.ws_cols, P.cols.data(), sizeof(ColScan) * P.cols.size());
   put(P.ws_which, P.str_cols.data(), sizeof(int32_t) * P.str_cols.size());
   put(P.ws_snappy, P.snappy_segs.data(), sizeof(Segment) * P.snappy_segs.size());
-  put(P.ws_sblk, P.sblk_segs.data(), sizeof(Segment) * P.sblk_segs.size());
+  const uint64_t ws_sblk[2] = {P.ws_sblk, P.ws_sblk + sizeof(Segment) * P.sblk_segs[0].size()};
+  for (int b = 0; b < 2; ++b) put(ws_sblk[b], P.sblk_segs[b].data(), sizeof(Segment) * P.sblk_segs[b].size());
   put(P.ws_dba, P.dba_segs.data(), sizeof(Segment) * P.dba_segs.size());
   put(P.ws_edge, P.edge_segs.data(), sizeof(Segment) * P.edge_segs.size());
   put(P.ws_prep, P.prep_segs.data(), sizeof(Segment) * P.prep_segs.size());
@@ -2561,10 +2590,10 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
                          ws, 0, err);
       HIP_OR(hipGetLastError());
     }
-    if (P.sblk_wgs) {
+    for (int big = 1; big >= 0; --big) {
+      if (!P.sblk_wgs[big]) continue;
       ProfScope ps_(prof, KP_SNAPPY_BLK, s);
-      hipLaunchKernelGGL(k_snappy_blk, dim3(P.sblk_wgs), dim3(512), 0, s, d_cols,
-                         seg_table(P.sblk_segs, ws, P.ws_sblk), ws, err, 0);
+      launch_sblk(P.sblk_wgs[big], seg_table(P.sblk_segs[big], ws, ws_sblk[big]), big != 0, d_cols, ws, err, 0, s);
       HIP_OR(hipGetLastError());
     }
   } else {
@@ -2580,7 +2609,7 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
       if (sp.b1 > sp.b0) {
         ProfScope ps_(prof, KP_SNAPPY_BLK, s);
         std::vector<Segment> one{Segment{sp.cs, sp.b0, sp.b1, 0}};
-        hipLaunchKernelGGL(k_snappy_blk, dim3(sp.b1 - sp.b0), dim3(512), 0, s, d_cols, make_segs(one), ws, err, 0);
+        launch_sblk(sp.b1 - sp.b0, make_segs(one), true, d_cols, ws, err, 0, s);
         HIP_OR(hipGetLastError());
       }
     }

@@ -218,11 +218,19 @@ __global__ __launch_bounds__(SX_WG) void k_snap_index(const ColScan* cols, SegTa
 // 8 elements in flight together 10.8 ms, its densest block's 2,100 round trips,
 // however few the blocks.
 // ---------------------------------------------------------------------------
-constexpr uint32_t SB_WG = 512;
 constexpr uint32_t SB_BYTES = 16;  // stream bytes per thread and pass
-constexpr uint32_t SB_PASS = SB_WG * SB_BYTES;
-constexpr uint32_t SB_LIST = 944;  // copies done side by side: what the LDS of two workgroups per CU leaves
-static_assert(SB_LIST <= 2 * SB_WG, "a thread takes at most two copies of the list");
+// The shape for blocks of at most OUT output bytes: threads, and copies done side by
+// side (what the LDS of 2 and of 8 workgroups per CU leaves).
+template <uint32_t OUT>
+struct SbShape {
+  static constexpr uint32_t WG = 512, LIST = 944;
+};
+// A page of a few KiB is one or two of the large shape's passes, and two such
+// workgroups hold a CU.
+template <>
+struct SbShape<SNAP_SMALL> {
+  static constexpr uint32_t WG = 128, LIST = 240;
+};
 constexpr int SB_EL = SB_BYTES / 2;  // elements starting in a thread's bytes (each takes two or more)
 
 // Bits [a, a + n) of the pending map, n <= 64: whether any is set.
@@ -282,10 +290,13 @@ __device__ __forceinline__ void snap_copy(lds_u8* out, uint32_t o, uint32_t s, u
 }
 
 // dicts = 1 (open): dictionary pages too.
-__global__ __launch_bounds__(SB_WG, 4) void k_snappy_blk(const ColScan* cols, SegTable seg, uint8_t* ws, uint32_t* err,
-                                                         int dicts) {
-  __shared__ __align__(16) uint32_t s_out[SNAP_BLOCK / 4 + 4];  // (reads run up to 10 bytes past a source)
-  __shared__ uint32_t s_pend[SNAP_BLOCK / 32 + 2];
+template <uint32_t OUT>
+__global__ __launch_bounds__(SbShape<OUT>::WG, 4) void k_snappy_blk(const ColScan* cols, SegTable seg, uint8_t* ws,
+                                                                    uint32_t* err, int dicts) {
+  constexpr uint32_t SB_WG = SbShape<OUT>::WG, SB_LIST = SbShape<OUT>::LIST, SB_PASS = SB_WG * SB_BYTES;
+  static_assert(SB_LIST <= 2 * SB_WG, "a thread takes at most two copies of the list");
+  __shared__ __align__(16) uint32_t s_out[OUT / 4 + 4];  // (reads run up to 10 bytes past a source)
+  __shared__ uint32_t s_pend[OUT / 32 + 2];
   __shared__ u32x2s s_list[SB_LIST];
   __shared__ __align__(16) uint32_t s_x[2][SB_WG / 64][4];
   const Segment sg = seg_lookup(seg, blockIdx.x);
@@ -312,7 +323,11 @@ __global__ __launch_bounds__(SB_WG, 4) void k_snappy_blk(const ColScan* cols, Se
   const uint32_t blen = min(SNAP_BLOCK, total - kb * SNAP_BLOCK);
   const uint32_t q0 = src.m + i0, qe = src.m + i1;
   lds_u8* out = (lds_u8*)&s_out[0];
-  for (uint32_t i = tid; i < SNAP_BLOCK / 32 + 2; i += SB_WG) s_pend[i] = 0;
+  if (blen > OUT) {  // (the launch's pages are smaller)
+    if (tid == 0) set_err(err, ERR_SNAPPY, p);
+    return;
+  }
+  for (uint32_t i = tid; i < OUT / 32 + 2; i += SB_WG) s_pend[i] = 0;
 
   uint32_t A = q0 & ~15u;  // stream position of the pass
   u32x4s nw = {0u, 0u, 0u, 0u};
@@ -434,7 +449,7 @@ __global__ __launch_bounds__(SB_WG, 4) void k_snappy_blk(const ColScan* cols, Se
       if (__ballot(litm != 0xffffu || mask) == 0) {
         // 16 bytes of one literal in every lane: aligned dwords, and bytes at
         // the ends
-        const uint32_t D = dk[0] & (SNAP_BLOCK - 1), r = D & 3;
+        const uint32_t D = dk[0] & (OUT - 1), r = D & 3;
         lds_u32* o32 = (lds_u32*)out + (D >> 2);
         if (__ballot(r) == 0) {
           o32[0] = w0; o32[1] = w1; o32[2] = w2; o32[3] = w3;
@@ -458,7 +473,7 @@ __global__ __launch_bounds__(SB_WG, 4) void k_snappy_blk(const ColScan* cols, Se
 #pragma unroll
         for (uint32_t k = 0; k < SB_BYTES; ++k) {
           const uint32_t w = k < 4 ? w0 : k < 8 ? w1 : k < 12 ? w2 : w3;
-          if ((litm >> k) & 1u) out[(dk[k] + k) & (SNAP_BLOCK - 1)] = (uint8_t)(w >> (8 * (k & 3)));
+          if ((litm >> k) & 1u) out[(dk[k] + k) & (OUT - 1)] = (uint8_t)(w >> (8 * (k & 3)));
         }
       }
     }
@@ -534,5 +549,8 @@ __global__ __launch_bounds__(SB_WG, 4) void k_snappy_blk(const ColScan* cols, Se
   if (op != blen) bad = true;
   if (bad) set_err(err, ERR_SNAPPY, p);
 }
+
+template __global__ void k_snappy_blk<SNAP_SMALL>(const ColScan*, SegTable, uint8_t*, uint32_t*, int);
+template __global__ void k_snappy_blk<SNAP_BLOCK>(const ColScan*, SegTable, uint8_t*, uint32_t*, int);
 
 }  // namespace pqk
