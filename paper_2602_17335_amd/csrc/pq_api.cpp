@@ -600,7 +600,22 @@ static pq_status build_dicts(pq_file f, const uint8_t* scratch, bool copy_all, h
 // chip as the large one.  Scans of the 4M-row Snappy wide table, every column in
 // the large shape against columns of such pages in the small one: 4 KiB pages 2,281 ->
 // 1,474 us, 8 KiB 1,590 -> 1,133, 12 KiB 1,436 -> 1,009 (16 KiB pages, of a little
-// more than SNAP_SMALL bytes, take the large one: 1,290, 32 KiB 1,175).
+// more than SNAP_SMALL bytes, take the large one: 1,290, 32 KiB 1,175), about 12 ns
+// a block.  Its launch takes some 75 us of its own (64 files in one batch with few small
+// pages: 478 us all in the large shape, 551 us in two launches), so it is for SNAP_SMALL_MIN
+// blocks or more.
+constexpr uint32_t SNAP_SMALL_MIN = 8192;
+static void join_small(std::vector<Segment> (&segs)[2], uint32_t (&wgs)[2]) {
+  if (wgs[0] >= SNAP_SMALL_MIN) return;
+  segs[1].insert(segs[1].end(), segs[0].begin(), segs[0].end());
+  std::sort(segs[1].begin(), segs[1].end(), [](const Segment& a, const Segment& b) { return a.cs < b.cs; });
+  segs[0].clear();
+  wgs[0] = wgs[1] = 0;
+  for (Segment& sg : segs[1]) {
+    sg.wg0 = wgs[1];
+    wgs[1] += sg.t1 - sg.t0;
+  }
+}
 static void launch_sblk(uint32_t wgs, const SegTable& segs, bool big, const ColScan* cols, uint8_t* ws, uint32_t* err,
                         int dicts, hipStream_t s) {
   if (big) hipLaunchKernelGGL(k_snappy_blk<SNAP_BLOCK>, dim3(wgs), dim3(512), 0, s, cols, segs, ws, err, dicts);
@@ -1050,7 +1065,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       const uint32_t b0 = f->pages[P.p0].sblk_begin, b1 = P.p1 < npages ? f->pages[P.p1].sblk_begin : (uint32_t)sblk;
       if (b1 > b0) {
         std::vector<Segment> bsegs{Segment{0, b0, b1, 0}};
-        bool big = P.dict;
+        bool big = P.dict || b1 - b0 < SNAP_SMALL_MIN;
         for (uint32_t p : plist) big |= f->pages[p].scratch_len > SNAP_SMALL;
         launch_sblk(b1 - b0, make_segs(bsegs), big, d_cs, d_scratch, f->d_err, 1, s);
       }
@@ -1840,6 +1855,7 @@ pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& 
     P.str_spread[k] = true;
     P.str_units[k] = (uint32_t)P.str_segs[k].size() * most;
   }
+  join_small(P.sblk_segs, P.sblk_wgs);
   if (f->host && !P.cols.empty()) {
     uint64_t most = 0;
     for (int g = rg_b; g < rg_e; ++g) {
@@ -2417,6 +2433,7 @@ pq_status make_batch_plan(const pq_request* reqs, int32_t n, BatchPlan& P) {
       P.cols.push_back(cs);
     }
   }
+  join_small(P.sblk_segs, P.sblk_wgs);
   P.ws_total = std::max<uint64_t>(off, 256);
   return PQ_OK;
 }
