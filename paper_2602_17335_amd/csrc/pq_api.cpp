@@ -871,7 +871,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       pg.dict_page = dict;
       pg.row0 = row;
       row += pg.num_values;
-      // (its values are at most its rows)
+      // (k_dba refuses a page of more values than rows before any unit is written)
       if (cd.type == T_BYTE_ARRAY && pg.encoding == E_DBA) dba_units += ((uint64_t)pg.num_values + DBA_UNIT - 1) / DBA_UNIT;
       pg.tile_begin = (uint32_t)tiles;
       tiles += ((uint64_t)pg.num_values + TILE_ROWS - 1) / TILE_ROWS;

@@ -181,9 +181,9 @@ __device__ __forceinline__ void lane_lds_copy(lds_u8* dst, const lds_u32* src32,
 // k_dba, one wave per page (modes 0, 1: open) or per unit (mode 2: scans):
 //   mode 0 finds the page's value stream (as the index pass does) and the
 //     start of its second stream and of the suffix bytes, checks every
-//     prefix against the previous value's length, and stores the page's facts
-//     in pages_out (x_src, x_len, x_sfx, x_chars, xlen, x_total, x_scratch,
-//     x_ctx);
+//     prefix against the previous value's length and the value count against
+//     the page's rows, and stores the page's facts in pages_out (x_src, x_len,
+//     x_sfx, x_chars, xlen, x_total, x_scratch, x_ctx);
 //   mode 1 expands a page from its start and records its units;
 //   mode 2 expands one unit from its record: k_dba<true> the units of pages
 //     whose values are at most DBA_SMALL bytes (8 KiB of LDS: 16 waves per
@@ -312,6 +312,9 @@ __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, 
     }
     if (!code && ((uint64_t)chars + sfx_sum > vl || sum >= 0x80000000ull)) code = ERR_STRING;
     if (code == ERR_UNSUPPORTED) { if (lane == 0) pages_out[p].x_total = DBA_UNSUPPORTED; return; }
+    // the units and the bytes they keep are reserved by the page's rows: a
+    // stream of more values would have mode 1 write past them
+    if (!code && P.total > (uint32_t)pg.num_values) code = ERR_VALUES;
     if (code) { if (lane == 0) set_err(err, code, p); return; }
     for (int m = 32; m; m >>= 1) maxlen = max(maxlen, (uint32_t)__shfl_xor((int)maxlen, m));
     if (lane == 0) {
