@@ -207,7 +207,12 @@ __global__ __launch_bounds__(SX_WG) void k_snap_index(const ColScan* cols, SegTa
 //     are performed in order, a copy's bytes before its bits are cleared, and
 //     the first pending copy never waits.
 // Consecutive copies of one thread with the same offset of at most 64 (runs)
-// share one source, the bytes before the first of them.
+// share one source, the bytes before the first of them.  A copy whose source
+// lies within the thread's last copy takes that one's source instead: in a
+// column of sorted values every value copies most bytes of the value before it,
+// a chain as long as the page whose every link waits for the one before (a
+// sorted INT64 column of 31,000 pages of 4 KiB: 1,860 us, with the links between a
+// thread's four copies taken out 763; one lane per page, element by element, 723).
 // What bounds it: the rounds of copies of copies (up to 220 deep in a block
 // of the wide table, a few in most) and, in blocks of literals, the LDS byte
 // stores and the stream loads in flight.
@@ -481,17 +486,26 @@ __global__ __launch_bounds__(SbShape<OUT>::WG, 4) void k_snappy_blk(const ColSca
     for (uint32_t base = 0; base < ncopy; base += SB_LIST) {
       {
         uint32_t o = opb, poff = 0, rs = 0, c = copyb - base;
+        uint32_t po = 0, pn = 0, ps = 0;  // the thread's last copy without a period: output position, bytes, source
 #pragma unroll
         for (int j = 0; j < SB_EL; ++j) {
           const uint32_t off = ei[j] & 0xffffu, n = el[j];
           if (off) {
             if (off != poff || off > 64) rs = o;  // the run of copies with this offset starts here
             const bool wrap = o + n - rs > off;   // the source would reach past the run's start
-            const uint32_t src_o = wrap ? rs - off : o - off;
+            uint32_t src_o = wrap ? rs - off : o - off;
+            // bytes of the copy before: from where that one takes them
+            if (!wrap && src_o - po < pn && src_o - po + n <= pn) src_o = ps + (src_o - po);
+            po = o;
+            ps = src_o;
+            pn = wrap ? 0u : n;
             if (off > rs) bad = true;
             else if (c < SB_LIST)
               s_list[c] = u32x2s{o | (src_o << 16), n | (wrap ? (off << 8) | (((o - rs) % off) << 16) : 0u)};
-            if (off > rs && c < SB_LIST) s_list[c] = u32x2s{0u, 0u};
+            if (off > rs) {
+              pn = 0;
+              if (c < SB_LIST) s_list[c] = u32x2s{0u, 0u};
+            }
             ++c;
           }
           poff = off;
