@@ -318,7 +318,7 @@ struct pq_file_s {
   std::vector<ChunkDev> chunks;          // col-major
   std::vector<uint32_t> chunk_page0;     // first page of each chunk (+ sentinel)
   std::vector<uint32_t> chunk_tile0;     // first tile of each chunk (+ sentinel)
-  std::vector<uint8_t> chunk_big;        // chunks with a compressed data page of more than SNAP_SMALL bytes
+  std::vector<uint8_t> chunk_shape;      // k_snappy_blk's shape for the chunk's largest compressed data page
   std::vector<PageDev> pages;            // host copy (after the index pass)
   std::vector<uint64_t> scratch_prefix;  // per page (+ sentinel): file-wide scratch offset
   std::vector<uint64_t> xscratch_prefix; // per page (+ sentinel): expansion-layout offset (DELTA_BYTE_ARRAY pages)
@@ -595,37 +595,62 @@ static SegTable make_segs(const std::vector<Segment>& v, bool spread = false) {
 
 static pq_status build_dicts(pq_file f, const uint8_t* scratch, bool copy_all, hipStream_t s);
 
-// The Snappy blocks of a launch.  The small shape (blocks of at most SNAP_SMALL
-// bytes, 128 threads, 8 workgroups per CU) holds four times as many blocks on the
-// chip as the large one.  Scans of the 4M-row Snappy wide table, every column in
-// the large shape against columns of such pages in the small one: 4 KiB pages 2,281 ->
-// 1,474 us, 8 KiB 1,590 -> 1,133, 12 KiB 1,436 -> 1,009 (16 KiB pages, of a little
-// more than SNAP_SMALL bytes, take the large one: 1,290, 32 KiB 1,175), about 12 ns
-// a block.  Its launch takes some 75 us of its own (64 files in one batch with few small
-// pages: 478 us all in the large shape, 551 us in two launches), so it is for SNAP_SMALL_MIN
-// blocks or more.
+// The Snappy blocks of a scan's columns, by the shape of k_snappy_blk that holds
+// a column's largest page: blocks of up to 8 KiB by one wave, of up to 16 KiB by two
+// (15 and 8 workgroups per CU), larger ones by eight (two per CU).  Scans of 16
+// columns, us in k_snappy_blk with every column in the large shape / in the middle
+// one / by this rule: 75,500 pages of 4 KiB 909 / 581 / 440; 216,400 pages of 4 KiB
+// (a sorted column among them) - / 1,948 / 1,464; 37,700 pages of a little over 8 KiB
+// - / 491 / 491.  A launch takes some 75 us of its own (64 files in one batch with few
+// small pages: 478 us in the large shape, 551 us in two launches), so a small shape is
+// for SNAP_SMALL_MIN blocks or more.
 constexpr uint32_t SNAP_SMALL_MIN = 8192;
-static void join_small(std::vector<Segment> (&segs)[2], uint32_t (&wgs)[2]) {
-  if (wgs[0] >= SNAP_SMALL_MIN) return;
-  segs[1].insert(segs[1].end(), segs[0].begin(), segs[0].end());
-  std::sort(segs[1].begin(), segs[1].end(), [](const Segment& a, const Segment& b) { return a.cs < b.cs; });
-  segs[0].clear();
-  wgs[0] = wgs[1] = 0;
-  for (Segment& sg : segs[1]) {
-    sg.wg0 = wgs[1];
-    wgs[1] += sg.t1 - sg.t0;
+struct SnapLists {
+  std::vector<Segment> segs[SNAP_SHAPES];
+  uint32_t wgs[SNAP_SHAPES] = {};
+  void add(int shape, uint32_t cs, uint32_t b0, uint32_t b1) {
+    segs[shape].push_back(Segment{cs, b0, b1, wgs[shape]});
+    wgs[shape] += b1 - b0;
+  }
+  // shape k's blocks to shape k + 1
+  void move_up(int k) {
+    std::vector<Segment>& v = segs[k + 1];
+    v.insert(v.end(), segs[k].begin(), segs[k].end());
+    std::sort(v.begin(), v.end(), [](const Segment& a, const Segment& b) { return a.cs < b.cs; });
+    segs[k].clear();
+    wgs[k] = wgs[k + 1] = 0;
+    for (Segment& sg : v) {
+      sg.wg0 = wgs[k + 1];
+      wgs[k + 1] += sg.t1 - sg.t0;
+    }
+  }
+  // a list of too few blocks takes those of the shape below or, if these are too
+  // few as well, goes to the shape above
+  void join() {
+    for (int k = 0; k + 1 < SNAP_SHAPES; ++k) {
+      if (wgs[k] == 0 || wgs[k] >= SNAP_SMALL_MIN) continue;
+      move_up(k && wgs[k - 1] ? k - 1 : k);
+    }
+  }
+};
+static void launch_sblk(uint32_t wgs, const SegTable& segs, int shape, const ColScan* cols, uint8_t* ws, uint32_t* err,
+                        int dicts, hipStream_t s) {
+  switch (shape) {
+    case 0: hipLaunchKernelGGL(k_snappy_blk<SNAP_SHAPE[0]>, dim3(wgs), dim3(64), 0, s, cols, segs, ws, err, dicts); break;
+    case 1: hipLaunchKernelGGL(k_snappy_blk<SNAP_SHAPE[1]>, dim3(wgs), dim3(128), 0, s, cols, segs, ws, err, dicts); break;
+    default: hipLaunchKernelGGL(k_snappy_blk<SNAP_SHAPE[2]>, dim3(wgs), dim3(512), 0, s, cols, segs, ws, err, dicts);
   }
 }
-static void launch_sblk(uint32_t wgs, const SegTable& segs, bool big, const ColScan* cols, uint8_t* ws, uint32_t* err,
-                        int dicts, hipStream_t s) {
-  if (big) hipLaunchKernelGGL(k_snappy_blk<SNAP_BLOCK>, dim3(wgs), dim3(512), 0, s, cols, segs, ws, err, dicts);
-  else hipLaunchKernelGGL(k_snappy_blk<SNAP_SMALL>, dim3(wgs), dim3(128), 0, s, cols, segs, ws, err, dicts);
+static int snap_shape(uint64_t page_bytes) {
+  int k = 0;
+  while (k + 1 < SNAP_SHAPES && page_bytes > SNAP_SHAPE[k]) ++k;
+  return k;
 }
-// Whether column c has a data page for the large shape in row groups [g0, g1).
-static bool snap_big(pq_file f, int c, int g0, int g1) {
-  for (int g = g0; g < g1; ++g)
-    if (f->chunk_big[(size_t)c * f->nrg + g]) return true;
-  return false;
+// The shape for the data pages of column c in row groups [g0, g1).
+static int snap_shape(pq_file f, int c, int g0, int g1) {
+  int k = 0;
+  for (int g = g0; g < g1; ++g) k = std::max(k, (int)f->chunk_shape[(size_t)c * f->nrg + g]);
+  return k;
 }
 
 // Chars bytes of column c over row groups [g0, g1).
@@ -820,7 +845,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
 
   // ---- host layout: rows, dictionary links, tiles, scratch, checkpoints ----
   f->chunk_tile0.assign(nchunks + 1, 0);
-  f->chunk_big.assign(nchunks, 0);
+  f->chunk_shape.assign(nchunks, 0);
   f->scratch_prefix.assign(npages + 1, 0);
   f->dba_unit0.assign(npages + 1, 0);
   uint64_t dba_units = 0;
@@ -848,7 +873,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       }
       pg.scratch_len = (uint32_t)slen;
       pg.sblk_begin = (uint32_t)sblk;
-      if (slen > SNAP_SMALL && pg.kind != PAGE_DICT) f->chunk_big[q] = 1;
+      if (pg.kind != PAGE_DICT) f->chunk_shape[q] = (uint8_t)std::max((int)f->chunk_shape[q], snap_shape(slen));
       if (slen) {
         const uint64_t nb = (slen + SNAP_BLOCK - 1) / SNAP_BLOCK;
         for (uint64_t j = 0; j < nb; ++j) sblk_page.push_back(p);
@@ -1065,9 +1090,9 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       const uint32_t b0 = f->pages[P.p0].sblk_begin, b1 = P.p1 < npages ? f->pages[P.p1].sblk_begin : (uint32_t)sblk;
       if (b1 > b0) {
         std::vector<Segment> bsegs{Segment{0, b0, b1, 0}};
-        bool big = P.dict || b1 - b0 < SNAP_SMALL_MIN;
-        for (uint32_t p : plist) big |= f->pages[p].scratch_len > SNAP_SMALL;
-        launch_sblk(b1 - b0, make_segs(bsegs), big, d_cs, d_scratch, f->d_err, 1, s);
+        int shape = P.dict || b1 - b0 < SNAP_SMALL_MIN ? SNAP_SHAPES - 1 : 0;
+        for (uint32_t p : plist) shape = std::max(shape, snap_shape(f->pages[p].scratch_len));
+        launch_sblk(b1 - b0, make_segs(bsegs), shape, d_cs, d_scratch, f->d_err, 1, s);
       }
       hipLaunchKernelGGL(k_snappy, dim3(P.p1 - P.p0), dim3(64), 0, s, d_cs, st2, d_scratch, 1, f->d_err);
       if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_snappy launch failed"); }
@@ -1693,12 +1718,10 @@ struct Plan {
   std::vector<Segment> snappy_segs, prep_segs, fixed_segs[8], delta_segs, str_segs[2], edge_segs;
   std::vector<int32_t> str_cols;    // string ColScan indices (k_str_total)
   // units: pages (k_snappy), tiles (k_prep threads; one wave per tile elsewhere)
-  std::vector<Segment> sblk_segs[2];  // k_snappy_blk: blocks of the compressed pages, one workgroup each
-                                      // ([1]: columns for its large shape)
+  SnapLists sblk;                  // k_snappy_blk: blocks of the compressed pages, one workgroup each
   std::vector<Segment> dba_segs;   // k_dba: units of columns with DELTA_BYTE_ARRAY pages, one wave each
   uint32_t dba_waves = 0;
   bool dba_small = false, dba_big = false;
-  uint32_t sblk_wgs[2] = {0, 0};
   bool str_spread[2] = {false, false}, fixed_spread[8] = {};  // columns interleaved wave by wave
   uint32_t snappy_waves = 0, prep_threads = 0, fixed_units[8] = {}, delta_units = 0, str_units[2] = {0, 0},
            edge_threads = 0;
@@ -1821,11 +1844,7 @@ pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& 
     if (k.sbytes) {
       P.snappy_segs.push_back(Segment{idx, cs.page_begin, cs.page_end, P.snappy_waves});
       P.snappy_waves += cs.page_end - cs.page_begin;
-      if (k.b1 > k.b0) {
-        const int big = snap_big(f, c, rg_b, rg_e);
-        P.sblk_segs[big].push_back(Segment{idx, k.b0, k.b1, P.sblk_wgs[big]});
-        P.sblk_wgs[big] += k.b1 - k.b0;
-      }
+      if (k.b1 > k.b0) P.sblk.add(snap_shape(f, c, rg_b, rg_e), idx, k.b0, k.b1);
     }
     if (k.xbytes) {
       const uint32_t u0 = f->dba_unit0[cs.page_begin], u1 = f->dba_unit0[cs.page_end];
@@ -1855,7 +1874,7 @@ pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& 
     P.str_spread[k] = true;
     P.str_units[k] = (uint32_t)P.str_segs[k].size() * most;
   }
-  join_small(P.sblk_segs, P.sblk_wgs);
+  P.sblk.join();
   if (f->host && !P.cols.empty()) {
     uint64_t most = 0;
     for (int g = rg_b; g < rg_e; ++g) {
@@ -1920,7 +1939,7 @@ static void launch_dba(uint32_t units, const SegTable& segs, bool small, bool bi
 // d_cols).
 static pq_status enqueue_decompress(pq_file f, const Plan& P, const ColScan* d_cols, uint8_t* ws, uint32_t* err,
                                     hipStream_t s) {
-  for (const auto* v : {&P.snappy_segs, &P.sblk_segs[0], &P.sblk_segs[1], &P.dba_segs, &P.prep_segs, &P.fixed_segs[0], &P.fixed_segs[1], &P.fixed_segs[2],
+  for (const auto* v : {&P.snappy_segs, &P.sblk.segs[0], &P.sblk.segs[1], &P.sblk.segs[2], &P.dba_segs, &P.prep_segs, &P.fixed_segs[0], &P.fixed_segs[1], &P.fixed_segs[2],
                         &P.fixed_segs[3], &P.fixed_segs[4], &P.fixed_segs[6], &P.delta_segs, &P.str_segs[0], &P.str_segs[1],
                         &P.edge_segs})
     if (v->size() > MAX_SEGS) return fail(PQ_EUNSUPPORTED, "too many segments");
@@ -1929,10 +1948,10 @@ static pq_status enqueue_decompress(pq_file f, const Plan& P, const ColScan* d_c
     hipLaunchKernelGGL(k_snappy, dim3(P.snappy_waves), dim3(64), 0, s, d_cols, make_segs(P.snappy_segs), ws, 0, err);
     HIP_OR(hipGetLastError());
   }
-  for (int big = 1; big >= 0; --big) {
-    if (!P.sblk_wgs[big]) continue;
+  for (int k = SNAP_SHAPES; k-- > 0;) {
+    if (!P.sblk.wgs[k]) continue;
     ProfScope ps_(f, KP_SNAPPY_BLK, s);
-    launch_sblk(P.sblk_wgs[big], make_segs(P.sblk_segs[big]), big != 0, d_cols, ws, err, 0, s);
+    launch_sblk(P.sblk.wgs[k], make_segs(P.sblk.segs[k]), k, d_cols, ws, err, 0, s);
     HIP_OR(hipGetLastError());
   }
   if (P.dba_waves) {  // DELTA_BYTE_ARRAY pages (after their decompression) to the PLAIN layout
@@ -2308,8 +2327,9 @@ struct BatchPlan {
   std::vector<ColScan> cols;
   std::vector<int32_t> str_cols;
   std::vector<int64_t> chars;  // per column, in request order
-  std::vector<Segment> snappy_segs, sblk_segs[2], edge_segs, prep_segs, dba_segs;  // (sblk_segs: as Plan's)
-  uint32_t snappy_waves = 0, sblk_wgs[2] = {0, 0}, edge_threads = 0, prep_threads = 0, dba_waves = 0;
+  std::vector<Segment> snappy_segs, edge_segs, prep_segs, dba_segs;
+  SnapLists sblk;
+  uint32_t snappy_waves = 0, edge_threads = 0, prep_threads = 0, dba_waves = 0;
   bool dba_small = false, dba_big = false;
   // same-kind tile runs: consecutive pages of one column with one decoder
   // and work class
@@ -2386,11 +2406,7 @@ pq_status make_batch_plan(const pq_request* reqs, int32_t n, BatchPlan& P) {
       if (k.sbytes) {
         P.snappy_segs.push_back(Segment{idx, cs.page_begin, cs.page_end, P.snappy_waves});
         P.snappy_waves += cs.page_end - cs.page_begin;
-        if (k.b1 > k.b0) {
-          const int big = snap_big(f, c, q.rg_begin, q.rg_end);
-          P.sblk_segs[big].push_back(Segment{idx, k.b0, k.b1, P.sblk_wgs[big]});
-          P.sblk_wgs[big] += k.b1 - k.b0;
-        }
+        if (k.b1 > k.b0) P.sblk.add(snap_shape(f, c, q.rg_begin, q.rg_end), idx, k.b0, k.b1);
       }
       if (k.xbytes) {
         const uint32_t u0 = f->dba_unit0[cs.page_begin], u1 = f->dba_unit0[cs.page_end];
@@ -2433,7 +2449,7 @@ pq_status make_batch_plan(const pq_request* reqs, int32_t n, BatchPlan& P) {
       P.cols.push_back(cs);
     }
   }
-  join_small(P.sblk_segs, P.sblk_wgs);
+  P.sblk.join();
   P.ws_total = std::max<uint64_t>(off, 256);
   return PQ_OK;
 }
@@ -2585,8 +2601,11 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
   put(P.ws_cols, P.cols.data(), sizeof(ColScan) * P.cols.size());
   put(P.ws_which, P.str_cols.data(), sizeof(int32_t) * P.str_cols.size());
   put(P.ws_snappy, P.snappy_segs.data(), sizeof(Segment) * P.snappy_segs.size());
-  const uint64_t ws_sblk[2] = {P.ws_sblk, P.ws_sblk + sizeof(Segment) * P.sblk_segs[0].size()};
-  for (int b = 0; b < 2; ++b) put(ws_sblk[b], P.sblk_segs[b].data(), sizeof(Segment) * P.sblk_segs[b].size());
+  uint64_t ws_sblk[SNAP_SHAPES];
+  for (int k = 0; k < SNAP_SHAPES; ++k) {
+    ws_sblk[k] = k ? ws_sblk[k - 1] + sizeof(Segment) * P.sblk.segs[k - 1].size() : P.ws_sblk;
+    put(ws_sblk[k], P.sblk.segs[k].data(), sizeof(Segment) * P.sblk.segs[k].size());
+  }
   put(P.ws_dba, P.dba_segs.data(), sizeof(Segment) * P.dba_segs.size());
   put(P.ws_edge, P.edge_segs.data(), sizeof(Segment) * P.edge_segs.size());
   put(P.ws_prep, P.prep_segs.data(), sizeof(Segment) * P.prep_segs.size());
@@ -2607,10 +2626,10 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
                          ws, 0, err);
       HIP_OR(hipGetLastError());
     }
-    for (int big = 1; big >= 0; --big) {
-      if (!P.sblk_wgs[big]) continue;
+    for (int k = SNAP_SHAPES; k-- > 0;) {
+      if (!P.sblk.wgs[k]) continue;
       ProfScope ps_(prof, KP_SNAPPY_BLK, s);
-      launch_sblk(P.sblk_wgs[big], seg_table(P.sblk_segs[big], ws, ws_sblk[big]), big != 0, d_cols, ws, err, 0, s);
+      launch_sblk(P.sblk.wgs[k], seg_table(P.sblk.segs[k], ws, ws_sblk[k]), k, d_cols, ws, err, 0, s);
       HIP_OR(hipGetLastError());
     }
   } else {
@@ -2626,7 +2645,7 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
       if (sp.b1 > sp.b0) {
         ProfScope ps_(prof, KP_SNAPPY_BLK, s);
         std::vector<Segment> one{Segment{sp.cs, sp.b0, sp.b1, 0}};
-        launch_sblk(sp.b1 - sp.b0, make_segs(one), true, d_cols, ws, err, 0, s);
+        launch_sblk(sp.b1 - sp.b0, make_segs(one), SNAP_SHAPES - 1, d_cols, ws, err, 0, s);
         HIP_OR(hipGetLastError());
       }
     }

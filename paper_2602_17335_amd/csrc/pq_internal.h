@@ -202,8 +202,9 @@ constexpr uint8_t E_UNDECODED = 0xff;
 // boundary or a copy reaches before its block's start: such a page is
 // decompressed sequentially, the others one workgroup per block.
 constexpr uint32_t SNAP_BLOCK = 65536;
-// pages of at most this many bytes take k_snappy_blk's small shape
-constexpr uint32_t SNAP_SMALL = 16384;
+// k_snappy_blk's shapes, by the bytes of the pages (or blocks) they hold
+constexpr uint32_t SNAP_SHAPE[] = {8192, 16384, SNAP_BLOCK};
+constexpr int SNAP_SHAPES = 3;
 constexpr uint32_t SBLK_NONE = 0xffffffffu;
 // Start bits of a compressed page's elements, one per stream byte from the
 // 16-byte boundary at or before the stream's first byte (m bytes before it);

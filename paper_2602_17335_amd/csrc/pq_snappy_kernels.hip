@@ -225,7 +225,7 @@ __global__ __launch_bounds__(SX_WG) void k_snap_index(const ColScan* cols, SegTa
 // ---------------------------------------------------------------------------
 constexpr uint32_t SB_BYTES = 16;  // stream bytes per thread and pass
 // The shape for blocks of at most OUT output bytes: threads, and copies done side by
-// side (what the LDS of 2 and of 8 workgroups per CU leaves).
+// side (what the LDS of 2, 8 and 15 workgroups per CU leaves).
 template <uint32_t OUT>
 struct SbShape {
   static constexpr uint32_t WG = 512, LIST = 944;
@@ -233,8 +233,15 @@ struct SbShape {
 // A page of a few KiB is one or two of the large shape's passes, and two such
 // workgroups hold a CU.
 template <>
-struct SbShape<SNAP_SMALL> {
+struct SbShape<SNAP_SHAPE[1]> {
   static constexpr uint32_t WG = 128, LIST = 240;
+};
+// A page of up to 8 KiB: one wave, whose passes need no barrier (pages of 4 KiB that
+// are one literal, 30,000 of DOUBLE values: 152 us by two waves, now 112; by one lane
+// each 118).
+template <>
+struct SbShape<SNAP_SHAPE[0]> {
+  static constexpr uint32_t WG = 64, LIST = 120;
 };
 constexpr int SB_EL = SB_BYTES / 2;  // elements starting in a thread's bytes (each takes two or more)
 
@@ -564,7 +571,8 @@ __global__ __launch_bounds__(SbShape<OUT>::WG, 4) void k_snappy_blk(const ColSca
   if (bad) set_err(err, ERR_SNAPPY, p);
 }
 
-template __global__ void k_snappy_blk<SNAP_SMALL>(const ColScan*, SegTable, uint8_t*, uint32_t*, int);
-template __global__ void k_snappy_blk<SNAP_BLOCK>(const ColScan*, SegTable, uint8_t*, uint32_t*, int);
+template __global__ void k_snappy_blk<SNAP_SHAPE[0]>(const ColScan*, SegTable, uint8_t*, uint32_t*, int);
+template __global__ void k_snappy_blk<SNAP_SHAPE[1]>(const ColScan*, SegTable, uint8_t*, uint32_t*, int);
+template __global__ void k_snappy_blk<SNAP_SHAPE[2]>(const ColScan*, SegTable, uint8_t*, uint32_t*, int);
 
 }  // namespace pqk
