@@ -130,8 +130,11 @@ typedef struct {
  * level and value streams of each page, with checkpoints inside the tile)
  * that lets a scan start decoding at any tile.  The index is built in
  * passes: the dictionary pages first, then runs of data pages whose
- * decompressed bytes fit a 512 MiB window, each pass's compressed pages
- * decompressed into that window.  Every dictionary page is decoded once into
+ * decompressed bytes fit a 512 MiB window and whose chain tables (9 bytes per
+ * 32 of level data, 5 per 32 of dictionary indices, 4 per 128 DELTA values)
+ * fit 256 MiB, each pass's compressed pages decompressed into that window; the
+ * tables of long streams followed in segments take 52 MiB more (13 KiB per
+ * 32 KiB of the longest stream where that is more).  Every dictionary page is decoded once into
  * a resident dictionary kept by the handle (fixed-width arrays; string
  * positions, lengths and 64-byte slots), so scans never rebuild one.  Each
  * data pass also counts the DELTA sum or string bytes of its tiles of

@@ -15,6 +15,7 @@
 
 #include "pq.h"
 #include "pq_internal.h"
+#include "pq_open_passes.hpp"
 
 namespace pqk {
 __global__ void k_walk(const uint8_t* file, uint64_t file_lim, const ChunkDev* chunks, int nchunks, uint32_t* counts,
@@ -667,8 +668,6 @@ static void launch_scan(uint64_t* v, uint32_t n, uint64_t* sums, hipStream_t s) 
   hipLaunchKernelGGL(k_scan_prefix, dim3(scan_groups(n)), dim3(256), 0, s, v, n, (const uint64_t*)sums);
 }
 
-// Decompressed bytes of the data pages indexed together at open.
-constexpr uint64_t OPEN_SCRATCH_CAP = 512ull << 20;
 // Bytes allocated before an open-time window: the index walks' stream
 // readers fill their LDS windows from up to 256 bytes before the position
 // they move to, which for a pass's first page lies before the window.
@@ -928,18 +927,22 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   // Compressed pages are decompressed for the index in passes, each into one
   // window: first every dictionary page (their region follows the data
   // pages' in the scratch layout), then the data pages in runs of
-  // consecutive pages whose decompressed bytes fit OPEN_SCRATCH_CAP (a larger
-  // page is a run of its own).  The kernels of a pass address the window
+  // consecutive pages whose decompressed bytes fit OPEN_SCRATCH_CAP and whose
+  // chain tables fit OPEN_TABLE_CAP (a larger page is a run of its own).  The kernels of a pass address the window
   // through the file-wide scratch offsets, shifted by the pass's first one.
   struct OpenPass { bool dict; uint32_t p0, p1; uint64_t s0, s1; };
   std::vector<OpenPass> passes;
   passes.push_back(OpenPass{true, 0, npages, scratch, scratch + dict_scratch});
-  for (uint32_t p = 0; p < npages;) {
-    uint32_t p1 = p + 1;
-    const uint64_t a = f->scratch_prefix[p];
-    while (p1 < npages && f->scratch_prefix[p1 + 1] - a <= OPEN_SCRATCH_CAP) ++p1;
-    passes.push_back(OpenPass{false, p, p1, a, f->scratch_prefix[p1]});
-    p = p1;
+  {
+    std::vector<uint64_t> tables(npages + 1, 0);
+    for (uint32_t p = 0; p < npages; ++p) {
+      const PageDev& pg = f->pages[p];
+      const ChunkDev& cd = f->chunks[pg.chunk];
+      tables[p + 1] = tables[p] + (pg.kind == PAGE_DICT ? 0 : chain_table_bytes(pg, cd.type, cd.optional != 0));
+    }
+    const std::vector<uint32_t> at = cut_passes(f->scratch_prefix, tables, npages);
+    for (size_t k = 0; k + 1 < at.size(); ++k)
+      passes.push_back(OpenPass{false, at[k], at[k + 1], f->scratch_prefix[at[k]], f->scratch_prefix[at[k + 1]]});
   }
   uint64_t window = 0;
   for (const OpenPass& P : passes) window = std::max(window, P.s1 - P.s0);
@@ -1255,27 +1258,31 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     // workgroups (one per CU; each segment's exits are found twice) than the
     // longest page has segments.
     static constexpr int seg_list[SEG_KINDS] = {C_STRINGS, C_DI, C_DL};
+    struct SegGroup { int kind; uint32_t sp0, nsp, sg0, nsg; };  // its pages and its segments
     std::vector<SegPage> sps;
-    std::vector<uint32_t> seg_sp;
-    uint32_t sp0[SEG_KINDS], nsp[SEG_KINDS], sg0[SEG_KINDS], nsg[SEG_KINDS];
+    std::vector<uint32_t> seg_sp;  // per segment: its page in the group
+    std::vector<SegGroup> groups;
+    uint32_t nsp[SEG_KINDS] = {}, most_segs = 0;
     for (int k = 0; k < SEG_KINDS; ++k) {
-      sp0[k] = (uint32_t)sps.size();
-      sg0[k] = (uint32_t)seg_sp.size();
-      nsp[k] = nsg[k] = 0;
       const auto& l = lists[seg_list[k]];
-      auto segs_of = [](uint32_t len) { return (uint32_t)(((uint64_t)len + 15 + 32767) / 32768); };
       uint64_t all = 0;
-      for (uint32_t i = 0; i < nlong[seg_list[k]]; ++i) all += segs_of(l[i].first);
-      const uint32_t most = nlong[seg_list[k]] ? segs_of(l[0].first) : 0;
+      for (uint32_t i = 0; i < nlong[seg_list[k]]; ++i) all += stream_segs(l[i].first);
+      const uint32_t most = nlong[seg_list[k]] ? stream_segs(l[0].first) : 0;
       if (2 * ((all + CUS - 1) / CUS) + 2 >= most) continue;
       nsp[k] = nlong[seg_list[k]];
-      for (uint32_t i = 0; i < nsp[k]; ++i) {
-        const uint32_t ns = segs_of(l[i].first);
-        ixs[l[i].second].sp = (uint32_t)sps.size();
-        sps.push_back(SegPage{l[i].second, (uint32_t)seg_sp.size() - sg0[k], ns});
-        seg_sp.resize(seg_sp.size() + ns, i);
+      const std::vector<uint32_t> at = cut_groups(l, nsp[k]);
+      for (size_t g = 0; g + 1 < at.size(); ++g) {
+        SegGroup G{k, (uint32_t)sps.size(), at[g + 1] - at[g], (uint32_t)seg_sp.size(), 0};
+        for (uint32_t i = at[g]; i < at[g + 1]; ++i) {
+          const uint32_t ns = stream_segs(l[i].first);
+          ixs[l[i].second].sp = (uint32_t)sps.size();
+          sps.push_back(SegPage{l[i].second, G.nsg, ns, (uint32_t)seg_sp.size()});
+          seg_sp.resize(seg_sp.size() + ns, i - at[g]);
+          G.nsg += ns;
+        }
+        most_segs = std::max(most_segs, G.nsg);
+        groups.push_back(G);
       }
-      nsg[k] = (uint32_t)seg_sp.size() - sg0[k];
     }
     const size_t nspa = sps.size(), nsga = seg_sp.size();
     const size_t o_ord = align_up(sizeof(IxPage) * nix, 256), o_sp = align_up(o_ord + 4 * order.size(), 256),
@@ -1284,8 +1291,8 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
                  o_lent = align_up(o_lval + 4 * nlv, 256), o_vat = align_up(o_lent + nlv, 256),
                  o_vent = align_up(o_vat + 4 * nvp, 256), o_blk = align_up(o_vent + nvp, 256), o_sent = align_up(o_blk + 4 * nblk, 256),
                  o_stot = align_up(o_sent + 4 * nsga, 256), o_sseq = align_up(o_stot + 4 * nsga, 256),
-                 o_sat = align_up(o_sseq + 4 * nspa, 256), o_spe = align_up(o_sat + 4096 * nsga, 256),
-                 o_sex = align_up(o_spe + 1024 * nsga, 256), ix_total = o_sex + 8192 * nsga;
+                 o_sat = align_up(o_sseq + 4 * nspa, 256), o_spe = align_up(o_sat + 4096ull * most_segs, 256),
+                 o_sex = align_up(o_spe + 1024ull * most_segs, 256), ix_total = o_sex + 8192ull * most_segs;
     if (block_alloc(&d_ix, ix_total ? ix_total : 256) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: chain tables"); }
     up.assign(o_lat, 0);
     memcpy(up.data(), ixs.data(), sizeof(IxPage) * nix);
@@ -1321,63 +1328,58 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       hipLaunchKernelGGL(k_values, dim3((nix + 63) / 64), dim3(64), 0, s, d_ixs, nix, f->d_pages, f->d_chunks, bufs,
                          d_flag, f->d_err);
     }
-    // kind k's pages in segments (SEG_RUN), those that could not be linked by one
-    // workgroup each, then the rest of the kind's list
+    // kind k's pages in segments (SEG_RUN, group by group), those that could not be
+    // linked by one workgroup each, then the rest of the kind's list
     const SegPage* d_sp = reinterpret_cast<const SegPage*>(d_ix + o_sp);
     const uint32_t* d_sgs = reinterpret_cast<const uint32_t*>(d_ix + o_sgs);
     uint32_t* d_sent = reinterpret_cast<uint32_t*>(d_ix + o_sent);
     uint32_t* d_stot = reinterpret_cast<uint32_t*>(d_ix + o_stot);
     uint32_t* d_sseq = reinterpret_cast<uint32_t*>(d_ix + o_sseq);
-    uint32_t* d_sat = reinterpret_cast<uint32_t*>(d_ix + o_sat);
+    uint32_t* d_sat = reinterpret_cast<uint32_t*>(d_ix + o_sat);  // (as d_spe and d_sex, of one group at a time)
     uint8_t* d_spe = d_ix + o_spe;
     uint32_t* d_sex = reinterpret_cast<uint32_t*>(d_ix + o_sex);
 #define SEG_RUN(k, at_, ent_)                                                                                         \
   do {                                                                                                                \
-    const size_t g0 = sg0[k];                                                                                         \
-    hipLaunchKernelGGL(k_seg_cand<k>, dim3(nsg[k]), dim3(1024), 0, s, d_ixs, d_sp + sp0[k], d_sgs + g0, f->d_pages,   \
-                       f->d_chunks, bufs, d_sex + 2048 * g0, d_flag, f->d_err);                                       \
-    hipLaunchKernelGGL(k_seg_link<k>, dim3(nsp[k]), dim3(256), 0, s, d_ixs, d_sp + sp0[k], f->d_pages, bufs,          \
-                       d_sex + 2048 * g0, d_sent + g0, d_sseq + sp0[k], d_flag, f->d_err);                            \
-    hipLaunchKernelGGL(k_seg_fill<k>, dim3(nsg[k]), dim3(1024), 0, s, d_ixs, d_sp + sp0[k], d_sgs + g0, f->d_pages,   \
-                       f->d_chunks, bufs, d_sent + g0, d_sseq + sp0[k], at_, ent_, d_stot + g0, d_flag, f->d_err);    \
-    hipLaunchKernelGGL(k_seg_base<k>, dim3(nsp[k]), dim3(64), 0, s, d_ixs, d_sp + sp0[k], f->d_pages, d_stot + g0,    \
-                       d_sseq + sp0[k], d_flag, f->d_err);                                                            \
+    hipLaunchKernelGGL(k_seg_cand<k>, dim3(G.nsg), dim3(1024), 0, s, d_ixs, d_sp + G.sp0, d_sgs + G.sg0, f->d_pages,  \
+                       f->d_chunks, bufs, d_sex, d_flag, f->d_err);                                                   \
+    hipLaunchKernelGGL(k_seg_link<k>, dim3(G.nsp), dim3(256), 0, s, d_ixs, d_sp + G.sp0, f->d_pages, bufs, d_sex,     \
+                       d_sent + G.sg0, d_sseq + G.sp0, d_flag, f->d_err);                                             \
+    hipLaunchKernelGGL(k_seg_fill<k>, dim3(G.nsg), dim3(1024), 0, s, d_ixs, d_sp + G.sp0, d_sgs + G.sg0, f->d_pages,  \
+                       f->d_chunks, bufs, d_sent + G.sg0, d_sseq + G.sp0, at_, ent_, d_stot + G.sg0, d_flag,          \
+                       f->d_err);                                                                                     \
+    hipLaunchKernelGGL(k_seg_base<k>, dim3(G.nsp), dim3(64), 0, s, d_ixs, d_sp + G.sp0, f->d_pages, d_stot + G.sg0,   \
+                       d_sseq + G.sp0, d_flag, f->d_err);                                                             \
   } while (0)
 #define SEG_REST(k, kern, ...)                                                                                        \
   do {                                                                                                                \
-    hipLaunchKernelGGL(kern<1024>, dim3(nsp[k]), dim3(1024), 0, s, d_ixs, d_ord + first[seg_list[k]], __VA_ARGS__,    \
-                       d_sseq + sp0[k]);                                                                              \
-    first[seg_list[k]] += nsp[k];                                                                                     \
-    nlong[seg_list[k]] -= nsp[k];                                                                                     \
+    hipLaunchKernelGGL(kern<1024>, dim3(G.nsp), dim3(1024), 0, s, d_ixs, d_ord + first[seg_list[k]], __VA_ARGS__,     \
+                       d_sseq + G.sp0);                                                                               \
+    first[seg_list[k]] += G.nsp;                                                                                      \
+    nlong[seg_list[k]] -= G.nsp;                                                                                      \
   } while (0)
+    for (const SegGroup& G : groups) {
+      if (G.kind == SEG_STR) {
+        SEG_RUN(SEG_STR, d_sat, d_spe);
+        hipLaunchKernelGGL(k_str_ck, dim3(4 * G.nsg), dim3(256), 0, s, d_ixs, d_sp + G.sp0, d_sgs + G.sg0, f->d_pages,
+                           bufs, d_stot + G.sg0, d_sat, d_spe, d_sseq + G.sp0, f->d_strck, d_flag, f->d_err);
+        SEG_REST(SEG_STR, k_strings, f->d_pages, bufs, f->d_strck, d_flag, f->d_err);
+      } else if (G.kind == SEG_DI) {
+        SEG_RUN(SEG_DI, d_vat, d_vent);
+        SEG_REST(SEG_DI, k_di, f->d_pages, bufs, d_vat, d_vent, d_flag, f->d_err);
+      } else {
+        SEG_RUN(SEG_DL, d_sat, d_spe);
+        hipLaunchKernelGGL(k_dl_ck, dim3(4 * G.nsg), dim3(256), 0, s, d_ixs, d_sp + G.sp0, d_sgs + G.sg0, f->d_pages,
+                           f->d_chunks, bufs, d_stot + G.sg0, d_sat, d_spe, d_sseq + G.sp0, d_blk, d_flag, f->d_err);
+        SEG_REST(SEG_DL, k_dl, f->d_pages, f->d_chunks, bufs, d_blk, d_flag, f->d_err);
+      }
+    }
     const uint32_t* no_seq = nullptr;
-    if (nsp[SEG_STR]) {
-      const size_t g0 = sg0[SEG_STR];
-      SEG_RUN(SEG_STR, d_sat + 1024 * g0, d_spe + 1024 * g0);
-      hipLaunchKernelGGL(k_str_ck, dim3(4 * nsg[SEG_STR]), dim3(256), 0, s, d_ixs, d_sp + sp0[SEG_STR], d_sgs + g0,
-                         f->d_pages, bufs, d_stot + g0, d_sat + 1024 * g0, d_spe + 1024 * g0, d_sseq + sp0[SEG_STR],
-                         f->d_strck, d_flag, f->d_err);
-      SEG_REST(SEG_STR, k_strings, f->d_pages, bufs, f->d_strck, d_flag, f->d_err);
-    }
     CHAINS(C_STRINGS, k_strings, f->d_pages, bufs, f->d_strck, d_flag, f->d_err, no_seq);
-    if (nsp[SEG_DI]) {
-      SEG_RUN(SEG_DI, d_vat, d_vent);
-      SEG_REST(SEG_DI, k_di, f->d_pages, bufs, d_vat, d_vent, d_flag, f->d_err);
-    }
     CHAINS(C_DI, k_di, f->d_pages, bufs, d_vat, d_vent, d_flag, f->d_err, no_seq);
-    if (nsp[SEG_DL]) {
-      const size_t g0 = sg0[SEG_DL];
-      SEG_RUN(SEG_DL, d_sat + 1024 * g0, d_spe + 1024 * g0);
-      hipLaunchKernelGGL(k_dl_ck, dim3(4 * nsg[SEG_DL]), dim3(256), 0, s, d_ixs, d_sp + sp0[SEG_DL], d_sgs + g0,
-                         f->d_pages, f->d_chunks, bufs, d_stot + g0, d_sat + 1024 * g0, d_spe + 1024 * g0,
-                         d_sseq + sp0[SEG_DL], d_blk, d_flag, f->d_err);
-      SEG_REST(SEG_DL, k_dl, f->d_pages, f->d_chunks, bufs, d_blk, d_flag, f->d_err);
-    }
     CHAINS(C_DL, k_dl, f->d_pages, f->d_chunks, bufs, d_blk, d_flag, f->d_err, no_seq);
     if (ntl)
       hipLaunchKernelGGL(k_value_tiles, dim3((uint32_t)((ntl + 3) / 4)), dim3(64), 0, s, d_ixs, nix, (uint32_t)tile0,
-                         (uint32_t)ntl, f->d_pages, f->d_chunks, bufs, d_vat, d_vent, d_blk, f->d_strck, d_sp,
-                         d_stot + sg0[SEG_DI], d_sseq, d_flag, f->d_tiles, f->d_ckv, f->d_err);
+                         (uint32_t)ntl, f->d_pages, f->d_chunks, bufs, d_vat, d_vent, d_blk, f->d_strck, d_sp, d_stot, d_sseq, d_flag, f->d_tiles, f->d_ckv, f->d_err);
     // the pages that were left
     hipLaunchKernelGGL(k_index, dim3(nix), dim3(64), 0, s, file, scr, f->d_pages, d_ixs, d_flag, f->d_chunks, f->d_tiles,
                        f->d_strck, f->d_ckl, f->d_ckv, f->d_err, flim, scr_lim, xscr, xscr_lim);

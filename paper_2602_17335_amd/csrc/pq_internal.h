@@ -161,10 +161,10 @@ struct OpenBufs {
 // threads (8 KiB segments, five per CU), longer ones those of 1024 (32 KiB).
 constexpr uint32_t CHAIN_SMALL = 8192;
 // A page whose value stream's 32 KiB segments are done side by side: segments
-// [seg0, seg0 + nseg) of its kind's list.
+// [seg0, seg0 + nseg) of its group, from base0 on among those of all groups.
 enum : int { SEG_STR, SEG_DI, SEG_DL, SEG_KINDS };
 struct SegPage {
-  uint32_t ix, seg0, nseg;
+  uint32_t ix, seg0, nseg, base0;
 };
 __host__ __device__ inline uint32_t chain_pieces(uint64_t len) { return (uint32_t)((len + 15 + 31) / 32); }
 // x_total of a DELTA_BYTE_ARRAY page the scan does not decode (a value longer

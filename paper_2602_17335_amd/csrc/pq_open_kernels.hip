@@ -1507,8 +1507,8 @@ __global__ __launch_bounds__(256) void k_seg_link(const IxPage* ixs, const SegPa
   }
 }
 
-// at, ent: the pieces of page ix from v0 on (SEG_DI), or of segment sg from
-// sg SEG_NT on.
+// at, ent: the pieces of page ix from v0 on (SEG_DI), or of segment sg of the group
+// from sg SEG_NT on.
 template <int F>
 __global__ __launch_bounds__(SEG_NT) void k_seg_fill(const IxPage* ixs, const SegPage* sps, const uint32_t* seg_sp,
                                                      PageDev* pages, const ChunkDev* chunks, OpenBufs bufs,
@@ -1682,8 +1682,8 @@ __global__ __launch_bounds__(64) void k_value_tiles(const IxPage* ixs, uint32_t 
     uint32_t pc, before = 0;
     if (ix.sp != ~0u && !seq[ix.sp]) {  // counts within the segment
       const SegPage sp = sps[ix.sp];
-      const uint32_t j = piece_of(base + sp.seg0, sp.nseg, v);
-      before = base[sp.seg0 + j];
+      const uint32_t j = piece_of(base + sp.base0, sp.nseg, v);
+      before = base[sp.base0 + j];
       pc = j * SEG_NT;
       pc += piece_of(at + ix.v0 + pc, min(SEG_NT, ix.nv - pc), v - before);
     } else {
