@@ -424,8 +424,8 @@ const char* pq_server_last_error(void);
 /* Frees the handle's host and device memory (not dev_buf), after waiting for
    the device's work.  Device blocks of 1 MiB or more of closed handles and
    finished opens are kept for the next open on the device, at most 256 MiB in
-   all (those unused for 10 s go at the next open or close, all of a device's when
-   an allocation of this library fails).  Sec. 2: the handle is the reader's state
+   all: those unused for 2 s are freed by a thread of the library, all of a
+   device's when an allocation of this library fails.  Sec. 2: the handle is the reader's state
    for one file. */
 void pq_close(pq_file f);
 
