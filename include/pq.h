@@ -108,7 +108,10 @@ typedef struct {
   double open_ms_device;  /* time of the open-time passes: page walk, tile index,
                              dictionaries and tile prefix (device events) */
   uint64_t device_bytes;  /* device memory the handle holds until pq_close
-                             (index, checkpoints, resident dictionaries) */
+                             (index, checkpoints, resident dictionaries; for
+                             compressed pages one bit per compressed byte);
+                             a block taken over from an earlier open may be up
+                             to half as large again as the handle needs */
 } pq_file_stats;
 
 /*

@@ -536,35 +536,48 @@ static hipError_t small_alloc(T** p, size_t n) {
   return e;
 }
 
-// a block that block_release frees
+// a block that block_release frees, of n bytes or (a kept one) up to half as many
+// more; `held`, if given, grows by its bytes
 template <class T>
-static hipError_t block_alloc(T** p, size_t n) {
+static hipError_t block_alloc(T** p, size_t n, uint64_t* held = nullptr) {
   void* q = nullptr;
-  if (n < BLOCK_MIN) return small_alloc(p, n);
+  size_t got = n;
+  if (n < BLOCK_MIN) {
+    const hipError_t e = small_alloc(p, n);
+    if (e == hipSuccess && held) *held += n;
+    return e;
+  }
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   DevBlocks& B = dev_blocks();
-  {
-    std::lock_guard<std::mutex> g(B.m);
-    size_t best = B.kept.size();
-    for (size_t i = 0; i < B.kept.size(); ++i) {
-      const DevBlock& b = B.kept[i];
-      if (b.dev == dev && b.n >= n && b.n <= n + n / 2 && (best == B.kept.size() || b.n < B.kept[best].n)) best = i;
+  try {
+    {
+      std::lock_guard<std::mutex> g(B.m);
+      size_t best = B.kept.size();
+      for (size_t i = 0; i < B.kept.size(); ++i) {
+        const DevBlock& b = B.kept[i];
+        if (b.dev == dev && b.n >= n && b.n <= n + n / 2 && (best == B.kept.size() || b.n < B.kept[best].n)) best = i;
+      }
+      if (best < B.kept.size()) {
+        B.in_use[B.kept[best].p] = B.kept[best];
+        q = B.kept[best].p;
+        got = B.kept[best].n;
+        B.bytes -= got;
+        B.kept.erase(B.kept.begin() + (ptrdiff_t)best);
+      }
     }
-    if (best < B.kept.size()) {
-      q = B.kept[best].p;
-      B.in_use[q] = B.kept[best];
-      B.bytes -= B.kept[best].n;
-      B.kept.erase(B.kept.begin() + (ptrdiff_t)best);
+    if (!q) {
+      e = pq_dev_malloc(&q, n);
+      if (e != hipSuccess) return e;
+      std::lock_guard<std::mutex> g(B.m);
+      B.in_use[q] = DevBlock{q, n, dev, {}};
     }
+  } catch (...) {  // (no host memory)
+    if (q) (void)hipFree(q);
+    return hipErrorOutOfMemory;
   }
-  if (!q) {
-    e = pq_dev_malloc(&q, n);
-    if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> g(B.m);
-    B.in_use[q] = DevBlock{q, n, dev, {}};
-  }
+  if (held) *held += got;
   *p = static_cast<T*>(q);
   return hipSuccess;
 }
@@ -868,7 +881,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   for (int q = 0; q < nchunks; ++q) f->chunk_page0[q + 1] = f->chunk_page0[q] + counts[q];
   const uint32_t npages = f->chunk_page0[nchunks];
   if (npages > 0) {
-    OPEN_HIP(block_alloc(&f->d_pages, sizeof(PageDev) * npages));
+    OPEN_HIP(block_alloc(&f->d_pages, sizeof(PageDev) * npages, &f->device_bytes));
     OPEN_HIP(hipMemcpyAsync(d_base, f->chunk_page0.data(), sizeof(uint32_t) * nchunks, hipMemcpyHostToDevice, s));
     std::vector<uint32_t> page_chunk;
     if (!overflow) {
@@ -1037,9 +1050,9 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   // Snappy block index, built by the decompression below
   f->total_sblk = sblk;
   if (sblk) {
-    if (block_alloc(&f->d_sblk, sizeof(uint32_t) * sblk) != hipSuccess ||
-        block_alloc(&f->d_sblk_page, sizeof(uint32_t) * sblk) != hipSuccess ||
-        block_alloc(&f->d_sbits, sizeof(uint16_t) * (sbits + 2)) != hipSuccess) {
+    if (block_alloc(&f->d_sblk, sizeof(uint32_t) * sblk, &f->device_bytes) != hipSuccess ||
+        block_alloc(&f->d_sblk_page, sizeof(uint32_t) * sblk, &f->device_bytes) != hipSuccess ||
+        block_alloc(&f->d_sbits, sizeof(uint16_t) * (sbits + 2), &f->device_bytes) != hipSuccess) {
       cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: block index allocation");
     }
     if (hipMemcpy(f->d_sblk_page, sblk_page.data(), sizeof(uint32_t) * sblk, hipMemcpyHostToDevice) != hipSuccess) {
@@ -1052,19 +1065,18 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   }
   if (small_alloc(&d_cs, sizeof(ColScan)) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: allocation failed"); }
   if (tiles) {
-    if (block_alloc(&f->d_tiles, sizeof(TileDev) * tiles) != hipSuccess ||
-        block_alloc(&f->d_ckl, sizeof(uint32_t) * NLCK * tiles) != hipSuccess ||
-        block_alloc(&f->d_ckv, sizeof(Ck) * NSUB * tiles) != hipSuccess) {
+    if (block_alloc(&f->d_tiles, sizeof(TileDev) * tiles, &f->device_bytes) != hipSuccess ||
+        block_alloc(&f->d_ckl, sizeof(uint32_t) * NLCK * tiles, &f->device_bytes) != hipSuccess ||
+        block_alloc(&f->d_ckv, sizeof(Ck) * NSUB * tiles, &f->device_bytes) != hipSuccess) {
       cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: tile index allocation");
     }
   }
   if (strck) {
-    if (block_alloc(&f->d_strck, sizeof(uint32_t) * strck) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: checkpoint allocation"); }
+    if (block_alloc(&f->d_strck, sizeof(uint32_t) * strck, &f->device_bytes) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: checkpoint allocation"); }
   }
   if (dba_units) {
-    if (block_alloc(&f->d_dbau, sizeof(DbaUnit) * dba_units) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: unit allocation"); }
+    if (block_alloc(&f->d_dbau, sizeof(DbaUnit) * dba_units, &f->device_bytes) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: unit allocation"); }
     OPEN_HIP(hipMemsetAsync(f->d_dbau, 0xff, sizeof(DbaUnit) * dba_units, s));
-    f->device_bytes += sizeof(DbaUnit) * dba_units;
   }
   // the tile prefixes: each pass stores its tiles' values, then their sums
   std::vector<bool> need((size_t)f->ncols, false), need_dlba((size_t)f->ncols, false);
@@ -1208,9 +1220,8 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         }
         if (ctx) {
           uint8_t* b = nullptr;
-          if (block_alloc(&b, ctx) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: unit allocation"); }
+          if (block_alloc(&b, ctx, &f->device_bytes) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: unit allocation"); }
           f->d_dbactx.push_back(b);
-          f->device_bytes += ctx;
           for (uint32_t pp = P.p0; pp < P.p1; ++pp) {
             PageDev& pg = f->pages[pp];
             if (pg.kind == PAGE_DICT || pg.encoding != E_DBA || f->chunks[pg.chunk].type != T_BYTE_ARRAY ||
@@ -1561,10 +1572,8 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   }
   S.tiles = (int64_t)tiles;
   S.open_ms_device = ms;
-  f->device_bytes += 4 + sizeof(ChunkDev) * (uint64_t)nchunks + sizeof(PageDev) * (uint64_t)npages +
-                     (sizeof(TileDev) + 4ull * NLCK + sizeof(Ck) * NSUB) * tiles + 4ull * strck +
-                     8ull * sblk + 2ull * sbits +  // Snappy block index: offset, page; element start bits
-                     8ull * (tiles + 1) + sizeof(DictSlot) * (uint64_t)nchunks;
+  // (the blocks were counted as they were allocated)
+  f->device_bytes += 4 + sizeof(ChunkDev) * (uint64_t)nchunks + 8ull * (tiles + 1) + sizeof(DictSlot) * (uint64_t)nchunks;
   S.device_bytes = f->device_bytes;
   (void)t0;
   *out = f;
@@ -1703,8 +1712,7 @@ static pq_status build_dicts(pq_file f, const uint8_t* scratch, bool copy_all, h
     }
   }
   if (off) {
-    if (block_alloc(&f->d_dict_arena, off) != hipSuccess) return fail(PQ_ENOMEM, "open: no device memory for dictionaries");
-    f->device_bytes += off;
+    if (block_alloc(&f->d_dict_arena, off, &f->device_bytes) != hipSuccess) return fail(PQ_ENOMEM, "open: no device memory for dictionaries");
   }
   auto rebase = [&](const uint8_t* x) { return f->d_dict_arena + reinterpret_cast<uintptr_t>(x); };
   for (int q = 0; q < nchunks; ++q) {

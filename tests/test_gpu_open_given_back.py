@@ -3,7 +3,7 @@ open takes it, without a further call into the library: after a few seconds the
 device has as much free memory as before the file was opened (but for the 64 MiB of
 freed memory that the runtime itself may hold), also where another thread is in the
 middle of a stream capture when that happens, whose graph replays as the same work
-done eagerly."""
+done eagerly.  A handle's device_bytes count the whole of the memory it took over."""
 import gc
 import time
 
@@ -18,10 +18,10 @@ MiB = 1 << 20
 RUNTIME = 66 * MiB  # freed memory the runtime may hold, and page-sized remainders
 
 
-def _file():
-    # 16 columns of runs: a small file with 350,000 tiles (146 MB of index)
+def _file(rows=22_000_000):
+    # 16 columns of runs: a small file with 344,000 tiles (143 MB of index)
     cols = [dg.Col(dg.INT32, dg.RLE_DICTIONARY, True, dg.CONST, 0.0, lo=7, hi=8) for _ in range(16)]
-    return dg.write(dg.FileSpec(cols=cols, num_rows=22_000_000, rg_rows=22_000_000, page_bytes=1 << 20, seed=3))
+    return dg.write(dg.FileSpec(cols=cols, num_rows=rows, rg_rows=rows, page_bytes=1 << 20, seed=3))
 
 
 def _free():
@@ -90,3 +90,23 @@ def test_given_back_during_a_capture():
         want = want * 3 + x
         torch.cuda.synchronize()
         assert torch.equal(y, want)
+
+
+def test_device_bytes():
+    import paper_2602_17335_amd as pqs
+    bufs = [pqs.to_device(_file(rows)) for rows in (10_000_000, 13_000_000)]
+
+    def opened(k):
+        f = pqs.DeviceFile(*bufs[k])
+        n = f.stats().device_bytes
+        f.close()
+        return n
+
+    opened(0)
+    _settled()
+    own = opened(0)
+    _settled()
+    larger = opened(1)
+    after = opened(0)  # in the larger file's blocks
+    assert own < larger
+    assert 1.1 * own < after <= larger
