@@ -28,7 +28,7 @@ __global__ void k_walk(const uint8_t* file, uint64_t file_lim, const ChunkDev* c
 __global__ void k_walk_rec(const uint8_t* file, const ChunkDev* chunks, const uint64_t* rec, const uint32_t* rec_base,
                            const uint32_t* page_base, const uint32_t* page_chunk, uint32_t npages, PageDev* pages,
                            uint32_t* err);
-__global__ void k_layout(uint32_t p0, uint32_t p1, int dicts, PageDev* pages, const ChunkDev* chunks,
+__global__ void k_layout(uint32_t p0, uint32_t p1, int dicts, PageDev* pages, const PageX* pagex, const ChunkDev* chunks,
                          const uint8_t* file, const uint8_t* scratch, uint32_t* err);
 template <uint32_t NT>
 __global__ void k_levels(const IxPage* ixs, const uint32_t* list, PageDev* pages, OpenBufs bufs, uint32_t* at,
@@ -37,8 +37,8 @@ __global__ void k_tiles(const IxPage* ixs, uint32_t nix, uint32_t tile0, uint32_
                         const ChunkDev* chunks, OpenBufs bufs, const uint32_t* at, const uint32_t* val,
                         const uint8_t* ent, const uint32_t* flag, TileDev* tiles, uint32_t* ckl, Ck* ckv,
                         const uint32_t* err);
-__global__ void k_values(const IxPage* ixs, uint32_t nix, PageDev* pages, const ChunkDev* chunks, OpenBufs bufs,
-                         const uint32_t* flag, uint32_t* err);
+__global__ void k_values(const IxPage* ixs, uint32_t nix, PageDev* pages, const PageX* pagex, const ChunkDev* chunks,
+                         OpenBufs bufs, const uint32_t* flag, uint32_t* err);
 template <uint32_t NT>
 __global__ void k_strings(const IxPage* ixs, const uint32_t* list, PageDev* pages, OpenBufs bufs, uint32_t* strck,
                           uint32_t* flag, const uint32_t* err, const uint32_t* seq);
@@ -76,7 +76,7 @@ __global__ void k_value_tiles(const IxPage* ixs, uint32_t nix, uint32_t tile0, u
 __global__ void k_index(const uint8_t* file, const uint8_t* scratch, PageDev* pages, const IxPage* ixs,
                         const uint32_t* flag, const ChunkDev* chunks, TileDev* tiles, uint32_t* strck, uint32_t* ckl,
                         Ck* ckv, uint32_t* err, uint64_t file_lim, uint64_t scratch_lim, const uint8_t* xscratch,
-                        uint64_t xscratch_lim);
+                        uint64_t xscratch_lim, const PageX* pagex);
 __global__ void k_snappy(const ColScan* cols, SegTable seg, uint8_t* ws, int record, uint32_t* err);
 template <uint32_t OUT>
 __global__ void k_snappy_blk(const ColScan* cols, SegTable seg, uint8_t* ws, uint32_t* err, int dicts);
@@ -93,7 +93,7 @@ __global__ void k_str_total(const ColScan* cols, const int32_t* which, int32_t n
 __global__ void k_copy(uint8_t* dst, const uint8_t* src, uint64_t n);
 template <bool SMALL>
 __global__ void k_dba(const ColScan* cols, SegTable seg, uint8_t* ws, const uint8_t* open_scratch, uint8_t* open_out,
-                      PageDev* pages_out, DbaUnit* units_out, int mode, uint32_t* err);
+                      PageX* px_out, DbaUnit* units_out, int mode, uint32_t* err);
 enum : int { FX_DICT = 1, FX_WIDE = 2, FX_BSS = 4 };
 template <int KIND>
 __global__ void k_decode_fixed(uint8_t* ws, const ColScan* cols, SegTable seg, uint32_t* err);
@@ -331,7 +331,9 @@ struct pq_file_s {
   DbaUnit* d_dbau = nullptr;             // the units, and the bytes they keep (one buffer per open pass)
   std::vector<uint8_t*> d_dbactx;
   uint64_t total_tiles = 0, total_strck = 0;
+  std::vector<PageX> pagex;              // their DELTA_BYTE_ARRAY part (empty when the file needs none)
   PageDev* d_pages = nullptr;
+  PageX* d_pagex = nullptr;
   TileDev* d_tiles = nullptr;
   uint32_t* d_strck = nullptr;
   uint32_t* d_sblk = nullptr;       // Snappy block index (stream offset per 64 KiB output block)
@@ -620,7 +622,7 @@ static void free_handle(pq_file f) {
   bool idle = f->d_err != nullptr;
   for (void* p : {(void*)f->d_err, (void*)f->d_chunks, (void*)f->d_tpfx, (void*)f->d_tpfx2, (void*)f->d_dicts})
     if (p && hipFree(p) != hipSuccess) idle = false;
-  for (void* p : {(void*)f->d_pages, (void*)f->d_tiles, (void*)f->d_strck, (void*)f->d_sblk, (void*)f->d_sblk_page,
+  for (void* p : {(void*)f->d_pages, (void*)f->d_pagex, (void*)f->d_tiles, (void*)f->d_strck, (void*)f->d_sblk, (void*)f->d_sblk_page,
                   (void*)f->d_sbits, (void*)f->d_dbau, (void*)f->d_ckl, (void*)f->d_ckv, (void*)f->d_dict_arena})
     if (p) block_release(p, idle);
   for (uint8_t* b : f->d_dbactx) block_release(b, idle);
@@ -916,8 +918,10 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   f->scratch_prefix.assign(npages + 1, 0);
   f->dba_unit0.assign(npages + 1, 0);
   uint64_t dba_units = 0;
-  uint64_t tiles = 0, strck = 0, scratch = 0, sblk = 0, sbits = 0;
+  bool any_dba = false;
+  uint64_t tiles = 0, strck = 0, scratch = 0, sblk = 0, sbits = 0;  // (sbits: bytes)
   std::vector<uint32_t> sblk_page;
+  f->pagex.assign(npages, PageX{});
   for (int q = 0; q < nchunks; ++q) {
     const ChunkDev& cd = f->chunks[q];
     const int g = q % f->nrg;
@@ -927,12 +931,12 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     for (uint32_t p = f->chunk_page0[q]; p < f->chunk_page0[q + 1]; ++p) {
       PageDev& pg = f->pages[p];
       f->dba_unit0[p] = (uint32_t)dba_units;
-      pg.x_unit0 = (uint32_t)dba_units;
+      f->pagex[p].x_unit0 = (uint32_t)dba_units;
       pg.scratch_off = scratch;  // (dictionary pages: placed after the data pages below)
       f->scratch_prefix[p] = scratch;
       uint64_t slen = 0;
       if (cd.codec == 1) {
-        if (pg.kind == PAGE_DATA_V2) slen = pg.v2_compressed ? pg.uncomp_size - pg.rep_len - pg.def_len : 0;
+        if (pg.kind == PAGE_DATA_V2) slen = pg.v2_compressed ? pg.uncomp_size - pg.def_len : 0;
         else slen = pg.uncomp_size;
         // V1/dictionary pages are always compressed with the chunk codec; an
         // empty page still decompresses to 0 bytes
@@ -945,9 +949,9 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         const uint64_t nb = (slen + SNAP_BLOCK - 1) / SNAP_BLOCK;
         for (uint64_t j = 0; j < nb; ++j) sblk_page.push_back(p);
         sblk += nb;
-        const uint32_t lev = pg.kind == PAGE_DATA_V2 ? (uint32_t)pg.rep_len + (uint32_t)pg.def_len : 0u;
-        pg.sbit_begin = sbits;
-        sbits += 2ull * snap_bit_words((uint32_t)((pg.payload + lev) & 15), pg.comp_size > lev ? pg.comp_size - lev : 0);
+        const uint32_t lev = pg.kind == PAGE_DATA_V2 ? (uint32_t)pg.def_len : 0u;
+        pg.sbit0 = (uint32_t)(sbits / 16);  // (128 bits a unit: files of less than 512 GiB)
+        sbits += align_up(4ull * snap_bit_words((uint32_t)((pg.payload + lev) & 15), pg.comp_size > lev ? pg.comp_size - lev : 0), 16);
       }
       if (cd.codec == 1 && (pg.kind != PAGE_DATA_V2 || pg.v2_compressed) && pg.kind != PAGE_DICT)
         scratch += align_up(slen + SCRATCH_PAD, 16);
@@ -964,7 +968,10 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       pg.row0 = row;
       row += pg.num_values;
       // (k_dba refuses a page of more values than rows before any unit is written)
-      if (cd.type == T_BYTE_ARRAY && pg.encoding == E_DBA) dba_units += ((uint64_t)pg.num_values + DBA_UNIT - 1) / DBA_UNIT;
+      if (cd.type == T_BYTE_ARRAY && pg.encoding == E_DBA) {
+        any_dba = true;
+        dba_units += ((uint64_t)pg.num_values + DBA_UNIT - 1) / DBA_UNIT;
+      }
       pg.tile_begin = (uint32_t)tiles;
       tiles += ((uint64_t)pg.num_values + TILE_ROWS - 1) / TILE_ROWS;
       if (cd.type == T_BYTE_ARRAY && (pg.encoding == E_PLAIN || pg.encoding == E_DBA)) {
@@ -1047,12 +1054,17 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     d_cs = nullptr;
   };
   if (npages) OPEN_HIP(hipMemcpyAsync(f->d_pages, f->pages.data(), sizeof(PageDev) * npages, hipMemcpyHostToDevice, s));
+  if (!any_dba) f->pagex.clear();
+  if (!f->pagex.empty()) {
+    OPEN_HIP(block_alloc(&f->d_pagex, sizeof(PageX) * npages, &f->device_bytes));
+    OPEN_HIP(hipMemcpyAsync(f->d_pagex, f->pagex.data(), sizeof(PageX) * npages, hipMemcpyHostToDevice, s));
+  }
   // Snappy block index, built by the decompression below
   f->total_sblk = sblk;
   if (sblk) {
     if (block_alloc(&f->d_sblk, sizeof(uint32_t) * sblk, &f->device_bytes) != hipSuccess ||
         block_alloc(&f->d_sblk_page, sizeof(uint32_t) * sblk, &f->device_bytes) != hipSuccess ||
-        block_alloc(&f->d_sbits, sizeof(uint16_t) * (sbits + 2), &f->device_bytes) != hipSuccess) {
+        block_alloc(&f->d_sbits, sbits + 16, &f->device_bytes) != hipSuccess) {
       cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: block index allocation");
     }
     if (hipMemcpy(f->d_sblk_page, sblk_page.data(), sizeof(uint32_t) * sblk, hipMemcpyHostToDevice) != hipSuccess) {
@@ -1103,6 +1115,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   }
   f->fd.file = file;
   f->fd.pages = f->d_pages;
+  f->fd.pagex = f->d_pagex;
   f->fd.tiles = f->d_tiles;
   f->fd.ckl = f->d_ckl;
   f->fd.ckv = f->d_ckv;
@@ -1183,6 +1196,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         memset(&cs, 0, sizeof(cs));
         cs.fd.file = file;
         cs.fd.pages = f->d_pages;
+        cs.fd.pagex = f->d_pagex;
         cs.type = T_BYTE_ARRAY;
         cs.optional = f->cols[c].optional;
         cs.col = c;
@@ -1199,45 +1213,47 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         if (small_alloc(&d_xcols, sizeof(ColScan) * xc.size()) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: allocation failed"); }
         OPEN_HIP(hipMemcpyAsync(d_xcols, xc.data(), sizeof(ColScan) * xc.size(), hipMemcpyHostToDevice, s));
         hipLaunchKernelGGL(k_dba<false>, dim3(xw), dim3(64), 0, s, d_xcols, make_segs(xs), (uint8_t*)nullptr, scr,
-                           (uint8_t*)nullptr, f->d_pages, (DbaUnit*)nullptr, 0, f->d_err);
+                           (uint8_t*)nullptr, f->d_pagex, (DbaUnit*)nullptr, 0, f->d_err);
         if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_dba launch failed"); }
         {
           pq_status stx = read_err(f, s);
           if (stx != PQ_OK) { cleanup_open(); free_handle(f); return stx; }
         }
-        OPEN_HIP(hipMemcpy(f->pages.data() + P.p0, f->d_pages + P.p0, sizeof(PageDev) * (P.p1 - P.p0),
+        OPEN_HIP(hipMemcpy(f->pagex.data() + P.p0, f->d_pagex + P.p0, sizeof(PageX) * (P.p1 - P.p0),
                            hipMemcpyDeviceToHost));
         uint64_t ctx = 0;  // bytes the pass's units keep
         for (uint32_t pp = P.p0; pp < P.p1; ++pp) {
-          PageDev& pg = f->pages[pp];
+          const PageDev& pg = f->pages[pp];
+          PageX& px = f->pagex[pp];
           f->xscratch_prefix[pp] = xscratch;
           if (pg.kind == PAGE_DICT || pg.encoding != E_DBA || f->chunks[pg.chunk].type != T_BYTE_ARRAY ||
-              pg.x_total == DBA_UNSUPPORTED)
+              px.x_total == DBA_UNSUPPORTED)
             continue;
-          pg.x_off = xscratch;
-          xscratch += align_up((uint64_t)pg.xlen + SCRATCH_PAD, 16);
-          ctx += pg.x_ctx;
+          px.x_off = xscratch;
+          xscratch += align_up((uint64_t)px.xlen + SCRATCH_PAD, 16);
+          ctx += px.x_ctx;
         }
         if (ctx) {
           uint8_t* b = nullptr;
           if (block_alloc(&b, ctx, &f->device_bytes) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: unit allocation"); }
           f->d_dbactx.push_back(b);
           for (uint32_t pp = P.p0; pp < P.p1; ++pp) {
-            PageDev& pg = f->pages[pp];
+            const PageDev& pg = f->pages[pp];
+            PageX& px = f->pagex[pp];
             if (pg.kind == PAGE_DICT || pg.encoding != E_DBA || f->chunks[pg.chunk].type != T_BYTE_ARRAY ||
-                pg.x_total == DBA_UNSUPPORTED)
+                px.x_total == DBA_UNSUPPORTED)
               continue;
-            pg.x_ctxp = b;
-            b += pg.x_ctx;
+            px.x_ctxp = b;
+            b += px.x_ctx;
           }
         }
-        OPEN_HIP(hipMemcpyAsync(f->d_pages + P.p0, f->pages.data() + P.p0, sizeof(PageDev) * (P.p1 - P.p0),
+        OPEN_HIP(hipMemcpyAsync(f->d_pagex + P.p0, f->pagex.data() + P.p0, sizeof(PageX) * (P.p1 - P.p0),
                                 hipMemcpyHostToDevice, s));
         if (xscratch > xs0) {
           if (block_alloc(&d_xscratch_mem, OPEN_GUARD + (xscratch - xs0)) != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_ENOMEM, "open: no device memory for expansion"); }
           d_xscratch = d_xscratch_mem + OPEN_GUARD;
           hipLaunchKernelGGL(k_dba<false>, dim3(xw), dim3(64), 0, s, d_xcols, make_segs(xs), (uint8_t*)nullptr, scr,
-                             d_xscratch - xs0, f->d_pages, f->d_dbau, 1, f->d_err);
+                             d_xscratch - xs0, f->d_pagex, f->d_dbau, 1, f->d_err);
           if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_dba launch failed"); }
           xscr = d_xscratch - xs0;
           xscr_lim = xscratch;
@@ -1257,7 +1273,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     // those of earlier pages), then all tiles side by side
     const uint32_t nix = (uint32_t)plist.size();
     hipLaunchKernelGGL(k_layout, dim3((P.p1 - P.p0 + 63) / 64), dim3(64), 0, s, P.p0, P.p1, P.dict ? 1 : 0, f->d_pages,
-                       f->d_chunks, file, scr, f->d_err);
+                       f->d_pagex, f->d_chunks, file, scr, f->d_err);
     if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "k_layout launch failed"); }
     if (!P.dict) {  // the streams' lengths
       OPEN_HIP(hipMemcpyAsync(f->pages.data() + P.p0, f->d_pages + P.p0, sizeof(PageDev) * (P.p1 - P.p0),
@@ -1391,8 +1407,8 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         hipLaunchKernelGGL(k_tiles, dim3((uint32_t)((ntl + 3) / 4)), dim3(256), 0, s, d_ixs, nix, (uint32_t)tile0,
                            (uint32_t)ntl, f->d_pages, f->d_chunks, bufs, d_lat, d_lval, d_lent, d_flag, f->d_tiles,
                            f->d_ckl, f->d_ckv, f->d_err);
-      hipLaunchKernelGGL(k_values, dim3((nix + 63) / 64), dim3(64), 0, s, d_ixs, nix, f->d_pages, f->d_chunks, bufs,
-                         d_flag, f->d_err);
+      hipLaunchKernelGGL(k_values, dim3((nix + 63) / 64), dim3(64), 0, s, d_ixs, nix, f->d_pages, f->d_pagex, f->d_chunks,
+                         bufs, d_flag, f->d_err);
     }
     // kind k's pages in segments (SEG_RUN, group by group), those that could not be
     // linked by one workgroup each, then the rest of the kind's list
@@ -1448,7 +1464,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
                          (uint32_t)ntl, f->d_pages, f->d_chunks, bufs, d_vat, d_vent, d_blk, f->d_strck, d_sp, d_stot, d_sseq, d_flag, f->d_tiles, f->d_ckv, f->d_err);
     // the pages that were left
     hipLaunchKernelGGL(k_index, dim3(nix), dim3(64), 0, s, file, scr, f->d_pages, d_ixs, d_flag, f->d_chunks, f->d_tiles,
-                       f->d_strck, f->d_ckl, f->d_ckv, f->d_err, flim, scr_lim, xscr, xscr_lim);
+                       f->d_strck, f->d_ckl, f->d_ckv, f->d_err, flim, scr_lim, xscr, xscr_lim, f->d_pagex);
     if (hipGetLastError() != hipSuccess) { cleanup_open(); free_handle(f); return fail(PQ_EHIP, "index launch failed"); }
 #undef CHAINS
 #undef SEG_RUN
@@ -1836,7 +1852,7 @@ void col_setup(pq_file f, int c, int32_t rg_b, int32_t rg_e, int64_t rows, uint6
   for (uint32_t p = cs.page_begin; p < cs.page_end; ++p) {
     if (f->pages[p].kind == PAGE_DICT) continue;
     const int e = f->pages[p].encoding;
-    if (e == E_DBA && cs.type == T_BYTE_ARRAY) (f->pages[p].x_maxlen <= DBA_SMALL ? k.dba_small : k.dba_big) = true;
+    if (e == E_DBA && cs.type == T_BYTE_ARRAY) (f->pagex[p].x_maxlen <= DBA_SMALL ? k.dba_small : k.dba_big) = true;
     if (e == E_DELTA) {
       k.has_delta = true;
     } else if (e == E_BSS && cs.type != T_BYTE_ARRAY) {
@@ -1994,10 +2010,10 @@ static void launch_dba(uint32_t units, const SegTable& segs, bool small, bool bi
                        uint32_t* err, hipStream_t s) {
   if (small)
     hipLaunchKernelGGL(k_dba<true>, dim3(units), dim3(64), 0, s, d_cols, segs, ws, (const uint8_t*)nullptr,
-                       (uint8_t*)nullptr, (PageDev*)nullptr, (DbaUnit*)nullptr, 2, err);
+                       (uint8_t*)nullptr, (PageX*)nullptr, (DbaUnit*)nullptr, 2, err);
   if (big)
     hipLaunchKernelGGL(k_dba<false>, dim3(units), dim3(64), 0, s, d_cols, segs, ws, (const uint8_t*)nullptr,
-                       (uint8_t*)nullptr, (PageDev*)nullptr, (DbaUnit*)nullptr, 2, err);
+                       (uint8_t*)nullptr, (PageX*)nullptr, (DbaUnit*)nullptr, 2, err);
 }
 
 // Snappy decompression of the plan's compressed data pages (column table

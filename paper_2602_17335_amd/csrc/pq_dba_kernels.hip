@@ -182,7 +182,7 @@ __device__ __forceinline__ void lane_lds_copy(lds_u8* dst, const lds_u32* src32,
 //   mode 0 finds the page's value stream (as the index pass does) and the
 //     start of its second stream and of the suffix bytes, checks every
 //     prefix against the previous value's length and the value count against
-//     the page's rows, and stores the page's facts in pages_out (x_src, x_len,
+//     the page's rows, and stores the page's facts in px_out (x_src, x_len,
 //     x_sfx, x_chars, xlen, x_total, x_scratch, x_ctx);
 //   mode 1 expands a page from its start and records its units;
 //   mode 2 expands one unit from its record: k_dba<true> the units of pages
@@ -198,7 +198,7 @@ __device__ __forceinline__ void lane_lds_copy(lds_u8* dst, const lds_u32* src32,
 // ---------------------------------------------------------------------------
 template <bool SMALL>
 __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, SegTable seg, uint8_t* ws, const uint8_t* open_scratch,
-                                            uint8_t* open_out, PageDev* pages_out, DbaUnit* units_out, int mode,
+                                            uint8_t* open_out, PageX* px_out, DbaUnit* units_out, int mode,
                                             uint32_t* err) {
   constexpr uint32_t PREV = SMALL ? DBA_SMALL : DBA_PREV;  // longest value
   constexpr uint32_t OUT = SMALL ? 2048 : 4096;            // a group's expanded bytes in LDS
@@ -222,7 +222,8 @@ __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, 
   }
   const PageDev pg = fd.pages[p];
   if (pg.kind == PAGE_DICT || pg.encoding != E_DBA || csp->type != T_BYTE_ARRAY) return;
-  if (mode == 2 && (pg.x_maxlen <= DBA_SMALL) != SMALL) return;
+  const PageX px = fd.pagex[p];
+  if (mode == 2 && (px.x_maxlen <= DBA_SMALL) != SMALL) return;
   // the decompression layout (file-wide offsets)
   const uint8_t* sbase = open_scratch ? open_scratch : ws + csp->ws_scratch - csp->scratch_base;
   lds_u32* bp = (lds_u32*)&s_p[0];
@@ -254,7 +255,7 @@ __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, 
       vo = pg.scratch_off;
       vl = pg.scratch_len;
     } else {
-      const uint64_t lv = (uint64_t)pg.rep_len + (uint64_t)pg.def_len;
+      const uint64_t lv = (uint64_t)pg.def_len;
       vo = pg.payload + lv;
       vl = lv <= pg.comp_size ? pg.comp_size - lv : 0;
     }
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, 
     if (!S.bad && S.mb < S.used_mb) S.q = S.mbq + S.per * S.w / 8;
     const uint32_t chars = sfx + S.q;
     if (P.unsupported || S.unsupported) {  // valid, but not decoded here: reported when scanned
-      if (lane == 0) pages_out[p].x_total = DBA_UNSUPPORTED;
+      if (lane == 0) px_out[p].x_total = DBA_UNSUPPORTED;
       return;
     }
     if (P.bad || S.bad || S.total != P.total) {
@@ -311,14 +312,14 @@ __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, 
       wave_sync();
     }
     if (!code && ((uint64_t)chars + sfx_sum > vl || sum >= 0x80000000ull)) code = ERR_STRING;
-    if (code == ERR_UNSUPPORTED) { if (lane == 0) pages_out[p].x_total = DBA_UNSUPPORTED; return; }
+    if (code == ERR_UNSUPPORTED) { if (lane == 0) px_out[p].x_total = DBA_UNSUPPORTED; return; }
     // the units and the bytes they keep are reserved by the page's rows: a
     // stream of more values would have mode 1 write past them
     if (!code && P.total > (uint32_t)pg.num_values) code = ERR_VALUES;
     if (code) { if (lane == 0) set_err(err, code, p); return; }
     for (int m = 32; m; m >>= 1) maxlen = max(maxlen, (uint32_t)__shfl_xor((int)maxlen, m));
     if (lane == 0) {
-      PageDev& o = pages_out[p];
+      PageX& o = px_out[p];
       o.x_maxlen = maxlen;
       o.x_src = vo;
       o.x_len = (uint32_t)vl;
@@ -332,27 +333,27 @@ __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, 
     return;
   }
   // modes 1 and 2: the values in the PLAIN layout
-  if (pg.x_total == DBA_UNSUPPORTED) return;
-  const uint8_t* src = (pg.x_scratch ? sbase : fd.file) + pg.x_src;
-  uint8_t* out = open_out ? open_out + pg.x_off : ws + csp->ws_xscratch + (pg.x_off - csp->xscratch_base);
+  if (px.x_total == DBA_UNSUPPORTED) return;
+  const uint8_t* src = (px.x_scratch ? sbase : fd.file) + px.x_src;
+  uint8_t* out = open_out ? open_out + px.x_off : ws + csp->ws_xscratch + (px.x_off - csp->xscratch_base);
   lds_u8* prev = (lds_u8*)&s_prev[0];
   DeltaSeq P, S;
-  uint32_t pos = 0, c = 0, last = pg.x_total, ctx = 0;
+  uint32_t pos = 0, c = 0, last = px.x_total, ctx = 0;
   if (!SMALL && mode == 1) {
-    P.init(src, pg.x_len, wp);
-    S.init(src + pg.x_sfx, pg.x_len - pg.x_sfx, wsq);
+    P.init(src, px.x_len, wp);
+    S.init(src + px.x_sfx, px.x_len - px.x_sfx, wsq);
   } else {
     const DbaUnit u = *unit;
-    P.resume(src, pg.x_len, wp, u.p, pg.x_total, u.first);
-    S.resume(src + pg.x_sfx, pg.x_len - pg.x_sfx, wsq, u.s, pg.x_total, u.first);
+    P.resume(src, px.x_len, wp, u.p, px.x_total, u.first);
+    S.resume(src + px.x_sfx, px.x_len - px.x_sfx, wsq, u.s, px.x_total, u.first);
     pos = u.pos;
     c = u.c;
-    last = min(u.first + DBA_UNIT, pg.x_total);
+    last = min(u.first + DBA_UNIT, px.x_total);
     for (uint32_t i = lane; i < min(u.ctx_len, PREV); i += 64) prev[i] = u.ctx[i];
   }
   if (P.bad || S.bad) { if (lane == 0) set_err(err, ERR_DELTA, p); return; }
-  const uint8_t* chars = src + pg.x_chars;
-  const uint32_t nchars = pg.x_len - pg.x_chars;
+  const uint8_t* chars = src + px.x_chars;
+  const uint32_t nchars = px.x_len - px.x_chars;
   lds_u8* ob = (lds_u8*)&s_out[0];
   while (P.done < last) {
     const uint32_t n = min(64u, last - P.done), at = P.done;
@@ -366,12 +367,12 @@ __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, 
     const uint32_t pl = lane < n ? bp[lane] : 0u, sl = lane < n ? bs[lane] : 0u;
     if (rec) {
       const uint32_t cl = min(first_lane(pl), PREV);
-      for (uint32_t i = lane; i < cl; i += 64) pg.x_ctxp[ctx + i] = prev[i];
+      for (uint32_t i = lane; i < cl; i += 64) px.x_ctxp[ctx + i] = prev[i];
       if (lane == 0) {
-        DbaUnit& u = units_out[pg.x_unit0 + at / DBA_UNIT];
+        DbaUnit& u = units_out[px.x_unit0 + at / DBA_UNIT];
         u.p = ps;
         u.s = ss;
-        u.ctx = pg.x_ctxp + ctx;
+        u.ctx = px.x_ctxp + ctx;
         u.ctx_len = cl;
         u.first = at;
         u.c = c;
@@ -384,7 +385,7 @@ __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, 
     const uint32_t L = pl + sl;
     const uint32_t si = wave_incl_scan_u32(sl), oi = wave_incl_scan_u32(lane < n ? 4 + L : 0u);
     if ((uint64_t)c + (uint32_t)__builtin_amdgcn_readlane((int)si, 63) > nchars ||
-        (uint64_t)pos + (uint32_t)__builtin_amdgcn_readlane((int)oi, 63) > pg.xlen) {
+        (uint64_t)pos + (uint32_t)__builtin_amdgcn_readlane((int)oi, 63) > px.xlen) {
       if (lane == 0) set_err(err, ERR_STRING, p);
       return;
     }
@@ -485,9 +486,9 @@ __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, 
   }
 }
 
-template __global__ void k_dba<false>(const ColScan*, SegTable, uint8_t*, const uint8_t*, uint8_t*, PageDev*, DbaUnit*, int,
+template __global__ void k_dba<false>(const ColScan*, SegTable, uint8_t*, const uint8_t*, uint8_t*, PageX*, DbaUnit*, int,
                                       uint32_t*);
-template __global__ void k_dba<true>(const ColScan*, SegTable, uint8_t*, const uint8_t*, uint8_t*, PageDev*, DbaUnit*, int,
+template __global__ void k_dba<true>(const ColScan*, SegTable, uint8_t*, const uint8_t*, uint8_t*, PageX*, DbaUnit*, int,
                                      uint32_t*);
 
 }  // namespace pqk

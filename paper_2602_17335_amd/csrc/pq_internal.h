@@ -99,7 +99,7 @@ struct PageDev {
   uint8_t flags;         // bit0: level stream in scratch; bit1: value stream in scratch;
                          // bit2: value stream in the expansion region (DELTA_BYTE_ARRAY)
   int32_t def_len;       // level bytes (V2 header; V1 from the body)
-  int32_t rep_len;       // V2 header
+  uint32_t sbit0;        // compressed pages: first 16-byte unit of the page's element start bits
   uint64_t def_off;      // file offset, or offset inside the page's scratch region
   uint64_t val_off;      // same for the value stream
   uint32_t val_len;
@@ -122,21 +122,24 @@ struct PageDev {
   uint32_t sblk_begin;   // compressed pages: first entry of the page in the Snappy block index
   uint32_t chars_at;     // DELTA_LENGTH_BYTE_ARRAY pages: value-stream offset of the chars
                          // (the end of the lengths' DELTA_BINARY_PACKED stream)
-  // DELTA_BYTE_ARRAY string pages (found by the open-time pass of k_dba):
-  // the encoded value stream (x_src: offset in the file, or in the
-  // decompression layout when x_scratch), its prefix-length stream from 0,
-  // suffix-length stream from x_sfx and suffix bytes from x_chars; the
-  // page's values laid out as PLAIN (u32 length + bytes, xlen bytes) at
-  // x_off of the expansion layout
+};
+static_assert(sizeof(PageDev) == 128, "two cache lines: every tile's wave reads the entry");
+
+// DELTA_BYTE_ARRAY string pages (a table of its own, in files that have any; found
+// by the open-time pass of k_dba): the encoded value stream (x_src: offset in the
+// file, or in the decompression layout when x_scratch), its prefix-length stream
+// from 0, suffix-length stream from x_sfx and suffix bytes from x_chars; the page's
+// values laid out as PLAIN (u32 length + bytes, xlen bytes) at x_off of the
+// expansion layout
+struct PageX {
   uint64_t x_src;
   uint32_t x_len, x_sfx, x_chars, xlen, x_total, x_scratch;
   uint64_t x_off;
   uint32_t x_unit0;      // first unit (DbaUnit)
   uint32_t x_maxlen;     // its longest value
-  uint32_t x_ctx;        // bytes its units keep of the values before them (16-byte steps)
-  uint32_t x_pad_;
-  uint8_t* x_ctxp;       // and where
-  uint64_t sbit_begin;   // compressed pages: first 16-bit entry of the page's element start bits
+  uint8_t* x_ctxp;       // the bytes its units keep of the values before them
+  uint32_t x_ctx;        // how many (16-byte steps)
+  uint32_t pad_;
 };
 
 // A page of an open pass (k_layout .. k_index): its tiles and its entries in
@@ -208,7 +211,7 @@ constexpr int SNAP_SHAPES = 3;
 constexpr uint32_t SBLK_NONE = 0xffffffffu;
 // Start bits of a compressed page's elements, one per stream byte from the
 // 16-byte boundary at or before the stream's first byte (m bytes before it);
-// a page's bits start at an even 16-bit entry, sbit_begin.
+// a page's bits start at the 16-byte unit sbit0.
 __host__ __device__ inline uint32_t snap_bit_words(uint32_t m, uint32_t n) { return (m + n + 31) / 32; }
 
 // One tile: rows [row0, row0 + min(TILE_ROWS, num_values - row0)) of page `page`.
@@ -262,6 +265,7 @@ struct DictSlot {
 struct FileDev {
   const uint8_t* file;         // the file bytes (borrowed device buffer)
   const PageDev* pages;        // page table
+  const PageX* pagex;          // its DELTA_BYTE_ARRAY part (NULL when the file needs none)
   const TileDev* tiles;        // tile index
   const uint32_t* ckl;         // level checkpoints, NLCK per tile
   const Ck* ckv;               // value-stream checkpoints, NSUB per tile

@@ -135,12 +135,11 @@ __device__ __forceinline__ PageDev make_page(const PageHdr& h, uint64_t payload,
   p.v2_compressed = (uint8_t)(h.type == PAGE_DATA_V2 ? h.is_comp : 1);
   p.flags = 0;
   p.def_len = h.type == PAGE_DATA_V2 ? h.def_len : 0;
-  p.rep_len = h.type == PAGE_DATA_V2 ? h.rep_len : 0;
+  p.sbit0 = 0;  // (and no repetition levels: such pages are refused)
   p.def_off = 0; p.val_off = 0; p.val_len = 0;
   p.scratch_len = 0; p.scratch_off = 0; p.row0 = 0;
   p.tile_begin = 0; p.nonnull = 0; p.strck_begin = 0; p.dict_page = ~0u; p.dict_maxlen = 0;
   p.enc_w = 0; p.enc_m = 0; p.delta_first = 0; p.blocks_at = 0; p.sblk_begin = 0; p.chars_at = 0;
-  p.x_src = 0; p.x_len = 0; p.x_sfx = 0; p.x_chars = 0; p.xlen = 0; p.x_total = 0; p.x_scratch = 0; p.x_off = 0;
   return p;
 }
 
@@ -353,7 +352,7 @@ __global__ __launch_bounds__(64) void k_index(const uint8_t* file, const uint8_t
                                               const IxPage* ixs, const uint32_t* flag, const ChunkDev* chunks,
                                               TileDev* tiles, uint32_t* strck, uint32_t* ckl, Ck* ckv, uint32_t* err,
                                               uint64_t file_lim, uint64_t scratch_lim, const uint8_t* xscratch,
-                                              uint64_t xscratch_lim) {
+                                              uint64_t xscratch_lim, const PageX* pagex) {
   __shared__ wr_u4 s_win[WIN / 16];
   // DELTA pages of at most TC tiles: first value, value count and value
   // entry of every tile, so that the block walk reads no tile from memory
@@ -500,7 +499,7 @@ __global__ __launch_bounds__(64) void k_index(const uint8_t* file, const uint8_t
     uint64_t w = ch.type == T_INT32 ? 4 : 8;
     if ((uint64_t)nonnull * w > val_len) { set_err(err, ERR_VALUES, p); return; }
   } else if (enc == E_PLAIN || enc == E_DBA) {
-    if (enc == E_DBA && pg.x_total != nonnull) { set_err(err, ERR_VALUES, p); return; }
+    if (enc == E_DBA && pagex[p].x_total != nonnull) { set_err(err, ERR_VALUES, p); return; }
     uint64_t q = val_off;
     uint32_t t = 0;
     for (uint32_t k = 0; k <= nonnull; ++k) {
@@ -652,7 +651,7 @@ constexpr uint32_t LV_PAY = 1024;         // longest payload of a bit-packed lev
 constexpr uint32_t LV_SLACK = LV_PAY + 64;
 
 // One thread per page of [p0, p1), dictionary pages or the others.
-__global__ void k_layout(uint32_t p0, uint32_t p1, int dicts, PageDev* pages, const ChunkDev* chunks,
+__global__ void k_layout(uint32_t p0, uint32_t p1, int dicts, PageDev* pages, const PageX* pagex, const ChunkDev* chunks,
                          const uint8_t* file, const uint8_t* scratch, uint32_t* err) {
   const uint32_t p = p0 + blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= p1) return;
@@ -685,7 +684,7 @@ __global__ void k_layout(uint32_t p0, uint32_t p1, int dicts, PageDev* pages, co
     }
     pg.flags = in_scratch ? 3 : 0;
   } else {
-    def_off = pg.payload + (uint64_t)pg.rep_len;
+    def_off = pg.payload;
     def_len = (uint64_t)pg.def_len;
     if (in_scratch) {
       val_off = pg.scratch_off;
@@ -693,17 +692,17 @@ __global__ void k_layout(uint32_t p0, uint32_t p1, int dicts, PageDev* pages, co
       pg.flags = 2;
     } else {
       val_off = def_off + def_len;
-      val_len = pg.comp_size - (uint64_t)pg.rep_len - def_len;
+      val_len = pg.comp_size - def_len;
       pg.flags = 0;
     }
   }
-  if (pg.encoding == E_DBA && type == T_BYTE_ARRAY && pg.x_total == DBA_UNSUPPORTED) {
+  if (pg.encoding == E_DBA && type == T_BYTE_ARRAY && pagex[p].x_total == DBA_UNSUPPORTED) {
     pg.encoding = E_UNDECODED;  // reported by the decode kernels when the column is scanned
   } else if (pg.encoding == E_DBA && type == T_BYTE_ARRAY) {
     // DELTA_BYTE_ARRAY: the values, expanded to the PLAIN layout by k_dba,
     // are indexed and decoded like a PLAIN page
-    val_off = pg.x_off;
-    val_len = pg.xlen;
+    val_off = pagex[p].x_off;
+    val_len = pagex[p].xlen;
     pg.flags = (uint8_t)((pg.flags & 1) | 4);
   }
   pg.def_off = def_off;
@@ -1048,8 +1047,8 @@ __global__ __launch_bounds__(256) void k_tiles(const IxPage* ixs, uint32_t nix, 
 // k_values: one thread per data page, after its levels: the checks of its value
 // stream's header and the facts the later kernels read from it.
 // ---------------------------------------------------------------------------
-__global__ void k_values(const IxPage* ixs, uint32_t nix, PageDev* pages, const ChunkDev* chunks, OpenBufs bufs,
-                         const uint32_t* flag, uint32_t* err) {
+__global__ void k_values(const IxPage* ixs, uint32_t nix, PageDev* pages, const PageX* pagex, const ChunkDev* chunks,
+                         OpenBufs bufs, const uint32_t* flag, uint32_t* err) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nix || flag[i]) return;
   const uint32_t p = ixs[i].page;
@@ -1067,7 +1066,7 @@ __global__ void k_values(const IxPage* ixs, uint32_t nix, PageDev* pages, const 
     const uint64_t w = ch.type == T_INT32 ? 4 : 8;
     if ((uint64_t)nonnull * w > val_len) set_err(err, ERR_VALUES, p);
   } else if (enc == E_DBA) {
-    if (pg.x_total != nonnull) set_err(err, ERR_VALUES, p);
+    if (pagex[p].x_total != nonnull) set_err(err, ERR_VALUES, p);
   } else if (enc == E_PLAIN_DICT || enc == E_RLE_DICT) {
     if (pg.dict_page == ~0u) { set_err(err, ERR_DICT_MISSING, p); return; }
     if (nonnull > 0) {

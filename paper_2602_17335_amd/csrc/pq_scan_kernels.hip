@@ -1097,7 +1097,7 @@ __global__ __launch_bounds__(64) void k_snappy(const ColScan* cols, SegTable seg
   if ((mode == 0 && pg.kind == PAGE_DICT) || (mode == 1 && !open_sel_ok(cs, pg)) || sblk[pg.sblk_begin] != SBLK_NONE)
     return;
   uint64_t src_off = pg.payload, src_len64 = pg.comp_size;
-  if (pg.kind == PAGE_DATA_V2) { src_off += (uint64_t)pg.rep_len + (uint64_t)pg.def_len; src_len64 -= (uint64_t)pg.rep_len + (uint64_t)pg.def_len; }
+  if (pg.kind == PAGE_DATA_V2) { src_off += (uint64_t)pg.def_len; src_len64 -= (uint64_t)pg.def_len; }
   const uint8_t* src = cs.fd.file + src_off;
   uint8_t* dst = ws + cs.ws_scratch + (pg.scratch_off - cs.scratch_base);
   lds_u8* ring = (lds_u8*)&s_ring[0];

@@ -58,7 +58,7 @@ struct SnapSrc {
 __device__ __forceinline__ SnapSrc snap_src(const uint8_t* file, const PageDev& pg) {
   uint64_t off = pg.payload, len = pg.comp_size;
   if (pg.kind == PAGE_DATA_V2) {
-    const uint64_t lev = (uint64_t)pg.rep_len + (uint64_t)pg.def_len;
+    const uint64_t lev = (uint64_t)pg.def_len;
     off += lev;
     len = len > lev ? len - lev : 0;
   }
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(SX_WG) void k_snap_index(const ColScan* cols, SegTa
   if (total == 0) return;
   const SnapSrc src = snap_src(cs->fd.file, *pg);
   uint32_t* sblk = cs->fd.sblk + pg->sblk_begin;
-  uint32_t* bits = reinterpret_cast<uint32_t*>(cs->fd.sbits + pg->sbit_begin);
+  uint32_t* bits = reinterpret_cast<uint32_t*>(cs->fd.sbits + 8ull * pg->sbit0);
   const uint32_t nbits = snap_bit_words(src.m, src.n);  // words of the page's start bits
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint32_t iend = src.m + src.n;
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(SbShape<OUT>::WG, 4) void k_snappy_blk(const ColSca
     if (tid == 0) set_err(err, ERR_SNAPPY, p);
     return;
   }
-  const uint16_t* bits = cs->fd.sbits + pg->sbit_begin;
+  const uint16_t* bits = cs->fd.sbits + 8ull * pg->sbit0;
   uint8_t* dst = ws + cs->ws_scratch + (pg->scratch_off - cs->scratch_base) + (uint64_t)kb * SNAP_BLOCK;
   const uint32_t blen = min(SNAP_BLOCK, total - kb * SNAP_BLOCK);
   const uint32_t q0 = src.m + i0, qe = src.m + i1;
