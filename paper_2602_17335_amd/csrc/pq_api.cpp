@@ -1793,6 +1793,7 @@ constexpr uint64_t WS_HEADER = 256;
 
 struct Plan {
   std::vector<ColScan> cols;
+  int32_t rg_begin = 0, rg_end = 0;
   int64_t rows = 0;
   uint64_t ws_cols = 0, ws_which = 0, ws_total = 0;
   // launch lists
@@ -1880,6 +1881,8 @@ void col_setup(pq_file f, int c, int32_t rg_b, int32_t rg_e, int64_t rows, uint6
 pq_status make_plan(pq_file f, uint64_t mask, int32_t rg_b, int32_t rg_e, Plan& P) {
   if (rg_b < 0 || rg_e > f->nrg || rg_b > rg_e) return fail(PQ_EINVAL, "bad row-group range [%d, %d)", rg_b, rg_e);
   if (f->ncols < 64 && (mask >> f->ncols)) return fail(PQ_EINVAL, "column mask selects missing columns");
+  P.rg_begin = rg_b;
+  P.rg_end = rg_e;
   P.rows = f->rg_row0[rg_e] - f->rg_row0[rg_b];
   int ncs = __builtin_popcountll(mask);
   P.ws_cols = WS_HEADER;
@@ -1994,10 +1997,17 @@ static FixedKernel fixed_kernel(int K) {
   }
 }
 
-// The workspace header of a plan: the cleared error word, the column table
+// The error word of a scan that writes `chars` bytes to string column cs: a chars
+// buffer too small is reported before whatever the decode kernels find.
+static uint32_t capacity_error(const ColScan& cs, int64_t chars) {
+  return (uint64_t)chars > cs.chars_capacity ? ERR_CAPACITY | ((uint32_t)cs.col << 8) : 0u;
+}
+
+// The workspace header of a plan: the error word (cleared, or err0), the column table
 // and the string-column list, in one host-to-device copy.
-static pq_status upload_header(Plan& P, uint8_t* ws, hipStream_t s) {
+static pq_status upload_header(Plan& P, uint8_t* ws, hipStream_t s, uint32_t err0 = 0) {
   std::vector<uint8_t> hdr(P.ws_which + sizeof(int32_t) * P.str_cols.size(), 0);
+  memcpy(hdr.data(), &err0, sizeof(err0));
   if (!P.cols.empty()) memcpy(hdr.data() + P.ws_cols, P.cols.data(), sizeof(ColScan) * P.cols.size());
   if (!P.str_cols.empty()) memcpy(hdr.data() + P.ws_which, P.str_cols.data(), sizeof(int32_t) * P.str_cols.size());
   HIP_OR(hipMemcpyAsync(ws, hdr.data(), hdr.size(), hipMemcpyHostToDevice, s));
@@ -2044,7 +2054,12 @@ static pq_status enqueue_decompress(pq_file f, const Plan& P, const ColScan* d_c
 
 // Decompression and the upload.
 static pq_status enqueue_front(pq_file f, Plan& P, uint8_t* ws, uint32_t* err, hipStream_t s) {
-  pq_status st = upload_header(P, ws, s);
+  uint32_t err0 = 0;
+  for (size_t k = P.str_cols.size(); k-- > 0;) {
+    const ColScan& cs = P.cols[(size_t)P.str_cols[k]];
+    if (const uint32_t e = capacity_error(cs, chars_of(f, cs.col, P.rg_begin, P.rg_end))) err0 = e;
+  }
+  pq_status st = upload_header(P, ws, s, err0);
   if (st != PQ_OK) return st;
   return enqueue_decompress(f, P, reinterpret_cast<ColScan*>(ws + P.ws_cols), ws, err, s);
 }
@@ -2679,6 +2694,10 @@ pq_status enqueue_batch(const BatchPlan& P, const pq_tuning& T, uint8_t* ws, hip
   // runs or units, queue bounds and heads, in one copy
   std::vector<uint8_t> hdr(direct ? P.ws_units + sizeof(Segment) * run_segs.size() : P.ws_hdr_end, 0);
   auto put = [&](uint64_t at, const void* src, size_t n) { if (n) memcpy(hdr.data() + at, src, n); };
+  for (size_t k = P.str_cols.size(); k-- > 0;) {
+    const size_t c = (size_t)P.str_cols[k];
+    if (const uint32_t e = capacity_error(P.cols[c], P.chars[c])) put(0, &e, sizeof(e));
+  }
   put(P.ws_cols, P.cols.data(), sizeof(ColScan) * P.cols.size());
   put(P.ws_which, P.str_cols.data(), sizeof(int32_t) * P.str_cols.size());
   put(P.ws_snappy, P.snappy_segs.data(), sizeof(Segment) * P.snappy_segs.size());
