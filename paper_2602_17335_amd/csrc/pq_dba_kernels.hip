@@ -18,6 +18,11 @@ namespace pqk {
 
 constexpr uint32_t DBA_PREV = 16384;  // longest value (a page with a longer one: PQ_EUNSUPPORTED when scanned)
 constexpr uint32_t DBA_SEQ = 1024;    // LDS window over a length stream
+// Stretches of a group with a value longer than this: all lanes copy one value at a
+// time (a lane per value idles 64 less the few that fit the buffer).  A scan of 60 MB
+// of values, a lane per value / all lanes: up to 100 bytes 265 / 303 us, 150 380 / 352
+// (of shared prefixes 361 / 374), 200 540 / 442, 600 2,190 / 750, 4,000 10,050 / 896.
+constexpr uint32_t DBA_WHOLE = 160;
 
 typedef uint32_t u32x4d __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) u32x4d lds_u32x4d;
@@ -175,6 +180,32 @@ __device__ __forceinline__ void lane_lds_copy(lds_u8* dst, const lds_u32* src32,
     for (uint32_t k = 0; k < 8; ++k)
       if (k < left) dst[i + k] = (uint8_t)((k < 4 ? lo : hi) >> (8 * (k & 3)));
   }
+}
+
+// All lanes copy n bytes of LDS from byte a of src to byte d of dst (no overlap),
+// four dwords each in flight (reads run up to 4 bytes past the source).
+__device__ __forceinline__ void wave_lds_copy(lds_u32* dst, uint32_t d, const lds_u32* src, uint32_t a, uint32_t n) {
+  const uint32_t lane = threadIdx.x & 63, h = min((4u - (d & 3u)) & 3u, n);
+  lds_u8* db = (lds_u8*)dst;
+  const lds_u8* sb = (const lds_u8*)src;
+  if (lane < h) db[d + lane] = sb[a + lane];
+  d += h;
+  a += h;
+  n -= h;
+  const uint32_t m = n >> 2, q = d >> 2, j = a >> 2, f = a & 3u;
+  for (uint32_t k = lane; k < m; k += 256) {
+    uint32_t lo[4], hi[4];
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint32_t i = j + min(k + 64 * u, m - 1);
+      lo[u] = src[i];
+      hi[u] = src[i + 1];
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u)
+      if (k + 64 * u < m) dst[q + k + 64 * u] = __builtin_amdgcn_alignbyte(hi[u], lo[u], f);
+  }
+  if (lane < (n & 3u)) db[d + 4 * m + lane] = sb[a + 4 * m + lane];
 }
 
 // ---------------------------------------------------------------------------
@@ -355,6 +386,35 @@ __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, 
   const uint8_t* chars = src + px.x_chars;
   const uint32_t nchars = px.x_len - px.x_chars;
   lds_u8* ob = (lds_u8*)&s_out[0];
+  lds_u32 *ob32 = (lds_u32*)&s_out[0], *prev32 = (lds_u32*)&s_prev[0], *win32 = (lds_u32*)&s_win[0];
+  // suffix bytes [at, at + m) to the window, m <= OUT; returns where the first lies
+  auto load_win = [&](uint32_t at, uint32_t m) -> uint32_t {
+    const uintptr_t g0 = (uintptr_t)(chars + at) & ~(uintptr_t)15;
+    const uint32_t lead = (uint32_t)((uintptr_t)(chars + at) - g0);
+    const uintptr_t gend = (uintptr_t)(chars + nchars);
+    for (uint32_t k = lane; 16 * k < lead + m; k += 64) {
+      u32x4d v = {0u, 0u, 0u, 0u};
+      if (g0 + 16 * k < gend) v = *(glb_u32x4d*)(g0 + 16 * k);
+      *(lds_u32x4d*)((lds_u32*)&s_win[0] + 4 * k) = v;
+    }
+    return lead;
+  };
+  // m bytes of the LDS buffer from byte head on to o (whose place in its 16 bytes is head)
+  auto flush = [&](uint8_t* o, uint32_t head, uint32_t m) {
+    uint8_t* g = o - head;
+    const uint32_t tot = head + m;
+    for (uint32_t k = 16 * lane; k < tot; k += 1024) {
+      const u32x4d v = *(const lds_u32x4d*)((lds_u32*)&s_out[0] + (k >> 2));
+      if (k >= head && k + 16 <= tot) {
+        *(__attribute__((address_space(1))) u32x4d*)(g + k) = v;
+      } else {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (uint32_t i = 0; i < 16; ++i)
+          if (k + i >= head && k + i < tot) g[k + i] = (uint8_t)(w[i >> 2] >> (8 * (i & 3)));
+      }
+    }
+  };
   while (P.done < last) {
     const uint32_t n = min(64u, last - P.done), at = P.done;
     DbaStream ps{}, ss{};
@@ -399,84 +459,89 @@ __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, 
     }
     s_so[lane] = si - sl;
     s_par[lane] = (uint8_t)par;
-    // runs of values [a, b) whose expanded bytes fit the LDS buffer
+    // stretches of the group's expanded bytes that fit the LDS buffer: whole
+    // values [a, b), or a part of one value over the buffer
     for (uint32_t a = 0; a < n;) {
       const uint32_t o0 = a ? (uint32_t)__builtin_amdgcn_readlane((int)oi, (int)(a - 1)) : 0u;
       const uint32_t s0 = a ? (uint32_t)__builtin_amdgcn_readlane((int)si, (int)(a - 1)) : 0u;
       const uint64_t fit = __ballot(lane >= a && lane < n && oi - o0 <= OUT);
       uint32_t b = a + (uint32_t)__popcll(fit);
-      const bool alone = b == a;  // one value over the buffer
-      if (alone) {
+      if (b == a) {  // one value over the buffer
         b = a + 1;
         const uint32_t vp = (uint32_t)__builtin_amdgcn_readlane((int)pl, (int)a);
-        const uint32_t vl = (uint32_t)__builtin_amdgcn_readlane((int)L, (int)a);
-        wave_sync();
-        for (uint32_t i = lane; i < 4 + vl; i += 64) {
-          uint32_t x;
-          if (i < 4) {
-            x = (vl >> (8 * i)) & 0xffu;
-          } else if (i - 4 < vp) {
-            x = prev[i - 4];
-          } else {
-            x = chars[c + s0 + (i - 4 - vp)];
-            prev[i - 4] = (uint8_t)x;
+        const uint32_t vn = 4 + (uint32_t)__builtin_amdgcn_readlane((int)L, (int)a);
+        for (uint32_t x0 = 0; x0 < vn; x0 += OUT) {
+          const uint32_t x1 = min(vn, x0 + OUT), xs = max(x0, 4 + vp);  // its bytes; those from xs on are suffix
+          uint32_t lead = 0;
+          wave_sync();
+          if (xs < x1) lead = load_win(c + s0 + (xs - 4 - vp), x1 - xs);
+          const uint32_t head = (uint32_t)((uintptr_t)(out + pos + o0 + x0) & 15);
+          wave_sync();
+          const uint32_t xp = max(x0, 4u);
+          if (x0 == 0 && lane < 4) ob[head + lane] = (uint8_t)((vn - 4) >> (8 * lane));
+          if (xp < min(x1, 4 + vp)) wave_lds_copy(ob32, head + (xp - x0), prev32, xp - 4, min(x1, 4 + vp) - xp);
+          if (xs < x1) {
+            wave_lds_copy(ob32, head + (xs - x0), win32, lead, x1 - xs);
+            wave_lds_copy(prev32, xs - 4, win32, lead, x1 - xs);
           }
-          out[pos + o0 + i] = (uint8_t)x;
+          wave_sync();
+          flush(out + pos + o0 + x0, head, x1 - x0);
         }
         wave_sync();
       } else {
         const uint32_t s1 = (uint32_t)__builtin_amdgcn_readlane((int)si, (int)(b - 1));
         const uint32_t o1 = (uint32_t)__builtin_amdgcn_readlane((int)oi, (int)(b - 1));
-        // the run's suffix bytes: window byte lead + i is suffix byte c + s0 + i
-        const uintptr_t g0 = (uintptr_t)(chars + c + s0) & ~(uintptr_t)15;
-        const uint32_t lead = (uint32_t)((uintptr_t)(chars + c + s0) - g0);
-        const uintptr_t gend = (uintptr_t)(chars + nchars);
         wave_sync();
-        for (uint32_t k = lane; 16 * k < lead + (s1 - s0); k += 64) {
-          u32x4d v = {0u, 0u, 0u, 0u};
-          if (g0 + 16 * k < gend) v = *(glb_u32x4d*)(g0 + 16 * k);
-          *(lds_u32x4d*)((lds_u32*)&s_win[0] + 4 * k) = v;
-        }
+        const uint32_t lead = load_win(c + s0, s1 - s0);
         // the LDS buffer has the output's place in its 16 bytes
         const uint32_t head = (uint32_t)((uintptr_t)(out + pos + o0) & 15);
         wave_sync();
-        if (lane >= a && lane < b) {
-          lds_u8* d = ob + head + (oi - 4 - L - o0);
+        if (__ballot(lane >= a && lane < b && L > DBA_WHOLE)) {
+          // long values: one after the other
+          uint32_t from = 0, keep = ~0u;
+          for (uint32_t j = a; j < b; ++j) {
+            const uint32_t vp = (uint32_t)__builtin_amdgcn_readlane((int)pl, (int)j);
+            const uint32_t vl = (uint32_t)__builtin_amdgcn_readlane((int)L, (int)j);
+            const uint32_t at = head + (uint32_t)__builtin_amdgcn_readlane((int)oi, (int)j) - o0 - 4 - vl;
+            const uint32_t w0 = lead + (uint32_t)__builtin_amdgcn_readlane((int)(si - sl), (int)j) - s0;
+            if (lane < 4) ob[at + lane] = (uint8_t)(vl >> (8 * lane));
+            if (vp) wave_lds_copy(ob32, at + 4, j == a ? prev32 : ob32, j == a ? 0u : from, vp);
+            if (vl > vp) wave_lds_copy(ob32, at + 4 + vp, win32, w0, vl - vp);
+            wave_sync();
+            from = at + 4;
+            keep = min(keep, vp);
+          }
+          // the last one is the next stretch's predecessor; its bytes that all the
+          // stretch's values share with the one before it are there
+          const uint32_t vl = (uint32_t)__builtin_amdgcn_readlane((int)L, (int)(b - 1));
+          if (vl > keep) wave_lds_copy(prev32, keep, ob32, from + keep, vl - keep);
+        } else {
+          if (lane >= a && lane < b) {
+            lds_u8* d = ob + head + (oi - 4 - L - o0);
 #pragma unroll
-          for (uint32_t k = 0; k < 4; ++k) d[k] = (uint8_t)(L >> (8 * k));
-          d += 4;
-          lane_lds_copy(d + pl, (const lds_u32*)&s_win[0], lead + (si - sl - s0), sl);
-          // the prefix, from its end: pieces of the values with shorter
-          // prefixes, the rest from the value before the run
-          uint32_t hi = pl, j = par;
-          while (hi) {
-            if (j == 0xffu || j < a) {
-              lane_lds_copy(d, (const lds_u32*)&s_prev[0], 0, hi);
-              break;
+            for (uint32_t k = 0; k < 4; ++k) d[k] = (uint8_t)(L >> (8 * k));
+            d += 4;
+            lane_lds_copy(d + pl, (const lds_u32*)&s_win[0], lead + (si - sl - s0), sl);
+            // the prefix, from its end: pieces of the values with shorter
+            // prefixes, the rest from the value before the run
+            uint32_t hi = pl, j = par;
+            while (hi) {
+              if (j == 0xffu || j < a) {
+                lane_lds_copy(d, (const lds_u32*)&s_prev[0], 0, hi);
+                break;
+              }
+              const uint32_t lo = bp[j];
+              lane_lds_copy(d + lo, (const lds_u32*)&s_win[0], lead + (s_so[j] - s0), hi - lo);
+              hi = lo;
+              j = s_par[j];
             }
-            const uint32_t lo = bp[j];
-            lane_lds_copy(d + lo, (const lds_u32*)&s_win[0], lead + (s_so[j] - s0), hi - lo);
-            hi = lo;
-            j = s_par[j];
           }
+          wave_sync();
+          // the run's last value is the next one's predecessor
+          const uint32_t vl = (uint32_t)__builtin_amdgcn_readlane((int)L, (int)(b - 1));
+          for (uint32_t i = lane; i < vl; i += 64) prev[i] = ob[head + (o1 - o0) - vl + i];
         }
-        wave_sync();
-        // the run's last value is the next one's predecessor
-        const uint32_t vl = (uint32_t)__builtin_amdgcn_readlane((int)L, (int)(b - 1));
-        for (uint32_t i = lane; i < vl; i += 64) prev[i] = ob[head + (o1 - o0) - vl + i];
-        uint8_t* g = out + pos + o0 - head;  // 16-byte aligned
-        const uint32_t tot = head + (o1 - o0);
-        for (uint32_t k = 16 * lane; k < tot; k += 1024) {
-          const u32x4d v = *(const lds_u32x4d*)((lds_u32*)&s_out[0] + (k >> 2));
-          if (k >= head && k + 16 <= tot) {
-            *(__attribute__((address_space(1))) u32x4d*)(g + k) = v;
-          } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (uint32_t i = 0; i < 16; ++i)
-              if (k + i >= head && k + i < tot) g[k + i] = (uint8_t)(w[i >> 2] >> (8 * (i & 3)));
-          }
-        }
+        flush(out + pos + o0, head, o1 - o0);
         wave_sync();
       }
       a = b;

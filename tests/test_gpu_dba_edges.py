@@ -1,7 +1,8 @@
 """GPU parity of DELTA_BYTE_ARRAY pages around a unit of 256 values and around the
 longest value (1,024 bytes) of the kernel for pages of short values: value counts
 next to a unit's end, longest values of 1,023, 1,024 and 1,025 bytes whose prefixes
-reach over the start of a unit, and columns that hold pages of both kernels, in
+reach over the start of a unit, values and prefixes next to the lengths from which
+values are copied by all lanes and in pieces, and columns that hold pages of both kernels, in
 single scans, in batches of both forms and streamed.  Every output buffer is compared
 with the oracle byte for byte."""
 import io
@@ -44,6 +45,21 @@ def test_unit_and_length_edges(n, longest):
     vals = _values(n, longest, rng)
     for nulls in (False, True):
         check_file(_file(vals, nulls, rng), label=f"dba {n} values, longest {longest}, nulls {nulls}")
+
+
+@pytest.mark.parametrize("near", [160, 1020, 2040, 4092, 8188, 16_380])
+def test_lengths_and_prefixes_near(near):
+    """Values and prefixes that end a few bytes from a length at which the expansion
+    changes its way: copied by a lane or by all, in one piece or in several."""
+    rng = np.random.default_rng(near)
+    base = rng.integers(0, 256, 16_384, dtype=np.uint8).tobytes()
+    vals = []
+    for i in range(400):
+        cut = max(0, min(near + int(rng.integers(-9, 10)), 16_384)) if rng.random() < 0.8 else int(rng.integers(0, near))
+        tail = rng.integers(0, 256, int(rng.choice([0, 1, 3, 5, 300])), dtype=np.uint8).tobytes()
+        vals.append((base[:cut] + tail)[:16_384])
+    for nulls in (False, True):
+        check_file(_file(vals, nulls, rng, page=300_000 if nulls else 1 << 24), label=f"dba near {near}, nulls {nulls}")
 
 
 def _mixed(rng, compression):
