@@ -1115,7 +1115,6 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   }
   f->fd.file = file;
   f->fd.pages = f->d_pages;
-  f->fd.pagex = f->d_pagex;
   f->fd.tiles = f->d_tiles;
   f->fd.ckl = f->d_ckl;
   f->fd.ckv = f->d_ckv;
@@ -1123,7 +1122,6 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
   f->fd.sblk = f->d_sblk;
   f->fd.sblk_page = f->d_sblk_page;
   f->fd.sbits = f->d_sbits;
-  f->fd.dbau = f->d_dbau;
   f->fd.tpfx = f->d_tpfx;
   f->fd.tpfx2 = f->d_tpfx2;
   const uint64_t flim = (len + 15) & ~15ull;  // the file is readable up to len rounded up to 16
@@ -1196,7 +1194,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         memset(&cs, 0, sizeof(cs));
         cs.fd.file = file;
         cs.fd.pages = f->d_pages;
-        cs.fd.pagex = f->d_pagex;
+        cs.pagex = f->d_pagex;
         cs.type = T_BYTE_ARRAY;
         cs.optional = f->cols[c].optional;
         cs.col = c;
@@ -1831,6 +1829,8 @@ void col_setup(pq_file f, int c, int32_t rg_b, int32_t rg_e, int64_t rows, uint6
   ColScan& cs = k.cs;
   memset(&cs, 0, sizeof(cs));
   cs.fd = f->fd;
+  cs.pagex = f->d_pagex;
+  cs.dbau = f->d_dbau;
   cs.type = f->cols[c].type;
   cs.optional = f->cols[c].optional;
   cs.width = cs.type == T_INT32 ? 4 : (cs.type == T_BYTE_ARRAY ? 0 : 8);

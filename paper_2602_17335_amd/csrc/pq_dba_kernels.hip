@@ -247,13 +247,13 @@ __global__ __launch_bounds__(64, SMALL ? 4 : 2) void k_dba(const ColScan* cols, 
   const FileDev fd = csp->fd;
   const DbaUnit* unit = nullptr;
   if (mode == 2) {
-    unit = fd.dbau + p;
+    unit = csp->dbau + p;
     p = unit->page;
     if (p == ~0u) return;
   }
   const PageDev pg = fd.pages[p];
   if (pg.kind == PAGE_DICT || pg.encoding != E_DBA || csp->type != T_BYTE_ARRAY) return;
-  const PageX px = fd.pagex[p];
+  const PageX px = csp->pagex[p];
   if (mode == 2 && (px.x_maxlen <= DBA_SMALL) != SMALL) return;
   // the decompression layout (file-wide offsets)
   const uint8_t* sbase = open_scratch ? open_scratch : ws + csp->ws_scratch - csp->scratch_base;

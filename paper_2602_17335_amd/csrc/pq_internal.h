@@ -265,7 +265,6 @@ struct DictSlot {
 struct FileDev {
   const uint8_t* file;         // the file bytes (borrowed device buffer)
   const PageDev* pages;        // page table
-  const PageX* pagex;          // its DELTA_BYTE_ARRAY part (NULL when the file needs none)
   const TileDev* tiles;        // tile index
   const uint32_t* ckl;         // level checkpoints, NLCK per tile
   const Ck* ckv;               // value-stream checkpoints, NSUB per tile
@@ -277,7 +276,6 @@ struct FileDev {
   const uint32_t* sblk_page;   // page of each Snappy block
   uint16_t* sbits;             // start bits of the Snappy elements (written with sblk)
   const DictSlot* dicts;       // resident dictionaries, one per chunk (col * nrg + rg)
-  const DbaUnit* dbau;         // units of the DELTA_BYTE_ARRAY pages
 };
 
 // Per-scan, per-selected-column table (built on the host, copied into the
@@ -307,6 +305,9 @@ struct ColScan {
   uint64_t ws_edge;       // workspace offset of per-tile validity edge words (OPTIONAL columns)
   int32_t open_sel;       // open-time decompression: 0 every page, 1 dictionary pages, 2 data pages
   int32_t pad_;
+  // the file's DELTA_BYTE_ARRAY tables (NULL when it has no such pages)
+  const PageX* pagex;
+  const DbaUnit* dbau;
 };
 // Whether the open-time decompression pass of ColScan cs takes page pg.
 __host__ __device__ inline bool open_sel_ok(const ColScan& cs, const PageDev& pg) {
