@@ -2082,7 +2082,11 @@ static pq_status enqueue_str_total(pq_file f, const Plan& P, const ColScan* d_co
 // fixed-width columns (5 kinds) at 6M rows (76,000) 338 -> 333 us, at 8M rows
 // (101,600) 446 -> 455 us; six PLAIN columns (2 kinds) at 2M rows (11,700) 45 -> 44
 // us, at 4M rows (23,400) 70 -> 74 us; three string columns (1 kind) at 2M rows
-// (5,900) 120 -> 110 us, at 4M rows (11,700) 148 -> 163 us.
+// (5,900) 120 -> 110 us, at 4M rows (11,700) 148 -> 163 us.  One kind of OPTIONAL columns
+// has no launch to save but that of the string totals, and its tiles take longer in
+// the larger kernel: alone and with 100,000 rows PLAIN strings 48.8 -> 53.6 us, BYTE_STREAM_SPLIT
+// 12.0 -> 12.9, PLAIN INT32 8.9 -> 9.8; strings of slot dictionaries, as fast in both, gain
+// the launch (a scan 29.4 -> 28.5 us).
 constexpr uint32_t ALL_UNITS = 3000;
 
 // The segments of every kind in one table (units: their tiles), the slowest
@@ -2107,6 +2111,7 @@ static bool all_segments(const Plan& P, std::vector<Segment>& segs, uint32_t& un
   add(P.fixed_segs[FX_WIDE], TK_FIXED2);
   add(P.fixed_segs[0], TK_FIXED0);
   units = (uint32_t)n;
+  if (kinds == 1 && P.prep_segs.empty() && P.str_segs[1].empty()) return false;
   return n > 0 && segs.size() <= (size_t)MAX_SEGS && n <= (uint64_t)ALL_UNITS * kinds * (kinds + 1) && P.str_cols.size() <= 64;
 }
 
