@@ -1282,6 +1282,9 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
     enum { C_LEVELS, C_STRINGS, C_DI, C_DL, NCHAINS };
     std::vector<IxPage> ixs(nix);
     std::vector<std::pair<uint32_t, uint32_t>> lists[NCHAINS];  // (stream bytes, page of the list)
+    auto string_list = [](uint32_t len, int32_t n) {  // (those of few values: short ones)
+      return long_strings(len, n > 0 ? (uint64_t)n : 0) ? std::min(len, CHAIN_SMALL) : len;
+    };
     uint64_t nlv = 0, nvp = 0, nblk = 0, tile0 = 0, ntl = 0;
     for (uint32_t i = 0; i < nix; ++i) {
       const PageDev& pg = f->pages[plist[i]];
@@ -1289,7 +1292,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
       IxPage& x = ixs[i];
       x = IxPage{plist[i], 0, 0, 0, 0, 0, 0, ~0u};
       if (P.dict) {
-        if (str) lists[C_STRINGS].push_back({pg.uncomp_size, i});
+        if (str) lists[C_STRINGS].push_back({string_list(pg.uncomp_size, pg.num_values), i});
         continue;
       }
       const uint32_t nv = pg.num_values > 0 ? (uint32_t)pg.num_values : 0u;
@@ -1315,7 +1318,7 @@ static pq_status open_impl(const void* dev_buf, uint64_t len, pq_stream stream, 
         nblk += ((uint64_t)nv + 127) / 128 + 1;  // blocks hold 128 values or more
         lists[C_DL].push_back({pg.val_len, i});
       } else if (str && (pg.encoding == E_PLAIN || pg.encoding == E_DBA)) {
-        lists[C_STRINGS].push_back({pg.val_len, i});
+        lists[C_STRINGS].push_back({string_list(pg.val_len, pg.num_values), i});
       }
     }
     if (nlv > 0xffffffffull || nvp > 0xffffffffull || nblk > 0xffffffffull) { cleanup_open(); free_handle(f); return fail(PQ_EUNSUPPORTED, "too many stream pieces"); }

@@ -163,6 +163,12 @@ struct OpenBufs {
 // Streams of at most this many bytes take the chain kernels' workgroups of 256
 // threads (8 KiB segments, five per CU), longer ones those of 1024 (32 KiB).
 constexpr uint32_t CHAIN_SMALL = 8192;
+// Whether a string stream of `len` bytes has so few values, 4 KiB each or more, that
+// one thread follows them from one to the next (1 us each) instead of the chain
+// kernels, which look at every byte (8 to 20 us per 32 KiB, and segments of such streams
+// cannot be linked: two dictionaries of 500 values of 45 KB 4.2 ms, so 1.3 ms; of
+// values of 3 KB the chain kernels 5.4 ms, one thread 6.1 ms).
+__host__ __device__ inline bool long_strings(uint64_t len, uint64_t n) { return n * 4096 <= len; }
 // A page whose value stream's 32 KiB segments are done side by side: segments
 // [seg0, seg0 + nseg) of its group, from base0 on among those of all groups.
 enum : int { SEG_STR, SEG_DI, SEG_DL, SEG_KINDS };

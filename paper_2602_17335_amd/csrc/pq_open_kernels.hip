@@ -1126,6 +1126,20 @@ __global__ __launch_bounds__(NT) void k_strings(const IxPage* ixs, const uint32_
   uint32_t* ck = strck + pg.strck_begin;
   const uint32_t iend = st.m + st.len;
   uint32_t ip = st.m, k = 0, maxlen = 0;
+  if (long_strings(st.len, n)) {
+    if (tid != 0) return;
+    while (k < n && iend - ip >= 4) {
+      const uint32_t len = ld_u32(st.base, ip);
+      if (len > iend - ip - 4) break;
+      if (k % STR_CK == 0) ck[k / STR_CK] = ip - st.m;
+      maxlen = max(maxlen, len);
+      ip += 4 + len;
+      ++k;
+    }
+    if (dict) pg.dict_maxlen = maxlen;
+    if (k < n) flag[ixi] = 1;
+    return;
+  }
   if (tid == 0) s_max = 0;
   auto step = [](uint32_t lo, uint32_t, uint32_t left, uint32_t) -> uint32_t { return str_step(lo, left); };
   while (ip < iend && k < n) {
