@@ -227,8 +227,8 @@ pq_status pq_scan_noalloc(pq_file f, uint64_t col_mask, int32_t rg_begin, int32_
  * the handle -- and tile prefix) and frees it; host_buf is borrowed until
  * pq_close and should be pinned (hipHostMalloc, or a pinned torch tensor),
  * or the copies cannot overlap.  pq_plan of such a handle includes in
- * workspace_bytes two staging slots (each the largest row group's selected
- * chunks) and a column table per row group.  pq_scan, pq_scan_noalloc and
+ * workspace_bytes two staging slots (each the file range that spans the
+ * largest row group's selected chunks) and a column table per row group.  pq_scan, pq_scan_noalloc and
  * the batch calls refuse such a handle (PQ_EINVAL).
  */
 pq_status pq_open_host(const void* host_buf, uint64_t len, pq_stream stream, pq_file* out);

@@ -2079,8 +2079,8 @@ static pq_status enqueue_str_total(pq_file f, const Plan& P, const ColScan* d_co
 
 // Scans of at most ALL_UNITS k (k + 1) tiles of k kinds decode in one launch of
 // k_decode_all: it saves k - 1 launches and runs kinds with different bounds
-// side by side, but holds fewer waves per SIMD.  Measured, one launch per kind
-// against one for all: the wide table's 6 kinds at 1M rows (15,600 tiles) 169 ->
+// side by side, but holds fewer waves per SIMD.  Measured, scans one after another
+// with one launch per kind against one for all: the wide table's 6 kinds at 1M rows (15,600 tiles) 169 ->
 // 96 us, at 4M rows (62,500) 391 -> 374 us, at 8M rows (125,000) 772 -> 773 us; its
 // fixed-width columns (5 kinds) at 6M rows (76,000) 338 -> 333 us, at 8M rows
 // (101,600) 446 -> 455 us; six PLAIN columns (2 kinds) at 2M rows (11,700) 45 -> 44
@@ -2646,7 +2646,7 @@ void make_run_segs(const BatchPlan& P, std::vector<Segment>& segs, uint32_t& uni
 // SIMD for k_decode_all's 4.  Measured, the
 // former default of 8 queues, 8 waves per CU and 2 tiles per unit / the best of 24
 // schedules with queues / one wave per tile: 64 files of up to 1M rows 754 / 602 /
-// 444 us, 16 files of up to 200,000 rows 387 / 253 / 192 us, 8 files of up to 50,000
+// 478 us, 16 files of up to 200,000 rows 387 / 253 / 192 us, 8 files of up to 50,000
 // rows 183 / 140 / 122 us.
 bool default_schedule(const pq_tuning& T) {
   if (T.form != PQ_FORM_BATCHED || T.queues == 1) return false;

@@ -8,7 +8,8 @@
 // without waiting for each other: a lane follows its value's chain of shorter
 // prefixes (the nearest earlier value with a shorter one, and so on) and
 // copies each piece from the suffix it comes from; only bytes older than the
-// group come from the value before it, kept in LDS.
+// group come from the value before it, kept in LDS.  Longer values are few to a
+// group's buffer; all lanes copy them one after the other.
 #include <hip/hip_runtime.h>
 
 #include "pq_device.hpp"

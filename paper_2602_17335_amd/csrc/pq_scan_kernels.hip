@@ -1544,8 +1544,8 @@ __global__ void k_str_total(const ColScan* __restrict__ cols, const int32_t* __r
 // ---------------------------------------------------------------------------
 // The tile prefix from the tiles' values, in place (open): v[0, n) becomes its
 // exclusive prefix sum and v[n] the total.  k_scan_sums: each workgroup's sum;
-// k_scan_prefix: every workgroup adds up the sums before it (a file of 10^9 rows
-// has 256 workgroups) and scans its own values.  k_pick: out[i] = v[at[i]].
+// k_scan_prefix: every workgroup adds up the sums before it (245 workgroups for 16
+// columns of 64M rows) and scans its own values.  k_pick: out[i] = v[at[i]].
 // ---------------------------------------------------------------------------
 constexpr uint32_t SCAN_PER = 16, SCAN_WG = WG * SCAN_PER;
 __global__ __launch_bounds__(WG) void k_scan_sums(const uint64_t* __restrict__ v, uint32_t n, uint64_t* __restrict__ sums) {
