@@ -1,8 +1,8 @@
 """GPU parity of DELTA_BYTE_ARRAY pages at the edges of their expansion: value
-counts around a group of 64 and a unit of 1024 values; prefix chains that reach
-before the group and before the unit (sorted keys, growing and shrinking
-values, one value repeated); empty values; groups over the 4 KiB LDS buffer and
-single values over it.  Every output buffer is compared with the oracle byte
+counts around a group of 64 values and around several units of 256; prefix chains that
+reach before the group and before the unit (sorted keys, growing and shrinking
+values, one value repeated); empty values; groups over the LDS buffer (4 KiB, 2 KiB
+for pages of short values) and single values over it.  Every output buffer is compared with the oracle byte
 for byte, with one page and with many."""
 import io
 
